@@ -158,7 +158,7 @@ struct SelectExtras {
     int64_t k_row_stride = 0;           // dense, generic: elements between consecutive keys of one head in k and v,
     int64_t k_head_stride = 0;          //        and between heads (0, 0: as q, see `in`)
     InStride in;                        // layout of q (generic kernels: of k and v too)
-    // dense, MFMA, blocks of 64 or 128 tokens: the key units are cut into n_split equal shares, each worked on
+    // dense, MFMA: the key units are cut into n_split equal shares, each worked on
     // by workgroups of its own; share i leaves its normalised result at out_f32 [i][n_tok][heads][64] and the
     // base-2 logarithm of its sum of exponentials at part_lse [i][n_tok][heads] (launch_dense_combine adds
     // the shares up).  For few query rows: more, shorter workgroups spread evenly over the CUs.

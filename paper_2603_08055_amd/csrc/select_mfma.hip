@@ -206,7 +206,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
     const int32_t *sel = nullptr;
     if constexpr (DENSE) {
         n_steps = static_cast<int>(n_units1 + n_units2);
-        if constexpr (EXTRA && !SMALL) {  // key splits: units [u_begin, u_begin + n_steps)
+        if constexpr (EXTRA) {  // key splits: units [u_begin, u_begin + n_steps)
             if (x.n_split > 1) {
                 const int64_t u_all = n_units1 + n_units2;
                 u_begin = static_cast<int>(u_all * split / x.n_split);
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
 
     // step s -> key unit (global unit index); 32-bit arithmetic: these run once per step on the scalar unit
     auto unit_of = [&](int s) -> int {
-        if constexpr (DENSE) return (EXTRA && !SMALL) ? s + u_begin : s;
+        if constexpr (DENSE) return s + u_begin;  // (u_begin: 0 at compile time without EXTRA)
         else return (sel_at(sel, s >> upb_shift) << upb_shift) + (s & upb_mask);
     };
     // SMALL: the blocks a 64-key unit is put together from; missing ones (short last unit) point at the
@@ -259,12 +259,13 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         if (bpu_shift == 2) { b2 = block_at(s, 2); b3 = block_at(s, 3); }
         return UnitBlocks{f0, b1 >= 0 ? b1 : f0, b2 >= 0 ? b2 : f0, b3 >= 0 ? b3 : f0};
     };
-    auto issue = [&](int s, int stage) {  // this wave's share of unit s -> LDS stage `stage`
+    auto issue = [&](int s, int stage) {  // this wave's share of step s -> LDS stage `stage`
         const unsigned stage_byte = ring_base + static_cast<unsigned>(stage) * (kStageParts * kUnitElems * 2);
         if constexpr (SMALL) {
             // (dense: the second key segment is stored as plain 64-key units)
-            const bool small = !(DENSE && s >= n_units1);
-            const UnitBlocks b = blocks_of(small ? s : 0);
+            const int u = s + u_begin;
+            const bool small = !(DENSE && u >= n_units1);
+            const UnitBlocks b = blocks_of(small ? u : 0);
             const int64_t tile = static_cast<int64_t>(block) * 64;  // elements of a block's K (or V) tile
             // Chunk c * QW + wave for c = 0 .. CPW - 1: the tile half mt a chunk belongs to is then a
             // compile-time constant (chunks 0..7 = K (mt, channel step), 8..15 = V (v = 2 mt + hw, dt)),
@@ -295,7 +296,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
                         else src = vb_h + (hw ? hi : lo) * tile + (dt * 64 + lane) * 8;
                     }
                 } else {
-                    const int64_t w2 = s - n_units1;
+                    const int64_t w2 = u - n_units1;
                     src = (is_k ? kb2_h : vb2_h) + w2 * kUnitElems + (chunk & 7) * 512 + lane * 8;
                 }
                 lds_dma_16(src + part, __builtin_amdgcn_readfirstlane(stage_byte + chunk * 1024));
@@ -333,14 +334,14 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
     float m_run = -1e30f, l_run = 0.f;
 
-    // which of unit s's 64 keys exist (wave-uniform)
+    // which of the 64 keys of step s's unit exist (wave-uniform)
     auto unit_mask = [&](int s) -> unsigned long long {
-        if (SMALL && !(DENSE && s >= n_units1)) {
+        if (SMALL && !(DENSE && s + u_begin >= n_units1)) {
             unsigned long long vm = 0ull;
 #pragma unroll
             for (int c = 0; c < 4; ++c)
                 if (c < (1 << bpu_shift)) {
-                    const int j = block_at(s, c);
+                    const int j = block_at(s + u_begin, c);
                     const int len = j >= 0 ? block_tokens(j) : 0;
                     vm |= ((1ull << len) - 1ull) << (c * block);
                 }
@@ -649,7 +650,7 @@ static hipError_t run_select_x(const SelectArgs &a, hipStream_t stream)
         if (per_launch > sets) per_launch = sets;
     }
     if ((per_launch + 8) * a.heads * (a.x.n_split > 1 ? a.x.n_split : 1) > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (a.x.n_split > 1 && (!DENSE || SMALL || a.x.out_f32 == nullptr || a.x.part_lse == nullptr)) return hipErrorInvalidValue;
+    if (a.x.n_split > 1 && (!DENSE || a.x.out_f32 == nullptr || a.x.part_lse == nullptr)) return hipErrorInvalidValue;
     const int map_mode = DENSE ? 0 : 2;
     for (int64_t s0 = 0; s0 < sets; s0 += per_launch) {
         const int64_t ns = (sets - s0 < per_launch) ? sets - s0 : per_launch;

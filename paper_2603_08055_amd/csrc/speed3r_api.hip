@@ -53,20 +53,25 @@ bool mfma_ok(s3r_dtype dtype, int block) { (void)dtype; (void)block; return g_ke
 // copies of a K (or V) tile array the MFMA kernels read: fp32 problems keep bf16 parts hi, lo and (K) lo2
 size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 
-// Dense attention of few query rows (the special tokens) in key splits: as many as make the workgroups fill
-// the CUs most evenly (MI355X: 256 CUs x 3 workgroups of the dense kernel each), at least 4 key units each.
-constexpr int kDenseSlots = 256 * 3;
-constexpr int kMaxDenseSplit = 8;
-int dense_splits(int64_t n_rows, int heads, int64_t n_units)
+// Dense attention of few query rows (the special tokens) in key splits.  The CUs hold `slots` workgroups of the
+// dense kernel (MI355X: 256 CUs, three on each for bf16, one for fp32 with its 120 KiB ring); s splits take ceil(workgroups * s / slots) rounds, each as long as a
+// split's key units plus what a workgroup costs besides them (its start and end, and its row of partial results,
+// about as long as kSplitOverhead units).  The number of splits with the shortest total is taken.  Without splits
+// a handful of workgroups each walk every key: 500 special rows of 100 views (16 heads, blocks of 16 tokens, 64
+// workgroups) took 3.96 ms, in 12 splits 0.36 ms; 1000 rows of 200 views (blocks of 64) 1.42 ms in 6.
+constexpr int kMaxDenseSplit = 64;
+constexpr int kSplitOverhead = 10;
+int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype)
 {
+    const int64_t slots = dtype == S3R_BF16 ? 256 * 3 : 256;
     const int64_t wgs = (n_rows + 127) / 128 * heads;
-    if (wgs >= 4 * kDenseSlots) return 1;
+    if (wgs >= 4 * slots) return 1;
     int best = 1;
-    double best_fill = 0.0;
+    int64_t best_time = INT64_MAX;
     for (int s = 1; s <= kMaxDenseSplit && (s == 1 || s * 4 <= n_units); ++s) {
-        const double rounds = static_cast<double>(wgs) * s / kDenseSlots;
-        const double fill = rounds / static_cast<double>(static_cast<int64_t>(rounds + 0.999999));
-        if (fill > best_fill + 1e-9) { best_fill = fill; best = s; }
+        const int64_t rounds = (wgs * s + slots - 1) / slots;
+        const int64_t time = rounds * ((n_units + s - 1) / s + kSplitOverhead);
+        if (time < best_time) { best_time = time; best = s; }
     }
     return best;
 }
@@ -147,8 +152,8 @@ Layout make_layout(int64_t n_tok, int heads, int block, int topk, int n_forced, 
     L.oc_tok = take(token_queries ? static_cast<size_t>(L.n_blk) * block * heads * 64 * sizeof(float) : 0);
     // special rows in key splits: normalised partial results and their log-sums
     L.spec_split = 1;
-    if (n_spec > 0 && mfma_ok(dtype, block) && block >= 64)
-        L.spec_split = dense_splits(n_spec, heads, L.n_blk * (block / 64) + (n_spec + 63) / 64);
+    if (n_spec > 0 && mfma_ok(dtype, block))
+        L.spec_split = dense_splits(n_spec, heads, (L.n_blk * block + 63) / 64 + (n_spec + 63) / 64, dtype);
     const size_t part_rows = L.spec_split > 1 ? static_cast<size_t>(L.spec_split) * n_spec * heads : 0;
     L.spec_part_o = take(part_rows * 64 * sizeof(float));
     L.spec_part_lse = take(part_rows * sizeof(float));
