@@ -211,5 +211,8 @@ hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream);
 // outputs): few workgroups per CU, each wave software-pipelined (launch_select_mfma routes here).
 hipError_t launch_select_pipe(const SelectArgs &a, hipStream_t stream);
 
+// MFMA selection for blocks of 16 and 32 tokens, bf16 and fp32: one wave per query block, operands straight to
+// registers (launch_select_mfma routes here).
+hipError_t launch_select_direct(const SelectArgs &a, hipStream_t stream);
 
 }  // namespace s3r

@@ -37,12 +37,10 @@ namespace s3r {
 // QW    : waves per workgroup = query rows / 32 (block / 32 for selection: one query block)
 // DENSE : every key unit instead of an index list
 // NS    : LDS stages of the unit ring
-// SMALL : key blocks of 16 or 32 tokens (4 x 4 spatial windows and the like): a 64-key unit is put
-//         together from 4 or 2 blocks, each lane of an LDS-direct load fetching its 16 bytes from the
-//         block its unit row belongs to (the pooling kernel stores such blocks as small tiles in the
-//         same operand order), and a query block fills only the first `block` of a wave's 32 query
-//         columns.  At 16 FLOP per byte of K/V such blocks are bound by the gather alone, so the
-//         empty MFMA columns cost nothing.
+// SMALL : dense attention over key blocks of 16 or 32 tokens (4 x 4 spatial windows and the like): a 64-key
+//         unit is put together from 4 or 2 blocks, each lane of an LDS-direct load fetching its 16 bytes
+//         from the block its unit row belongs to (the pooling kernel stores such blocks as small tiles in
+//         the same operand order).  (Selection with such blocks: select_direct.hip.)
 // EXTRA : the rarely used arguments of SelectExtras are honoured (a second instantiation, so that the plain
 //         path carries none of their instructions: they cost the selection kernel 2.4 % when always compiled in)
 // ASMQ  : Q is loaded by inline asm after the first unit requests instead of by plain loads (see below)
@@ -78,6 +76,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
     constexpr int D = NS - 1;          // units in flight
     static_assert(NCH % NW == 0 && 16 % NW == 0, "waves must split the chunks of a unit evenly");
     static_assert(CPW * D < 64, "vmcnt budget");
+    static_assert(!SMALL || DENSE, "selection with small blocks: select_direct.hip");
     static_assert(!F32 || (!PAIR && !PROBE), "operand parts: the plain and the dense kernels");
     // [stage][K 8 KiB | V 8 KiB] (F32: then [K lo 8 KiB | V lo 8 KiB | K lo2 8 KiB])
     constexpr int kStageParts = F32 ? 5 : 2;
@@ -115,10 +114,6 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
     const int64_t qgroup = set;
     int64_t t = qgroup * (32 * QW) + wave * 32 + (lane & 31);
     bool row_valid = t < n_tok;
-    if constexpr (SMALL && !DENSE) {  // one query block of `block` rows per wave
-        t = qgroup * block + (lane & 31);
-        row_valid = (lane & 31) < block && t < n_tok;
-    }
     if (!DENSE && !PAIR && blk_len != nullptr) row_valid = wave * 32 + (lane & 31) < blk_len[qgroup];  // spatial windows
     if constexpr (PAIR) {
         static_assert(!PAIR || (QW == 4 && !DENSE && !SMALL && ASMQ), "two query blocks of 64 rows, two waves each");
@@ -215,7 +210,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         }
     } else {
         sel = idx + (static_cast<int64_t>(h) * n_blk + (PAIR ? 2 * qgroup : qgroup)) * kk;
-        n_steps = SMALL ? (kk + (1 << bpu_shift) - 1) >> bpu_shift : kk << upb_shift;
+        n_steps = kk << upb_shift;
     }
     // An entry of the index list, held into [0, n_blk): the lists of the library's own TopK are always in range,
     // a caller's (speed3r_select_attn) are not trusted with the address arithmetic.
@@ -223,11 +218,10 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         const int j = list[pos];
         return j < 0 ? 0 : (j >= static_cast<int>(n_blk) ? static_cast<int>(n_blk) - 1 : j);
     };
-    // SMALL: the c-th key block of unit s, or -1 past the end of the list
+    // SMALL: the c-th key block of unit s, or -1 past the end of the sequence
     auto block_at = [&](int s, int c) -> int {
         const int pos = (s << bpu_shift) + c;
-        if constexpr (DENSE) return pos < n_blk ? pos : -1;
-        else return pos < kk ? sel_at(sel, pos) : -1;
+        return pos < n_blk ? pos : -1;
     };
     auto block_tokens = [&](int j) -> int {  // tokens of key block j (j >= 0)
         if (blk_len != nullptr) return blk_len[j];
@@ -264,7 +258,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         if constexpr (SMALL) {
             // (dense: the second key segment is stored as plain 64-key units)
             const int u = s + u_begin;
-            const bool small = !(DENSE && u >= n_units1);
+            const bool small = u < n_units1;
             const UnitBlocks b = blocks_of(small ? u : 0);
             const int64_t tile = static_cast<int64_t>(block) * 64;  // elements of a block's K (or V) tile
             // Chunk c * QW + wave for c = 0 .. CPW - 1: the tile half mt a chunk belongs to is then a
@@ -336,7 +330,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
 
     // which of the 64 keys of step s's unit exist (wave-uniform)
     auto unit_mask = [&](int s) -> unsigned long long {
-        if (SMALL && !(DENSE && s + u_begin >= n_units1)) {
+        if (SMALL && s + u_begin < n_units1) {
             unsigned long long vm = 0ull;
 #pragma unroll
             for (int c = 0; c < 4; ++c)
@@ -695,7 +689,7 @@ hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream)
                          : run_select<4, true, 3, false, true, false, true>(a, stream);
         }
         if (a.n_keys != a.n_tok || a.n_keys2 != 0) return hipErrorInvalidValue;
-        return small          ? run_select<1, false, 2, true, false, false, true>(a, stream)
+        return small          ? launch_select_direct(a, stream)
                : a.block == 64 ? run_select<2, false, 2, false, false, false, true>(a, stream)
                                : run_select<4, false, 2, false, false, false, true>(a, stream);
     }
@@ -741,10 +735,9 @@ hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream)
         return (a.kk > 96 && 2 * a.n_common >= a.kk) ? run_select<4, false, 2, false, true, true>(a, stream)
                : a.kk > 96                            ? run_select<2, false, 2, false, true>(a, stream)
                                                       : run_select<2, false, 2>(a, stream);
-    // measured: the inline-asm Q load is 2 % faster for blocks of 128 and 32 tokens, 2 % slower for 16
+    // measured: the inline-asm Q load is 2 % faster for blocks of 128 tokens
     if (a.block == 128) return run_select<4, false, 2, false, true>(a, stream);
-    if (a.block == 32) return run_select<1, false, 2, true, true>(a, stream);
-    if (a.block == 16) return run_select<1, false, 2, true>(a, stream);
+    if (a.block == 16 || a.block == 32) return launch_select_direct(a, stream);
     return hipErrorInvalidValue;
 }
 

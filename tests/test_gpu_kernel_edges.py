@@ -3,6 +3,7 @@ the line between two kernels, against the oracle with the tolerances of test_gpu
 import pytest
 
 from paper_2603_08055_amd import workloads
+from tests.parity_util import compare_with_oracle, log, run_device, to_host_f32
 from tests.test_gpu_parity import layer_case, s3r  # noqa: F401  (s3r: fixture)
 
 pytestmark = pytest.mark.gpu
@@ -20,3 +21,25 @@ def test_special_rows_in_key_splits(s3r, oracle, dtype, block, views, tpv, speci
     wl = workloads.Workload(f"splits_{dtype}_{block}_{views}x{tpv}_{special}", views, tpv, heads, 64, dtype, block, 3,
                             93, "normal")
     layer_case(s3r, oracle, wl, special, with_gate=True)
+
+
+@pytest.mark.parametrize("dtype,block,n_tok,topk,heads", [
+    ("bf16", 16, 16, 1, 1),           # one block, one entry
+    ("bf16", 16, 16 * 5 - 1, 5, 3),   # a list one block longer than the four worked on at a time, short last block
+    ("bf16", 16, 16 * 70 + 3, 64, 2), # a full load of the index row
+    ("bf16", 16, 16 * 70 + 3, 66, 1), # ... and two entries more
+    ("bf16", 32, 33, 2, 2),           # two blocks, the second of one token
+    ("bf16", 32, 32 * 9 + 5, 3, 5),   # odd list, ten query blocks: the last workgroup half empty
+    ("bf16", 32, 32 * 140, 131, 1),   # three loads of the index row
+    ("f32", 16, 16 * 6 + 1, 5, 2),
+    ("f32", 16, 16 * 90 + 9, 67, 1),
+    ("f32", 32, 32 * 7 - 3, 3, 2),
+    ("f32", 32, 31, 1, 1),
+])
+def test_selection_of_small_blocks(s3r, oracle, dtype, block, n_tok, topk, heads):
+    wl = workloads.Workload(f"small_{dtype}_{block}_{n_tok}_{topk}", 1, n_tok, heads, 64, dtype, block, topk, 94, "normal")
+    q, k, v = workloads.make_inputs(wl)
+    gate = workloads.make_gate_logits(wl)
+    res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), block, topk, gate=gate.cuda())
+    log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v),
+                                                 to_host_f32(gate), block, topk, dtype, label=wl.name)))
