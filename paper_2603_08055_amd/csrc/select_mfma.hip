@@ -708,7 +708,7 @@ hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream)
     // plain rows of at most 128 blocks of 64 tokens: the software-pipelined kernel of select_pipe.hip (rows that
     // are mostly forced blocks stay with the PAIR variant below)
     if (a.block == 64 && !a.loads_only && a.kk <= 128 && !(a.kk > 96 && 2 * a.n_common >= a.kk) &&
-        a.x.o_comp_tok == nullptr && a.x.in.tok == 0)
+        a.x.o_comp_tok == nullptr)
         return launch_select_pipe(a, stream);
     if (a.loads_only) {  // the data movement of the plain kernels for blocks of 64 and 128 tokens, no arithmetic
         if (a.x.o_comp_tok != nullptr || a.x.in.tok != 0 || a.qmap.period != 0 || a.blk_len != nullptr) return hipErrorInvalidValue;

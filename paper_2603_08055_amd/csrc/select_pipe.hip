@@ -39,7 +39,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     const int32_t *__restrict__ idx, const float *__restrict__ o_comp, const bf16_t *__restrict__ gate,
     bf16_t *__restrict__ out, bf16_t *__restrict__ o_sel, float *__restrict__ lse, int64_t n_tok, int64_t n_blk,
     int heads, int kk, float scale_log2, int64_t n_sets, TokenMap qmap, int64_t n_keys, int64_t lse_stride,
-    const int32_t *__restrict__ blk_len)
+    const int32_t *__restrict__ blk_len, InStride in)
 {
     constexpr int BLOCK = 64;
     constexpr int L = 8;                                  // 1 KiB chunks a wave requests per iteration
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     {
         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
         u32x4 q0, q1, q2, q3;
-        const bf16_t *qrow = q + (trow * heads + h) * 64 + 8 * g;
+        const bf16_t *qrow = q + in.at(trow, h, heads) + 8 * g;
         asm volatile("global_load_dwordx4 %0, %4, off\n\t"
                      "global_load_dwordx4 %1, %4, off offset:32\n\t"
                      "global_load_dwordx4 %2, %4, off offset:64\n\t"
@@ -431,17 +431,16 @@ static hipError_t run_pipe(const SelectArgs &a, hipStream_t stream)
                        static_cast<const bf16_t *>(a.q), static_cast<const bf16_t *>(a.kb),
                        static_cast<const bf16_t *>(a.vb), a.idx, a.o_comp, static_cast<const bf16_t *>(a.gate),
                        static_cast<bf16_t *>(a.out), static_cast<bf16_t *>(a.o_sel), a.lse, a.n_tok, a.n_blk, a.heads,
-                       a.kk, a.scale * kLog2e, sets, a.qmap, a.n_keys, a.lse_stride, a.blk_len);
+                       a.kk, a.scale * kLog2e, sets, a.qmap, a.n_keys, a.lse_stride, a.blk_len, a.x.in);
     return hipGetLastError();
 }
 
-// Plain selection (index rows of at most 128 blocks, packed q, per-block compressed outputs) for bf16 blocks
-// of 64 tokens.
+// Plain selection (index rows of at most 128 blocks, per-block compressed outputs) for bf16 blocks of 64 tokens.
 hipError_t launch_select_pipe(const SelectArgs &a, hipStream_t stream)
 {
     if (!a.is_bf16 || a.kb == nullptr || a.vb == nullptr || a.idx == nullptr) return hipErrorInvalidValue;
     if (a.n_keys != a.n_tok || a.n_keys2 != 0 || a.kk < 1 || a.kk > 128 || a.block != 64) return hipErrorInvalidValue;
-    if (a.x.o_comp_tok != nullptr || a.x.in.tok != 0) return hipErrorInvalidValue;
+    if (a.x.o_comp_tok != nullptr) return hipErrorInvalidValue;
     if (a.qmap.period != 0 && a.n_tok > 0x7fffffffLL) return hipErrorInvalidValue;
     // Measured on MI355X (1000 views x 1374 tokens, 16 heads, clustered keys; ms of this kernel for 8 / 16 / 32 /
     // 48 / 64 / 96 blocks per row): one pair of waves per query block, four workgroups per CU 5.2 / 9.1 / 18.5 /
@@ -449,6 +448,8 @@ hipError_t launch_select_pipe(const SelectArgs &a, hipStream_t stream)
     // of select_mfma.hip, five workgroups per CU: 5.6 / 10.1 / 19.2 / 28.5 / 38.5 / 59.3).  Long rows on long
     // sequences are bound by the arrival of K/V units and gain from fewer query blocks in progress; short rows
     // and short sequences (100 views: one pair is 5 to 10 % ahead at every row length) from more of them.
+    // Strided q (slices of one projection output) comes here as well, the strides enter one address per lane: the
+    // layer on 150 views, 8 x 8 windows, top-32 takes 3.92 ms, 4.35 with the selection in select_mfma.hip.
     if (a.kk >= 40 && a.n_blk >= 3000) return run_pipe<2, 2, 2, 3>(a, stream);
     return run_pipe<1, 2, 2, 3>(a, stream);
 }

@@ -1,6 +1,7 @@
 """Parity at the edges of kernel variants and dispatch rules: sizes on either side of a tile, of a remainder and of
 the line between two kernels, against the oracle with the tolerances of test_gpu_parity."""
 import pytest
+import torch
 
 from paper_2603_08055_amd import workloads
 from tests.parity_util import compare_with_oracle, log, run_device, to_host_f32
@@ -43,3 +44,14 @@ def test_selection_of_small_blocks(s3r, oracle, dtype, block, n_tok, topk, heads
     res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), block, topk, gate=gate.cuda())
     log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v),
                                                  to_host_f32(gate), block, topk, dtype, label=wl.name)))
+
+
+@pytest.mark.parametrize("views,tpv,topk", [(3, 1000, 39), (150, 1281, 40)])   # one and two pairs of waves per query block
+def test_strided_queries_in_the_pipelined_selection(s3r, views, tpv, topk):  # noqa: F811
+    wl = workloads.Workload(f"pipe_strided_{views}", views, tpv, 1, 64, "bf16", 64, topk, 95, "normal")
+    q, k, v = workloads.make_inputs(wl, device="cuda")
+    big = torch.stack([q, k, v], dim=1)
+    want = run_device(s3r, q, k, v, 64, topk)
+    got = run_device(s3r, big[:, 0], big[:, 1], big[:, 2], 64, topk)
+    for key in ("idx", "o_comp", "out", "o_sel", "lse"):   # the same arithmetic on the same values
+        assert torch.equal(got[key], want[key]), key
