@@ -85,16 +85,16 @@ hipError_t launch_pool(const void *q, const void *k, const void *v, float *qc, f
 // L2 norm of a scaled pooled key (rounded up).
 struct HeadStats { float sq, sk, sqsk, inv_sqsk, kn; };
 constexpr int kStatSlots = 64;
-// slots: scratch of heads * 3 * kStatSlots words; stats: [heads].
+// Partial maxima of the head figures.  slots: scratch of heads * 3 * kStatSlots words.
 hipError_t launch_pooled_stats(const float *qc, const float *kc, int64_t n_blk, int heads, void *slots,
-                               HeadStats *stats, hipStream_t stream);
+                               hipStream_t stream);
 
 // Pooled fp32 -> bf16 hi/lo operand tiles ([heads][tiles_padded][32 * 64] each, zero padded).
-// vt_lo may be null.  q_f16, k_f16 (optional, need stats): Qc and Kc as fp16 tiles of the same
-// shape, scaled by the head's sq and sk.
+// vt_lo may be null.  q_f16, k_f16 (optional, need slots and stats): Qc and Kc as fp16 tiles of the
+// same shape, scaled by the head's sq and sk.  slots: as written by launch_pooled_stats; stats ([heads]) is written.
 hipError_t launch_split(const float *qc, const float *kc, const float *vc, void *qs_hi, void *qs_lo,
                         void *ks_hi, void *ks_lo, void *vt_hi, void *vt_lo, void *q_f16, void *k_f16,
-                        const HeadStats *stats, int64_t n_blk, int heads, hipStream_t stream);
+                        const void *slots, HeadStats *stats, int64_t n_blk, int heads, hipStream_t stream);
 
 // S_guide rows + compressed attention for `heads` heads (operand tiles as written by launch_split).
 // forced_words (optional): bit b of word kt set = pooled key 64 kt + b is a forced block; its

@@ -268,16 +268,18 @@ s3r_status run_compress_topk(const float *qc, const float *kc, const float *vc, 
 {
     // Without S_guide in memory when k allows it.  Should a candidate list run over (long runs of
     // equal scores), the overflow word makes the two plain launches that follow redo the chunk;
-    // otherwise they return at once.
+    // otherwise they return at once.  A row's two lists divide its keys evenly, 16 of every 32 each, so up
+    // to 2 kCandCap blocks no list can run over and the two launches are left out: at 4.6 us each they
+    // and the two launches saved in front of the split (split.hip) were 14 of 66 us at 4 x 256 tokens.
     const bool fused = want_topk && fb.thr != nullptr && kk >= 1 && kk <= s3r::kFusedTopkMaxK && g_kernel_choice != 2;
     {
         StageTimer tm(S3R_STAGE_SPLIT, stream);
         if (fused)
-            S3R_HIP(s3r::launch_pooled_stats(qc, kc, n_blk, heads, fb.stat_slots, fb.head_stats, stream),
+            S3R_HIP(s3r::launch_pooled_stats(qc, kc, n_blk, heads, fb.stat_slots, stream),
                     "pooled statistics kernel launch");
         S3R_HIP(s3r::launch_split(qc, kc, vc, tile[0], tile[1], tile[2], tile[3], tile[4],
                                   accurate_pv ? tile[5] : nullptr, fused ? tile[6] : nullptr, fused ? tile[7] : nullptr,
-                                  fused ? fb.head_stats : nullptr, n_blk, heads, stream),
+                                  fused ? fb.stat_slots : nullptr, fused ? fb.head_stats : nullptr, n_blk, heads, stream),
                 "split kernel launch");
     }
     const size_t tile_head = static_cast<size_t>(tiles) * 32 * 64 * 2;  // bytes per head per array
@@ -297,6 +299,7 @@ s3r_status run_compress_topk(const float *qc, const float *kc, const float *vc, 
         S3R_HIP(s3r::launch_topk_candidates(qc, kc, fb.cand, fb.cand_count, kCandCap, idx, n_blk, heads, kk, stream),
                 "candidate topk kernel launch");
     }
+    if (fused && n_blk <= 2 * kCandCap) return S3R_OK;
     const int *run_flag = fused ? fb.overflow : nullptr;
     for (int h0 = 0; h0 < heads; h0 += head_chunk) {
         const int hc = (heads - h0 < head_chunk) ? heads - h0 : head_chunk;

@@ -55,3 +55,32 @@ def test_strided_queries_in_the_pipelined_selection(s3r, views, tpv, topk):  # n
     got = run_device(s3r, big[:, 0], big[:, 1], big[:, 2], 64, topk)
     for key in ("idx", "o_comp", "out", "o_sel", "lse"):   # the same arithmetic on the same values
         assert torch.equal(got[key], want[key]), key
+
+
+@pytest.mark.parametrize("n_blk", [127, 511, 512, 513, 545])   # up to 512 blocks the candidate lists cannot run over
+def test_lists_filled_to_the_last_slot(s3r, oracle, n_blk):
+    """Equal keys: every block is a candidate of every row, and the smallest indices win."""
+    n_tok, heads, topk = 16 * n_blk, 2, 64
+    wl = workloads.Workload(f"equal_keys_{n_blk}", 1, n_tok, heads, 64, "bf16", 16, topk, 96, "normal")
+    q, k, v = workloads.make_inputs(wl)
+    k[:] = k[:1].clone()
+    res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), 16, topk)
+    assert torch.equal(res["idx"].cpu(), torch.arange(topk, dtype=torch.int32).expand(heads, n_blk, topk))
+    log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v), None, 16,
+                                                 topk, "bf16", label=wl.name)))
+
+
+@pytest.mark.parametrize("dtype,which", [("bf16", "q"), ("bf16", "k"), ("f32", "k")])
+@pytest.mark.parametrize("n_blk,peak", [(1, 0), (33, 32), (2048, 2047), (2049, 2048), (2500, 2111), (4130, 4129)])
+def test_head_maxima_wherever_they_sit(s3r, oracle, dtype, which, n_blk, peak):
+    """Pooled entries that overflow fp16 unless the head's scale factor has seen them, on either side of the 2048 rows
+    that the statistics kernel covers in one step.  The other operand is as much smaller: logits stay ordinary."""
+    wl = workloads.Workload(f"peak_{which}_{dtype}_{n_blk}_{peak}", 1, 16 * n_blk - 5, 2, 64, dtype, 16, 5, 97, "normal")
+    q, k, v = workloads.make_inputs(wl)
+    large, small = (q, k) if which == "q" else (k, q)
+    large[16 * peak:16 * peak + 16, 1] *= 2.0 ** 20
+    small[:, 1] *= 2.0 ** -20
+    res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), 16, 5)
+    rows = sorted({0, n_blk // 2, max(0, peak - 1), peak, n_blk - 1})
+    log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v), None, 16,
+                                                 5, dtype, rows=rows, label=wl.name)))
