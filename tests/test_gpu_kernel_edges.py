@@ -84,3 +84,18 @@ def test_head_maxima_wherever_they_sit(s3r, oracle, dtype, which, n_blk, peak):
     rows = sorted({0, n_blk // 2, max(0, peak - 1), peak, n_blk - 1})
     log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v), None, 16,
                                                  5, dtype, rows=rows, label=wl.name)))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_blk,topk,lean", [(100, 64, -1.0), (700, 1, -1.0), (700, 64, -1.0), (700, 64, 1.0), (700, 64, 0.0), (60, 64, -1.0)])
+def test_bound_of_scores_of_one_sign(s3r, oracle, dtype, n_blk, topk, lean):  # noqa: F811
+    """The bound on the k-th score where all scores are negative, positive or of both signs, and where fewer than k
+    blocks exist."""
+    wl = workloads.Workload(f"lean_{dtype}_{n_blk}_{topk}_{lean}", 1, 16 * n_blk, 1, 64, dtype, 16, topk, 98, "normal")
+    q, k, v = workloads.make_inputs(wl)
+    if lean != 0.0:
+        q.add_(lean)
+        k.add_(1.0)
+    res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), 16, topk)
+    log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v), None, 16,
+                                                 topk, dtype, label=wl.name)))
