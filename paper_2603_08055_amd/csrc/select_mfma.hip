@@ -566,8 +566,9 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
                 for (int i = 0; i < 4; ++i) o4[i] = oacc[dt][4 * r4 + i] * inv;
                 *reinterpret_cast<floatx4 *>(x.out_f32 + slot * 64 + 32 * dt + 8 * r4 + 4 * g) = o4;
             }
-        // base-2 logarithm of the split's sum of exponentials: what weighs it against the other splits
-        if (x.part_lse != nullptr && g == 0) x.part_lse[slot] = l_tot > 0.f ? m_run + __builtin_log2f(l_tot) : -INFINITY;
+        // base-2 logarithm of the split's sum of exponentials: what weighs it against the other splits.  Only an empty sum
+        // stands for a share without keys: one that is not a number has to reach the row
+        if (x.part_lse != nullptr && g == 0) x.part_lse[slot] = l_tot == 0.f ? -INFINITY : m_run + __builtin_log2f(l_tot);
         return;
     }
 #pragma unroll

@@ -24,6 +24,20 @@ def test_special_rows_in_key_splits(s3r, oracle, dtype, block, views, tpv, speci
     layer_case(s3r, oracle, wl, special, with_gate=True)
 
 
+@pytest.mark.parametrize("dtype,block", [("bf16", 16), ("bf16", 64), ("f32", 32), ("f32", 64)])
+def test_a_key_that_is_not_a_number_in_one_key_split(s3r, dtype, block):  # noqa: F811
+    """The softmax of every special row runs over that key, whichever split holds it: NaN in the whole row.  The key
+    is a special token's, so that the image rows and the other head never see it."""
+    views, tpv, special, heads = 2, 400, 3, 2
+    wl = workloads.Workload(f"nan_key_{dtype}_{block}", views, tpv, heads, 64, dtype, block, 3, 99, "normal")
+    q, k, v = workloads.make_inputs(wl)
+    k[tpv + 1, 1, 5] = float("nan")
+    out = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), block, 3, tokens_per_view=tpv, special_per_view=special)["out"]
+    is_nan = out.view(views, tpv, heads, 64).isnan()
+    assert is_nan[:, :special, 1].all()
+    assert not is_nan[:, :special, 0].any() and not is_nan[:, special:].any()
+
+
 @pytest.mark.parametrize("dtype,block,n_tok,topk,heads", [
     ("bf16", 16, 16, 1, 1),           # one block, one entry
     ("bf16", 16, 16 * 5 - 1, 5, 3),   # a list one block longer than the four worked on at a time, short last block
