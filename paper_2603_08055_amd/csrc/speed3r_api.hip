@@ -53,27 +53,54 @@ bool mfma_ok(s3r_dtype dtype, int block) { (void)dtype; (void)block; return g_ke
 // copies of a K (or V) tile array the MFMA kernels read: fp32 problems keep bf16 parts hi, lo and (K) lo2
 size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 
-// Dense attention of few query rows (the special tokens) in key splits.  The CUs hold `slots` workgroups of the
-// dense kernel (MI355X: 256 CUs, three on each for bf16, one for fp32 with its 120 KiB ring); s splits take ceil(workgroups * s / slots) rounds, each as long as a
-// split's key units plus what a workgroup costs besides them (its start and end, and its row of partial results,
-// about as long as kSplitOverhead units).  The number of splits with the shortest total is taken.  Without splits
-// a handful of workgroups each walk every key: 500 special rows of 100 views (16 heads, blocks of 16 tokens, 64
-// workgroups) took 3.96 ms, in 12 splits 0.36 ms; 1000 rows of 200 views (blocks of 64) 1.42 ms in 6.
+// Dense attention of few query rows (the special tokens) in key splits: the number of splits with the shortest time
+// by a model of the launch, in microseconds on MI355X (256 CUs; a CU holds three workgroups of the bf16 kernel, one
+// of the fp32 kernel with its 120 KiB ring).  A CU works through n = ceil(workgroups * s / 256) of them:
+//   * each takes 0.68 us per key unit (1.1 with the gathered units of small blocks; fp32: 8 and 3.8) and 4 us at its
+//     start and end;
+//   * the bf16 kernel needs two to three workgroups on a CU to fill it: one left over in the last round costs as
+//     much as 1.75, two as 2.3 (0.85 to 0.91 us per unit with one, 0.69 to 0.71 with two, 0.68 with three);
+//   * the workgroups of later rounds no longer walk the keys in step and share less of them in the L2s: 2.5 % per
+//     round, 30 % at most (26 300 units, 768 workgroups: 49.1 ms in one split, 50.4 in 2, 57.1 in 8, 64.6 in 24);
+//   * the combine kernel reads s partial rows one after the other (0.6 us each) and moves them at 4 TB/s.
+// Measured, 16 heads, 5 special rows per view, dense kernel and combine (ms for the number of splits, * = chosen):
+//   bf16, blocks of 64, 20 views    1: 0.361   8: 0.062  16: 0.048*  48: 0.067
+//                       100 views   1: 1.80    8: 0.380  12: 0.367*  24: 0.409  64: 0.562
+//                       950 views   1: 37.1    2: 32.9    5: 33.6*   8: 35.1    24: 39.9
+//                       1000 views  1: 39.8    2: 34.5*   3: 37.4    6: 37.5    12: 42.2
+//                       1250 views  1: 66.4    3: 57.6    4: 57.6*   8: 60.4    47: 67.5
+//   bf16, blocks of 16, 100 views   1: 3.96    8: 0.656  12: 0.576*  24: 0.596  64: 0.658
+//   fp32, blocks of 64, 60 views    5: 2.10    8: 2.72   10: 2.19    16: 2.12*  32: 2.17
+// fp32 takes at least 8 splits, although fewer can be faster (200 views: 17.4 ms in 2, 17.8 in 8; 400 views 68.8 in 3,
+// 70.2 in 8): the error of a row against 64 bits grows with the units in one chain of sums (200 views: 1.0e-5 in one
+// split, 7.6e-6 in 2, 5.7e-6 in 6, 5.4e-6 in 8, 5.0e-6 in 16).  In bf16 it is the rounding of P, whatever the splits.
 constexpr int kMaxDenseSplit = 64;
-constexpr int kSplitOverhead = 10;
-int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype)
+int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, int block)
 {
-    const int64_t slots = dtype == S3R_BF16 ? 256 * 3 : 256;
+    const bool bf16 = dtype == S3R_BF16;
     const int64_t wgs = (n_rows + 127) / 128 * heads;
-    if (wgs >= 4 * slots) return 1;
-    int best = 1;
-    int64_t best_time = INT64_MAX;
-    for (int s = 1; s <= kMaxDenseSplit && (s == 1 || s * 4 <= n_units); ++s) {
-        const int64_t rounds = (wgs * s + slots - 1) / slots;
-        const int64_t time = rounds * ((n_units + s - 1) / s + kSplitOverhead);
-        if (time < best_time) { best_time = time; best = s; }
+    if (wgs >= 3072) return 1;  // 12 workgroups and more per CU: even enough
+    const double unit_us = bf16 ? (block >= 64 ? 0.68 : 1.1) : (block >= 64 ? 8.0 : 3.8);
+    const int64_t at_once = bf16 ? 3 : 1;
+    const double left_over[3] = {0.0, bf16 ? 0.75 : 0.0, bf16 ? 0.3 : 0.0};
+    auto time_us = [&](int s) {
+        const int64_t n = (wgs * s + 255) / 256, rounds = (n + at_once - 1) / at_once;
+        const double drift = 0.025 * static_cast<double>(rounds - 1);
+        const double walk = (static_cast<double>(n) + left_over[n % 3]) * (static_cast<double>((n_units + s - 1) / s) * unit_us + 4.0) *
+                            (1.0 + (drift < 0.3 ? drift : 0.3));
+        return s == 1 ? walk : walk + s * (0.6 + 1.3e-4 * static_cast<double>(n_rows * heads));
+    };
+    int most = static_cast<int>(n_units / 4 < kMaxDenseSplit ? n_units / 4 : kMaxDenseSplit);  // at least 4 units each
+    if (most < 1) most = 1;
+    const int least = bf16 ? 1 : (most < 8 ? most : 8);
+    double us[kMaxDenseSplit + 1], shortest = INFINITY;
+    for (int s = least; s <= most; ++s) {
+        us[s] = time_us(s);
+        if (us[s] < shortest) shortest = us[s];
     }
-    return best;
+    int s = least;
+    while (us[s] > 1.01 * shortest) ++s;  // the fewest that come within 1 %: their partial results take workspace
+    return s;
 }
 
 constexpr int kCandCap = 256;  // candidate slots per list of the TopK-in-the-sweep path (two lists per row)
@@ -153,7 +180,7 @@ Layout make_layout(int64_t n_tok, int heads, int block, int topk, int n_forced, 
     // special rows in key splits: normalised partial results and their log-sums
     L.spec_split = 1;
     if (n_spec > 0 && mfma_ok(dtype, block))
-        L.spec_split = dense_splits(n_spec, heads, (L.n_blk * block + 63) / 64 + (n_spec + 63) / 64, dtype);
+        L.spec_split = dense_splits(n_spec, heads, (L.n_blk * block + 63) / 64 + (n_spec + 63) / 64, dtype, block);
     const size_t part_rows = L.spec_split > 1 ? static_cast<size_t>(L.spec_split) * n_spec * heads : 0;
     L.spec_part_o = take(part_rows * 64 * sizeof(float));
     L.spec_part_lse = take(part_rows * sizeof(float));

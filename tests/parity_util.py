@@ -301,3 +301,23 @@ def compare_windows_with_oracle(oracle, dev_res, qf, kf, vf, gate_f, topk, dtype
         got = to_host_f32(dev_res["out"].index_select(0, torch.from_numpy(spec_rows).to(dev_res["out"].device)))
         stats["o_spec"] = assert_close(got, dense, tol, f"{label} special rows")
     return stats
+
+
+def special_row_splits(s3r, views, tpv, special, heads, block, dtype, grid=None) -> int:
+    """Key splits that the library cuts the dense attention of the special rows into, read off the workspace: one more
+    than a problem of the image rows alone are the special rows' K and V tiles (whole units of 64, fp32 in three
+    parts) and, from two splits on, 64 + 1 fp32 words per split, special row and head."""
+    code = s3r.S3R_F32 if dtype == "f32" else s3r.S3R_BF16
+    whole = s3r.speed3r_workspace_bytes_ex(views * tpv, heads, 64, block, 1, code, tokens_per_view=tpv,
+                                           special_per_view=special, grid=grid)
+    image = s3r.speed3r_workspace_bytes_ex(views * (tpv - special), heads, 64, block, 1, code,
+                                           tokens_per_view=tpv - special, grid=grid)
+    assert whole > 0 and image > 0
+    rows = views * special * heads
+    up = lambda x: (x + 255) // 256 * 256
+    rest = whole - image - 2 * up(heads * -(-views * special // 64) * 64 * 64 * 2 * (3 if dtype == "f32" else 1))
+    if rest == 0:
+        return 1
+    splits = round(rest / (rows * 65 * 4))
+    assert rest == up(splits * rows * 64 * 4) + up(splits * rows * 4), (rest, splits)
+    return splits

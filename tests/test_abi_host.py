@@ -176,6 +176,36 @@ def test_workspace_bytes_and_shape_validation(s3r):
     assert lib.speed3r_set_kernel_choice(0) == s3r.S3R_OK
 
 
+@pytest.mark.parametrize("dtype,block,views,tpv,special,heads,grid,splits", [
+    # the splits that came within 5 % of the shortest time measured (dense kernel and combine)
+    ("bf16", 64, 20, 1374, 5, 16, None, range(13, 17)),
+    ("bf16", 64, 19, 872, 5, 16, None, range(10, 17)),
+    ("bf16", 64, 100, 1374, 5, 16, None, range(8, 13)),
+    ("bf16", 64, 200, 1374, 5, 16, None, range(4, 13)),
+    ("bf16", 64, 950, 1374, 5, 16, None, range(2, 6)),
+    ("bf16", 64, 1000, 1374, 5, 16, None, (2, 4)),
+    ("bf16", 64, 1225, 1374, 5, 16, None, (1, 2)),
+    ("bf16", 64, 1250, 1374, 5, 16, None, range(2, 8)),
+    ("bf16", 64, 132, 200, 64, 16, None, range(2, 8)),
+    ("bf16", 32, 25, 800, 5, 3, None, range(16, 33)),
+    ("bf16", 16, 50, 1374, 5, 16, (37, 37, 4), range(16, 25)),
+    ("bf16", 16, 100, 1374, 5, 16, (37, 37, 4), range(12, 25)),
+    # ... and in fp32 no fewer than 8, for the length of the chains of sums
+    ("f32", 64, 10, 1374, 5, 16, None, (16,)),
+    ("f32", 64, 60, 1374, 5, 16, None, range(10, 17)),
+    ("f32", 64, 200, 1374, 5, 16, None, range(8, 13)),
+    ("f32", 64, 400, 1374, 5, 16, None, range(8, 13)),
+    ("f32", 64, 132, 200, 64, 16, None, range(8, 11)),
+    ("f32", 16, 30, 1374, 5, 16, (37, 37, 4), (8, 16)),
+    ("f32", 64, 2, 500, 3, 2, None, range(4, 5)),         # 17 units: four splits of at least four
+    ("bf16", 64, 1, 200, 5, 2, None, (1,)),               # five units: none
+    ("bf16", 64, 100, 600, 300, 16, None, (1,)),          # 3760 workgroups
+])
+def test_key_splits_of_the_special_rows(s3r, dtype, block, views, tpv, special, heads, grid, splits):
+    from tests.parity_util import special_row_splits
+    assert special_row_splits(s3r, views, tpv, special, heads, block, dtype, grid) in splits
+
+
 def test_noalloc_entry_refuses_oversized_problems_on_the_host(s3r):
     """The entry point for callers that cannot allocate checks the size against its fixed scratch before any
     device work (the pointers are never dereferenced)."""
