@@ -169,9 +169,11 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     const bf16x2 ones = {static_cast<bf16_t>(1.f), static_cast<bf16_t>(1.f)};
 
     // keys that do not exist, then the running maximum: raised only when a unit exceeds it by more than the
-    // slack (rare after the first unit).  A raise rescales what has been summed so far: the accumulators, the
-    // row sum, and P(i - 1), whose product with V is still to come.
-    auto soft_pre = [&](floatx16 (&acc)[2], bf16x8 (&p_pending)[4], unsigned long long vmask) __attribute__((always_inline)) {
+    // slack (rare after the first unit).  A raise rescales what has been summed so far: the row sum here, the accumulators
+    // (rescale) once P(i - 1) V(i - 1) has been added to them, which is still in the old scale.  (Scaling P(i - 1)
+    // instead would round it to bf16 a second time, where the row sum has it as it was: up to 0.4 %.)
+    float alpha;  // what the accumulators are to be scaled by
+    auto soft_pre = [&](floatx16 (&acc)[2], unsigned long long vmask) __attribute__((always_inline)) -> bool {
         if (vmask != ~0ull) {
             asm volatile("" ::: "memory");  // keep this rare path a real branch
 #pragma unroll
@@ -189,21 +191,21 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
         }
         const float mx = fmaxf(fmaxf(mx4[0], mx4[1]), fmaxf(mx4[2], mx4[3]));
         const float m_tile = max_with_other_half(mx) * scale_log2;
-        const bool grow = m_tile > m_run + kRescaleSlack;
-        if (__any(grow)) {
+        const bool grow = m_tile > m_run + kRescaleSlack, raised = __any(grow);
+        if (__builtin_expect(raised, 0)) {
             const float m_new = grow ? m_tile : m_run;
-            const float alpha = fast_exp2(m_run - m_new);
+            alpha = fast_exp2(m_run - m_new);
             m_run = m_new;
             l_run *= alpha;
-#pragma unroll
-            for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-                for (int x = 0; x < 16; ++x) oacc[dt][x] *= alpha;
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) p_pending[v][e] = static_cast<bf16_t>(static_cast<float>(p_pending[v][e]) * alpha);
         }
+        return raised;
+    };
+    auto rescale = [&]() __attribute__((always_inline)) {
+        asm volatile("" ::: "memory");  // keep this rare path a real branch
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int x = 0; x < 16; ++x) oacc[dt][x] *= alpha;
     };
     // Operand m of an iteration's 16 MFMAs, in order of need: m < 8 the K chunks of unit i + 1, the two
     // 32-key tiles taking turns so that no MFMA waits for the one issued just before it (chunk (m & 1) * 4 +
@@ -255,8 +257,8 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     };
     // the same three phases one after the other, each only if its unit exists (first and last iterations)
     auto plain = [&](bool soft, bool pv, bool ss, floatx16 (&acc)[2], floatx16 (&acc_next)[2], bf16x8 (&p_out)[4],
-                     bf16x8 (&p_in)[4], const bf16_t *k_src, const bf16_t *v_src, unsigned long long vmask) __attribute__((always_inline)) {
-        if (soft) soft_pre(acc, p_in, vmask);
+                     const bf16x8 (&p_in)[4], const bf16_t *k_src, const bf16_t *v_src, unsigned long long vmask) __attribute__((always_inline)) {
+        const bool raised = soft && soft_pre(acc, vmask);
         if (pv) {
 #pragma unroll
             for (int m = 0; m < 8; ++m) {
@@ -264,6 +266,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
                 oacc[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, p_in[m >> 1], oacc[m & 1], 0, 0, 0);
             }
         }
+        if (__builtin_expect(raised, 0)) rescale();
         if (soft) {
             float lsum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -324,8 +327,9 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
         bf16x8 rd[16];
 #pragma unroll
         for (int m = 0; m < kAhead; ++m) rd[m] = operand(m, k_src, v_src);
-        soft_pre(accs[PAR], ps[1 - PAR], unit_mask(unit_of(i * P + p)));
+        const bool raised = soft_pre(accs[PAR], unit_mask(unit_of(i * P + p)));
         overlapped(accs[PAR], accs[1 - PAR], ps[PAR], ps[1 - PAR], rd, k_src, v_src);
+        if (__builtin_expect(raised, 0)) rescale();
     };
     // the first and last iterations
     auto edge = [&](auto par_tag, int i) __attribute__((always_inline)) {

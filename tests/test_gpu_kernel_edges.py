@@ -1,5 +1,7 @@
 """Parity at the edges of kernel variants and dispatch rules: sizes on either side of a tile, of a remainder and of
 the line between two kernels, against the oracle with the tolerances of test_gpu_parity."""
+import math
+
 import pytest
 import torch
 
@@ -69,6 +71,36 @@ def test_strided_queries_in_the_pipelined_selection(s3r, views, tpv, topk):  # n
     got = run_device(s3r, big[:, 0], big[:, 1], big[:, 2], 64, topk)
     for key in ("idx", "o_comp", "out", "o_sel", "lse"):   # the same arithmetic on the same values
         assert torch.equal(got[key], want[key]), key
+
+
+@pytest.mark.parametrize("n_blk,kk", [(8, 3), (9, 8), (3000, 48)])   # edge iterations only; full ones; two pairs of waves
+def test_probabilities_waiting_while_the_maximum_rises(s3r, n_blk, kk):  # noqa: F811
+    """Pipelined selection: the running maximum rises by just under 9 (powers of two) while the probabilities of the
+    block before still wait for their product with V.  These are 128 and the factor is 1.00385 / 512, the worst for
+    a second rounding to bf16 (0.4 %), which the row sum would not share.  The weights of that block (V = 1) and of the
+    one that raises the maximum (V = -1) all but cancel, so that it would show as 1.9e-3.  The single roundings
+    left are below 1e-4: 128 (1 + 4e-5) to 128, 1 / 1.00385 to 0.99609."""
+    n_tok, f64 = 64 * n_blk, torch.float64
+    level = torch.full((n_tok,), -40.0, dtype=f64)     # log2 of a key's weight
+    v_of = torch.zeros(n_tok, dtype=f64)
+    order = [0, 1, 2] if kk < 40 else [0, 2, 4]        # two pairs take the blocks of a list in turn
+    base, mid, top = (order[i] * 64 for i in range(3))
+    level[base:base + 64] = 0.0
+    level[mid:mid + 64], v_of[mid:mid + 64] = 7.0, 1.0
+    level[top:top + 16], v_of[top:top + 16] = 9.0 - math.log2(1.00385), -1.0
+    s = level * math.log(2.0)                          # q.k / 8 in two bf16 parts
+    hi = s.to(torch.bfloat16)
+    k = torch.zeros((n_tok, 1, 64), dtype=torch.bfloat16)
+    k[:, 0, 0], k[:, 0, 1] = hi, (s - hi.to(f64)).to(torch.bfloat16)
+    q = torch.zeros_like(k)
+    q[:, 0, :2] = 8.0
+    v = v_of.to(torch.bfloat16)[:, None, None].expand(n_tok, 1, 64).contiguous()
+    idx = torch.arange(kk, dtype=torch.int32).expand(1, n_blk, kk).contiguous()
+    out = torch.full_like(q, float("nan")).cuda()
+    s3r.speed3r_select_attn(q.cuda(), k.cuda(), v.cuda(), idx.cuda(), out, 64)
+    w = torch.exp(k[:64 * kk, 0, :2].to(f64).sum(-1))
+    want = ((w * v_of[:64 * kk]).sum() / w.sum()).item()
+    assert (out.double().cpu() - want).abs().max().item() < 2e-4
 
 
 @pytest.mark.parametrize("n_blk", [127, 511, 512, 513, 545])   # up to 512 blocks the candidate lists cannot run over
