@@ -170,19 +170,24 @@ __global__ __launch_bounds__(256, OCC) void select_direct_kernel(
                 if constexpr (B == 16) sacc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x, sacc[b], 0, 0, 0);
                 else sacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, x, sacc[b], 0, 0, 0);
             };
+            // Products of the smaller parts first: what their sums lose is rounding of their own size, and only the products
+            // of the high parts are added up at the size of the score.  With each step's products together, o_sel
+            // of blocks of 16 was 3.68e-6 off 64 bits on outlier keys (12 x 1374, top-40), 3.57e-6 with q 16 times as large;
+            // in this order it is 3.62e-6 and 2.74e-6, in the same time (32x32x16 products, step by step: 3.66e-6, 3.39e-6).
+            if constexpr (F32) {
+#pragma unroll
+                for (int o = 2; o > 0; --o)
+#pragma unroll
+                    for (int s = 0; s < KS; ++s)
+#pragma unroll
+                        for (int a = 0; a <= o; ++a)
+#pragma unroll
+                            for (int b = 0; b < NBU; ++b) mfma_s(b, kf[b][a][s], qf[o - a][s]);
+            }
 #pragma unroll
             for (int s = 0; s < KS; ++s)
 #pragma unroll
-                for (int b = 0; b < NBU; ++b) {
-                    mfma_s(b, kf[b][0][s], qf[0][s]);
-                    if constexpr (F32) {
-                        mfma_s(b, kf[b][0][s], qf[1][s]);
-                        mfma_s(b, kf[b][1][s], qf[0][s]);
-                        mfma_s(b, kf[b][0][s], qf[2][s]);
-                        mfma_s(b, kf[b][1][s], qf[1][s]);
-                        mfma_s(b, kf[b][2][s], qf[0][s]);
-                    }
-                }
+                for (int b = 0; b < NBU; ++b) mfma_s(b, kf[b][0][s], qf[0][s]);
             if (u + 1 < n_units) load_k(u + 1);
             if (((is_short >> (u * NBU)) & ((1ull << NBU) - 1ull)) != 0ull) {  // keys that do not exist
                 asm volatile("" ::: "memory");  // keep this rare path a real branch

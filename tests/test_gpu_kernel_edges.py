@@ -73,6 +73,26 @@ def test_strided_queries_in_the_pipelined_selection(s3r, views, tpv, topk):  # n
         assert torch.equal(got[key], want[key]), key
 
 
+@pytest.mark.parametrize("block", [16, 32])
+def test_scores_of_small_fp32_blocks_are_added_up_exactly_enough(s3r, block):  # noqa: F811
+    """Peaked softmaxes over outlier keys (scores of some hundred): the rounding of the scores shows.  Two bf16 parts of
+    P and V leave 2.7e-6; scores that round each of their partial products at full size bring it to 3.4e-6 and more."""
+    wl = workloads.Workload(f"sums_{block}", 12, 1374, 4, 64, "f32", block, 40, 100, "outliers")
+    q, k, v = workloads.make_inputs(wl, device="cuda")
+    q.mul_(16.0)
+    res = run_device(s3r, q, k, v, block, 40)
+    off = total = 0.0
+    for h in range(wl.heads):
+        qh, kh, vh = (x[:, h].double() for x in (q, k, v))
+        for b in range(0, wl.n_tok // block, 16):
+            keys = (res["idx"][h, b].long()[:, None] * block + torch.arange(block, device="cuda")).reshape(-1)
+            keys = keys[keys < wl.n_tok]
+            want = torch.softmax(qh[block * b:block * (b + 1)] @ kh[keys].T / 8.0, dim=-1) @ vh[keys]
+            off += (res["o_sel"][block * b:block * (b + 1), h].double() - want).square().sum().item()
+            total += want.square().sum().item()
+    assert math.sqrt(off / total) < 3.0e-6
+
+
 @pytest.mark.parametrize("n_blk,kk", [(8, 3), (9, 8), (3000, 48)])   # edge iterations only; full ones; two pairs of waves
 def test_probabilities_waiting_while_the_maximum_rises(s3r, n_blk, kk):  # noqa: F811
     """Pipelined selection: the running maximum rises by just under 9 (powers of two) while the probabilities of the
