@@ -6,16 +6,17 @@ import pytest
 import torch
 
 from paper_2603_08055_amd import workloads
-from tests.parity_util import compare_with_oracle, log, run_device, to_host_f32
+from tests.parity_util import (compare_windows_with_oracle, compare_with_oracle, log, run_device, special_row_splits,
+                               to_host_f32)
 from tests.test_gpu_parity import layer_case, s3r  # noqa: F401  (s3r: fixture)
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype,block,views,tpv,special,heads", [
-    ("bf16", 16, 1, 230, 6, 2),       # 14 blocks = 3.5 units + 1 special unit: the last unit of a split is short
+    ("bf16", 16, 1, 530, 6, 2),       # 33 blocks = 8 units and a quarter: the last split ends in a short unit and the special one
     ("bf16", 16, 2, 250, 3, 1),       # 8 + 1 units, two splits; the second ends in the special-token segment
-    ("bf16", 32, 3, 401, 2, 3),       # blocks of 32, odd number of them
+    ("bf16", 32, 3, 434, 2, 3),       # blocks of 32, an odd number of them (41): half a unit in the last split
     ("bf16", 16, 5, 611, 61, 2),      # 305 special rows: three row groups, five special units
     ("bf16", 64, 2, 700, 1, 1),       # one row group of two rows over many splits
     ("f32", 32, 2, 411, 2, 2),        # fp32 operand parts
@@ -23,7 +24,30 @@ pytestmark = pytest.mark.gpu
 def test_special_rows_in_key_splits(s3r, oracle, dtype, block, views, tpv, special, heads):  # noqa: F811
     wl = workloads.Workload(f"splits_{dtype}_{block}_{views}x{tpv}_{special}", views, tpv, heads, 64, dtype, block, 3,
                             93, "normal")
+    assert special_row_splits(s3r, views, tpv, special, heads, block, dtype) > 1
     layer_case(s3r, oracle, wl, special, with_gate=True)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("views,special,grid", [
+    (4, 3, (13, 11, 4)),              # 48 windows of 16, 12, 4 and 3 cells: the lengths of units past the first split
+    (6, 1, (9, 11, 4)),               # 54 windows: half a unit at the end
+    (2, 5, (37, 37, 4)),              # 200 windows over many splits
+    (4, 3, (13, 11, 8)),              # 8 x 8 windows
+])
+def test_special_rows_in_key_splits_over_windows(s3r, oracle, dtype, views, special, grid):  # noqa: F811
+    grid_h, grid_w, window = grid
+    tpv, heads = special + grid_h * grid_w, 2
+    wl = workloads.Workload(f"splits_windows_{dtype}_{views}x{grid_h}x{grid_w}_w{window}", views, tpv, heads, 64, dtype,
+                            window * window, 3, 101, "normal")
+    assert special_row_splits(s3r, views, tpv, special, heads, wl.block, dtype, grid) > 1
+    q, k, v = workloads.make_inputs(wl)
+    gate = workloads.make_gate_logits(wl)
+    res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), wl.block, 3, gate=gate.cuda(), tokens_per_view=tpv,
+                     special_per_view=special, grid=grid)
+    log(f"{wl.name}: " + str(compare_windows_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v),
+                                                         to_host_f32(gate), 3, dtype, views, tpv, special, grid,
+                                                         label=wl.name)))
 
 
 @pytest.mark.parametrize("dtype,block", [("bf16", 16), ("bf16", 64), ("f32", 32), ("f32", 64)])
@@ -62,13 +86,23 @@ def test_selection_of_small_blocks(s3r, oracle, dtype, block, n_tok, topk, heads
                                                  to_host_f32(gate), block, topk, dtype, label=wl.name)))
 
 
+@pytest.mark.parametrize("layout", ["one projection", "head major", "padded heads"])
 @pytest.mark.parametrize("views,tpv,topk", [(3, 1000, 39), (150, 1281, 40)])   # one and two pairs of waves per query block
-def test_strided_queries_in_the_pipelined_selection(s3r, views, tpv, topk):  # noqa: F811
-    wl = workloads.Workload(f"pipe_strided_{views}", views, tpv, 1, 64, "bf16", 64, topk, 95, "normal")
-    q, k, v = workloads.make_inputs(wl, device="cuda")
-    big = torch.stack([q, k, v], dim=1)
-    want = run_device(s3r, q, k, v, 64, topk)
-    got = run_device(s3r, big[:, 0], big[:, 1], big[:, 2], 64, topk)
+def test_strided_queries_in_the_pipelined_selection(s3r, views, tpv, topk, layout):  # noqa: F811
+    heads = 3
+    wl = workloads.Workload(f"pipe_strided_{views}", views, tpv, heads, 64, "bf16", 64, topk, 95, "normal")
+    tensors = workloads.make_inputs(wl, device="cuda")
+    if layout == "one projection":
+        big = torch.stack(tensors, dim=1)
+        strided = [big[:, i] for i in range(3)]
+    elif layout == "head major":
+        strided = [t.permute(1, 0, 2).contiguous().permute(1, 0, 2) for t in tensors]
+    else:
+        strided = [torch.full((wl.n_tok, heads, 80), float("nan"), dtype=t.dtype, device="cuda")[:, :, :64].copy_(t)
+                   for t in tensors]
+    assert not strided[0].is_contiguous()
+    want = run_device(s3r, *tensors, 64, topk)
+    got = run_device(s3r, *strided, 64, topk)
     for key in ("idx", "o_comp", "out", "o_sel", "lse"):   # the same arithmetic on the same values
         assert torch.equal(got[key], want[key]), key
 

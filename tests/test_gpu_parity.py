@@ -693,7 +693,7 @@ def test_forced_blocks_view_stride_sampled_rows(s3r, oracle):
 
 
 @pytest.mark.parametrize("dtype,block,n_tok,topk,forced", [
-    ("f32", 16, 333, 4, [0, 1, 20]),                 # generic kernels, ragged tail, last block forced
+    ("f32", 16, 333, 4, [0, 1, 20]),                 # ragged tail, last block forced
     ("f32", 64, 1000, 3, [5]),
     ("f32", 128, 1100, 2, [0, 8]),                   # fp32 on the matrix cores, two units per block, ragged tail
     ("bf16", 64, 1000, 5, [0, 3, 4, 15]),            # 16 blocks; last (ragged) one forced
@@ -766,7 +766,7 @@ def test_special_tokens_vggt_8_views(s3r, oracle):
 
 
 @pytest.mark.parametrize("dtype,block,views,tpv,special,topk", [
-    ("f32", 16, 3, 111, 2, 3),           # generic kernels, blocks straddle views, ragged tail
+    ("f32", 16, 3, 111, 2, 3),           # blocks straddle views, ragged tail
     ("f32", 64, 2, 300, 7, 2),
     ("f32", 64, 1, 1000, 100, 3),        # fp32 operand pairs: special rows over two key segments, two special units
     ("f32", 128, 3, 700, 5, 2),
@@ -834,10 +834,10 @@ def test_special_tokens_untouched_outputs_and_zero_special(s3r):
     ("bf16", 2, 0, 37, 37, 8, 4, None),        # the pi3 layout: no special tokens
     ("bf16", 4, 1, 16, 24, 8, 3, None),        # windows divide the grid: every block full
     ("bf16", 2, 5, 37, 37, 8, 5, [0, 4, 24]),  # forced windows incl. the corner one of view 0
-    ("f32", 2, 2, 9, 10, 4, 3, None),          # 4 x 4 windows (block 16): generic kernels
+    ("f32", 2, 2, 9, 10, 4, 3, None),          # 4 x 4 windows (block 16) in fp32
     ("f32", 3, 0, 8, 8, 4, 2, [1]),
     ("f32", 2, 5, 37, 37, 8, 5, [0, 4, 24]),   # fp32 on the matrix cores: cut windows, special rows, forced windows
-    ("bf16", 2, 3, 11, 13, 4, 4, None),        # block 16 in bf16: generic kernels
+    ("bf16", 2, 3, 11, 13, 4, 4, None),        # block 16 in bf16
     ("bf16", 1, 0, 5, 5, 8, 1, None),          # a single cut window
 ])
 def test_spatial_windows(s3r, oracle, dtype, views, special, grid_h, grid_w, window, topk, forced):
@@ -1055,7 +1055,7 @@ def test_token_queries_leave_everything_else_unchanged_and_reject_bad_values(s3r
     ("bf16", 64, 4, 333, 5, 4, None, "packed_qkv"),        # special tokens: both pooling launches and the dense rows
     ("bf16", 128, 3, 500, 0, 2, None, "head_major"),       # [heads, n_tok, 64] seen as [n_tok, heads, 64]
     ("bf16", 16, 2, 3 + 11 * 13, 3, 4, (11, 13, 4), "padded_heads"),   # windows; heads padded to 96 channels
-    ("f32", 64, 2, 300, 7, 2, None, "packed_qkv"),         # generic kernels: k and v follow the same strides
+    ("f32", 64, 2, 300, 7, 2, None, "packed_qkv"),         # fp32: k and v follow the same strides
     ("f32", 16, 3, 111, 0, 3, None, "head_major"),
 ])
 def test_strided_inputs_match_packed_inputs(s3r, oracle, dtype, block, views, tpv, special, topk, grid, layout):
