@@ -240,9 +240,10 @@ def main():
     sel_ms = stage_ms["select"] / max(stage_n["select"], 1)
     achieved = sel_flops / (sel_ms * 1e-3) / 1e12
     traffic = None if (args.special or n_forced or args.compress_queries or args.kernel_choice) else measured_traffic(wl)
-    pipe = (args.kernel_choice != 1 and wl.dtype == "bf16" and wl.block == 64 and kk <= 128 and not args.special
+    pipe = (args.kernel_choice != 1 and wl.dtype == "bf16" and wl.block == 64 and kk <= 128
             and not args.compress_queries and not (kk > 96 and 2 * n_forced >= kk))
     roofline = {"kernel": ("select_generic_kernel" if args.kernel_choice == 1 else
+                           "select_direct_kernel" if wl.block in (16, 32) else
                            "select_pipe_kernel" if pipe else "select_mfma_kernel"),
                 "bound": "mfma", "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / MFMA_BF16_PEAK_TFLOPS,

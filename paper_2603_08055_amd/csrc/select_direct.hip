@@ -5,17 +5,19 @@
 // one query block and shares its K/V with nobody: staging units in LDS, as the kernels for larger blocks do to
 // share them between waves, would only take the LDS that limits how many waves a CU holds.  The operand-order
 // copies written by the pooling kernel are read with plain vector loads, one contiguous run per operand, and the
-// waves of a CU (16, against 5 with a 32 KiB ring each) hide each other's latency.
+// waves of a CU hide each other's latency: by their registers 12 for blocks of 16 in bf16, 8 for 32 in bf16 and for 16
+// in fp32, 4 for 32 in fp32, against 5 with a 32 KiB ring each (two in fp32).
 //   scores      S^T[key][query] = K Q^T: 16x16x32 MFMAs for blocks of 16 (two per block), 32x32x16 for 32 (four)
 //   softmax     keys of ONE query per lane: in-lane reductions and one (32) or two (16) exchanges between lanes
 //   P.V         O^T[channel][query] += V^T P^T: the probabilities sit in the operand order of 16x16x16 (32x32x16)
 // A 16-token block's tiles (pool.hip) are half tiles of the 32-row layout; what a 16x16 operand needs of them is
 // again one contiguous KiB (K) or two runs of 256 bytes (V) per load instruction.
 //
-// Bound.  The ring kernel ran at 7000 cycles per 64-key unit and wave with 1.25 waves per SIMD: a serial chain, the
+// Bound.  The ring kernel ran at 7000 cycles per 64-key unit and wave with one wave per SIMD: a serial chain, the
 // matrix pipe 7 % and the vector ALU 30 % busy, half of both for columns that hold no query (blocks of 16).  Now i.i.d.
 // keys are delivered at the 7.8 TB/s the fabric has for L2 misses; with keys that neighbouring query blocks share
-// (78 % L2 hits at 100 views in 4 x 4 windows) the units arrive at 18 TB/s, and what is left is vector work and issue.
+// (74 % L2 hits at 100 views in 4 x 4 windows) 21 GB of tiles arrive in 1.32 ms, 16 TB/s, with 2.8 waves per SIMD, the
+// matrix pipe 16 % and the vector ALU 43 % busy: what is left is vector work, issue and the latency of the loads.
 //
 // Pipelining.  NBU blocks are worked on at a time; the K of the next ones is requested as soon as the scores have
 // consumed the registers of the current ones, V after P.V likewise, and the compiler's own counts wait for them.

