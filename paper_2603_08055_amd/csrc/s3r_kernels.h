@@ -207,7 +207,8 @@ hipError_t launch_select_generic(const SelectArgs &a, hipStream_t stream);
 // bf16 MFMA kernels (any supported block size).
 hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream);
 
-// bf16 MFMA selection for plain index rows (at most 128 blocks of 64 tokens each, per-block compressed outputs): few workgroups per CU, each wave software-pipelined (launch_select_mfma routes here).
+// bf16 MFMA selection for plain index rows (at most 128 blocks of 64 tokens each, per-block compressed outputs):
+// few workgroups per CU, each wave software-pipelined (launch_select_mfma routes here).
 hipError_t launch_select_pipe(const SelectArgs &a, hipStream_t stream);
 
 // MFMA selection for blocks of 16 and 32 tokens, bf16 and fp32: one wave per query block, operands straight to
