@@ -1,0 +1,208 @@
+// Compression branch and TopK (Sec. 3.2, eqs. 3-4 and "Selection Branch") for short sequences of pooled blocks, in one
+// launch: block scores, compressed attention and the index lists straight from the pooled means.
+//
+// What bounds it.  With a few hundred pooled blocks the products are a fraction of a microsecond; what the sweeps of
+// compress.hip cost there is a chain of five launches (statistics, operand tiles, threshold sweep, filter sweep,
+// candidates), each a few waves long and each waiting for the one before.  Here a row of scores fits in LDS, so no bound,
+// no candidates and no operand tiles are needed: one workgroup takes 16 pooled queries of a head and goes through
+//   scores    S = Qc Kc^T, 16 keys per wave and step, fp32 MFMAs (16x16x4) on the fp32 means themselves
+//   rows      one wave per query: softmax over its row, and the k largest scores by a bitwise search with wave ballots
+//   P.V       Oc' = P Vc, each wave 16 channels of a quarter of the keys, partial sums added up in LDS
+// The fp32 matrix pipe is 1/16 as fast as the bf16 one, and still not what the time goes into; scores and
+// probabilities are fp32 throughout, at least as exact as the two-part and fp16 scores of the sweeps.
+// Measured (MI355X, whole call, the launches this one took the place of -> this one): see launch_compress_small.
+#include "s3r_device.h"
+#include "s3r_kernels.h"
+
+namespace s3r {
+
+constexpr int kSmallQ = 16;      // pooled queries of a workgroup
+constexpr int kSmallWaves = 16;  // one per query in the row phase
+
+__device__ __forceinline__ float wave_max(float x)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) x = fmaxf(x, __shfl_xor(x, d, 64));
+    return x;
+}
+
+__device__ __forceinline__ float wave_sum(float x)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) x += __shfl_xor(x, d, 64);
+    return x;
+}
+
+// NV: score registers of a lane, n_blk <= 64 NV.  grid: (ceil(n_blk / 16), heads)
+template <int NV>
+__global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
+    const float *__restrict__ qc, const float *__restrict__ kc, const float *__restrict__ vc,
+    float *__restrict__ o_comp, int32_t *__restrict__ idx, int n_blk, int k, float scale_log2,
+    const unsigned long long *__restrict__ forced_words)
+{
+    // (+ 4: the rows that a wave writes or reads at a time start in different banks, 16-byte aligned)
+    constexpr int kStride = NV * 64 + 4;
+    __shared__ __attribute__((aligned(16))) float s[kSmallQ][kStride];       // scores, then probabilities
+    __shared__ float part[4][kSmallQ][68];                                   // P.V of a quarter of the keys each
+    __shared__ float inv_sum[kSmallQ];
+
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = blockIdx.y, q0 = blockIdx.x * kSmallQ;
+    const int64_t head = static_cast<int64_t>(h) * n_blk * 64;
+    const int n_tiles = (n_blk + 15) / 16;
+
+    // ---- scores.  Operands of step t: channel 16 g + t of row `col`, so that a lane reads 64 contiguous bytes of a row
+    // (the order of the channels in a sum is free).  Rows past the end repeat the last one; nothing of them is kept.
+    {
+        float a[16];
+        const float *qrow = qc + head + static_cast<int64_t>(q0 + col < n_blk ? q0 + col : n_blk - 1) * 64 + 16 * g;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const floatx4 f = *reinterpret_cast<const floatx4 *>(qrow + 4 * c);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[4 * c + i] = f[i];
+        }
+        for (int kt = wave; kt < n_tiles; kt += kSmallWaves) {
+            const int key = kt * 16 + col;
+            const float *krow = kc + head + static_cast<int64_t>(key < n_blk ? key : n_blk - 1) * 64 + 16 * g;
+            floatx4 f[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) f[c] = *reinterpret_cast<const floatx4 *>(krow + 4 * c);
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < 16; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], f[t >> 2][t & 3], acc, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s[4 * g + r][key] = acc[r];
+        }
+    }
+    // Values of the first steps of P.V, requested early: their latency runs under the row phase.
+    const int ct = wave & 3, kq = wave >> 2;  // 16 channels; every fourth run of 16 keys
+    constexpr int kEarly = NV < 4 ? NV : 4;
+    float v[kEarly][4];
+    const float *vcol = vc + head + 16 * ct + col;
+    auto value = [&](int run, int i) -> float {
+        const int key = run * 16 + 4 * g + i;
+        return key < n_blk ? vcol[static_cast<int64_t>(key) * 64] : 0.f;
+    };
+#pragma unroll
+    for (int e = 0; e < kEarly; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[e][i] = value(kq + 4 * e, i);
+    __syncthreads();
+
+    // ---- one row per wave
+    const int row = q0 + wave;
+    {
+        float x[NV];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+            const int key = 64 * t + lane;
+            x[t] = key < n_blk ? s[wave][key] : -INFINITY;
+            mx = fmaxf(mx, x[t]);
+        }
+        mx = wave_max(mx);
+        float sum = 0.f;
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {  // (keys that do not exist: probability 0)
+            const float p = fast_exp2((x[t] - mx) * scale_log2);
+            s[wave][64 * t + lane] = p;
+            sum += p;
+        }
+        sum = wave_sum(sum);
+        if (lane == 0) inv_sum[wave] = 1.f / sum;
+        if (k > 0 && row < n_blk) {  // wave-uniform
+            // order-preserving keys; 0 for blocks that do not take part: past the end, or forced (Sec. 3.3)
+            uint32_t key[NV];
+#pragma unroll
+            for (int t = 0; t < NV; ++t) {
+                uint32_t o = order_key(x[t]);
+                o = o > 1u ? o : 1u;
+                bool out = 64 * t + lane >= n_blk;
+                if (forced_words != nullptr && 64 * t < n_blk) out = out || ((forced_words[t] >> lane) & 1ull) != 0ull;
+                key[t] = out ? 0u : o;
+            }
+            // k-th largest key, bit by bit; done as soon as exactly k keys are at or above the trial value
+            uint32_t T = 0u;
+            bool exact = false;
+            for (int bit = 31; bit >= 0; --bit) {
+                const uint32_t trial = T | (1u << bit);
+                int c = 0;
+#pragma unroll
+                for (int t = 0; t < NV; ++t) c += __popcll(__ballot(key[t] >= trial));
+                if (c >= k) T = trial;
+                if (c == k) { exact = true; break; }
+            }
+            int ties = n_blk;  // how many keys equal to T are taken, the smallest indices first
+            if (!exact) {
+                ties = k;
+#pragma unroll
+                for (int t = 0; t < NV; ++t) ties -= __popcll(__ballot(key[t] > T));
+            }
+            int n_out = 0, n_eq = 0;
+            int32_t *dst = idx + (static_cast<int64_t>(h) * n_blk + row) * k;
+#pragma unroll
+            for (int t = 0; t < NV; ++t) {
+                const bool eq = key[t] == T;
+                const unsigned long long eq_mask = __ballot(eq);
+                const bool take = key[t] > T || (eq && n_eq + lanes_below(eq_mask) < ties);
+                const unsigned long long mask = __ballot(take);
+                if (take) dst[n_out + lanes_below(mask)] = 64 * t + lane;
+                n_out += __popcll(mask);
+                n_eq += __popcll(eq_mask);
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- P.V: 16 keys per step, key 4 g + i of the run in MFMA i
+    {
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        auto step = [&](int run, const float (&w)[4]) __attribute__((always_inline)) {
+            const floatx4 p = *reinterpret_cast<const floatx4 *>(&s[col][run * 16 + 4 * g]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(p[i], w[i], acc, 0, 0, 0);
+        };
+#pragma unroll
+        for (int e = 0; e < kEarly; ++e)
+            if (kq + 4 * e < n_tiles) step(kq + 4 * e, v[e]);  // wave-uniform
+        for (int run = kq + 4 * kEarly; run < n_tiles; run += 4) {
+            float w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = value(run, i);
+            step(run, w);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[kq][4 * g + r][16 * ct + col] = acc[r];
+    }
+    __syncthreads();
+    if (row < n_blk) {
+        const float o = (part[0][wave][lane] + part[1][wave][lane]) + (part[2][wave][lane] + part[3][wave][lane]);
+        o_comp[head + static_cast<int64_t>(row) * 64 + lane] = o * inv_sum[wave];
+    }
+}
+
+hipError_t launch_compress_small(const float *qc, const float *kc, const float *vc, float *o_comp, int32_t *idx,
+                                 int64_t n_blk, int heads, int k, float scale, const unsigned long long *forced_words,
+                                 hipStream_t stream)
+{
+    if (n_blk < 1 || n_blk > kSmallMaxBlk || heads < 1 || heads > 65535 || k < 0 || k > n_blk) return hipErrorInvalidValue;
+    if (k > 0 && idx == nullptr) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<unsigned>((n_blk + kSmallQ - 1) / kSmallQ), static_cast<unsigned>(heads));
+#define S3R_SMALL(NV)                                                                                                   \
+    if (n_blk <= (NV) * 64) {                                                                                           \
+        hipLaunchKernelGGL(compress_small_kernel<NV>, grid, dim3(kSmallWaves * 64), 0, stream, qc, kc, vc, o_comp, idx, \
+                           static_cast<int>(n_blk), k, scale * kLog2e, forced_words);                                   \
+        return hipGetLastError();                                                                                       \
+    }
+    S3R_SMALL(1)
+    S3R_SMALL(2)
+    S3R_SMALL(4)
+    S3R_SMALL(8)
+    S3R_SMALL(16)
+#undef S3R_SMALL
+    return hipErrorInvalidValue;
+}
+
+}  // namespace s3r

@@ -24,6 +24,15 @@
 // and brings nothing: the work mapping already runs neighbours on the same XCD at the same time,
 // so their shared key blocks hit in that XCD's L2.
 //
+// What else binds: power.  Under these loops the clock falls to 1.8 to 2.0 GHz, and every vector instruction taken out of
+// a unit shows as a lower clock as much as in fewer cycles (dense attention of 21 984 rows, 16 heads: 36.5 million
+// cycles at 2.03 GHz -> 29.7 at 1.80, 2.24 -> 2.06 ms; without the exponentials 24.6 at 1.65).  So the loop is kept to the
+// instructions that the softmax needs (115 of a unit's vector instructions, 144 before): addresses on the scalar unit, no
+// exchange between the lanes of a query unless the maximum rises, the row sum in running chains, and masks that hold no
+// registers when they are not needed (162 -> 108, four waves per SIMD).  Measured and not kept, all within 1 %: LDS
+// operands read 4 or 8 ahead, P.V in the gaps of the exponentials, 256 or 512 query rows per workgroup (a half or a
+// quarter of the traffic into LDS, and as much more time spent waiting at its barriers).
+//
 // Softmax.  The running row maximum is only raised when a unit exceeds it by more than
 // kRescaleSlack (log2 units), so the rescale of the output accumulators is skipped for almost every
 // unit; probabilities then range up to 2^kRescaleSlack, which fp32 sums and bf16 operands carry as
@@ -125,7 +134,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
     if constexpr (EXTRA && DENSE)
         if (x.q_blk_len != nullptr && row_valid) row_valid = t % x.q_block < x.q_blk_len[t / x.q_block];
     const int64_t trow = qmap.row(row_valid ? t : 0);  // the caller's row of this query
-    // Q.  Dense attention (rings of three stages, two units on their way while one is worked on) loads it with
+    // Q.  Dense attention loads it with
     // inline-asm loads that carry their wait in the same statement: the compiler does not count the LDS-direct
     // loads of the key units, so a wait of its own for a load it knows of comes out as vmcnt(0), and with Q
     // loaded in plain code that wait lands in front of the first MFMA of the loop, in every iteration, where it
@@ -191,19 +200,21 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         qb[2] = __builtin_bit_cast(bf16x8, row_valid ? q2 : zero);
         qb[3] = __builtin_bit_cast(bf16x8, row_valid ? q3 : zero);
     };
-    const int64_t n_units1 = SMALL ? (n_blk + (1 << bpu_shift) - 1) >> bpu_shift
-                                   : (n_keys + kUnitKeys - 1) / kUnitKeys;  // units of the first key segment
-    const int64_t n_units2 = (n_keys2 + kUnitKeys - 1) / kUnitKeys;    // dense only: second segment
+    const int n_units1 = static_cast<int>(SMALL ? (n_blk + (1 << bpu_shift) - 1) >> bpu_shift
+                                                : (n_keys + kUnitKeys - 1) / kUnitKeys);  // units of the first key segment
+    const int n_units2 = static_cast<int>((n_keys2 + kUnitKeys - 1) / kUnitKeys);    // dense only: second segment
+    // units all of whose 64 keys exist, of either segment, when blocks are runs of the sequence
+    const int n_full1 = static_cast<int>(n_keys / kUnitKeys), n_full2 = static_cast<int>(n_keys2 / kUnitKeys);
 
     // ---- the list of key blocks this workgroup visits ---------------------------------------
     int n_steps;  // units to process (host side keeps this below 2^31)
     int u_begin = 0;  // dense attention: first unit
     const int32_t *sel = nullptr;
     if constexpr (DENSE) {
-        n_steps = static_cast<int>(n_units1 + n_units2);
+        n_steps = n_units1 + n_units2;
         if constexpr (EXTRA) {  // key splits: units [u_begin, u_begin + n_steps)
             if (x.n_split > 1) {
-                const int64_t u_all = n_units1 + n_units2;
+                const int64_t u_all = static_cast<int64_t>(n_units1) + n_units2;
                 u_begin = static_cast<int>(u_all * split / x.n_split);
                 n_steps = static_cast<int>(u_all * (split + 1) / x.n_split) - u_begin;
             }
@@ -297,7 +308,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
             }
             return;
         }
-        const int64_t w = unit_of(s);
+        const int w = unit_of(s);
         if constexpr (F32) {  // chunk = 16 * part + (0..7: K, 8..15: V), part 0 = hi, 1 = lo, 2 = lo2 (K only)
             const bool second = DENSE && w >= n_units1;
             const int64_t wu = second ? w - n_units1 : w;
@@ -311,14 +322,13 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
             }
             return;
         }
-        // all chunks of a wave are of one kind (K or V) here
-        static_assert(SMALL || F32 || CPW <= 8, "a wave's chunks must be all K or all V");
-        const bf16_t *unit = (DENSE && w >= n_units1) ? seg2 + (w - n_units1) * kUnitElems : seg1 + w * kUnitElems;
-#pragma unroll
-        for (int c = 0; c < CPW; ++c) {
-            const int chunk = wave * CPW + c;  // 0..7: K, 8..15: V
-            lds_dma_16(unit + (chunk & 7) * 512 + lane * 8, __builtin_amdgcn_readfirstlane(stage_byte + chunk * 1024));
-        }
+        // all chunks of a wave are of one kind (K or V) here: runs of 4 KiB with a wave-uniform start
+        static_assert(SMALL || F32 || CPW == 4 || CPW == 8, "a wave's chunks must be all K or all V");
+        const bool second = DENSE && w >= n_units1;
+        const bf16_t *unit = (second ? seg2 : seg1) + static_cast<int64_t>(second ? w - n_units1 : w) * kUnitElems + ((wave * CPW) & 7) * 512;
+        const unsigned dst = stage_byte + wave * (CPW * 1024);
+        lds_dma_16_x4(unit, lane * 16, dst);
+        if constexpr (CPW == 8) lds_dma_16_x4(unit, lane * 16 + 4096, dst + 4096);
     };
 
     floatx16 oacc[2];
@@ -326,8 +336,19 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
-    float m_run = -1e30f, l_run = 0.f;
+    float m_run = -1e30f;
+    float m_lim = -1e30f + kRescaleSlack;      // what a unit's largest logit must exceed to raise m_run
+    float l_run[4] = {0.f, 0.f, 0.f, 0.f};     // the row sum in four chains
 
+    // how many of unit w's 64 keys exist, 64 or more: all (wave-uniform)
+    auto unit_left = [&](int w) -> int {
+        if (DENSE && w >= n_units1) return w - n_units1 < n_full2 ? kUnitKeys : static_cast<int>(n_keys2) - (w - n_units1) * kUnitKeys;
+        if (blk_len != nullptr) return blk_len[w >> upb_shift] - (w & upb_mask) * kUnitKeys;  // wave-uniform load
+        return w < n_full1 ? kUnitKeys : static_cast<int>(n_keys - static_cast<int64_t>(w) * kUnitKeys);
+    };
+    auto first_keys = [](int left) -> unsigned long long {
+        return left >= kUnitKeys ? ~0ull : left <= 0 ? 0ull : (1ull << left) - 1ull;
+    };
     // which of the 64 keys of step s's unit exist (wave-uniform)
     auto unit_mask = [&](int s) -> unsigned long long {
         if (SMALL && s + u_begin < n_units1) {
@@ -341,22 +362,20 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
                 }
             return vm;
         }
-        const int64_t w = unit_of(s);
-        int64_t left;
-        if (DENSE && w >= n_units1) left = n_keys2 - (w - n_units1) * kUnitKeys;
-        else if (blk_len != nullptr) left = blk_len[w >> upb_shift] - (static_cast<int>(w) & upb_mask) * kUnitKeys;  // wave-uniform load
-        else left = n_keys - w * kUnitKeys;
-        return left >= kUnitKeys ? ~0ull : left <= 0 ? 0ull : (1ull << left) - 1ull;
+        const int w = unit_of(s);
+        return first_keys(unit_left(w));
     };
 
+    float lowest = -INFINITY;  // where the maxima start; the compiler takes two scores per v_max3 if it does not know the value
+    asm("" : "+v"(lowest));
+    lowest = fmaxf(lowest, lowest);
     floatx16 sacc[2];
     bf16x8 pb[4];  // probabilities of one unit as MFMA operands
     bf16x8 pl[F32 ? 4 : 1];  // F32: their lo parts
     const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     // S^T = K Q^T of the unit whose K sits in `ks`.  Selection: the two 32-key tiles take turns, so that
     // no MFMA waits for the one issued just before it (3 % faster at 64 blocks per row, 7 % at 288).
-    // Dense attention: one tile after the other; alternating takes a few registers more there, which
-    // costs a workgroup per CU (15 % slower), and with the register count capped the two orders tie.
+    // Dense attention: one tile after the other (the two orders tie).
     auto scores = [&](const bf16_t *ks) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -377,21 +396,27 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
     // keys past the end of a block or of the sequence do not exist
     auto mask_scores = [&](unsigned long long vmask) __attribute__((always_inline)) {
         asm volatile("" ::: "memory");    // keep this rare path a real branch
+        // In every run of 16 keys the first n exist; n compared with constants, because a bit test per register would
+        // have its 32 masks held in registers all through the loop (54 registers, a wave per SIMD fewer).
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int c = 0; c < 4; ++c) {
+            const int n = __builtin_popcount(static_cast<unsigned>(vmask >> (16 * c)) & 0xffffu) - 4 * g;
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (!((vmask >> (mt * 32 + acc_row(lane, r))) & 1ull)) sacc[mt][r] = -INFINITY;
+            for (int i = 0; i < 8; ++i)
+                if (8 * (i >> 2) + (i & 3) >= n) sacc[c >> 1][8 * (c & 1) + i] = -INFINITY;
+        }
     };
-    // the running maximum after a unit whose largest score (per lane) is mx
+    // The running maximum after a unit whose largest score (per lane) is mx.  The two lanes of a query look at their own
+    // halves of the unit; they exchange them only when either has to raise the maximum (rare after the first unit).
     auto raise_max = [&](float mx) __attribute__((always_inline)) {
-        const float m_tile = max_with_other_half(mx) * scale_log2;
-        const bool grow = m_tile > m_run + kRescaleSlack;
-        if (__any(grow)) {  // rare after the first unit: raise the maximum, rescale the accumulators
-            const float m_new = grow ? m_tile : m_run;
+        if (__builtin_expect(__any(mx * scale_log2 > m_lim), 0)) {
+            const float m_tile = max_with_other_half(mx) * scale_log2;
+            const float m_new = m_tile > m_lim ? m_tile : m_run;
             const float alpha = fast_exp2(m_run - m_new);
             m_run = m_new;
-            l_run *= alpha;
+            m_lim = m_new + kRescaleSlack;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) l_run[i] *= alpha;
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
@@ -401,16 +426,15 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
     // online softmax of sacc[X] -> pb[X]
     auto softmax = [&](unsigned long long vmask) __attribute__((always_inline)) {
         if (vmask != ~0ull) mask_scores(vmask);
-        float mx = sacc[0][0];
+        float mx[2] = {lowest, lowest};  // two chains of v_max3
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[mt][r]);
-        raise_max(mx);
+            for (int r = 0; r < 16; r += 2) mx[mt] = fmaxf(fmaxf(mx[mt], sacc[mt][r]), sacc[mt][r + 1]);
+        raise_max(fmaxf(mx[0], mx[1]));
         // The row sum adds the probabilities as the MFMA will see them (rounded to bf16), two per
         // v_dot2_f32_bf16 with a vector of ones: half the instructions of fp32 adds, and numerator and
         // denominator of the softmax then carry the same rounding.
-        float lsum[4] = {0.f, 0.f, 0.f, 0.f};
         if constexpr (F32) {  // probabilities in fp32, split into operand pairs; the row sum adds the fp32 values
 #pragma unroll
             for (int v = 0; v < 4; ++v)
@@ -418,11 +442,10 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
                 for (int i = 0; i < 8; ++i) {
                     const int mt = v >> 1, r = 8 * (v & 1) + i;
                     const float p = fast_exp2(sacc[mt][r] * scale_log2 - m_run);
-                    lsum[i & 3] += p;
+                    l_run[i & 3] += p;
                     pb[v][i] = static_cast<bf16_t>(p);
                     pl[v][i] = static_cast<bf16_t>(p - static_cast<float>(pb[v][i]));
                 }
-            l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
             return;
         }
         const bf16x2 ones = {static_cast<bf16_t>(1.f), static_cast<bf16_t>(1.f)};
@@ -433,11 +456,10 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
                 const int mt = v >> 1, r = 8 * (v & 1) + i;
                 const bf16x2 pr = {static_cast<bf16_t>(fast_exp2(sacc[mt][r] * scale_log2 - m_run)),
                                    static_cast<bf16_t>(fast_exp2(sacc[mt][r + 1] * scale_log2 - m_run))};
-                lsum[(i >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum[(i >> 1) & 3], false);
+                l_run[(i >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l_run[(i >> 1) & 3], false);
                 pb[v][i] = pr[0];
                 pb[v][i + 1] = pr[1];
             }
-        l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
     };
     // O^T += V^T P^T for the unit whose V sits in `vs`
     auto accumulate = [&](const bf16_t *vs) __attribute__((always_inline)) {
@@ -547,7 +569,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         for (int s = 0; s < 4; ++s) *reinterpret_cast<bf16x8 *>(out + (trow * heads + h) * 64 + 16 * s + 8 * g) = qb[s];
         return;
     }
-    const float l_tot = sum_with_other_half(l_run);
+    const float l_tot = sum_with_other_half((l_run[0] + l_run[1]) + (l_run[2] + l_run[3]));
     const float inv = (EXTRA && DENSE && l_tot == 0.f) ? 0.f : 1.f / l_tot;  // (a key split of empty units only)
     if (lse != nullptr && g == 0)
         lse[static_cast<int64_t>(h) * lse_stride + trow] = (m_run + __builtin_log2f(l_tot)) * kLn2;
@@ -701,8 +723,9 @@ hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream)
     if (a.qmap.period != 0 && a.n_tok > 0x7fffffffLL) return hipErrorInvalidValue;
     if (a.idx == nullptr) {
         if (a.n_keys2 > 0 && (a.kb2 == nullptr || a.vb2 == nullptr)) return hipErrorInvalidValue;
-        if (a.block == 64 || a.block == 128) return run_select<4, true, 3>(a, stream);
-        if (a.block == 16 || a.block == 32) return run_select<4, true, 3, true>(a, stream);
+        // two stages: 32 KiB let a CU hold four workgroups, three with a third stage (2.10 -> 2.06 ms at 21 984 rows, 16 heads)
+        if (a.block == 64 || a.block == 128) return run_select<4, true, 2>(a, stream);
+        if (a.block == 16 || a.block == 32) return run_select<4, true, 2, true>(a, stream);
         return hipErrorInvalidValue;
     }
     if (a.n_keys != a.n_tok || a.n_keys2 != 0) return hipErrorInvalidValue;  // selection: keys = the query sequence

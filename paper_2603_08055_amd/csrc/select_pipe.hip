@@ -153,7 +153,12 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
         for (int x = 0; x < 16; ++x) oacc[dt][x] = 0.f;
-    float m_run = -1e30f, l_run = 0.f;
+    float m_run = -1e30f;
+    float m_lim = -1e30f + kRescaleSlack;      // what a unit's largest logit must exceed to raise m_run
+    float l_run[4] = {0.f, 0.f, 0.f, 0.f};     // the row sum in four chains
+    float lowest = -INFINITY;  // where the maxima start; the compiler takes two scores per v_max3 if it does not know the value
+    asm("" : "+v"(lowest));
+    lowest = fmaxf(lowest, lowest);
     const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     floatx16 accs[2][2];  // scores, then probabilities, of unit j in accs[j & 1][32-key tile]
     bf16x8 ps[2][4];      // P(j) as MFMA operands in ps[j & 1][16-key step]
@@ -176,27 +181,35 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     auto soft_pre = [&](floatx16 (&acc)[2], unsigned long long vmask) __attribute__((always_inline)) -> bool {
         if (vmask != ~0ull) {
             asm volatile("" ::: "memory");  // keep this rare path a real branch
+            // In every run of 16 keys the first n exist; n compared with constants, because a bit test per register
+            // would have its 32 masks held in registers all through the loop (228 -> 181 registers; with the exchange
+            // of maxima left out and the row sum in running chains 2.12 -> 2.07 ms a call at 100 views, 43.2 -> 42.3 at
+            // 1000, 12.9 -> 12.4 with 46 forced blocks in rows of 110 at 200).
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
+            for (int c = 0; c < 4; ++c) {
+                const int n = __builtin_popcount(static_cast<unsigned>(vmask >> (16 * c)) & 0xffffu) - 4 * g;
 #pragma unroll
-                for (int x = 0; x < 16; ++x)
-                    if (!((vmask >> (mt * 32 + acc_row(lane, x))) & 1ull)) acc[mt][x] = -INFINITY;
+                for (int e = 0; e < 8; ++e)
+                    if (8 * (e >> 2) + (e & 3) >= n) acc[c >> 1][8 * (c & 1) + e] = -INFINITY;
+            }
         }
-        float mx4[4];  // four independent chains instead of one of 32 dependent instructions
+        float mx[2] = {lowest, lowest};  // two chains of v_max3
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            mx4[c] = acc[c >> 1][8 * (c & 1)];
+        for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-            for (int x = 1; x < 8; ++x) mx4[c] = fmaxf(mx4[c], acc[c >> 1][8 * (c & 1) + x]);
-        }
-        const float mx = fmaxf(fmaxf(mx4[0], mx4[1]), fmaxf(mx4[2], mx4[3]));
-        const float m_tile = max_with_other_half(mx) * scale_log2;
-        const bool grow = m_tile > m_run + kRescaleSlack, raised = __any(grow);
+            for (int x = 0; x < 16; x += 2) mx[mt] = fmaxf(fmaxf(mx[mt], acc[mt][x]), acc[mt][x + 1]);
+        // The two lanes of a query look at their own halves of the unit; they exchange them only when either has to
+        // raise the maximum.
+        const float mx_own = fmaxf(mx[0], mx[1]);
+        const bool raised = __any(mx_own * scale_log2 > m_lim);
         if (__builtin_expect(raised, 0)) {
-            const float m_new = grow ? m_tile : m_run;
+            const float m_tile = max_with_other_half(mx_own) * scale_log2;
+            const float m_new = m_tile > m_lim ? m_tile : m_run;
             alpha = fast_exp2(m_run - m_new);
             m_run = m_new;
-            l_run *= alpha;
+            m_lim = m_new + kRescaleSlack;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) l_run[c] *= alpha;
         }
         return raised;
     };
@@ -220,7 +233,6 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     // their LDS latency runs under it.
     auto overlapped = [&](floatx16 (&acc)[2], floatx16 (&acc_next)[2], bf16x8 (&p_out)[4], const bf16x8 (&p_in)[4],
                           bf16x8 (&rd)[16], const bf16_t *k_src, const bf16_t *v_src) __attribute__((always_inline)) {
-        float lsum[4] = {0.f, 0.f, 0.f, 0.f};
         auto mfma = [&](int m) __attribute__((always_inline)) {
             if (m < 8) acc_next[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd[m], qb[m >> 1], m < 2 ? zero16 : acc_next[m & 1], 0, 0, 0);
             else oacc[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd[m], p_in[(m - 8) >> 1], oacc[m & 1], 0, 0, 0);
@@ -245,15 +257,14 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
                 const int x = x0 + c;
                 p_out[2 * mt + (x >> 3)][x & 7] = pr[0];
                 p_out[2 * mt + (x >> 3)][(x & 7) + 1] = pr[1];
-                lsum[(q4 * 2 + (c >> 1)) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum[(q4 * 2 + (c >> 1)) & 3], false);
+                l_run[(q4 * 2 + (c >> 1)) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l_run[(q4 * 2 + (c >> 1)) & 3], false);
             }
             // nothing needs these values before the next barrier: tie them to this group, or the compiler
             // moves the vector work away from the MFMAs it is meant to overlap with
-            asm volatile("" : "+v"(lsum[(q4 * 2) & 3]), "+v"(lsum[(q4 * 2 + 1) & 3]));
+            asm volatile("" : "+v"(l_run[(q4 * 2) & 3]), "+v"(l_run[(q4 * 2 + 1) & 3]));
             if (q4 & 1) asm volatile("" : "+v"(p_out[2 * mt + (x0 >> 3)]));
             __builtin_amdgcn_sched_barrier(0);
         }
-        l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
     };
     // the same three phases one after the other, each only if its unit exists (first and last iterations)
     auto plain = [&](bool soft, bool pv, bool ss, floatx16 (&acc)[2], floatx16 (&acc_next)[2], bf16x8 (&p_out)[4],
@@ -268,7 +279,6 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
         }
         if (__builtin_expect(raised, 0)) rescale();
         if (soft) {
-            float lsum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -278,9 +288,8 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
                                        static_cast<bf16_t>(fast_exp2(acc[mt][x + 1] * scale_log2 - m_run))};
                     p_out[v][e] = pr[0];
                     p_out[v][e + 1] = pr[1];
-                    lsum[(e >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum[(e >> 1) & 3], false);
+                    l_run[(e >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l_run[(e >> 1) & 3], false);
                 }
-            l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
         }
         if (ss) {
 #pragma unroll
@@ -356,7 +365,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     // ---- the softmax over all selected keys from the P partial ones of each row group
     constexpr int kShare = 32 / P;           // accumulator registers each partner adds up and writes
     float osum[kShare];
-    float m_all = m_run, l_all = sum_with_other_half(l_run);
+    float m_all = m_run, l_all = sum_with_other_half((l_run[0] + l_run[1]) + (l_run[2] + l_run[3]));
     if constexpr (P == 1) {
 #pragma unroll
         for (int x = 0; x < 32; ++x) osum[x] = oacc[x >> 4][x & 15];

@@ -8,7 +8,7 @@ import torch
 from paper_2603_08055_amd import workloads
 from tests.parity_util import (compare_windows_with_oracle, compare_with_oracle, log, run_device, special_row_splits,
                                to_host_f32)
-from tests.test_gpu_parity import layer_case, s3r  # noqa: F401  (s3r: fixture)
+from tests.test_gpu_parity import TOL, assert_close, draw, layer_case, s3r  # noqa: F401  (s3r: fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -84,6 +84,17 @@ def test_selection_of_small_blocks(s3r, oracle, dtype, block, n_tok, topk, heads
     res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), block, topk, gate=gate.cuda())
     log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v),
                                                  to_host_f32(gate), block, topk, dtype, label=wl.name)))
+
+
+@pytest.mark.parametrize("tail", [1, 4, 5, 16, 17, 31, 32, 33, 44, 48, 49, 63, 64])
+def test_dense_attention_with_a_short_last_unit(s3r, oracle, tail):
+    """The keys of a unit that exist, counted in runs of 16 and of 4 of them per lane."""
+    n_tok, heads = 128 + tail, 2
+    q, k, v = (draw(n_tok, heads, "bf16", 3100 + i) for i in range(3))
+    out = torch.full_like(q, float("nan")).cuda()
+    s3r.speed3r_dense_attn(q.cuda(), k.cuda(), v.cuda(), out)
+    ref = oracle.dense_attn(*(to_host_f32(x) for x in (q, k, v)), 0.125)
+    assert_close(to_host_f32(out), ref, TOL["bf16"], f"dense tail={tail}")
 
 
 @pytest.mark.parametrize("layout", ["one projection", "head major", "padded heads"])
