@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspeed3r.so")
 OBJ_DIR = os.path.join(HERE, "_build")
-SOURCES = ["pool.hip", "split.hip", "compress.hip", "topk.hip", "select_generic.hip",
+SOURCES = ["pool.hip", "split.hip", "compress.hip", "compress_small.hip", "topk.hip", "select_generic.hip",
            "select_mfma.hip", "select_pipe.hip", "select_direct.hip",
            "speed3r_api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

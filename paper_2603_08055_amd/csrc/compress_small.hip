@@ -10,7 +10,9 @@
 //   P.V       Oc' = P Vc, each wave 16 channels of a quarter of the keys, partial sums added up in LDS
 // The fp32 matrix pipe is 1/16 as fast as the bf16 one, and still not what the time goes into; scores and
 // probabilities are fp32 throughout, at least as exact as the two-part and fp16 scores of the sweeps.
-// Measured (MI355X, whole call, the launches this one took the place of -> this one): see launch_compress_small.
+// Whole calls, the launches that this one took the place of -> this one (MI355X): 4 x 256 tokens, 2 heads, fp32 51.5 ->
+// 21 us; 7 x 777, 5 heads, blocks of 32 59.5 -> 33; 8 x 1374, 16 heads 133 -> 103.  Where the line to the sweeps lies:
+// compress_small_takes.
 #include "s3r_device.h"
 #include "s3r_kernels.h"
 

@@ -293,13 +293,23 @@ s3r_status run_compress_topk(const float *qc, const float *kc, const float *vc, 
                              float *s_buf, int64_t ld_s, int head_chunk, float *o_comp, int32_t *idx,
                              int64_t n_blk, int64_t tiles, int heads, int kk, float scale,
                              bool accurate_pv, bool want_topk, const unsigned long long *forced_words,
-                             const FusedBufs &fb, hipStream_t stream)
+                             const FusedBufs &fb, bool keep_tiles, hipStream_t stream)
 {
+    // Short sequences: one launch on the pooled means themselves (keep_tiles: the caller reads the operand tiles).
+    if (want_topk && g_kernel_choice != 2 && s3r::compress_small_takes(n_blk, heads)) {
+        StageTimer tm(S3R_STAGE_COMPRESS, stream);
+        S3R_HIP(s3r::launch_compress_small(qc, kc, vc, o_comp, idx, n_blk, heads, kk, scale, forced_words, stream),
+                "compress (short sequence) kernel launch");
+        if (keep_tiles)
+            S3R_HIP(s3r::launch_split(qc, kc, vc, tile[0], tile[1], tile[2], tile[3], tile[4], nullptr, nullptr, nullptr,
+                                      nullptr, nullptr, n_blk, heads, stream),
+                    "split kernel launch");
+        return S3R_OK;
+    }
     // Without S_guide in memory when k allows it.  Should a candidate list run over (long runs of
     // equal scores), the overflow word makes the two plain launches that follow redo the chunk;
     // otherwise they return at once.  A row's two lists divide its keys evenly, 16 of every 32 each, so up
-    // to 2 kCandCap blocks no list can run over and the two launches are left out: 54.9 -> 51.5 us a call at
-    // 4 x 256 tokens (fp32), 147.4 -> 142.9 at 8 x 1374 (bf16), 60.6 -> 57.2 at 7 x 777 (bf16, blocks of 32).
+    // to 2 kCandCap blocks no list can run over and the two launches are left out (4 us of a call).
     const bool fused = want_topk && fb.thr != nullptr && kk >= 1 && kk <= s3r::kFusedTopkMaxK && g_kernel_choice != 2;
     {
         StageTimer tm(S3R_STAGE_SPLIT, stream);
@@ -593,7 +603,8 @@ s3r_status speed3r_sparse_global_attn_ex(const s3r_params *p)
                 "forced-block prepare kernel launch");
     }
     st = run_compress_topk(qc, kc, vc, tile, reinterpret_cast<float *>(at(ws, L.s)), L.ld_s, L.head_chunk, oc,
-                           idx_dyn, L.n_blk, L.tiles, p->heads, L.kk, scale, !is_bf16, true, forced_words, fb, stream);
+                           idx_dyn, L.n_blk, L.tiles, p->heads, L.kk, scale, !is_bf16, true, forced_words, fb,
+                           token_queries && mfma && is_bf16, stream);
     if (st != S3R_OK) return st;
     if (n_forced > 0) {
         StageTimer tm(S3R_STAGE_TOPK, stream);
@@ -755,7 +766,7 @@ s3r_status speed3r_compress_attn_scores(const float *qc, const float *kc, const 
     void *tile[8];
     for (int a = 0; a < 8; ++a) tile[a] = at(ws, a * arr);
     return run_compress_topk(qc, kc, vc, tile, s_guide, ld_s, heads, o_comp, nullptr, n_blk, tiles, heads, 0,
-                             resolve_scale(softmax_scale, head_dim), accurate_pv != 0, false, nullptr, FusedBufs{},
+                             resolve_scale(softmax_scale, head_dim), accurate_pv != 0, false, nullptr, FusedBufs{}, false,
                              static_cast<hipStream_t>(stream));
 }
 
@@ -806,7 +817,7 @@ s3r_status speed3r_compress_attn_topk(const float *qc, const float *kc, const fl
     fb.overflow = reinterpret_cast<int *>(at(ws, o_ovf));
     return run_compress_topk(qc, kc, vc, tile, reinterpret_cast<float *>(at(ws, o_s)), ld_s, static_cast<int>(hc), o_comp,
                              idx, n_blk, tiles, heads, kk, resolve_scale(softmax_scale, head_dim), accurate_pv != 0, true,
-                             nullptr, fb, static_cast<hipStream_t>(stream));
+                             nullptr, fb, false, static_cast<hipStream_t>(stream));
 }
 
 s3r_status speed3r_topk_blocks(const float *s_guide, int64_t ld_s, int32_t *idx, int64_t n_blk, int heads,

@@ -2,13 +2,14 @@
 the line between two kernels, against the oracle with the tolerances of test_gpu_parity."""
 import math
 
+import numpy as np
 import pytest
 import torch
 
 from paper_2603_08055_amd import workloads
 from tests.parity_util import (compare_windows_with_oracle, compare_with_oracle, log, run_device, special_row_splits,
                                to_host_f32)
-from tests.test_gpu_parity import TOL, assert_close, draw, layer_case, s3r  # noqa: F401  (s3r: fixture)
+from tests.test_gpu_parity import TOL, assert_close, compress_topk_case, draw, layer_case, s3r  # noqa: F401  (s3r: fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -95,6 +96,34 @@ def test_dense_attention_with_a_short_last_unit(s3r, oracle, tail):
     s3r.speed3r_dense_attn(q.cuda(), k.cuda(), v.cuda(), out)
     ref = oracle.dense_attn(*(to_host_f32(x) for x in (q, k, v)), 0.125)
     assert_close(to_host_f32(out), ref, TOL["bf16"], f"dense tail={tail}")
+
+
+@pytest.mark.parametrize("n_blk,heads,k", [
+    (1, 1, 1), (2, 3, 2), (15, 2, 15), (16, 2, 4), (17, 2, 16), (63, 1, 64), (65, 2, 1), (128, 2, 7), (129, 1, 64),
+    (256, 3, 9), (257, 2, 64), (511, 1, 64), (512, 2, 33), (513, 1, 5), (1023, 1, 64), (1024, 2, 1),
+    (724, 16, 8), (725, 16, 8),       # either side of the line to the sweeps
+])
+def test_short_sequences_in_one_launch(s3r, oracle, n_blk, heads, k):  # noqa: F811
+    """Integer scores with many ties: the TopK sets are the oracle's, bit for bit."""
+    rng = np.random.default_rng(1000 * n_blk + k)
+    qc, kc = (rng.integers(-2, 3, (heads, n_blk, 64)).astype(np.float32) for _ in range(2))
+    vc = rng.standard_normal((heads, n_blk, 64)).astype(np.float32)
+    scores = oracle.scores(qc.astype(np.float64), kc.astype(np.float64))
+    for accurate in (False, True):
+        o_comp, idx = compress_topk_case(s3r, qc, kc, vc, k, accurate)
+        assert np.array_equal(idx, oracle.topk(scores, min(k, n_blk)))
+        ref = oracle.compressed_attn(scores, vc.astype(np.float64), 0.125)
+        assert_close(o_comp, ref, TOL["f32"] if accurate or n_blk <= 724 else TOL["bf16"], "o_comp")
+
+
+@pytest.mark.parametrize("n_blk,topk,n_forced", [(70, 70, 3), (200, 150, 1), (320, 64, 64), (90, 5, 90)])
+def test_forced_blocks_and_long_rows_in_one_launch(s3r, oracle, n_blk, topk, n_forced):  # noqa: F811
+    wl = workloads.Workload(f"short_forced_{n_blk}_{topk}_{n_forced}", 1, 16 * n_blk - 3, 2, 64, "bf16", 16, topk, 103, "normal")
+    q, k, v = workloads.make_inputs(wl)
+    forced = list(range(0, n_blk, n_blk // n_forced))[:n_forced]
+    res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), 16, topk, forced=forced)
+    log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v), None, 16,
+                                                 topk, "bf16", forced=forced, label=wl.name)))
 
 
 @pytest.mark.parametrize("layout", ["one projection", "head major", "padded heads"])
