@@ -338,7 +338,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
     float m_run = -1e30f;
     float m_lim = -1e30f + kRescaleSlack;      // what a unit's largest logit must exceed to raise m_run
-    float l_run[4] = {0.f, 0.f, 0.f, 0.f};     // the row sum in four chains
+    float l_run[4] = {0.f, 0.f, 0.f, 0.f};     // the row sum, bf16: in four chains
 
     // how many of unit w's 64 keys exist, 64 or more: all (wave-uniform)
     auto unit_left = [&](int w) -> int {
@@ -435,17 +435,22 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         // The row sum adds the probabilities as the MFMA will see them (rounded to bf16), two per
         // v_dot2_f32_bf16 with a vector of ones: half the instructions of fp32 adds, and numerator and
         // denominator of the softmax then carry the same rounding.
-        if constexpr (F32) {  // probabilities in fp32, split into operand pairs; the row sum adds the fp32 values
+        // fp32: probabilities split into operand pairs, the row sum adds the fp32 values, a unit's among themselves first:
+        // in one chain per register position their rounding shows (special rows of 200 views, outlier keys, against 64
+        // bits: 3.43e-6, 6.72e-6 in running chains; in bf16 both ways 1.69376e-3).
+        if constexpr (F32) {
+            float lsum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int v = 0; v < 4; ++v)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const int mt = v >> 1, r = 8 * (v & 1) + i;
                     const float p = fast_exp2(sacc[mt][r] * scale_log2 - m_run);
-                    l_run[i & 3] += p;
+                    lsum[i & 3] += p;
                     pb[v][i] = static_cast<bf16_t>(p);
                     pl[v][i] = static_cast<bf16_t>(p - static_cast<float>(pb[v][i]));
                 }
+            l_run[0] += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
             return;
         }
         const bf16x2 ones = {static_cast<bf16_t>(1.f), static_cast<bf16_t>(1.f)};

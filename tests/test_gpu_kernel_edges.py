@@ -167,6 +167,24 @@ def test_scores_of_small_fp32_blocks_are_added_up_exactly_enough(s3r, block):  #
     assert math.sqrt(off / total) < 3.0e-6
 
 
+def test_row_sums_of_long_fp32_rows_are_added_up_exactly_enough(s3r):  # noqa: F811
+    """Rows over 274 800 outlier keys, whose sum one weight may dominate: added up unit by unit the sum leaves 3.5e-6 with
+    the two bf16 parts of P and V, one key after the other onto the whole sum 6.3e-6."""
+    views, tpv, special, heads = 200, 1374, 5, 2
+    wl = workloads.Workload("long_row_sums", views, tpv, heads, 64, "f32", 64, 4, 104, "outliers")
+    q, k, v = workloads.make_inputs(wl, device="cuda")
+    out = run_device(s3r, q, k, v, 64, 4, want=(), tokens_per_view=tpv, special_per_view=special)["out"]
+    off = total = 0.0
+    for h in range(heads):
+        k64, v64 = k[:, h].double(), v[:, h].double()
+        for view in range(0, views, 5):
+            rows = view * tpv + torch.arange(special, device="cuda")
+            want = torch.softmax(q[rows, h].double() @ k64.T / 8.0, dim=-1) @ v64
+            off += (out[rows, h].double() - want).square().sum().item()
+            total += want.square().sum().item()
+    assert math.sqrt(off / total) < 4.5e-6
+
+
 @pytest.mark.parametrize("n_blk,kk", [(8, 3), (9, 8), (3000, 48)])   # edge iterations only; full ones; two pairs of waves
 def test_probabilities_waiting_while_the_maximum_rises(s3r, n_blk, kk):  # noqa: F811
     """Pipelined selection: the running maximum rises by just under 9 (powers of two) while the probabilities of the
