@@ -68,9 +68,14 @@ namespace s3r {
 //         enters the result in absolute terms, so it must not grow with the size of the entries); P.V takes
 //         two parts each, hi.hi + hi.lo + lo.hi (2^-17 relative, of values in [0, 1] times V).  All on the
 //         bf16 matrix pipe with fp32 accumulation: fp32-grade results at nine MFMAs per tile step in place of two.
+// KS    : 2: twice the waves, the second half of them on the second 32 keys of every unit for the same query rows, with a
+//         softmax of their own; the two partial results (m, l, O) of a row are added up through LDS at the end.  For
+//         fp32 selection with blocks of 64: two workgroups of two waves were all that an 80 KiB ring lets a CU
+//         hold, one wave per SIMD (30 views, top-16: 1.10 -> 0.98 ms a call; the shorter chains of sums also leave
+//         less error, outlier keys against 64 bits 3.6e-6 -> 3.3e-6).
 template <int QW, bool DENSE, int NS, bool SMALL, bool EXTRA, bool ASMQ, bool PAIR = false, bool PROBE = false,
-          bool F32 = false>
-__global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
+          bool F32 = false, int KS = 1>
+__global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     const bf16_t *__restrict__ q, const bf16_t *__restrict__ kb, const bf16_t *__restrict__ vb,
     const int32_t *__restrict__ idx, const float *__restrict__ o_comp, const bf16_t *__restrict__ gate,
     bf16_t *__restrict__ out, bf16_t *__restrict__ o_sel, float *__restrict__ lse, int64_t n_tok,
@@ -79,13 +84,15 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
     const bf16_t *__restrict__ vb2, int64_t n_keys2, const int32_t *__restrict__ blk_len, SelectExtras x,
     int64_t lo_off, int64_t lo_off2)
 {
-    constexpr int NW = QW;             // waves per workgroup
+    constexpr int NW = QW * KS;        // waves per workgroup
+    constexpr int NMT = 2 / KS;        // 32-key tiles of a unit that a wave works on
     constexpr int NCH = F32 ? 40 : 16; // 1 KiB chunks of a unit: 8 K + 8 V (F32: then 8 K lo + 8 V lo + 8 K lo2)
     constexpr int CPW = NCH / NW;      // ... issued by each wave
     constexpr int D = NS - 1;          // units in flight
     static_assert(NCH % NW == 0 && 16 % NW == 0, "waves must split the chunks of a unit evenly");
     static_assert(CPW * D < 64, "vmcnt budget");
     static_assert(!SMALL || DENSE, "selection with small blocks: select_direct.hip");
+    static_assert(KS == 1 || (KS == 2 && !DENSE && !PAIR && !PROBE), "key halves: plain selection");
     static_assert(!F32 || (!PAIR && !PROBE), "operand parts: the plain and the dense kernels");
     // [stage][K 8 KiB | V 8 KiB] (F32: then [K lo 8 KiB | V lo 8 KiB | K lo2 8 KiB])
     constexpr int kStageParts = F32 ? 5 : 2;
@@ -94,6 +101,8 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
 
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rg = KS == 1 ? wave : wave & (QW - 1);  // which 32 query rows
+    const int kh = KS == 1 ? 0 : wave / QW;            // which half of every unit's keys
     int h;
     int64_t set;    // query group (query block for selection) of this workgroup
     int split = 0;  // dense attention in key splits: which share of the key units
@@ -121,9 +130,9 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
     const int upb_mask = (1 << upb_shift) - 1;
     const int bpu_shift = SMALL ? (block == 16 ? 2 : 1) : 0;  // SMALL: blocks per unit: 4 or 2, as a shift
     const int64_t qgroup = set;
-    int64_t t = qgroup * (32 * QW) + wave * 32 + (lane & 31);
+    int64_t t = qgroup * (32 * QW) + rg * 32 + (lane & 31);
     bool row_valid = t < n_tok;
-    if (!DENSE && !PAIR && blk_len != nullptr) row_valid = wave * 32 + (lane & 31) < blk_len[qgroup];  // spatial windows
+    if (!DENSE && !PAIR && blk_len != nullptr) row_valid = rg * 32 + (lane & 31) < blk_len[qgroup];  // spatial windows
     if constexpr (PAIR) {
         static_assert(!PAIR || (QW == 4 && !DENSE && !SMALL && ASMQ), "two query blocks of 64 rows, two waves each");
         const int64_t qblk = 2 * qgroup + (wave >> 1);
@@ -311,14 +320,14 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         const int w = unit_of(s);
         if constexpr (F32) {  // chunk = 16 * part + (0..7: K, 8..15: V), part 0 = hi, 1 = lo, 2 = lo2 (K only)
             const bool second = DENSE && w >= n_units1;
-            const int64_t wu = second ? w - n_units1 : w;
+            const int64_t unit = static_cast<int64_t>(second ? w - n_units1 : w) * kUnitElems;
+            const int64_t lo = second ? lo_off2 : lo_off;
+            static_assert(!F32 || NW == 4, "chunk c * 4 + wave: its kind and part are those of c * 4, known at compile time");
 #pragma unroll
             for (int c = 0; c < CPW; ++c) {
-                const int chunk = wave * CPW + c;
-                const bf16_t *arr = (chunk & 8) ? (second ? vb2_h : vb_h) : (second ? kb2_h : kb_h);
-                const int64_t part = (chunk >> 4) * (second ? lo_off2 : lo_off);
-                lds_dma_16(arr + part + wu * kUnitElems + (chunk & 7) * 512 + lane * 8,
-                           __builtin_amdgcn_readfirstlane(stage_byte + chunk * 1024));
+                const int base = c * NW;
+                const bf16_t *arr = (base & 8) ? (second ? vb2_h : vb_h) : (second ? kb2_h : kb_h);
+                lds_dma_16_x1(arr + unit + (base >> 4) * lo + ((base & 7) + wave) * 512, lane * 16, stage_byte + (base + wave) * 1024);
             }
             return;
         }
@@ -378,8 +387,8 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
     // Dense attention: one tile after the other (the two orders tie).
     auto scores = [&](const bf16_t *ks) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int mt = DENSE ? i >> 2 : i & 1, c = DENSE ? i & 3 : i >> 1;
+        for (int i = 0; i < 4 * NMT; ++i) {
+            const int mt = DENSE ? i >> 2 : i & (NMT - 1), c = DENSE ? i & 3 : i / NMT;
             const bf16x8 ka = *reinterpret_cast<const bf16x8 *>(ks + ((mt * 4 + c) * 64 + lane) * 8);
             sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[c], c == 0 ? zero16 : sacc[mt], 0, 0, 0);
             if constexpr (F32) {
@@ -399,8 +408,8 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         // In every run of 16 keys the first n exist; n compared with constants, because a bit test per register would
         // have its 32 masks held in registers all through the loop (54 registers, a wave per SIMD fewer).
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int n = __builtin_popcount(static_cast<unsigned>(vmask >> (16 * c)) & 0xffffu) - 4 * g;
+        for (int c = 0; c < 2 * NMT; ++c) {
+            const int n = __builtin_popcount(static_cast<unsigned>(vmask >> (32 * kh + 16 * c)) & 0xffffu) - 4 * g;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 if (8 * (i >> 2) + (i & 3) >= n) sacc[c >> 1][8 * (c & 1) + i] = -INFINITY;
@@ -428,7 +437,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         if (vmask != ~0ull) mask_scores(vmask);
         float mx[2] = {lowest, lowest};  // two chains of v_max3
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
             for (int r = 0; r < 16; r += 2) mx[mt] = fmaxf(fmaxf(mx[mt], sacc[mt][r]), sacc[mt][r + 1]);
         raise_max(fmaxf(mx[0], mx[1]));
@@ -441,7 +450,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         if constexpr (F32) {
             float lsum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
+            for (int v = 0; v < 2 * NMT; ++v)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const int mt = v >> 1, r = 8 * (v & 1) + i;
@@ -455,7 +464,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         }
         const bf16x2 ones = {static_cast<bf16_t>(1.f), static_cast<bf16_t>(1.f)};
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int v = 0; v < 2 * NMT; ++v)
 #pragma unroll
             for (int i = 0; i < 8; i += 2) {
                 const int mt = v >> 1, r = 8 * (v & 1) + i;
@@ -469,7 +478,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
     // O^T += V^T P^T for the unit whose V sits in `vs`
     auto accumulate = [&](const bf16_t *vs) __attribute__((always_inline)) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int v = 0; v < 2 * NMT; ++v)
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt) {
                 const bf16x8 va = *reinterpret_cast<const bf16x8 *>(vs + ((v * 2 + dt) * 64 + lane) * 8);
@@ -560,11 +569,34 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         if (s + D < n_steps) issue(s + D, stage_ahead);
         if constexpr (PROBE) continue;
         const unsigned long long vmask = unit_mask(s);
-        if (vmask == 0ull) continue;  // second half of a short last block
-        scores(&ring[stage][0]);
+        if ((KS == 1 ? vmask : vmask >> (32 * kh)) == 0ull) continue;  // second half of a short last block
+        // (a key half: the second 32-row tile of K, the second two key steps of V)
+        scores(&ring[stage][kh * kRowTileElems]);
         softmax(vmask);
-        accumulate(&ring[stage][kUnitElems]);
+        accumulate(&ring[stage][kUnitElems + kh * kRowTileElems]);
     }
+    }
+
+    if constexpr (KS == 2) {  // the second half's result to LDS, added to the first half's there
+        float *buf = reinterpret_cast<float *>(&ring[0][0]) + rg * (37 * 64) + lane;  // [QW][37 registers][64 lanes]
+        static_assert(sizeof(ring) >= QW * 37 * 64 * sizeof(float), "partial results in the ring's place");
+        lds_barrier();        // every wave is done with the ring
+        if (kh == 1) {
+            buf[0] = m_run;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) buf[(1 + i) * 64] = l_run[i];
+#pragma unroll
+            for (int x = 0; x < 32; ++x) buf[(5 + x) * 64] = oacc[x >> 4][x & 15];
+        }
+        lds_barrier();
+        if (kh == 1) return;
+        const float m_all = fmaxf(m_run, buf[0]);
+        const float f0 = fast_exp2(m_run - m_all), f1 = fast_exp2(buf[0] - m_all);
+        m_run = m_all;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) l_run[i] = l_run[i] * f0 + buf[(1 + i) * 64] * f1;
+#pragma unroll
+        for (int x = 0; x < 32; ++x) oacc[x >> 4][x & 15] = oacc[x >> 4][x & 15] * f0 + buf[(5 + x) * 64] * f1;
     }
 
     if (!row_valid) return;
@@ -644,7 +676,7 @@ __global__ __launch_bounds__(QW * 64, 2) void select_mfma_kernel(
         }
 }
 
-template <int QW, bool DENSE, int NS, bool SMALL, bool EXTRA, bool ASMQ, bool PAIR, bool PROBE = false, bool F32 = false>
+template <int QW, bool DENSE, int NS, bool SMALL, bool EXTRA, bool ASMQ, bool PAIR, bool PROBE = false, bool F32 = false, int KS = 1>
 static hipError_t run_select_x(const SelectArgs &a, hipStream_t stream)
 {
     // The load probe can hold the number of workgroups per CU down: unused dynamic LDS on top of the ring makes
@@ -655,7 +687,7 @@ static hipError_t run_select_x(const SelectArgs &a, hipStream_t stream)
         if (share < ring) return hipErrorInvalidValue;
         pad_bytes = static_cast<unsigned>(share - ring);
         const hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void *>(&select_mfma_kernel<QW, DENSE, NS, SMALL, EXTRA, ASMQ, PAIR, PROBE, F32>),
+            reinterpret_cast<const void *>(&select_mfma_kernel<QW, DENSE, NS, SMALL, EXTRA, ASMQ, PAIR, PROBE, F32, KS>),
             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(pad_bytes));
         if (e != hipSuccess) return e;
     }
@@ -678,8 +710,8 @@ static hipError_t run_select_x(const SelectArgs &a, hipStream_t stream)
         const int64_t ns = (sets - s0 < per_launch) ? sets - s0 : per_launch;
         const int64_t n_split = (DENSE && a.x.n_split > 1) ? a.x.n_split : 1;
         const int64_t grid = (map_mode == 2) ? (ns + 7) / 8 * 8 * a.heads : ns * n_split * a.heads;
-        hipLaunchKernelGGL((select_mfma_kernel<QW, DENSE, NS, SMALL, EXTRA, ASMQ, PAIR, PROBE, F32>), dim3(static_cast<unsigned>(grid)),
-                           dim3(QW * 64), pad_bytes, stream, static_cast<const bf16_t *>(a.q),
+        hipLaunchKernelGGL((select_mfma_kernel<QW, DENSE, NS, SMALL, EXTRA, ASMQ, PAIR, PROBE, F32, KS>), dim3(static_cast<unsigned>(grid)),
+                           dim3(QW * KS * 64), pad_bytes, stream, static_cast<const bf16_t *>(a.q),
                            static_cast<const bf16_t *>(a.kb), static_cast<const bf16_t *>(a.vb), a.idx,
                            a.o_comp, static_cast<const bf16_t *>(a.gate), static_cast<bf16_t *>(a.out),
                            static_cast<bf16_t *>(a.o_sel), a.lse, a.n_tok, a.n_blk, a.heads, a.block,
@@ -692,14 +724,14 @@ static hipError_t run_select_x(const SelectArgs &a, hipStream_t stream)
     return hipSuccess;
 }
 
-template <int QW, bool DENSE, int NS, bool SMALL = false, bool ASMQ = DENSE, bool PAIR = false, bool F32 = false>
+template <int QW, bool DENSE, int NS, bool SMALL = false, bool ASMQ = DENSE, bool PAIR = false, bool F32 = false, int KS = 1>
 static hipError_t run_select(const SelectArgs &a, hipStream_t stream)
 {
     const SelectExtras &x = a.x;
     const bool extra = x.o_comp_tok != nullptr || x.out_f32 != nullptr || x.kv_head_stride != 0 ||
                        x.q_blk_len != nullptr || x.in.tok != 0;
-    return extra ? run_select_x<QW, DENSE, NS, SMALL, true, ASMQ, PAIR, false, F32>(a, stream)
-                 : run_select_x<QW, DENSE, NS, SMALL, false, ASMQ, PAIR, false, F32>(a, stream);
+    return extra ? run_select_x<QW, DENSE, NS, SMALL, true, ASMQ, PAIR, false, F32, KS>(a, stream)
+                 : run_select_x<QW, DENSE, NS, SMALL, false, ASMQ, PAIR, false, F32, KS>(a, stream);
 }
 
 hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream)
@@ -713,12 +745,14 @@ hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream)
         if (a.qmap.period != 0 && a.n_tok > 0x7fffffffLL) return hipErrorInvalidValue;
         if (a.idx == nullptr) {
             if (a.n_keys2 > 0 && (a.kb2 == nullptr || a.vb2 == nullptr || a.lo_off2 <= 0)) return hipErrorInvalidValue;
-            return small ? run_select<4, true, 3, true, true, false, true>(a, stream)
-                         : run_select<4, true, 3, false, true, false, true>(a, stream);
+            // two stages, 80 KiB: two workgroups per CU (three stages and addresses from scratch memory: 8256 rows,
+            // 16 heads 3.95 ms, now 1.15)
+            return small ? run_select<4, true, 2, true, true, false, true>(a, stream)
+                         : run_select<4, true, 2, false, true, false, true>(a, stream);
         }
         if (a.n_keys != a.n_tok || a.n_keys2 != 0) return hipErrorInvalidValue;
         return small          ? launch_select_direct(a, stream)
-               : a.block == 64 ? run_select<2, false, 2, false, false, false, true>(a, stream)
+               : a.block == 64 ? run_select<2, false, 2, false, false, false, true, 2>(a, stream)
                                : run_select<4, false, 2, false, false, false, true>(a, stream);
     }
     // One query block per workgroup, two LDS stages: measured best on MI355X.  A third stage is slower even

@@ -54,47 +54,47 @@ bool mfma_ok(s3r_dtype dtype, int block) { (void)dtype; (void)block; return g_ke
 size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 
 // Dense attention of few query rows (the special tokens) in key splits: the number of splits with the shortest time
-// by a model of the launch, in microseconds on MI355X (256 CUs; a CU holds three workgroups of the bf16 kernel, one
-// of the fp32 kernel with its 120 KiB ring).  A CU works through n = ceil(workgroups * s / 256) of them:
-//   * each takes 0.68 us per key unit (1.1 with the gathered units of small blocks; fp32: 8 and 3.8) and 4 us at its
-//     start and end;
+// by a model of the launch, in microseconds on MI355X (256 CUs; three workgroups fill a CU, of the fp32 kernel with its
+// 80 KiB ring two).  A CU works through n = ceil(workgroups * s / 256) of them:
+//   * each takes 0.64 us per key unit (0.7 over small blocks; fp32: 1.95 and 1.8) and 4 us at its start and end;
 //   * the bf16 kernel needs two to three workgroups on a CU to fill it: one left over in the last round costs as
-//     much as 1.75, two as 2.3 (0.85 to 0.91 us per unit with one, 0.69 to 0.71 with two, 0.68 with three);
+//     much as 1.75, two as 2.3; of the fp32 kernel one costs as much as 1.2;
 //   * the workgroups of later rounds no longer walk the keys in step and share less of them in the L2s: 2.5 % per
-//     round, 30 % at most (26 300 units, 768 workgroups: 49.1 ms in one split, 50.4 in 2, 57.1 in 8, 64.6 in 24);
+//     round, 30 % at most;
 //   * the combine kernel reads s partial rows one after the other (0.6 us each) and moves them at 4 TB/s.
 // Measured, 16 heads, 5 special rows per view, dense kernel and combine (ms for the number of splits, * = chosen):
-//   bf16, blocks of 64, 20 views    1: 0.361   8: 0.062  16: 0.048*  48: 0.067
-//                       100 views   1: 1.80    8: 0.380  12: 0.367*  24: 0.409  64: 0.562
-//                       950 views   1: 37.1    2: 32.9    5: 33.6*   8: 35.1    24: 39.9
-//                       1000 views  1: 39.8    2: 34.5*   3: 37.4    6: 37.5    12: 42.2
-//                       1250 views  1: 66.4    3: 57.6    4: 57.6*   8: 60.4    47: 67.5
-//   bf16, blocks of 16, 100 views   1: 3.96    8: 0.656  12: 0.576*  24: 0.596  64: 0.658
-//   fp32, blocks of 64, 60 views    5: 2.10    8: 2.72   10: 2.19    16: 2.12*  32: 2.17
-// fp32 takes at least 8 splits, although fewer can be faster (200 views: 17.4 ms in 2, 17.8 in 8; 400 views 68.8 in 3,
-// 70.2 in 8): the error of a row against 64 bits grows with the units in one chain of sums (200 views: 1.0e-5 in one
-// split, 7.6e-6 in 2, 5.7e-6 in 6, 5.4e-6 in 8, 5.0e-6 in 16).  In bf16 it is the
-// rounding of P, which hardly depends on the splits and gains from them, every split's largest probability being exact
-// (30 views in 4 x 4 windows, 8 heads, outlier keys: 1.80e-3 in one split, 1.69e-3 in the 32 taken, 1.67e-3 in 48).
+//   bf16, blocks of 64, 20 views    1: 0.340   8: 0.060  16: 0.046*  24: 0.051  32: 0.053
+//                       100 views   4: 0.481   8: 0.359  12: 0.354*  24: 0.407  32: 0.431
+//                       300 views   2: 3.75    3: 3.87    4: 3.01*   6: 3.38    8: 3.03   12: 3.32
+//                       1000 views  1: 36.1    2: 32.1*   3: 33.6    4: 32.5    6: 33.8
+//   bf16, blocks of 16, 20 views    8: 0.076  16: 0.056*  24: 0.059  32: 0.061
+//                       100 views   8: 0.447  12: 0.413*  16: 0.440  32: 0.493
+//   fp32, blocks of 64, 20 views    8: 0.120  16: 0.082*  24: 0.092  32: 0.098
+//                       60 views    8: 0.589  10: 0.503   16: 0.512*  32: 0.548   (2.12 with a ring of 120 KiB, one
+//                       workgroup per CU and the operand array of a chunk looked up in scratch memory)
+// fp32 takes at least 16 splits, although fewer can be faster: the error of a row against 64 bits grows with the units in
+// one chain of sums (200 views: 1.0e-5 in one split, 7.6e-6 in 2, 5.7e-6 in 6, 5.4e-6 in 8, 5.0e-6 in 16).  In bf16 it is
+// the rounding of P, which hardly depends on the splits and gains from them, every split's largest probability being
+// exact (30 views in 4 x 4 windows, 8 heads, outlier keys: 1.80e-3 in one split, 1.69e-3 in 32, 1.67e-3 in 48).
 constexpr int kMaxDenseSplit = 64;
 int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, int block)
 {
     const bool bf16 = dtype == S3R_BF16;
     const int64_t wgs = (n_rows + 127) / 128 * heads;
     if (wgs >= 3072) return 1;  // 12 workgroups and more per CU: even enough
-    const double unit_us = bf16 ? (block >= 64 ? 0.68 : 1.1) : (block >= 64 ? 8.0 : 3.8);
-    const int64_t at_once = bf16 ? 3 : 1;
-    const double left_over[3] = {0.0, bf16 ? 0.75 : 0.0, bf16 ? 0.3 : 0.0};
+    const double unit_us = bf16 ? (block >= 64 ? 0.64 : 0.7) : (block >= 64 ? 1.95 : 1.8);
+    const int64_t at_once = bf16 ? 3 : 2;
+    const double left_over[3] = {0.0, bf16 ? 0.75 : 0.2, bf16 ? 0.3 : 0.0};
     auto time_us = [&](int s) {
         const int64_t n = (wgs * s + 255) / 256, rounds = (n + at_once - 1) / at_once;
         const double drift = 0.025 * static_cast<double>(rounds - 1);
-        const double walk = (static_cast<double>(n) + left_over[n % 3]) * (static_cast<double>((n_units + s - 1) / s) * unit_us + 4.0) *
+        const double walk = (static_cast<double>(n) + left_over[n % at_once]) * (static_cast<double>((n_units + s - 1) / s) * unit_us + 4.0) *
                             (1.0 + (drift < 0.3 ? drift : 0.3));
         return s == 1 ? walk : walk + s * (0.6 + 1.3e-4 * static_cast<double>(n_rows * heads));
     };
     int most = static_cast<int>(n_units / 4 < kMaxDenseSplit ? n_units / 4 : kMaxDenseSplit);  // at least 4 units each
     if (most < 1) most = 1;
-    const int least = bf16 ? 1 : (most < 8 ? most : 8);
+    const int least = bf16 ? 1 : (most < 16 ? most : 16);
     double us[kMaxDenseSplit + 1], shortest = INFINITY;
     for (int s = least; s <= most; ++s) {
         us[s] = time_us(s);
