@@ -406,13 +406,17 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     auto mask_scores = [&](unsigned long long vmask) __attribute__((always_inline)) {
         asm volatile("" ::: "memory");    // keep this rare path a real branch
         // In every run of 16 keys the first n exist; n compared with constants, because a bit test per register would
-        // have its 32 masks held in registers all through the loop (54 registers, a wave per SIMD fewer).
+        // have its 32 masks held in registers all through the loop (54 registers).  Runs that are whole are passed over.
 #pragma unroll
         for (int c = 0; c < 2 * NMT; ++c) {
-            const int n = __builtin_popcount(static_cast<unsigned>(vmask >> (32 * kh + 16 * c)) & 0xffffu) - 4 * g;
+            const int n16 = __builtin_popcount(static_cast<unsigned>(vmask >> (32 * kh + 16 * c)) & 0xffffu);
+            if (n16 < 16) {
+                asm volatile("" ::: "memory");
+                const int n = n16 - 4 * g;
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (8 * (i >> 2) + (i & 3) >= n) sacc[c >> 1][8 * (c & 1) + i] = -INFINITY;
+                for (int i = 0; i < 8; ++i)
+                    if (8 * (i >> 2) + (i & 3) >= n) sacc[c >> 1][8 * (c & 1) + i] = -INFINITY;
+            }
         }
     };
     // The running maximum after a unit whose largest score (per lane) is mx.  The two lanes of a query look at their own

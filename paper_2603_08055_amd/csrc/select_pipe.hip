@@ -99,6 +99,24 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     sel_lo = sel_lo < 0 ? 0 : (sel_lo >= static_cast<int>(n_blk) ? static_cast<int>(n_blk) - 1 : sel_lo);
     sel_hi = sel_hi < 0 ? 0 : (sel_hi >= static_cast<int>(n_blk) ? static_cast<int>(n_blk) - 1 : sel_hi);
     auto unit_of = [&](int u) -> int { return __builtin_amdgcn_readlane(u < 64 ? sel_lo : sel_hi, u & 63); };
+    // How many of a unit's 64 keys exist, beside the index row in the same way.  With blocks that are runs of the sequence
+    // only its last unit can be short; spatial windows have a length per block.
+    int len_lo, len_hi;
+    if (blk_len != nullptr) {
+        const int32_t *a_lo = blk_len + sel_lo, *a_hi = blk_len + sel_hi;
+        asm volatile("global_load_dword %0, %2, off\n\t"
+                     "global_load_dword %1, %3, off\n\t"
+                     "s_waitcnt vmcnt(0)"
+                     : "=&v"(len_lo), "=&v"(len_hi)
+                     : "v"(a_lo), "v"(a_hi)
+                     : "memory");
+    } else {
+        const int w_last = static_cast<int>((n_keys - 1) / kUnitKeys);
+        const int left_last = static_cast<int>(n_keys - static_cast<int64_t>(w_last) * kUnitKeys);  // 1..64
+        len_lo = sel_lo == w_last ? left_last : kUnitKeys;
+        len_hi = sel_hi == w_last ? left_last : kUnitKeys;
+    }
+    auto keys_of = [&](int u) -> int { return __builtin_amdgcn_readlane(u < 64 ? len_lo : len_hi, u & 63); };
 
     // ---- loads: of its pair's units the first wave moves the K part, the second the V part (eight 1 KiB chunks)
     const bool is_k = r == 0;
@@ -113,17 +131,6 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
         lds_dma_16_x4(src, voff_lo, dst);
         lds_dma_16_x4(src, voff_hi, dst + 4096);
     };
-    // which of unit w's 64 keys exist (wave-uniform): with blocks that are runs of the sequence only its last
-    // unit can be short; spatial windows have a length per block
-    const int w_last = static_cast<int>((n_keys - 1) / kUnitKeys);
-    const int left_last = static_cast<int>(n_keys - static_cast<int64_t>(w_last) * kUnitKeys);  // 1..64
-    const unsigned long long tail_mask = left_last >= kUnitKeys ? ~0ull : (1ull << left_last) - 1ull;
-    auto unit_mask = [&](int w) -> unsigned long long {
-        if (blk_len == nullptr) return w == w_last ? tail_mask : ~0ull;
-        const int left = blk_len[w];
-        return left >= kUnitKeys ? ~0ull : left <= 0 ? 0ull : (1ull << left) - 1ull;
-    };
-
     // K(j) is requested in iteration j - NSK (or before the loop), V(j) in iteration j + 2 - NSV: NSK - 1 and
     // NSV - 1 iterations before the barrier that needs them.
     for (int j = 0; j <= (is_k ? NSK - 2 : NSV - 4); ++j) issue_unit(j, j);
@@ -178,20 +185,21 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     // (rescale) once P(i - 1) V(i - 1) has been added to them, which is still in the old scale.  (Scaling P(i - 1)
     // instead would round it to bf16 a second time, where the row sum has it as it was: up to 0.4 %.)
     float alpha;  // what the accumulators are to be scaled by
-    auto soft_pre = [&](floatx16 (&acc)[2], unsigned long long vmask) __attribute__((always_inline)) -> bool {
-        if (vmask != ~0ull) {
+    auto soft_pre = [&](floatx16 (&acc)[2], int n_keys_u) __attribute__((always_inline)) -> bool {
+        if (n_keys_u < kUnitKeys) {
             asm volatile("" ::: "memory");  // keep this rare path a real branch
-            // In every run of 16 keys the first n exist; n compared with constants, because a bit test per register
-            // would have its 32 masks held in registers all through the loop (228 -> 181 registers; with the exchange
-            // of maxima left out and the row sum in running chains 2.12 -> 2.07 ms a call at 100 views, 43.2 -> 42.3 at
-            // 1000, 12.9 -> 12.4 with 46 forced blocks in rows of 110 at 200).
+            // Runs of 16 keys, compared with constants (a bit test per register would have its 32 masks held in
+            // registers all through the loop: 228 instead of 182); runs that are whole are passed over.  Lengths beside
+            // the index row and this: 3.74 -> 3.66 ms a call for 150 views in 8 x 8 windows of a 37 x 37 grid.
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int n = __builtin_popcount(static_cast<unsigned>(vmask >> (16 * c)) & 0xffffu) - 4 * g;
+            for (int c = 0; c < 4; ++c)
+                if (n_keys_u < 16 * c + 16) {
+                    asm volatile("" ::: "memory");
+                    const int n = n_keys_u - 16 * c - 4 * g;
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (8 * (e >> 2) + (e & 3) >= n) acc[c >> 1][8 * (c & 1) + e] = -INFINITY;
-            }
+                    for (int e = 0; e < 8; ++e)
+                        if (8 * (e >> 2) + (e & 3) >= n) acc[c >> 1][8 * (c & 1) + e] = -INFINITY;
+                }
         }
         float mx[2] = {lowest, lowest};  // two chains of v_max3
 #pragma unroll
@@ -268,8 +276,8 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     };
     // the same three phases one after the other, each only if its unit exists (first and last iterations)
     auto plain = [&](bool soft, bool pv, bool ss, floatx16 (&acc)[2], floatx16 (&acc_next)[2], bf16x8 (&p_out)[4],
-                     const bf16x8 (&p_in)[4], const bf16_t *k_src, const bf16_t *v_src, unsigned long long vmask) __attribute__((always_inline)) {
-        const bool raised = soft && soft_pre(acc, vmask);
+                     const bf16x8 (&p_in)[4], const bf16_t *k_src, const bf16_t *v_src, int n_keys_u) __attribute__((always_inline)) {
+        const bool raised = soft && soft_pre(acc, n_keys_u);
         if (pv) {
 #pragma unroll
             for (int m = 0; m < 8; ++m) {
@@ -336,7 +344,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
         bf16x8 rd[16];
 #pragma unroll
         for (int m = 0; m < kAhead; ++m) rd[m] = operand(m, k_src, v_src);
-        const bool raised = soft_pre(accs[PAR], unit_mask(unit_of(i * P + p)));
+        const bool raised = soft_pre(accs[PAR], keys_of(i * P + p));
         overlapped(accs[PAR], accs[1 - PAR], ps[PAR], ps[1 - PAR], rd, k_src, v_src);
         if (__builtin_expect(raised, 0)) rescale();
     };
@@ -346,7 +354,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
         open_iteration(i);
         const bool soft = i >= 0 && i < n_tiles, pv = i >= 1 && i <= n_tiles, ss = i + 1 < n_tiles;
         plain(soft, pv, ss, accs[PAR], accs[1 - PAR], ps[PAR], ps[1 - PAR], k_of(i), v_of(i),
-              soft ? unit_mask(unit_of(i * P + p)) : ~0ull);
+              soft ? keys_of(i * P + p) : kUnitKeys);
     };
     const std::integral_constant<int, 0> even{};
     const std::integral_constant<int, 1> odd{};
