@@ -279,7 +279,29 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
             // (dense: the second key segment is stored as plain 64-key units)
             const int u = s + u_begin;
             const bool small = u < n_units1;
-            const UnitBlocks b = blocks_of(small ? u : 0);
+            if (!small || ((u + 1) << bpu_shift) <= n_blk) {
+                // Blocks that follow one another: the unit is one run of 8 KiB in kb and one in vb, in operand order but
+                // for the K tiles of 16-row blocks, whose two blocks of a tile half interleave.  Addresses are a
+                // wave-uniform start and one offset per lane.  (With the masks read 64 at a time: special rows of 100 views
+                // in 4 x 4 windows 0.57 -> 0.41 ms.)
+                const int64_t at = static_cast<int64_t>(small ? u : u - n_units1) * kUnitElems;
+                const bf16_t *ku = (small ? kb_h : kb2_h) + at, *vu = (small ? vb_h : vb2_h) + at;
+                const bool halves = small && bpu_shift == 2;
+                const unsigned k_off = halves ? ((lane >> 4) & 1) * 2048 + ((lane >> 5) * 16 + (lane & 15)) * 16 : lane * 16;
+                static_assert(!SMALL || NW == 4, "chunk c * 4 + wave: its kind, part and tile half are those of c * 4");
+#pragma unroll
+                for (int c = 0; c < CPW; ++c) {
+                    const int base = c * NW;  // compile time
+                    const bf16_t *src;
+                    if ((base & 8) == 0) src = ku + ((base & 7) >> 2) * 2048 + wave * (halves ? 256 : 512);
+                    else src = vu + ((base & 7) + wave) * 512;
+                    if constexpr (F32) src += (base >> 4) * (small ? lo_off : lo_off2);
+                    lds_dma_16_x1(src, (base & 8) == 0 ? k_off : lane * 16, stage_byte + (base + wave) * 1024);
+                }
+                return;
+            }
+            // the last unit, put together from fewer blocks
+            const UnitBlocks b = blocks_of(u);
             const int64_t tile = static_cast<int64_t>(block) * 64;  // elements of a block's K (or V) tile
             // Chunk c * QW + wave for c = 0 .. CPW - 1: the tile half mt a chunk belongs to is then a
             // compile-time constant (chunks 0..7 = K (mt, channel step), 8..15 = V (v = 2 mt + hw, dt)),
@@ -291,27 +313,22 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
                 const int chunk = base + wave;           // base .. base + QW - 1, all in the same mt
                 const int mt = (base & 7) >> 2;          // compile time
                 const bool is_k = (base & 15) < 8;       // compile time (F32: 16 chunks per operand part, K only in the third)
-                const int64_t part = F32 ? (base >> 4) * (small ? lo_off : lo_off2) : 0;
+                const int64_t part = F32 ? (base >> 4) * lo_off : 0;
                 const bf16_t *src;
-                if (small) {
-                    const int lo = mt == 0 ? b.b0 : (bpu_shift == 2 ? b.b2 : b.b1);   // first block of tile half mt
-                    const int hi = mt == 0 ? b.b1 : b.b3;                              // block 16 only: its second block
-                    if (is_k) {
-                        const int cs = chunk & 3;
-                        if (bpu_shift == 1) {  // block 32: the 32-row tile of block mt
-                            src = kb_h + lo * tile + cs * 512 + lane * 8;
-                        } else {               // block 16: rows 0..15 of the tile from its first block, rows 16..31 from its second
-                            const int blk = ((lane >> 4) & 1) ? hi : lo;
-                            src = kb_h + blk * tile + ((cs * 2 + (lane >> 5)) * 16 + (lane & 15)) * 8;
-                        }
-                    } else {
-                        const int hw = ((chunk & 7) >> 1) & 1, dt = chunk & 1;
-                        if (bpu_shift == 1) src = vb_h + lo * tile + ((hw * 2 + dt) * 64 + lane) * 8;
-                        else src = vb_h + (hw ? hi : lo) * tile + (dt * 64 + lane) * 8;
+                const int lo = mt == 0 ? b.b0 : (bpu_shift == 2 ? b.b2 : b.b1);   // first block of tile half mt
+                const int hi = mt == 0 ? b.b1 : b.b3;                              // block 16 only: its second block
+                if (is_k) {
+                    const int cs = chunk & 3;
+                    if (bpu_shift == 1) {  // block 32: the 32-row tile of block mt
+                        src = kb_h + lo * tile + cs * 512 + lane * 8;
+                    } else {               // block 16: rows 0..15 of the tile from its first block, rows 16..31 from its second
+                        const int blk = ((lane >> 4) & 1) ? hi : lo;
+                        src = kb_h + blk * tile + ((cs * 2 + (lane >> 5)) * 16 + (lane & 15)) * 8;
                     }
                 } else {
-                    const int64_t w2 = u - n_units1;
-                    src = (is_k ? kb2_h : vb2_h) + w2 * kUnitElems + (chunk & 7) * 512 + lane * 8;
+                    const int hw = ((chunk & 7) >> 1) & 1, dt = chunk & 1;
+                    if (bpu_shift == 1) src = vb_h + lo * tile + ((hw * 2 + dt) * 64 + lane) * 8;
+                    else src = vb_h + (hw ? hi : lo) * tile + (dt * 64 + lane) * 8;
                 }
                 lds_dma_16(src + part, __builtin_amdgcn_readfirstlane(stage_byte + chunk * 1024));
             }
@@ -358,21 +375,29 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     auto first_keys = [](int left) -> unsigned long long {
         return left >= kUnitKeys ? ~0ull : left <= 0 ? 0ull : (1ull << left) - 1ull;
     };
-    // which of the 64 keys of step s's unit exist (wave-uniform)
-    auto unit_mask = [&](int s) -> unsigned long long {
-        if (SMALL && s + u_begin < n_units1) {
-            unsigned long long vm = 0ull;
+    // Which of the 64 keys of a step's unit exist (wave-uniform).  SMALL: put together from the lengths of the blocks, for
+    // 64 steps at a time, one per lane (a length per block and unit loaded in its turn would hold up every unit).
+    unsigned masks_lo = 0u, masks_hi = 0u;
+    auto load_masks = [&](int s) {  // of steps s .. s + 63
+        const int u = s + u_begin + lane;
+        unsigned long long m = 0ull;
+        if (u >= n_units1) {
+            m = first_keys(static_cast<int>(n_keys2) - (u - n_units1) * kUnitKeys);
+        } else {
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (c < (1 << bpu_shift)) {
-                    const int j = block_at(s + u_begin, c);
-                    const int len = j >= 0 ? block_tokens(j) : 0;
-                    vm |= ((1ull << len) - 1ull) << (c * block);
-                }
-            return vm;
+            for (int c = 0; c < 4; ++c) {
+                const int j = (u << bpu_shift) + c;
+                if (c < (1 << bpu_shift) && j < n_blk) m |= ((1ull << block_tokens(j)) - 1ull) << (c * block);
+            }
         }
-        const int w = unit_of(s);
-        return first_keys(unit_left(w));
+        masks_lo = static_cast<unsigned>(m);
+        masks_hi = static_cast<unsigned>(m >> 32);
+    };
+    auto unit_mask = [&](int s) -> unsigned long long {
+        if constexpr (SMALL)
+            return static_cast<unsigned long long>(static_cast<unsigned>(__builtin_amdgcn_readlane(masks_hi, s & 63))) << 32 |
+                   static_cast<unsigned>(__builtin_amdgcn_readlane(masks_lo, s & 63));
+        return first_keys(unit_left(unit_of(s)));
     };
 
     float lowest = -INFINITY;  // where the maxima start; the compiler takes two scores per v_max3 if it does not know the value
@@ -572,6 +597,8 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         lds_barrier();
         if (s + D < n_steps) issue(s + D, stage_ahead);
         if constexpr (PROBE) continue;
+        if constexpr (SMALL)
+            if ((s & 63) == 0) load_masks(s);
         const unsigned long long vmask = unit_mask(s);
         if ((KS == 1 ? vmask : vmask >> (32 * kh)) == 0ull) continue;  // second half of a short last block
         // (a key half: the second 32-row tile of K, the second two key steps of V)

@@ -70,7 +70,7 @@ size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 //   bf16, blocks of 16, 20 views    8: 0.076  16: 0.056*  24: 0.059  32: 0.061
 //                       100 views   8: 0.447  12: 0.413*  16: 0.440  32: 0.493
 //   fp32, blocks of 64, 20 views    8: 0.120  16: 0.082*  24: 0.092  32: 0.098
-//                       60 views    8: 0.589  10: 0.503   16: 0.512*  32: 0.548   (2.12 with a ring of 120 KiB, one
+//                       60 views    8: 0.589  10: 0.503   16: 0.512  20: 0.536 (21 chosen)  32: 0.548   (2.12 with a ring of 120 KiB, one
 //                       workgroup per CU and the operand array of a chunk looked up in scratch memory)
 // fp32 takes at least 16 splits, although fewer can be faster: the error of a row against 64 bits grows with the units in
 // one chain of sums (200 views: 1.0e-5 in one split, 7.6e-6 in 2, 5.7e-6 in 6, 5.4e-6 in 8, 5.0e-6 in 16).  In bf16 it is
