@@ -2,6 +2,7 @@
 // explicit vmcnt waits, exchanges between the two halves of a wave, and the constants of the 64-key unit.
 #pragma once
 #include "s3r_device.h"
+#include "s3r_kernels.h"
 
 namespace s3r {
 
@@ -58,6 +59,42 @@ template <int N> __device__ __forceinline__ void wait_vmcnt()
 {
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// Work mapping of the selection kernels: workgroup id mod 8 is its XCD, and each XCD has an L2 of its own.  Neighbouring
+// query blocks share key blocks, so an XCD works on neighbours: on a contiguous eighth of every head's query blocks, all
+// XCDs on the same head at a time, or (whole_heads) on a contiguous eighth of all (head, query block) pairs.
+// The former keeps the key blocks in use together in the memory-side cache (1000 views: 43.9 ms, 52.5 the other way; 300
+// views, blocks of 128: 18.7 and 21.0); the latter lets an XCD read few heads only, which pays where a head's K and V fit
+// an L2 or two of 4 MiB (16 heads, blocks of 64, microseconds, former -> latter: 4 views 65.9 -> 63.5, 8 views 108.5 ->
+// 102, 12: 157.5 -> 153, 16: 200.6 -> 195.5, 24 views (8.4 MB a head) 322 -> 321, 40: 764 -> 763, 100: 2055 -> 2127; blocks of
+// 32, 8 views 127.3 -> 120, 20 views (7 MB) 334 -> 325; fp32, 8 views (7 MB) 247 -> 242, 16 views 514 -> 515).
+constexpr int64_t kWholeHeadBytes = int64_t(8) << 20;
+
+inline bool xcd_whole_heads(const SelectArgs &a)
+{
+    return a.n_blk * a.block * 64 * 2 * (a.is_bf16 ? 2 : 5) <= kWholeHeadBytes;  // fp32: three parts of K, two of V
+}
+
+inline int64_t xcd_grid(int64_t n_sets, int heads, bool whole_heads)
+{
+    return whole_heads ? (n_sets * heads + 7) / 8 * 8 : (n_sets + 7) / 8 * 8 * heads;
+}
+
+// Head and set of workgroup `bid`; false: none.
+__device__ __forceinline__ bool xcd_item(int64_t bid, int64_t n_sets, int heads, bool whole_heads, int &h, int64_t &set)
+{
+    if (whole_heads) {
+        const int64_t per = (n_sets * heads + 7) / 8, item = (bid & 7) * per + (bid >> 3);
+        h = static_cast<int>(item / n_sets);
+        set = item - h * n_sets;
+        return h < heads;
+    }
+    const int64_t per = (n_sets + 7) / 8;
+    h = static_cast<int>(bid / (8 * per));
+    const int64_t r = bid % (8 * per);
+    set = (r % 8) * per + r / 8;
+    return set < n_sets;
 }
 
 }  // namespace s3r

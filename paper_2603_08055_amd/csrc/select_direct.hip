@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256, OCC) void select_direct_kernel(
     const int32_t *__restrict__ idx, const float *__restrict__ o_comp, const void *__restrict__ gate_,
     void *__restrict__ out_, void *__restrict__ o_sel_, float *__restrict__ lse, int64_t n_tok, int64_t n_blk,
     int heads, int kk, float scale_log2, int64_t n_groups, TokenMap qmap, int64_t n_keys, int64_t lse_stride,
-    const int32_t *__restrict__ blk_len, const float *__restrict__ o_comp_tok, InStride in, int64_t lo_off)
+    const int32_t *__restrict__ blk_len, const float *__restrict__ o_comp_tok, InStride in, int64_t lo_off, bool whole_heads)
 {
     static_assert(B == 16 || B == 32, "one MFMA tile per query block");
     constexpr int NR = B * B / 64;          // score registers of a key block: 4 or 16
@@ -64,15 +64,10 @@ __global__ __launch_bounds__(256, OCC) void select_direct_kernel(
     const int col = lane & (B - 1), g = lane / B;  // the lane's query; which of the lanes that share it
     int h;
     int64_t set;
-    {   // head-major, each XCD (workgroup id mod 8) takes a contiguous range of query blocks, four per workgroup
-        const int64_t bid = blockIdx.x;
-        const int64_t per = (n_groups + 7) / 8;
-        h = static_cast<int>(bid / (8 * per));
-        const int64_t r = bid % (8 * per);
-        const int64_t group = (r % 8) * per + r / 8;
-        set = group * 4 + wave;
-        if (group >= n_groups || set >= n_blk) return;  // (no barriers in this kernel)
-    }
+    int64_t group;  // four query blocks of a head per workgroup
+    if (!xcd_item(blockIdx.x, n_groups, heads, whole_heads, h, group)) return;
+    set = group * 4 + wave;
+    if (set >= n_blk) return;  // (no barriers in this kernel)
     const int64_t t = set * B + col;
     const bool row_valid = blk_len != nullptr ? col < blk_len[set] : t < n_tok;
     const int64_t trow = qmap.row(row_valid ? t : set * B);  // the caller's row of this query
@@ -312,12 +307,13 @@ template <int B, bool F32, int NBU, int OCC>
 static hipError_t run_direct(const SelectArgs &a, hipStream_t stream)
 {
     const int64_t groups = (a.n_blk + 3) / 4;
-    const int64_t grid = (groups + 7) / 8 * 8 * a.heads;
+    const bool whole_heads = xcd_whole_heads(a);
+    const int64_t grid = xcd_grid(groups, a.heads, whole_heads);
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL((select_direct_kernel<B, F32, NBU, OCC>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, stream,
                        a.q, static_cast<const bf16_t *>(a.kb), static_cast<const bf16_t *>(a.vb), a.idx, a.o_comp,
                        a.gate, a.out, a.o_sel, a.lse, a.n_tok, a.n_blk, a.heads, a.kk, a.scale * kLog2e, groups, a.qmap,
-                       a.n_keys, a.lse_stride, a.blk_len, a.x.o_comp_tok, a.x.in, a.lo_off);
+                       a.n_keys, a.lse_stride, a.blk_len, a.x.o_comp_tok, a.x.in, a.lo_off, whole_heads);
     return hipGetLastError();
 }
 

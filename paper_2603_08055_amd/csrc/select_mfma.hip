@@ -117,12 +117,8 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
                     set /= x.n_split;
                 }
             }
-        } else {  // head-major, each XCD (workgroup id mod 8) takes a contiguous range of sets
-            const int64_t per = (n_sets + 7) / 8;
-            h = static_cast<int>(bid / (8 * per));
-            const int64_t r = bid % (8 * per);
-            set = (r % 8) * per + r / 8;
-            if (set >= n_sets) return;
+        } else if (!xcd_item(blockIdx.x, n_sets, heads, map_mode == 1, h, set)) {
+            return;
         }
         set += set_offset;
     }
@@ -736,11 +732,11 @@ static hipError_t run_select_x(const SelectArgs &a, hipStream_t stream)
     }
     if ((per_launch + 8) * a.heads * (a.x.n_split > 1 ? a.x.n_split : 1) > 0x7fffffffLL) return hipErrorInvalidValue;
     if (a.x.n_split > 1 && (!DENSE || a.x.out_f32 == nullptr || a.x.part_lse == nullptr)) return hipErrorInvalidValue;
-    const int map_mode = DENSE ? 0 : 2;
+    const int map_mode = DENSE ? 0 : xcd_whole_heads(a) ? 1 : 2;
     for (int64_t s0 = 0; s0 < sets; s0 += per_launch) {
         const int64_t ns = (sets - s0 < per_launch) ? sets - s0 : per_launch;
         const int64_t n_split = (DENSE && a.x.n_split > 1) ? a.x.n_split : 1;
-        const int64_t grid = (map_mode == 2) ? (ns + 7) / 8 * 8 * a.heads : ns * n_split * a.heads;
+        const int64_t grid = (map_mode != 0) ? xcd_grid(ns, a.heads, map_mode == 1) : ns * n_split * a.heads;
         hipLaunchKernelGGL((select_mfma_kernel<QW, DENSE, NS, SMALL, EXTRA, ASMQ, PAIR, PROBE, F32, KS>), dim3(static_cast<unsigned>(grid)),
                            dim3(QW * KS * 64), pad_bytes, stream, static_cast<const bf16_t *>(a.q),
                            static_cast<const bf16_t *>(a.kb), static_cast<const bf16_t *>(a.vb), a.idx,

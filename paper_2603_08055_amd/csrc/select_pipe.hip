@@ -39,7 +39,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     const int32_t *__restrict__ idx, const float *__restrict__ o_comp, const bf16_t *__restrict__ gate,
     bf16_t *__restrict__ out, bf16_t *__restrict__ o_sel, float *__restrict__ lse, int64_t n_tok, int64_t n_blk,
     int heads, int kk, float scale_log2, int64_t n_sets, TokenMap qmap, int64_t n_keys, int64_t lse_stride,
-    const int32_t *__restrict__ blk_len, InStride in)
+    const int32_t *__restrict__ blk_len, InStride in, bool whole_heads)
 {
     constexpr int BLOCK = 64;
     constexpr int L = 8;                                  // 1 KiB chunks a wave requests per iteration
@@ -58,14 +58,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int h;
     int64_t set;
-    {   // head-major, each XCD (workgroup id mod 8) takes a contiguous range of query blocks
-        const int64_t bid = blockIdx.x;
-        const int64_t per = (n_sets + 7) / 8;
-        h = static_cast<int>(bid / (8 * per));
-        const int64_t rr = bid % (8 * per);
-        set = (rr % 8) * per + rr / 8;
-        if (set >= n_sets) return;
-    }
+    if (!xcd_item(blockIdx.x, n_sets, heads, whole_heads, h, set)) return;
     const int r = wave & 1, p = wave >> 1;   // row group; which of an iteration's units
     const int64_t t = set * BLOCK + r * 32 + (lane & 31);
     bool row_valid = t < n_tok;
@@ -446,13 +439,14 @@ template <int P, int NSK, int NSV, int AHEAD>
 static hipError_t run_pipe(const SelectArgs &a, hipStream_t stream)
 {
     const int64_t sets = a.n_blk;
-    const int64_t grid = (sets + 7) / 8 * 8 * a.heads;
+    const bool whole_heads = xcd_whole_heads(a);
+    const int64_t grid = xcd_grid(sets, a.heads, whole_heads);
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL((select_pipe_kernel<P, NSK, NSV, AHEAD>), dim3(static_cast<unsigned>(grid)), dim3(128 * P), 0, stream,
                        static_cast<const bf16_t *>(a.q), static_cast<const bf16_t *>(a.kb),
                        static_cast<const bf16_t *>(a.vb), a.idx, a.o_comp, static_cast<const bf16_t *>(a.gate),
                        static_cast<bf16_t *>(a.out), static_cast<bf16_t *>(a.o_sel), a.lse, a.n_tok, a.n_blk, a.heads,
-                       a.kk, a.scale * kLog2e, sets, a.qmap, a.n_keys, a.lse_stride, a.blk_len, a.x.in);
+                       a.kk, a.scale * kLog2e, sets, a.qmap, a.n_keys, a.lse_stride, a.blk_len, a.x.in, whole_heads);
     return hipGetLastError();
 }
 
