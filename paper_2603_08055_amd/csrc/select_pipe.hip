@@ -178,7 +178,9 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     // (rescale) once P(i - 1) V(i - 1) has been added to them, which is still in the old scale.  (Scaling P(i - 1)
     // instead would round it to bf16 a second time, where the row sum has it as it was: up to 0.4 %.)
     float alpha;  // what the accumulators are to be scaled by
-    auto soft_pre = [&](floatx16 (&acc)[2], int n_keys_u) __attribute__((always_inline)) -> bool {
+    // lead(q4), q4 = 0..3: what the matrix pipe does under the maxima (the first scores of the unit after; 1000 views 42.9 ->
+    // 42.2 ms, 200 views with forced blocks 12.75 -> 12.53: the maxima used to leave it idle).
+    auto soft_pre = [&](floatx16 (&acc)[2], int n_keys_u, bool overlap, auto &&lead) __attribute__((always_inline)) -> bool {
         if (n_keys_u < kUnitKeys) {
             asm volatile("" ::: "memory");  // keep this rare path a real branch
             // Runs of 16 keys, compared with constants (a bit test per register would have its 32 masks held in
@@ -196,9 +198,17 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
         }
         float mx[2] = {lowest, lowest};  // two chains of v_max3
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int q4 = 0; q4 < 4; ++q4) {
+            lead(q4);
 #pragma unroll
-            for (int x = 0; x < 16; x += 2) mx[mt] = fmaxf(fmaxf(mx[mt], acc[mt][x]), acc[mt][x + 1]);
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int x = 4 * q4; x < 4 * q4 + 4; x += 2) mx[mt] = fmaxf(fmaxf(mx[mt], acc[mt][x]), acc[mt][x + 1]);
+            if (overlap) {
+                asm volatile("" : "+v"(mx[0]), "+v"(mx[1]));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
         // The two lanes of a query look at their own halves of the unit; they exchange them only when either has to
         // raise the maximum.
         const float mx_own = fmaxf(mx[0], mx[1]);
@@ -227,6 +237,13 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     auto operand = [&](int m, const bf16_t *k_src, const bf16_t *v_src) __attribute__((always_inline)) -> bf16x8 {
         return *reinterpret_cast<const bf16x8 *>(m < 8 ? k_src + ((m & 1) * 4 + (m >> 1)) * 512 : v_src + (m - 8) * 512);
     };
+    // MFMA m of an iteration, and the LDS read of the operand a few MFMAs ahead
+    auto matrix = [&](int m, floatx16 (&acc_next)[2], const bf16x8 (&p_in)[4], bf16x8 (&rd)[16], const bf16_t *k_src,
+                      const bf16_t *v_src) __attribute__((always_inline)) {
+        if (m < 8) acc_next[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd[m], qb[m >> 1], m < 2 ? zero16 : acc_next[m & 1], 0, 0, 0);
+        else oacc[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd[m], p_in[(m - 8) >> 1], oacc[m & 1], 0, 0, 0);
+        if (m + kAhead < 16) rd[m + kAhead] = operand(m + kAhead, k_src, v_src);
+    };
     // The overlapped part of an iteration, written out as 8 groups of two MFMAs (the scores of the unit after,
     // then P.V of the unit before; each with the LDS read of the operand a few MFMAs ahead) and the vector
     // work on four score registers (four exponents, issued next to each other so that none waits for the
@@ -234,16 +251,14 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     // their LDS latency runs under it.
     auto overlapped = [&](floatx16 (&acc)[2], floatx16 (&acc_next)[2], bf16x8 (&p_out)[4], const bf16x8 (&p_in)[4],
                           bf16x8 (&rd)[16], const bf16_t *k_src, const bf16_t *v_src) __attribute__((always_inline)) {
-        auto mfma = [&](int m) __attribute__((always_inline)) {
-            if (m < 8) acc_next[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd[m], qb[m >> 1], m < 2 ? zero16 : acc_next[m & 1], 0, 0, 0);
-            else oacc[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rd[m], p_in[(m - 8) >> 1], oacc[m & 1], 0, 0, 0);
-            if (m + kAhead < 16) rd[m + kAhead] = operand(m + kAhead, k_src, v_src);
-        };
+        // MFMAs 4 .. 15 spread over the 16 half groups
+        auto first_of = [](int half) { return 4 + (half * (16 - 4) + 15) / 16; };
+        auto mfma = [&](int m) __attribute__((always_inline)) { matrix(m, acc_next, p_in, rd, k_src, v_src); };
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q4 = 0; q4 < 8; ++q4) {  // four score registers and two MFMAs per group
             const int mt = q4 >> 2, x0 = 4 * (q4 & 3);
-            mfma(2 * q4);
+            if (first_of(2 * q4) < first_of(2 * q4 + 1)) mfma(first_of(2 * q4));
             // independent instructions next to each other: four exponents, then their two packs and sums
             float e[4];
 #pragma unroll
@@ -251,7 +266,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
 #pragma unroll
             for (int c = 0; c < 4; ++c) e[c] = fast_exp2(e[c]);
             __builtin_amdgcn_sched_barrier(0);
-            mfma(2 * q4 + 1);
+            if (first_of(2 * q4 + 1) < first_of(2 * q4 + 2)) mfma(first_of(2 * q4 + 1));
 #pragma unroll
             for (int c = 0; c < 4; c += 2) {
                 const bf16x2 pr = {static_cast<bf16_t>(e[c]), static_cast<bf16_t>(e[c + 1])};
@@ -270,7 +285,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     // the same three phases one after the other, each only if its unit exists (first and last iterations)
     auto plain = [&](bool soft, bool pv, bool ss, floatx16 (&acc)[2], floatx16 (&acc_next)[2], bf16x8 (&p_out)[4],
                      const bf16x8 (&p_in)[4], const bf16_t *k_src, const bf16_t *v_src, int n_keys_u) __attribute__((always_inline)) {
-        const bool raised = soft && soft_pre(acc, n_keys_u);
+        const bool raised = soft && soft_pre(acc, n_keys_u, false, [](int) {});
         if (pv) {
 #pragma unroll
             for (int m = 0; m < 8; ++m) {
@@ -337,7 +352,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
         bf16x8 rd[16];
 #pragma unroll
         for (int m = 0; m < kAhead; ++m) rd[m] = operand(m, k_src, v_src);
-        const bool raised = soft_pre(accs[PAR], keys_of(i * P + p));
+        const bool raised = soft_pre(accs[PAR], keys_of(i * P + p), true, [&](int q4) __attribute__((always_inline)) { if (q4 < 4) matrix(q4, accs[1 - PAR], ps[1 - PAR], rd, k_src, v_src); });
         overlapped(accs[PAR], accs[1 - PAR], ps[PAR], ps[1 - PAR], rd, k_src, v_src);
         if (__builtin_expect(raised, 0)) rescale();
     };
@@ -465,7 +480,10 @@ hipError_t launch_select_pipe(const SelectArgs &a, hipStream_t stream)
     // and short sequences (100 views: one pair is 5 to 10 % ahead at every row length) from more of them.
     // Strided q (slices of one projection output) comes here as well, the strides enter one address per lane: the
     // layer on 150 views, 8 x 8 windows, top-32 takes 3.92 ms, 4.35 with the selection in select_mfma.hip.
-    if (a.kk >= 40 && a.n_blk >= 3000) return run_pipe<2, 2, 2, 3>(a, stream);
+    // Rows with forced blocks, which all rows share, hit the L2s anyway: one pair (23 of 87 blocks forced, 200 views: two
+    // pairs 9.33 ms a call, one 8.99; 1000 views 51.96 and 50.13; 46 of 110 forced, 400 views 22.9 and 21.4).  40 blocks per
+    // row, 150 views: two 3.77, one 3.65; 200 views 5.14 and 5.27; 64 blocks, 150 views 5.45 and 5.67.
+    if (a.kk >= 40 && a.n_blk >= 3000 && a.kk * a.n_blk >= 160000 && a.n_common == 0) return run_pipe<2, 2, 2, 3>(a, stream);
     return run_pipe<1, 2, 2, 3>(a, stream);
 }
 
