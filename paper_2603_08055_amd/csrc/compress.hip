@@ -170,8 +170,9 @@ __device__ __forceinline__ float kth_bucket_maximum(const float (&bm)[64], int k
     return T < 0x03ffu ? -INFINITY : key_value(T);  // 0x03ff: the key of -inf; those below are NaN patterns
 }
 
-// One workgroup's share: query tiles bx * CW .. + CW - 1 of head by.
-template <bool SPLIT_PV, int NS, int CW, int MODE>
+// One workgroup's share: query tiles bx * CW .. + CW - 1 of head by.  FORCED (kThresholdPipe): there are forced blocks (a
+// second instantiation: with both loops in one kernel the registers allow two waves per SIMD, not three).
+template <bool SPLIT_PV, int NS, int CW, int MODE, bool FORCED>
 __device__ __forceinline__ void compress_block(
     const bf16_t *__restrict__ qs_hi, const bf16_t *__restrict__ qs_lo,
     const bf16_t *__restrict__ ks_hi, const bf16_t *__restrict__ ks_lo,
@@ -292,7 +293,12 @@ __device__ __forceinline__ void compress_block(
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
-        float m_run = -1e30f, l_run = 0.f;
+        float m_run = -1e30f;
+        float m_lim = -1e30f + kCompressRescaleSlack;  // what a half step's largest logit must exceed to raise m_run
+        float l_run[4] = {0.f, 0.f, 0.f, 0.f};         // the row sum in four chains
+        float lowest = -INFINITY;  // where the maxima start; the compiler takes two scores per v_max3 if it does not know the value
+        asm("" : "+v"(lowest));
+        lowest = fmaxf(lowest, lowest);
         half2_t bmax[2][16];  // [step parity][mt * 8 + register pair]
 #pragma unroll
         for (int par = 0; par < 2; ++par)
@@ -328,20 +334,23 @@ __device__ __forceinline__ void compress_block(
         auto soft_pre = [&](int kt, int mt, floatx16 &acc, bf16x8 (&p_pending)[2]) __attribute__((always_inline)) {
             if (kt * 64 + mt * 32 + 32 > n_blk) {
                 asm volatile("" ::: "memory");  // keep this rare path a real branch
+                const int left = static_cast<int>(n_blk - kt * 64 - mt * 32) - 4 * g;  // compared with constants
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    if (kt * 64 + mt * 32 + acc_row(lane, r) >= n_blk) acc[r] = -INFINITY;
+                    if (8 * (r >> 2) + (r & 3) >= left) acc[r] = -INFINITY;
             }
-            float mx = acc[0];
+            float mx = lowest;
 #pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, acc[r]);
-            const float m_tile = compress_max_halves(mx) * scale_log2_h;
-            const bool grow = m_tile > m_run + kCompressRescaleSlack;
-            if (__any(grow)) {
-                const float m_new = grow ? m_tile : m_run;
+            for (int r = 0; r < 16; r += 2) mx = fmaxf(fmaxf(mx, acc[r]), acc[r + 1]);
+            // the two lanes of a query look at their own keys and exchange maxima only when either has to raise it
+            if (__builtin_expect(__any(mx * scale_log2_h > m_lim), 0)) {
+                const float m_tile = compress_max_halves(mx) * scale_log2_h;
+                const float m_new = m_tile > m_lim ? m_tile : m_run;
                 const float alpha = fast_exp2(m_run - m_new);
                 m_run = m_new;
-                l_run *= alpha;
+                m_lim = m_new + kCompressRescaleSlack;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) l_run[c] *= alpha;
 #pragma unroll
                 for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
@@ -359,10 +368,9 @@ __device__ __forceinline__ void compress_block(
         // half step after (keys in stage k_stage, half k_mt, into acc_next).  The vector work: the softmax
         // of this half step (scores acc, half mt): bucket maxima, probabilities, their sum, bf16 operands
         // p_out.
-        auto half_step = [&](auto forced_tag, unsigned long long fw, int mt, floatx16 &acc, half2_t (&bm)[16],
+        auto half_step = [&](unsigned long long fw, int mt, floatx16 &acc, half2_t (&bm)[16],
                              bf16x8 (&p_out)[2], int pv_stage, int pv_mt, const bf16x8 (&p_in)[2], int k_stage,
                              int k_mt, floatx16 &acc_next) __attribute__((always_inline)) {
-            constexpr bool FORCED = decltype(forced_tag)::value;
             const bf16_t *v_src = &ring[pv_stage][1][0] + pv_mt * kRowTileElems + lane * 8;
             const bf16_t *khi_src = &ring[k_stage][0][0] + k_mt * kRowTileElems + lane * 8;
             bf16x8 rd[8];  // reads in order of need: V chunks 0..3, then the keys of channel steps 0..3
@@ -372,7 +380,6 @@ __device__ __forceinline__ void compress_block(
             read(0); read(1); read(2);
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc_next[r] = 0.f;
-            float lsum[4] = {0.f, 0.f, 0.f, 0.f};
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
@@ -387,7 +394,7 @@ __device__ __forceinline__ void compress_block(
                 if ((j & 1) == 0) {
                     float a0 = acc[j], a1 = acc[j + 1];
                     if constexpr (FORCED) {  // forced blocks do not compete (Sec. 3.3)
-                        const unsigned two = static_cast<unsigned>(fw >> (mt * 32 + acc_row(lane, j))) & 3u;
+                        const unsigned two = static_cast<unsigned>(fw >> (mt * 32 + 8 * (j >> 2) + (j & 3))) & 3u;
                         a0 = (two & 1u) ? -INFINITY : a0;
                         a1 = (two & 2u) ? -INFINITY : a1;
                     }
@@ -400,18 +407,17 @@ __device__ __forceinline__ void compress_block(
                     const bf16x2 pr = {static_cast<bf16_t>(acc[j - 1]), static_cast<bf16_t>(acc[j])};
                     p_out[j >> 3][(j & 7) - 1] = pr[0];
                     p_out[j >> 3][j & 7] = pr[1];
-                    lsum[(j >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, bf16x2{static_cast<bf16_t>(1.f), static_cast<bf16_t>(1.f)},
-                                                                         lsum[(j >> 1) & 3], false);
+                    l_run[(j >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, bf16x2{static_cast<bf16_t>(1.f), static_cast<bf16_t>(1.f)},
+                                                                         l_run[(j >> 1) & 3], false);
                 }
                 // nothing needs these values before the next barrier: tie them to this slot, or the
                 // compiler moves the vector work away from the MFMAs it is meant to overlap with
-                if (j & 1) asm volatile("" : "+v"(lsum[(j >> 1) & 3]));
+                if (j & 1) asm volatile("" : "+v"(l_run[(j >> 1) & 3]));
                 else asm volatile("" : "+v"(acc[j]));
                 if ((j & 1) == 0) asm volatile("" : "+v"(bm[mt * 8 + (j >> 1)]));
                 if ((j & 7) == 7) asm volatile("" : "+v"(p_out[j >> 3]));
                 __builtin_amdgcn_sched_barrier(0);
             }
-            l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
         };
 
         floatx16 sacc0, sacc1;
@@ -424,30 +430,30 @@ __device__ __forceinline__ void compress_block(
         scores(0, 0, sacc0);
         int kst = 0, vprev = 2;  // stage of the keys of step kt; stage of the values of step kt - 1
         // one 64-key step; PAR = step parity (which bucket set), as a compile-time choice
-        auto step = [&](auto forced_tag, auto par_tag, int kt) __attribute__((always_inline)) {
+        auto step = [&](auto par_tag, int kt) __attribute__((always_inline)) {
             constexpr int PAR = decltype(par_tag)::value;
-            const unsigned long long fw = decltype(forced_tag)::value ? forced_words[kt] : 0ull;  // wave-uniform
+            // forced blocks of this step, shifted so that the bit of score register r is a constant for every lane
+            const unsigned long long fw = FORCED ? forced_words[kt] >> (4 * g) : 0ull;
             const int knext = (kst + 1 == 3) ? 0 : kst + 1;
             // half step 0: softmax here; P.V of the previous half step and scores of half step 1 on the matrix pipe
             soft_pre(kt, 0, sacc0, p1);
-            half_step(forced_tag, fw, 0, sacc0, bmax[PAR], p0, vprev, 1, p1, kst, 1, sacc1);
+            half_step(fw, 0, sacc0, bmax[PAR], p0, vprev, 1, p1, kst, 1, sacc1);
             publish(kt + 1);  // group kt + 1: keys of step kt + 1, values of step kt
             // half step 1: softmax here; P.V of half step 0 and the first scores of the next step on the matrix pipe
             // (after the last step: a copy of its keys, result unused)
             soft_pre(kt, 1, sacc1, p0);
-            half_step(forced_tag, fw, 1, sacc1, bmax[PAR], p1, kst, 0, p0, knext, 0, sacc0);
+            half_step(fw, 1, sacc1, bmax[PAR], p1, kst, 0, p0, knext, 0, sacc0);
             vprev = kst;
             kst = knext;
         };
-        auto sweep = [&](auto forced_tag) __attribute__((always_inline)) {
+        {
             int kt = 0;
             for (; kt + 1 < n_kt; kt += 2) {
-                step(forced_tag, std::integral_constant<int, 0>{}, kt);
-                step(forced_tag, std::integral_constant<int, 1>{}, kt + 1);
+                step(std::integral_constant<int, 0>{}, kt);
+                step(std::integral_constant<int, 1>{}, kt + 1);
             }
-            if (kt < n_kt) step(forced_tag, std::integral_constant<int, 0>{}, kt);
-        };
-        if (forced_words != nullptr) sweep(std::true_type{}); else sweep(std::false_type{});
+            if (kt < n_kt) step(std::integral_constant<int, 0>{}, kt);
+        }
         pv(vprev, 1, p1);
 
         {
@@ -467,7 +473,7 @@ __device__ __forceinline__ void compress_block(
             if (qrow < n_blk && g == 0) ft.thr[row_id] = kth == -INFINITY ? kth : kth - margin;
         }
         if (qrow < n_blk) {
-            const float inv = 1.f / compress_sum_halves(l_run);
+            const float inv = 1.f / compress_sum_halves((l_run[0] + l_run[1]) + (l_run[2] + l_run[3]));
             float *orow = o_comp + (static_cast<int64_t>(h) * n_blk + qrow) * 64;
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt)
@@ -549,10 +555,13 @@ __device__ __forceinline__ void compress_block(
             // keys that do not exist or are forced never become candidates: -inf is below every bound
             if (kt * 64 + mt * 32 + 32 > n_blk || fw != 0ull) {
                 asm volatile("" ::: "memory");  // keep this rare path a real branch
+                // compared with constants: a mask or a shift amount per register would be held all through the sweep
+                const int left = static_cast<int>(n_blk - kt * 64 - mt * 32) - 4 * g;
+                const unsigned fwl = static_cast<unsigned>(fw >> (mt * 32)) >> (4 * g);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int b = mt * 32 + acc_row(lane, r);
-                    if (kt * 64 + b >= n_blk || ((fw >> b) & 1ull)) acc[r] = -INFINITY;
+                    const int b = 8 * (r >> 2) + (r & 3);
+                    if (b >= left || ((fwl >> b) & 1u)) acc[r] = -INFINITY;
                 }
             }
             const bf16_t *khi_src = &ring[k_stage][0][0] + k_mt * kRowTileElems + lane * 8;
@@ -821,8 +830,8 @@ __device__ __forceinline__ void compress_block(
 // The pipelined sweeps have no loader wave: all CW waves compute and each issues its share of the loads.
 template <int CW, int MODE> constexpr int compress_threads() { return (MODE == kThresholdPipe || MODE == kFilter) ? CW * 64 : (CW + 1) * 64; }
 
-template <bool SPLIT_PV, int NS, int CW, int MODE>
-__global__ __launch_bounds__((compress_threads<CW, MODE>()), (MODE == kFilter ? 4 : 2)) void compress_kernel(
+template <bool SPLIT_PV, int NS, int CW, int MODE, bool FORCED = false>
+__global__ __launch_bounds__((compress_threads<CW, MODE>()), (MODE == kFilter ? 4 : MODE == kThresholdPipe ? 3 : 2)) void compress_kernel(
     const bf16_t *__restrict__ qs_hi, const bf16_t *__restrict__ qs_lo,
     const bf16_t *__restrict__ ks_hi, const bf16_t *__restrict__ ks_lo,
     const bf16_t *__restrict__ vt_hi, const bf16_t *__restrict__ vt_lo, float *__restrict__ s_guide,
@@ -830,19 +839,19 @@ __global__ __launch_bounds__((compress_threads<CW, MODE>()), (MODE == kFilter ? 
     const unsigned long long *__restrict__ forced_words, FusedTopkArgs ft, unsigned gx, unsigned gy)
 {
     if (MODE != kStoreScores || ft.run_flag == nullptr) {
-        compress_block<SPLIT_PV, NS, CW, MODE>(qs_hi, qs_lo, ks_hi, ks_lo, vt_hi, vt_lo, s_guide, ld_s, o_comp, n_blk,
+        compress_block<SPLIT_PV, NS, CW, MODE, FORCED>(qs_hi, qs_lo, ks_hi, ks_lo, vt_hi, vt_lo, s_guide, ld_s, o_comp, n_blk,
                                                tiles_padded, scale_log2, forced_words, ft, blockIdx.x, blockIdx.y);
         return;
     }
     if (*ft.run_flag == 0) return;  // uniform over the grid
     for (unsigned v = blockIdx.x; v < gx * gy; v += gridDim.x) {
-        compress_block<SPLIT_PV, NS, CW, MODE>(qs_hi, qs_lo, ks_hi, ks_lo, vt_hi, vt_lo, s_guide, ld_s, o_comp, n_blk,
+        compress_block<SPLIT_PV, NS, CW, MODE, FORCED>(qs_hi, qs_lo, ks_hi, ks_lo, vt_hi, vt_lo, s_guide, ld_s, o_comp, n_blk,
                                                tiles_padded, scale_log2, forced_words, ft, v % gx, v / gx);
         __syncthreads();
     }
 }
 
-template <bool SPLIT_PV, int NS, int CW, int MODE>
+template <bool SPLIT_PV, int NS, int CW, int MODE, bool FORCED = false>
 static hipError_t run_compress(const void *qs_hi, const void *qs_lo, const void *ks_hi, const void *ks_lo,
                                const void *vt_hi, const void *vt_lo, float *s_guide, int64_t ld_s,
                                float *o_comp, int64_t n_blk, int heads, float scale_log2,
@@ -858,7 +867,7 @@ static hipError_t run_compress(const void *qs_hi, const void *qs_lo, const void 
         if (total > 0xffffffffull) return hipErrorInvalidValue;
         grid = dim3(total > kFlaggedGrid ? kFlaggedGrid : static_cast<unsigned>(total), 1);
     }
-    hipLaunchKernelGGL((compress_kernel<SPLIT_PV, NS, CW, MODE>), grid, dim3(compress_threads<CW, MODE>()), 0, stream,
+    hipLaunchKernelGGL((compress_kernel<SPLIT_PV, NS, CW, MODE, FORCED>), grid, dim3(compress_threads<CW, MODE>()), 0, stream,
                        static_cast<const bf16_t *>(qs_hi), static_cast<const bf16_t *>(qs_lo),
                        static_cast<const bf16_t *>(ks_hi), static_cast<const bf16_t *>(ks_lo),
                        static_cast<const bf16_t *>(vt_hi), static_cast<const bf16_t *>(vt_lo), s_guide, ld_s,
@@ -894,6 +903,8 @@ hipError_t launch_compress_threshold(const void *qs_hi, const void *qs_lo, const
     if (vt_lo != nullptr)
         return run_compress<true, 2, 3, kThreshold>(qs_hi, qs_lo, ks_hi, ks_lo, vt_hi, vt_lo, nullptr, 0, o_comp, n_blk, heads, sl, forced_words, ft, stream);
     // (the fp16 tiles travel through the kernel's bf16-typed operand pointers: same size, same tile layout)
+    if (forced_words != nullptr)
+        return run_compress<false, 3, 4, kThresholdPipe, true>(q_f16, nullptr, k_f16, nullptr, vt_hi, nullptr, nullptr, 0, o_comp, n_blk, heads, sl, forced_words, ft, stream);
     return run_compress<false, 3, 4, kThresholdPipe>(q_f16, nullptr, k_f16, nullptr, vt_hi, nullptr, nullptr, 0, o_comp, n_blk, heads, sl, forced_words, ft, stream);
 }
 
