@@ -484,6 +484,11 @@ hipError_t launch_select_pipe(const SelectArgs &a, hipStream_t stream)
     // pairs 9.33 ms a call, one 8.99; 1000 views 51.96 and 50.13; 46 of 110 forced, 400 views 22.9 and 21.4).  40 blocks per
     // row, 150 views: two 3.77, one 3.65; 200 views 5.14 and 5.27; 64 blocks, 150 views 5.45 and 5.67.
     if (a.kk >= 40 && a.n_blk >= 3000 && a.kk * a.n_blk >= 160000 && a.n_common == 0) return run_pipe<2, 2, 2, 3>(a, stream);
+    // Few query blocks: a CU has room for two workgroups of two pairs, and while all of them run at once a row is done in
+    // half the iterations (microseconds a call, one pair -> two: 258 query blocks, 4 blocks a row 22.6 -> 21.2, 16 blocks
+    // 34.6 -> 28.2; 344, 64 blocks 82.9 -> 57.7; 430, 32 blocks 51.2 -> 39.2; 512, 8 blocks 26.6 -> 23.4; but 540, 16
+    // blocks 38.7 -> 41.0; 688 35.2 -> 36.3; 903 44.1 -> 47.5).
+    if (a.kk >= 4 && a.n_blk * a.heads <= 512) return run_pipe<2, 2, 2, 3>(a, stream);
     return run_pipe<1, 2, 2, 3>(a, stream);
 }
 

@@ -126,6 +126,36 @@ def test_forced_blocks_and_long_rows_in_one_launch(s3r, oracle, n_blk, topk, n_f
                                                  topk, "bf16", forced=forced, label=wl.name)))
 
 
+@pytest.mark.parametrize("n_tok,heads,topk,n_forced", [
+    (64 * 3 + 1, 128, 3, 0), (64 * 3 + 1, 128, 4, 0),     # 512 query blocks, on either side of the shortest row of two pairs
+    (64 * 27, 19, 7, 0), (64 * 27 - 60, 18, 8, 2),        # 513 and 486 of them; an odd number of units, forced blocks
+    (64 * 130, 2, 127, 0), (64 * 130, 2, 126, 2),         # 260: the longest rows
+])
+def test_two_pairs_of_waves_for_few_query_blocks(s3r, oracle, n_tok, heads, topk, n_forced):  # noqa: F811
+    wl = workloads.Workload(f"few_{n_tok}_{heads}_{topk}", 1, n_tok, heads, 64, "bf16", 64, topk, 105, "normal")
+    q, k, v = workloads.make_inputs(wl)
+    forced = list(range(n_forced)) if n_forced else None
+    res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), 64, topk, forced=forced)
+    log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v), None, 64,
+                                                 topk, "bf16", forced=forced, label=wl.name)))
+
+
+@pytest.mark.parametrize("dtype,block,n_tok,heads,topk", [
+    ("bf16", 64, 700, 7, 3), ("bf16", 64, 64 * 512, 3, 5),     # a head's K and V of 8 MiB: the last size by whole heads
+    ("bf16", 64, 64 * 513, 3, 5), ("bf16", 16, 16 * 33, 5, 4), ("bf16", 128, 128 * 9 - 1, 3, 4), ("f32", 64, 64 * 11, 9, 3),
+    ("f32", 32, 32 * 19, 1, 3),
+])
+def test_every_head_and_query_block_is_mapped_to_an_xcd(s3r, oracle, dtype, block, n_tok, heads, topk):  # noqa: F811
+    wl = workloads.Workload(f"map_{dtype}_{block}_{n_tok}_{heads}", 1, n_tok, heads, 64, dtype, block, topk, 106, "normal")
+    q, k, v = workloads.make_inputs(wl)
+    res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), block, topk)
+    assert torch.isfinite(res["out"].float()).all()
+    n_blk = (n_tok + block - 1) // block
+    rows = sorted({0, n_blk // 3, n_blk - 1})
+    log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v), None, block,
+                                                 topk, dtype, rows=rows, label=wl.name)))
+
+
 @pytest.mark.parametrize("layout", ["one projection", "head major", "padded heads"])
 @pytest.mark.parametrize("views,tpv,topk", [(3, 1000, 39), (150, 1281, 40)])   # one and two pairs of waves per query block
 def test_strided_queries_in_the_pipelined_selection(s3r, views, tpv, topk, layout):  # noqa: F811
