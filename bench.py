@@ -241,7 +241,7 @@ def main():
     achieved = sel_flops / (sel_ms * 1e-3) / 1e12
     traffic = None if (args.special or n_forced or args.compress_queries or args.kernel_choice) else measured_traffic(wl)
     pipe = (args.kernel_choice != 1 and wl.dtype == "bf16" and wl.block == 64 and kk <= 128
-            and not args.compress_queries and not (kk > 96 and 2 * n_forced >= kk))
+            and not args.compress_queries)
     roofline = {"kernel": ("select_generic_kernel" if args.kernel_choice == 1 else
                            "select_direct_kernel" if wl.block in (16, 32) else
                            "select_pipe_kernel" if pipe else "select_mfma_kernel"),
@@ -280,7 +280,8 @@ def main():
 
         # the probe at the occupancy of the kernel that ran: long rows on long sequences run two workgroups per
         # CU (64 query blocks in progress per XCD), everything else as many as fit
-        probe_wg = 2 if (wl.block == 64 and kk >= 40 and seq.n_blk >= 3000) else 0
+        two_pairs = kk >= 40 and seq.n_blk >= 3000 and kk * seq.n_blk >= 160000 and n_forced == 0
+        probe_wg = 2 if wl.block == 64 and two_pairs else 0
         probe_ms = time_probe(0, probe_wg)
         assert torch.equal(probe_out, q), "the load probe must leave a copy of q in its output"
         sweep = None
@@ -335,6 +336,7 @@ def main():
         return 2.0 * n / (e0.elapsed_time(e1) / 5 * 1e-3) / 1e9
     sweep_flops = 2.0 * wl.head_dim * float(seq.n_blk) * float(seq.n_blk) * wl.heads     # one N_b x N_b x d product
     in_sweep = kk - n_forced <= 64
+    short = seq.n_blk <= 1024 and seq.n_blk * seq.n_blk * wl.heads <= 1 << 23 and args.kernel_choice != 2
     stages = {
         "pool": {"bound": "hbm", "unit": "GB/s", "peak": 8000.0, "achieved": pool_bytes / stage_s("pool") / 1e9,
                  "frac": pool_bytes / stage_s("pool") / 1e9 / 8000.0, "algorithmic_bytes": pool_bytes,
@@ -351,7 +353,9 @@ def main():
         stages["pool"]["device_copy_GBps"] = copy_gbps
         stages["pool"]["moved_over_device_copy"] = stages["pool"]["moved_GBps"] / copy_gbps
         say(f"pool stage moves {stages['pool']['moved_GBps']:.0f} GB/s; a plain device copy of as many bytes {copy_gbps:.0f} GB/s")
-    if in_sweep:
+    if short:
+        stages["topk"] = {"note": "inside the compress launch (short sequences: scores, Oc' and TopK in one kernel)"}
+    elif in_sweep:
         stages["topk"] = {"bound": "mfma", "unit": "TFLOP/s", "peak": MFMA_BF16_PEAK_TFLOPS,
                           "achieved": sweep_flops / stage_s("topk") / 1e12,
                           "frac": sweep_flops / stage_s("topk") / 1e12 / MFMA_BF16_PEAK_TFLOPS, "flops": sweep_flops,
@@ -360,7 +364,9 @@ def main():
         stages["topk"] = {"bound": "hbm", "unit": "GB/s", "peak": 8000.0, "achieved": topk_bytes / stage_s("topk") / 1e9,
                           "frac": topk_bytes / stage_s("topk") / 1e9 / 8000.0, "algorithmic_bytes": topk_bytes}
         stages["compress"]["note"] += "; this route also writes S_guide (4 N_b^2 H bytes)"
-    if kk - n_forced > 64:   # TopK from S_guide in memory (k > 64); otherwise TopK runs inside the compression sweep
+    if short:
+        hbm["topk_route"] = "scores, Oc' and TopK in one launch (S_guide not written to memory)"
+    elif kk - n_forced > 64:   # TopK from S_guide in memory (k > 64); otherwise TopK runs inside the compression sweep
         hbm["topk_GBps"] = topk_bytes / (stage_ms["topk"] / args.steps * 1e-3) / 1e9
     else:
         hbm["topk_route"] = "inside the compression sweep (S_guide not written to memory)"

@@ -158,15 +158,18 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, cons
         // V tile, contraction (key) index made contiguous per lane: see tr_tile_key().
         for (int ci = HP == 1 ? tid : tid & 127; ci < B * 8; ci += 256 / HP) {
             if (!have_head) break;
+            // (blocks of 16 rows: the two channel tiles of a 16-byte piece one after the other, see small_v_piece)
             const int l = ci & 63, dt = (ci >> 6) & 1, u = ci >> 7;
-            const int d = 32 * dt + (l & 31);
+            const int d = B == 16 ? 32 * dt + (l & 15) : 32 * dt + (l & 31);
+            auto row_of = [&](int i) { return hh * B + (B == 16 ? 4 * (l >> 4) + (i & 3) : tr_tile_key(u, l, i)); };
+            auto channel_of = [&](int i) { return B == 16 ? d + 16 * (i >> 2) : d; };
             bf16x8 o;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) o[i] = vs[hh * B + tr_tile_key(u, l, i)][d];
+            for (int i = 0; i < 8; ++i) o[i] = vs[row_of(i)][channel_of(i)];
             *reinterpret_cast<bf16x8 *>(vb + tile_base + static_cast<int64_t>(ci) * 8) = o;
             if constexpr (PAIRS) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) o[i] = vs_lo[hh * B + tr_tile_key(u, l, i)][d];
+                for (int i = 0; i < 8; ++i) o[i] = vs_lo[row_of(i)][channel_of(i)];
                 *reinterpret_cast<bf16x8 *>(vb + lo_off + tile_base + static_cast<int64_t>(ci) * 8) = o;
             }
         }

@@ -39,6 +39,11 @@ __device__ __forceinline__ int tr_tile_key(int u, int lane, int i)
     return 16 * u + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
 }
 
+// The V tile of a block of 16 keys (64 channels, 2 KiB) is made of 16-byte pieces instead: piece (cp, g, col), at element
+// offset small_v_piece, is keys 4 g .. 4 g + 3 of channel 32 cp + col and then of channel 32 cp + 16 + col.  A lane
+// (g, col) of the 16x16 MFMAs takes two channel tiles per load; the 32x32 ones take the halves of two pieces.
+__device__ __forceinline__ int small_v_piece(int cp, int g, int col) { return ((cp * 4 + g) * 16 + col) * 8; }
+
 // Row index inside a 32x32 MFMA result held by (lane, register r).
 __device__ __forceinline__ int acc_row(int lane, int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 

@@ -10,8 +10,11 @@
 //   scores      S^T[key][query] = K Q^T: 16x16x32 MFMAs for blocks of 16 (two per block), 32x32x16 for 32 (four)
 //   softmax     keys of ONE query per lane: in-lane reductions and one (32) or two (16) exchanges between lanes
 //   P.V         O^T[channel][query] += V^T P^T: the probabilities sit in the operand order of 16x16x16 (32x32x16)
-// A 16-token block's tiles (pool.hip) are half tiles of the 32-row layout; what a 16x16 operand needs of them is
-// again one contiguous KiB (K) or two runs of 256 bytes (V) per load instruction.
+// A 16-token block's K tile (pool.hip) is a half tile of the 32-row layout, its V tile has a layout of its own
+// (small_v_piece): what the operands need of them is one contiguous KiB per load instruction.  (With the transposed
+// tile of 32 rows V took two runs of 256 bytes per load, twice the load instructions: 100 views in 4 x 4 windows 3.06 -> 2.97 ms
+// a call, 60 views of clustered keys 1.20 -> 1.14, fp32 30 views in windows 1.48 -> 1.39, 8 views 166 -> 151 us; 60 views of
+// i.i.d. keys, where the fabric binds, 1.70 -> 1.72.)
 //
 // Bound.  The ring kernel ran at 7000 cycles per 64-key unit and wave with one wave per SIMD: a serial chain, the
 // matrix pipe 7 % and the vector ALU 30 % busy, half of both for columns that hold no query (blocks of 16).  Now i.i.d.
@@ -31,6 +34,7 @@
 namespace s3r {
 
 typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef short short8_t __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ float max_with_other_rows(float x)  // lanes 16 apart, within each half wave
 {
@@ -98,8 +102,7 @@ __global__ __launch_bounds__(256, OCC) void select_direct_kernel(
     const bf16_t *kb_h = kb + static_cast<int64_t>(h) * n_blk * (B * 64);
     const bf16_t *vb_h = vb + static_cast<int64_t>(h) * n_blk * (B * 64);
     const unsigned koff = lane * 8;
-    // V, blocks of 16: the lane's 4 keys (4 g ..) of channel col of channel tile 0; see tr_tile_key
-    const unsigned voff = B == 16 ? ((g & 1) * 32 + col) * 8 + (g >> 1) * 4 : lane * 8;
+    const unsigned voff = B == 16 ? small_v_piece(0, g, col) : lane * 8;
 
     acc_t oacc[NT];
 #pragma unroll
@@ -134,8 +137,12 @@ __global__ __launch_bounds__(256, OCC) void select_direct_kernel(
                 const bf16_t *base = vb_h + p * lo_off + static_cast<int64_t>(j) * (B * 64);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    if constexpr (B == 16) vf16[b][p][c] = *reinterpret_cast<const short4_t *>(base + voff + (c >> 1) * 512 + (c & 1) * 128);
-                    else vf32[b][p][c] = *reinterpret_cast<const bf16x8 *>(base + voff + c * 512);
+                    if constexpr (B == 16) {
+                        if ((c & 1) != 0) continue;
+                        const short8_t two = *reinterpret_cast<const short8_t *>(base + voff + small_v_piece(c >> 1, 0, 0));
+                        vf16[b][p][c] = __builtin_shufflevector(two, two, 0, 1, 2, 3);
+                        vf16[b][p][c + 1] = __builtin_shufflevector(two, two, 4, 5, 6, 7);
+                    } else vf32[b][p][c] = *reinterpret_cast<const bf16x8 *>(base + voff + c * 512);
                 }
             }
         }

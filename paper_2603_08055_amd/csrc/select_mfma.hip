@@ -41,6 +41,8 @@
 #include "s3r_attn_device.h"
 #include "s3r_kernels.h"
 
+#include <type_traits>
+
 namespace s3r {
 
 // QW    : waves per workgroup = query rows / 32 (block / 32 for selection: one query block)
@@ -501,15 +503,25 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
             }
     };
     // O^T += V^T P^T for the unit whose V sits in `vs`
-    auto accumulate = [&](const bf16_t *vs) __attribute__((always_inline)) {
+    // (pieces: V tiles of blocks of 16 keys, see small_v_piece)
+    auto accumulate = [&](const bf16_t *vs, auto pieces) __attribute__((always_inline)) {
+        auto operand = [&](const bf16_t *tiles, int v, int dt) __attribute__((always_inline)) -> bf16x8 {
+            if constexpr (decltype(pieces)::value) {
+                const bf16_t *at = tiles + v * 1024 + small_v_piece(dt, g, lane & 15) + ((lane >> 4) & 1) * 4;
+                const bf16x4 lo = *reinterpret_cast<const bf16x4 *>(at);
+                const bf16x4 hi = *reinterpret_cast<const bf16x4 *>(at + small_v_piece(0, 2, 0));
+                return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            }
+            return *reinterpret_cast<const bf16x8 *>(tiles + ((v * 2 + dt) * 64 + lane) * 8);
+        };
 #pragma unroll
         for (int v = 0; v < 2 * NMT; ++v)
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt) {
-                const bf16x8 va = *reinterpret_cast<const bf16x8 *>(vs + ((v * 2 + dt) * 64 + lane) * 8);
+                const bf16x8 va = operand(vs, v, dt);
                 oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[v], oacc[dt], 0, 0, 0);
                 if constexpr (F32) {
-                    const bf16x8 vl = *reinterpret_cast<const bf16x8 *>(vs + kLoElems + ((v * 2 + dt) * 64 + lane) * 8);
+                    const bf16x8 vl = operand(vs + kLoElems, v, dt);
                     oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pl[v], oacc[dt], 0, 0, 0);
                     oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vl, pb[v], oacc[dt], 0, 0, 0);
                 }
@@ -577,7 +589,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
             if (vmask == 0ull) continue;
             scores(&ring[stage][0]);
             softmax(vmask);
-            accumulate(&ring[stage][kUnitElems]);
+            accumulate(&ring[stage][kUnitElems], std::false_type{});
         }
     } else {
     for (int s = 0; s < D && s < n_steps; ++s) issue(s, s);  // D < NS: stage = s
@@ -600,7 +612,9 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         // (a key half: the second 32-row tile of K, the second two key steps of V)
         scores(&ring[stage][kh * kRowTileElems]);
         softmax(vmask);
-        accumulate(&ring[stage][kUnitElems + kh * kRowTileElems]);
+        const bf16_t *vs = &ring[stage][kUnitElems + kh * kRowTileElems];
+        if (SMALL && bpu_shift == 2 && s + u_begin < n_units1) accumulate(vs, std::integral_constant<bool, SMALL>{});  // wave-uniform
+        else accumulate(vs, std::false_type{});
     }
     }
 
