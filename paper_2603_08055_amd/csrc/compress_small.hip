@@ -6,7 +6,9 @@
 // candidates), each a few waves long and each waiting for the one before.  Here a row of scores fits in LDS, so no bound,
 // no candidates and no operand tiles are needed: one workgroup takes 16 pooled queries of a head and goes through
 //   scores    S = Qc Kc^T, 16 keys per wave and step, fp32 MFMAs (16x16x4) on the fp32 means themselves
-//   rows      one wave per query: softmax over its row, and the k largest scores by a bitwise search with wave ballots
+//   rows      one wave per query: softmax over its row, and the k largest scores by a bitwise search with wave ballots;
+//             keys too close to the k-th score to tell are compared by the dot product that topk_candidates_kernel takes,
+//             so that the index lists are the same as by the sweeps
 //   P.V       Oc' = P Vc, each wave 16 channels of a quarter of the keys, partial sums added up in LDS
 // The fp32 matrix pipe is 1/16 as fast as the bf16 one, and still not what the time goes into; scores and
 // probabilities are fp32 throughout, at least as exact as the two-part and fp16 scores of the sweeps.
@@ -21,19 +23,27 @@ namespace s3r {
 constexpr int kSmallQ = 16;      // pooled queries of a workgroup
 constexpr int kSmallWaves = 16;  // one per query in the row phase
 
-__device__ __forceinline__ float wave_max(float x)
+// Maximum and sum over the 64 lanes, the same value in all of them, on the vector ALU: exchanges inside a row of 16 lanes by
+// DPP, the rows by lane swaps (a shuffle through LDS takes over 100 cycles, and a row phase has a few dozen in a chain).
+template <int CTRL> __device__ __forceinline__ float dpp(float x)
 {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) x = fmaxf(x, __shfl_xor(x, d, 64));
-    return x;
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
 }
 
-__device__ __forceinline__ float wave_sum(float x)
+template <typename F> __device__ __forceinline__ float wave_reduce(float x, F &&f)
 {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) x += __shfl_xor(x, d, 64);
-    return x;
+    x = f(x, dpp<0xB1>(x));   // lanes 1 apart: quad_perm [1, 0, 3, 2]
+    x = f(x, dpp<0x4E>(x));   // 2 apart: quad_perm [2, 3, 0, 1]
+    x = f(x, dpp<0x141>(x));  // the other quad of 8: row_half_mirror
+    x = f(x, dpp<0x140>(x));  // the other 8 of 16: row_mirror
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return f(__uint_as_float(h[0]), __uint_as_float(h[1]));
 }
+
+__device__ __forceinline__ float wave_max(float x) { return wave_reduce(x, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float wave_sum(float x) { return wave_reduce(x, [](float a, float b) { return a + b; }); }
 
 // NV: score registers of a lane, n_blk <= 64 NV.  grid: (ceil(n_blk / 16), heads)
 template <int NV>
@@ -47,6 +57,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
     __shared__ __attribute__((aligned(16))) float s[kSmallQ][kStride];       // scores, then probabilities
     __shared__ float part[4][kSmallQ][68];                                   // P.V of a quarter of the keys each
     __shared__ float inv_sum[kSmallQ];
+    __shared__ float key_norm2[kSmallWaves];  // largest squared norm of the keys that each wave scored
 
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -65,6 +76,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
 #pragma unroll
             for (int i = 0; i < 4; ++i) a[4 * c + i] = f[i];
         }
+        float kn2 = 0.f;
         for (int kt = wave; kt < n_tiles; kt += kSmallWaves) {
             const int key = kt * 16 + col;
             const float *krow = kc + head + static_cast<int64_t>(key < n_blk ? key : n_blk - 1) * 64 + 16 * g;
@@ -76,7 +88,15 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
             for (int t = 0; t < 16; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], f[t >> 2][t & 3], acc, 0, 0, 0);
 #pragma unroll
             for (int r = 0; r < 4; ++r) s[4 * g + r][key] = acc[r];
+            float n2 = 0.f;
+#pragma unroll
+            for (int t = 0; t < 16; ++t) n2 = fmaf(f[t >> 2][t & 3], f[t >> 2][t & 3], n2);
+            n2 += __shfl_xor(n2, 16, 64);
+            n2 += __shfl_xor(n2, 32, 64);
+            kn2 = fmaxf(kn2, n2);
         }
+        kn2 = wave_max(kn2);
+        if (lane == 0) key_norm2[wave] = kn2;
     }
     // Values of the first steps of P.V, requested early: their latency runs under the row phase.
     const int ct = wave & 3, kq = wave >> 2;  // 16 channels; every fourth run of 16 keys
@@ -126,15 +146,74 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
                 key[t] = out ? 0u : o;
             }
             // k-th largest key, bit by bit; done as soon as exactly k keys are at or above the trial value
-            uint32_t T = 0u;
-            bool exact = false;
-            for (int bit = 31; bit >= 0; --bit) {
-                const uint32_t trial = T | (1u << bit);
-                int c = 0;
+            auto search = [&](uint32_t &T) __attribute__((always_inline)) -> bool {
+                T = 0u;
+                for (int bit = 31; bit >= 0; --bit) {
+                    const uint32_t trial = T | (1u << bit);
+                    int c = 0;
 #pragma unroll
-                for (int t = 0; t < NV; ++t) c += __popcll(__ballot(key[t] >= trial));
-                if (c >= k) T = trial;
-                if (c == k) { exact = true; break; }
+                    for (int t = 0; t < NV; ++t) c += __popcll(__ballot(key[t] >= trial));
+                    if (c >= k) T = trial;
+                    if (c == k) return true;
+                }
+                return false;
+            };
+            uint32_t T;
+            bool exact = search(T);
+            // Two orders of an fp32 dot product differ by at most eps = 2^-17 |q||k| (64 products and sums each).  Keys more
+            // than 2 eps above the k-th score are in by either, those more than 2 eps below are out; if others lie between than
+            // just as many as are wanted, the scores of topk_candidates_kernel decide among them.
+            {
+                const float qv = qc[head + static_cast<int64_t>(row) * 64 + lane];
+                const float kn2 = wave_max(key_norm2[lane & (kSmallWaves - 1)]);
+                const float two_eps = (1.f / 65536.f) * 1.01f * __builtin_sqrtf(wave_sum(qv * qv)) * __builtin_sqrtf(kn2) + 1e-36f;
+                // the k-th score itself: the smallest taken
+                float kth = INFINITY;
+#pragma unroll
+                for (int t = 0; t < NV; ++t)
+                    if (key[t] >= T && key[t] != 0u) kth = fminf(kth, x[t]);
+                kth = -wave_max(-kth);
+                int n_in = 0, n_near = 0;
+#pragma unroll
+                for (int t = 0; t < NV; ++t) {
+                    const bool in = key[t] != 0u && x[t] > kth + two_eps, near = key[t] != 0u && !in && x[t] >= kth - two_eps;
+                    n_in += __popcll(__ballot(in));
+                    n_near += __popcll(__ballot(near));
+                }
+                if (n_in + n_near > k) {  // (rare; never where the inputs are not numbers)
+                    const int sub = lane & 15;
+                    const floatx4 q4 = *reinterpret_cast<const floatx4 *>(qc + head + static_cast<int64_t>(row) * 64 + 4 * sub);
+#pragma unroll
+                    for (int t = 0; t < NV; ++t) {
+                        const bool in = key[t] != 0u && x[t] > kth + two_eps, near = key[t] != 0u && !in && x[t] >= kth - two_eps;
+                        key[t] = in ? 0xffffffffu : 0u;
+                        unsigned long long m = __ballot(near);
+                        while (m != 0ull) {  // four at a time, 16 lanes each, in the order of operations of that kernel
+                            int l4[4];
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                l4[i] = m != 0ull ? __ffsll(static_cast<long long>(m)) - 1 : -1;
+                                m &= m - 1ull;  // (0 stays 0)
+                            }
+                            const int mine = g == 0 ? l4[0] : g == 1 ? l4[1] : g == 2 ? l4[2] : l4[3];
+                            const floatx4 k4 = *reinterpret_cast<const floatx4 *>(
+                                kc + head + static_cast<int64_t>(64 * t + (mine < 0 ? l4[0] : mine)) * 64 + 4 * sub);
+                            float dot = 0.f;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) dot = __builtin_fmaf(q4[i], k4[i], dot);
+                            dot += __shfl_xor(dot, 1, 64);
+                            dot += __shfl_xor(dot, 2, 64);
+                            dot += __shfl_xor(dot, 4, 64);
+                            dot += __shfl_xor(dot, 8, 64);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const uint32_t o = order_key(__shfl(dot, 16 * i, 64));
+                                if (lane == l4[i]) key[t] = o > 1u ? (o < 0xfffffffeu ? o : 0xfffffffeu) : 1u;
+                            }
+                        }
+                    }
+                    exact = search(T);
+                }
             }
             int ties = n_blk;  // how many keys equal to T are taken, the smallest indices first
             if (!exact) {

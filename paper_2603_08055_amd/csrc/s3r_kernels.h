@@ -134,7 +134,7 @@ hipError_t launch_topk_candidates(const float *qc, const float *kc, const int32_
 
 // Block scores, compressed attention and TopK for at most kSmallMaxBlk pooled blocks per head in one launch, from the
 // pooled means ([heads][n_blk][64]): writes o_comp and, with k > 0, idx [heads][n_blk][k] (any k up to the number of
-// blocks that are not forced).
+// blocks that are not forced).  The index lists are those of launch_topk_candidates.
 constexpr int kSmallMaxBlk = 1024;
 hipError_t launch_compress_small(const float *qc, const float *kc, const float *vc, float *o_comp, int32_t *idx,
                                  int64_t n_blk, int heads, int k, float scale, const unsigned long long *forced_words,
@@ -143,10 +143,11 @@ hipError_t launch_compress_small(const float *qc, const float *kc, const float *
 // length of their chain of launches.  Whole calls, microseconds, sweeps -> this launch (MI355X, blocks of 64, top-16):
 // 16 heads: 169 -> 138 at 256 blocks, 309 -> 284 at 512, 453 -> 457 at 768, 599 -> 630 at 1024; fp32 789 -> 770 at 512,
 // 1583 -> 1614 at 1024; 4 heads: 120 -> 90 at 512, 195 -> 158 at 1024; one head: 101 -> 68 at 1024; 8 heads, top-100
-// (scores through memory): 570 -> 542 at 512, 1169 -> 1130 at 1024.
-inline bool compress_small_takes(int64_t n_blk, int heads)
+// (scores through memory): 570 -> 542 at 512, 1169 -> 1130 at 1024.  Rows of more than kFusedTopkMaxK entries stay with the scores in
+// memory all the same: that route decides near-ties by scores of its own, and its index lists stay what they are.
+inline bool compress_small_takes(int64_t n_blk, int heads, int k)
 {
-    return n_blk <= kSmallMaxBlk && n_blk * n_blk * heads <= (int64_t(1) << 23) && heads <= 65535;
+    return k <= kFusedTopkMaxK && n_blk <= kSmallMaxBlk && n_blk * n_blk * heads <= (int64_t(1) << 23) && heads <= 65535;
 }
 
 // Forced (always attended) blocks: clamp the caller's list into `forced_clean` and build the

@@ -296,7 +296,7 @@ s3r_status run_compress_topk(const float *qc, const float *kc, const float *vc, 
                              const FusedBufs &fb, bool keep_tiles, hipStream_t stream)
 {
     // Short sequences: one launch on the pooled means themselves (keep_tiles: the caller reads the operand tiles).
-    if (want_topk && g_kernel_choice != 2 && s3r::compress_small_takes(n_blk, heads)) {
+    if (want_topk && g_kernel_choice != 2 && s3r::compress_small_takes(n_blk, heads, kk)) {
         StageTimer tm(S3R_STAGE_COMPRESS, stream);
         S3R_HIP(s3r::launch_compress_small(qc, kc, vc, o_comp, idx, n_blk, heads, kk, scale, forced_words, stream),
                 "compress (short sequence) kernel launch");

@@ -116,7 +116,24 @@ def test_short_sequences_in_one_launch(s3r, oracle, n_blk, heads, k):  # noqa: F
         assert_close(o_comp, ref, TOL["f32"] if accurate or n_blk <= 724 else TOL["bf16"], "o_comp")
 
 
-@pytest.mark.parametrize("n_blk,topk,n_forced", [(70, 70, 3), (200, 150, 1), (320, 64, 64), (90, 5, 90)])
+@pytest.mark.parametrize("n_blk,k", [(130, 64), (500, 17)])   # (up to 512 blocks the sweeps' candidate lists hold every key)
+def test_near_ties_are_decided_as_by_the_sweeps(s3r, n_blk, k):  # noqa: F811
+    """Keys that differ by less than the rounding of a score: one launch for short sequences and (more heads: past the
+    line) the sweeps with their candidates give the same lists, entry by entry."""
+    rng = np.random.default_rng(n_blk + k)
+    line = 2 ** 23 // n_blk ** 2
+    base = rng.standard_normal((1, 1, 64))
+    one = [np.asarray(base + 2e-7 * rng.standard_normal((2, n_blk, 64)), dtype=np.float32),
+           np.asarray(base + 2e-7 * rng.standard_normal((2, n_blk, 64)), dtype=np.float32),
+           rng.standard_normal((2, n_blk, 64)).astype(np.float32)]
+    many = [np.concatenate([x, np.zeros((line - 1, n_blk, 64), dtype=np.float32)]) for x in one]
+    _, idx = compress_topk_case(s3r, *one, k, False)
+    _, want = compress_topk_case(s3r, *many, k, False)
+    assert (np.diff(idx, axis=2) > 0).all()
+    assert np.array_equal(idx, want[:2])
+
+
+@pytest.mark.parametrize("n_blk,topk,n_forced", [(70, 64, 3), (200, 65, 1), (320, 64, 64), (90, 5, 90)])   # (65: scores through memory)
 def test_forced_blocks_and_long_rows_in_one_launch(s3r, oracle, n_blk, topk, n_forced):  # noqa: F811
     wl = workloads.Workload(f"short_forced_{n_blk}_{topk}_{n_forced}", 1, 16 * n_blk - 3, 2, 64, "bf16", 16, topk, 103, "normal")
     q, k, v = workloads.make_inputs(wl)
