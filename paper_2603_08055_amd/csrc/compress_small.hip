@@ -160,13 +160,14 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
             };
             uint32_t T;
             bool exact = search(T);
-            // Two orders of an fp32 dot product differ by at most eps = 2^-17 |q||k| (64 products and sums each).  Keys more
-            // than 2 eps above the k-th score are in by either, those more than 2 eps below are out; if others lie between than
-            // just as many as are wanted, the scores of topk_candidates_kernel decide among them.
+            // This score and the one of topk_candidates_kernel differ by at most eps = 72 2^-24 |q||k| (64 roundings in a row
+            // here, 8 there: chains of 4 and a tree of 16).  Keys more than 2 eps above the k-th score are in by
+            // either, those more than 2 eps below are out; if others lie between than just as many as are wanted, the scores of
+            // topk_candidates_kernel decide among them.
             {
                 const float qv = qc[head + static_cast<int64_t>(row) * 64 + lane];
                 const float kn2 = wave_max(key_norm2[lane & (kSmallWaves - 1)]);
-                const float two_eps = (1.f / 65536.f) * 1.01f * __builtin_sqrtf(wave_sum(qv * qv)) * __builtin_sqrtf(kn2) + 1e-36f;
+                const float two_eps = (1.f / 131072.f) * 1.15f * __builtin_sqrtf(wave_sum(qv * qv)) * __builtin_sqrtf(kn2) + 1e-36f;
                 // the k-th score itself: the smallest taken
                 float kth = INFINITY;
 #pragma unroll

@@ -72,7 +72,7 @@ hipError_t launch_block_lens(TokenMap map, int block, int64_t n_tok, int64_t n_b
 
 // Block means of q, k, v (fp32 [heads][n_blk][64]; any of qc/kc/vc may be null together) and,
 // when kb/vb are given (bf16 input), the per-(head, block) K and V tiles in MFMA operand order:
-// kb, vb are bf16 [heads][n_blk][block * 64] (blocks of 16 rows: half tiles, see pool.hip).  fp32 input (blocks of
+// kb, vb are bf16 [heads][n_blk][block * 64] (blocks of 16 rows: K half tiles, V in pieces, see small_v_piece).  fp32 input (blocks of
 // 64 and 128 tokens only): kb, vb are [2][heads][n_blk][block * 64], the bf16 hi parts followed by the lo parts
 // (x - hi rounded to bf16).  n_tok counts the tokens of the
 // sub-sequence `map` picks out of q, k, v; blocks are runs of that sub-sequence.
