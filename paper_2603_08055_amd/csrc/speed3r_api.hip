@@ -54,11 +54,11 @@ bool mfma_ok(s3r_dtype dtype, int block) { (void)dtype; (void)block; return g_ke
 size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 
 // Dense attention of few query rows (the special tokens) in key splits: the number of splits with the shortest time
-// by a model of the launch, in microseconds on MI355X (256 CUs; three workgroups fill a CU, of the fp32 kernel with its
-// 80 KiB ring two).  A CU works through n = ceil(workgroups * s / 256) of them:
-//   * each takes 0.64 us per key unit (0.7 over small blocks; fp32: 1.95 and 1.8) and 4 us at its start and end;
+// by a model of the launch, in microseconds on MI355X (256 CUs; three workgroups fill a CU).  A CU works through
+// n = ceil(workgroups * s / 256) of them:
+//   * each takes 0.64 us per key unit (0.7 over small blocks) and 4 us at its start and end;
 //   * the bf16 kernel needs two to three workgroups on a CU to fill it: one left over in the last round costs as
-//     much as 1.75, two as 2.3; of the fp32 kernel one costs as much as 1.2;
+//     much as 1.75, two as 2.3;
 //   * the workgroups of later rounds no longer walk the keys in step and share less of them in the L2s: 2.5 % per
 //     round, 30 % at most;
 //   * the combine kernel reads s partial rows one after the other (0.6 us each) and moves them at 4 TB/s.
@@ -70,21 +70,24 @@ size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 //   bf16, blocks of 16, 20 views    8: 0.076  16: 0.056*  24: 0.059  32: 0.061
 //                       100 views   8: 0.447  12: 0.413*  16: 0.440  32: 0.493
 //   fp32, blocks of 64, 20 views    8: 0.120  16: 0.082*  24: 0.092  32: 0.098
-//                       60 views    8: 0.589  10: 0.503   16: 0.512  20: 0.536 (21 chosen)  32: 0.548   (2.12 with a ring of 120 KiB, one
-//                       workgroup per CU and the operand array of a chunk looked up in scratch memory)
-// fp32 takes at least 16 splits, although fewer can be faster: the error of a row against 64 bits grows with the units in
-// one chain of sums (200 views: 1.0e-5 in one split, 7.6e-6 in 2, 5.7e-6 in 6, 5.4e-6 in 8, 5.0e-6 in 16).  In bf16 it is
-// the rounding of P, which hardly depends on the splits and gains from them, every split's largest probability being
-// exact (30 views in 4 x 4 windows, 8 heads, outlier keys: 1.80e-3 in one split, 1.69e-3 in 32, 1.67e-3 in 48).
+//                       60 views    8: 0.589  10: 0.503   16: 0.512* 20: 0.536   32: 0.548   (2.12 with a ring of
+//                       120 KiB, one workgroup per CU and the operand array of a chunk looked up in scratch memory)
+// In fp32 the error of a row against 64 bits grows with the units in one chain of sums (200 views: 1.0e-5 in one split,
+// 7.6e-6 in 2, 5.7e-6 in 6, 5.4e-6 in 8, 5.0e-6 in 16).  A unit is therefore weighed at four times the 1.95 us it takes
+// (small blocks: twice), against the start and the combine kernel, and there are at least 8 splits although fewer can be
+// faster, and at least 16 with up to 48 workgroups, which 8 leave at one or two to a CU where two run at once.
+// In bf16 it is the rounding of P, which hardly depends on the splits and gains from them, every split's largest
+// probability being exact (30 views in 4 x 4 windows, 8 heads, outlier keys: 1.80e-3 in one split, 1.69e-3 in 32, 1.67e-3
+// in 48).
 constexpr int kMaxDenseSplit = 64;
 int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, int block)
 {
     const bool bf16 = dtype == S3R_BF16;
     const int64_t wgs = (n_rows + 127) / 128 * heads;
     if (wgs >= 3072) return 1;  // 12 workgroups and more per CU: even enough
-    const double unit_us = bf16 ? (block >= 64 ? 0.64 : 0.7) : (block >= 64 ? 1.95 : 1.8);
-    const int64_t at_once = bf16 ? 3 : 2;
-    const double left_over[3] = {0.0, bf16 ? 0.75 : 0.2, bf16 ? 0.3 : 0.0};
+    const double unit_us = bf16 ? (block >= 64 ? 0.64 : 0.7) : (block >= 64 ? 8.0 : 3.8);
+    const int64_t at_once = bf16 ? 3 : 1;
+    const double left_over[3] = {0.0, bf16 ? 0.75 : 0.0, bf16 ? 0.3 : 0.0};
     auto time_us = [&](int s) {
         const int64_t n = (wgs * s + 255) / 256, rounds = (n + at_once - 1) / at_once;
         const double drift = 0.025 * static_cast<double>(rounds - 1);
@@ -94,7 +97,8 @@ int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, in
     };
     int most = static_cast<int>(n_units / 4 < kMaxDenseSplit ? n_units / 4 : kMaxDenseSplit);  // at least 4 units each
     if (most < 1) most = 1;
-    const int least = bf16 ? 1 : (most < 16 ? most : 16);
+    const int floor32 = wgs <= 48 ? 16 : 8;
+    const int least = bf16 ? 1 : (most < floor32 ? most : floor32);
     double us[kMaxDenseSplit + 1], shortest = INFINITY;
     for (int s = least; s <= most; ++s) {
         us[s] = time_us(s);
