@@ -336,7 +336,7 @@ def main():
         return 2.0 * n / (e0.elapsed_time(e1) / 5 * 1e-3) / 1e9
     sweep_flops = 2.0 * wl.head_dim * float(seq.n_blk) * float(seq.n_blk) * wl.heads     # one N_b x N_b x d product
     in_sweep = kk - n_forced <= 64
-    short = seq.n_blk <= 1024 and seq.n_blk * seq.n_blk * wl.heads <= 1 << 23 and args.kernel_choice != 2
+    short = in_sweep and seq.n_blk <= 1024 and seq.n_blk * seq.n_blk * wl.heads <= 1 << 23 and args.kernel_choice != 2
     stages = {
         "pool": {"bound": "hbm", "unit": "GB/s", "peak": 8000.0, "achieved": pool_bytes / stage_s("pool") / 1e9,
                  "frac": pool_bytes / stage_s("pool") / 1e9 / 8000.0, "algorithmic_bytes": pool_bytes,

@@ -68,7 +68,7 @@ enum { S3R_DIAG_FORCED_RANGE = 1, S3R_DIAG_FORCED_ORDER = 2 };
 enum {
     S3R_STAGE_POOL = 0,     /* block pooling (+ K/V tile re-layout for the MFMA path) */
     S3R_STAGE_SPLIT = 1,    /* pooled fp32 -> operand tiles (+ their per-head statistics) */
-    S3R_STAGE_COMPRESS = 2, /* S_guide + compressed attention                         */
+    S3R_STAGE_COMPRESS = 2, /* S_guide + compressed attention (short sequences: + TopK) */
     S3R_STAGE_TOPK = 3,     /* per-query-block TopK (incl. its filter sweep)          */
     S3R_STAGE_SELECT = 4,   /* block-sparse attention + merge                         */
     S3R_STAGE_DENSE = 5,    /* dense attention                                        */
@@ -268,7 +268,8 @@ s3r_status speed3r_get_stage_ms(float *ms, int *launches);
 
 /* Selects kernel families, process-wide.  0 = automatic: MFMA attention kernels (fp32 problems in bf16
  * operand parts), and for up to 64 TopK blocks per row the TopK that runs
- * inside the compression sweep without writing S_guide to memory (supplementary Sec. 1).  1 = always
+ * inside the compression sweep, or with it in one launch, without writing
+ * S_guide to memory (supplementary Sec. 1).  1 = always
  * the generic attention kernel.  2 = like 0 but TopK always from S_guide written to memory. */
 s3r_status speed3r_set_kernel_choice(int choice);
 

@@ -19,8 +19,9 @@
 // Bound.  The ring kernel ran at 7000 cycles per 64-key unit and wave with one wave per SIMD: a serial chain, the
 // matrix pipe 7 % and the vector ALU 30 % busy, half of both for columns that hold no query (blocks of 16).  Now i.i.d.
 // keys are delivered at the 7.8 TB/s the fabric has for L2 misses; with keys that neighbouring query blocks share
-// (74 % L2 hits at 100 views in 4 x 4 windows) 21 GB of tiles arrive in 1.32 ms, 16 TB/s, with 2.8 waves per SIMD, the
-// matrix pipe 16 % and the vector ALU 43 % busy: what is left is vector work, issue and the latency of the loads.
+// (74 % L2 hits at 100 views in 4 x 4 windows) 21 GB of tiles arrive in 1.17 ms, 18 TB/s, with 2.8 waves per SIMD, the
+// matrix pipe under 20 % and the vector ALU half busy: what is left is the latency and issue of the loads (a fourth wave per
+// SIMD, and no exchange of maxima per unit, measured 0.5 % slower).
 //
 // Pipelining.  NBU blocks are worked on at a time; the K of the next ones is requested as soon as the scores have
 // consumed the registers of the current ones, V after P.V likewise, and the compiler's own counts wait for them.
