@@ -280,7 +280,7 @@ def main():
 
         # the probe at the occupancy of the kernel that ran: long rows on long sequences run two workgroups per
         # CU (64 query blocks in progress per XCD), everything else as many as fit
-        two_pairs = kk >= 40 and seq.n_blk >= 3000 and kk * seq.n_blk >= 160000 and n_forced == 0
+        two_pairs = kk >= 40 and seq.n_blk >= 3000 and not (kk > 96 and 2 * n_forced >= kk)
         probe_wg = 2 if wl.block == 64 and two_pairs else 0
         probe_ms = time_probe(0, probe_wg)
         assert torch.equal(probe_out, q), "the load probe must leave a copy of q in its output"

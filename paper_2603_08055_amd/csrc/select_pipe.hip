@@ -480,10 +480,13 @@ hipError_t launch_select_pipe(const SelectArgs &a, hipStream_t stream)
     // and short sequences (100 views: one pair is 5 to 10 % ahead at every row length) from more of them.
     // Strided q (slices of one projection output) comes here as well, the strides enter one address per lane: the
     // layer on 150 views, 8 x 8 windows, top-32 takes 3.92 ms, 4.35 with the selection in select_mfma.hip.
-    // Rows with forced blocks, which all rows share, hit the L2s anyway: one pair (23 of 87 blocks forced, 200 views: two
-    // pairs 9.33 ms a call, one 8.99; 1000 views 51.96 and 50.13; 46 of 110 forced, 400 views 22.9 and 21.4).  40 blocks per
-    // row, 150 views: two 3.77, one 3.65; 200 views 5.14 and 5.27; 64 blocks, 150 views 5.45 and 5.67.
-    if (a.kk >= 40 && a.n_blk >= 3000 && a.kk * a.n_blk >= 160000 && a.n_common == 0) return run_pipe<2, 2, 2, 3>(a, stream);
+    // Rows with forced blocks, which all rows share, take two pairs as well (ms a call for one pair and two, 1000 views,
+    // 64 blocks a row and 1 / 8 / 23 / 46 forced ones: 47.3, 42.4 / 47.5, 44.7 / 51.4, 50.7 / 60.5, 59.9).  Where many are forced
+    // and where a row has little more than 40 blocks one pair can be ahead (200 views, 64 + 23: 8.8, 9.2; 150 views, 40: 3.66,
+    // 3.73), but two leave less error, each pair's largest probability being exact: outlier keys, 150 views, against 64 bits
+    // 1.784e-3 in one pair and 1.759e-3 in two for 64 + 4, lse 7.5e-4 and 6.7e-4; 40 blocks 1.770e-3 and 1.749e-3.
+    // Rows of more than 96 blocks, most of them forced, run in one pair (50 + 60, 388 views: 20.1, two pairs 21.5).
+    if (a.kk >= 40 && a.n_blk >= 3000 && !(a.kk > 96 && 2 * a.n_common >= a.kk)) return run_pipe<2, 2, 2, 3>(a, stream);
     // Few query blocks: a CU has room for two workgroups of two pairs, and while all of them run at once a row is done in
     // half the iterations (microseconds a call, one pair -> two: 258 query blocks, 4 blocks a row 22.6 -> 21.2, 16 blocks
     // 34.6 -> 28.2; 344, 64 blocks 82.9 -> 57.7; 430, 32 blocks 51.2 -> 39.2; 512, 8 blocks 26.6 -> 23.4; but 540, 16

@@ -194,6 +194,24 @@ def test_strided_queries_in_the_pipelined_selection(s3r, views, tpv, topk, layou
         assert torch.equal(got[key], want[key]), key
 
 
+@pytest.mark.parametrize("topk,n_forced", [(40, 0), (64, 1), (64, 23), (30, 40)])
+def test_long_rows_keep_the_precision_of_two_pairs(s3r, topk, n_forced):  # noqa: F811
+    """Outlier keys: a few weights make up a row, and what is left against 64 bits is the rounding of P to bf16.  In two
+    pairs of waves the largest weight of each is exact: 6.4e-4 to 6.8e-4 in lse, 7.3e-4 to 7.6e-4 in one pair."""
+    wl = workloads.Workload("long_rows", 150, 1374, 1, 64, "bf16", 64, topk, 107, "outliers")
+    q, k, v = workloads.make_inputs(wl, device="cuda")
+    res = run_device(s3r, q, k, v, 64, topk, forced=list(range(n_forced)) if n_forced else None)
+    q64, k64 = q[:, 0].double(), k[:, 0].double()
+    off = count = 0.0
+    for b in range(0, wl.n_tok // 64, 8):
+        keys = (res["idx"][0, b].long()[:, None] * 64 + torch.arange(64, device="cuda")).reshape(-1)
+        keys = keys[keys < wl.n_tok]
+        want = torch.logsumexp(q64[64 * b:64 * (b + 1)] @ k64[keys].T / 8.0, dim=-1)
+        off += (res["lse"][0, 64 * b:64 * (b + 1)].double() - want).square().sum().item()
+        count += 64
+    assert math.sqrt(off / count) < 7.0e-4
+
+
 @pytest.mark.parametrize("block", [16, 32])
 def test_scores_of_small_fp32_blocks_are_added_up_exactly_enough(s3r, block):  # noqa: F811
     """Peaked softmaxes over outlier keys (scores of some hundred): the rounding of the scores shows.  Two bf16 parts of
