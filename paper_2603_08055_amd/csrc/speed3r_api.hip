@@ -56,7 +56,8 @@ size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 // Dense attention of few query rows (the special tokens) in key splits: the number of splits with the shortest time
 // by a model of the launch, in microseconds on MI355X (256 CUs; three workgroups fill a CU).  A CU works through
 // n = ceil(workgroups * s / 256) of them:
-//   * each takes 0.64 us per key unit (0.7 over small blocks) and 4 us at its start and end;
+//   * each is reckoned at 0.68 us per key unit (1.1 over small blocks, which take 0.7: see below) and 4 us at its start
+//     and end;
 //   * the bf16 kernel needs two to three workgroups on a CU to fill it: one left over in the last round costs as
 //     much as 1.75, two as 2.3;
 //   * the workgroups of later rounds no longer walk the keys in step and share less of them in the L2s: 2.5 % per
@@ -67,7 +68,7 @@ size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 //                       100 views   4: 0.481   8: 0.359  12: 0.354*  24: 0.407  32: 0.431
 //                       300 views   2: 3.75    3: 3.87    4: 3.01*   6: 3.38    8: 3.03   12: 3.32
 //                       1000 views  1: 36.1    2: 32.1*   3: 33.6    4: 32.5    6: 33.8
-//   bf16, blocks of 16, 20 views    8: 0.076  16: 0.056*  24: 0.059  32: 0.061
+//   bf16, blocks of 16, 20 views    8: 0.076  16: 0.056   24: 0.059  32: 0.061*
 //                       100 views   8: 0.447  12: 0.413*  16: 0.440  32: 0.493
 //   fp32, blocks of 64, 20 views    8: 0.120  16: 0.082*  24: 0.092  32: 0.098
 //                       60 views    8: 0.589  10: 0.503   16: 0.512* 20: 0.536   32: 0.548   (2.12 with a ring of
@@ -76,16 +77,17 @@ size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 // 7.6e-6 in 2, 5.7e-6 in 6, 5.4e-6 in 8, 5.0e-6 in 16).  A unit is therefore weighed at four times the 1.95 us it takes
 // (small blocks: twice), against the start and the combine kernel, and there are at least 8 splits although fewer can be
 // faster, and at least 16 with up to 48 workgroups, which 8 leave at one or two to a CU where two run at once.
-// In bf16 it is the rounding of P, which hardly depends on the splits and gains from them, every split's largest
-// probability being exact (30 views in 4 x 4 windows, 8 heads, outlier keys: 1.80e-3 in one split, 1.69e-3 in 32, 1.67e-3
-// in 48).
+// In bf16 it is the rounding of P, which gains from the splits, every split's largest probability being exact (outlier keys,
+// against 64 bits: 30 views in 4 x 4 windows, 8 heads 1.80e-3 in one split, 1.69e-3 in 32, 1.67e-3 in 48; 20 views, 4 heads
+// 1.680e-3 in 28 splits, 1.668e-3 in 36; blocks of 32, 40 views, 16 heads 1.705e-3 in 16, 1.689e-3 in 24).  So the units of
+// small blocks stay weighed at what they took with another kernel: as many splits as then, 10 % of this launch at 20 views.
 constexpr int kMaxDenseSplit = 64;
 int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, int block)
 {
     const bool bf16 = dtype == S3R_BF16;
     const int64_t wgs = (n_rows + 127) / 128 * heads;
     if (wgs >= 3072) return 1;  // 12 workgroups and more per CU: even enough
-    const double unit_us = bf16 ? (block >= 64 ? 0.64 : 0.7) : (block >= 64 ? 8.0 : 3.8);
+    const double unit_us = bf16 ? (block >= 64 ? 0.68 : 1.1) : (block >= 64 ? 8.0 : 3.8);
     const int64_t at_once = bf16 ? 3 : 1;
     const double left_over[3] = {0.0, bf16 ? 0.75 : 0.0, bf16 ? 0.3 : 0.0};
     auto time_us = [&](int s) {

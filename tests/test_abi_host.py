@@ -206,6 +206,16 @@ def test_key_splits_of_the_special_rows(s3r, dtype, block, views, tpv, special, 
     assert special_row_splits(s3r, views, tpv, special, heads, block, dtype, grid) in splits
 
 
+@pytest.mark.parametrize("block,views,tpv,special,heads,grid,splits", [
+    (16, 20, 1374, 5, 16, (37, 37, 4), 32), (16, 2, 1374, 5, 1, None, 11), (16, 100, 1370, 1, 3, (37, 37, 4), 63),
+    (32, 40, 1374, 5, 16, None, 24), (64, 20, 1374, 5, 1, None, 27), (64, 16, 400, 32, 16, None, 8),
+])
+def test_bf16_special_rows_keep_the_splits_that_their_precision_rests_on(s3r, block, views, tpv, special, heads, grid, splits):
+    """Fewer key splits leave more of the rounding of P (each split's largest probability is exact)."""
+    from tests.parity_util import special_row_splits
+    assert special_row_splits(s3r, views, tpv, special, heads, block, "bf16", grid) >= splits
+
+
 def test_noalloc_entry_refuses_oversized_problems_on_the_host(s3r):
     """The entry point for callers that cannot allocate checks the size against its fixed scratch before any
     device work (the pointers are never dereferenced)."""
