@@ -75,14 +75,15 @@ size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 //                       120 KiB, one workgroup per CU and the operand array of a chunk looked up in scratch memory)
 // In fp32 the error of a row against 64 bits grows with the units in one chain of sums (200 views: 1.0e-5 in one split,
 // 7.6e-6 in 2, 5.7e-6 in 6, 5.4e-6 in 8, 5.0e-6 in 16).  A unit is therefore weighed at four times the 1.95 us it takes
-// (small blocks: twice), against the start and the combine kernel, and there are at least 8 splits although fewer can be
-// faster, and at least 16 with up to 48 workgroups, which 8 leave at one or two to a CU where two run at once.
+// (small blocks: twice), against the start and the combine kernel: in fp32 this is a rule for exactness more than a model
+// of the time.  There are at least 8 splits although fewer can be faster, and with up to 48 workgroups, which 8 leave at one
+// or two to a CU where two run at once, at least 16 if the workspace has room (least32: the least number it is to be).
 // In bf16 it is the rounding of P, which gains from the splits, every split's largest probability being exact (outlier keys,
 // against 64 bits: 30 views in 4 x 4 windows, 8 heads 1.80e-3 in one split, 1.69e-3 in 32, 1.67e-3 in 48; 20 views, 4 heads
 // 1.680e-3 in 28 splits, 1.668e-3 in 36; blocks of 32, 40 views, 16 heads 1.705e-3 in 16, 1.689e-3 in 24).  So the units of
 // small blocks stay weighed at what they took with another kernel: as many splits as then, 10 % of this launch at 20 views.
 constexpr int kMaxDenseSplit = 64;
-int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, int block)
+int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, int block, int least32)
 {
     const bool bf16 = dtype == S3R_BF16;
     const int64_t wgs = (n_rows + 127) / 128 * heads;
@@ -99,8 +100,8 @@ int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, in
     };
     int most = static_cast<int>(n_units / 4 < kMaxDenseSplit ? n_units / 4 : kMaxDenseSplit);  // at least 4 units each
     if (most < 1) most = 1;
-    const int floor32 = wgs <= 48 ? 16 : 8;
-    const int least = bf16 ? 1 : (most < floor32 ? most : floor32);
+    if (wgs > 48) least32 = 8;
+    const int least = bf16 ? 1 : (most < least32 ? most : least32);
     double us[kMaxDenseSplit + 1], shortest = INFINITY;
     for (int s = least; s <= most; ++s) {
         us[s] = time_us(s);
@@ -139,9 +140,10 @@ struct Layout {
     int spec_split;  // key splits of the special rows' dense attention (1: none)
 };
 
-// n_tok: tokens on the sparse path (the image tokens); n_spec: special tokens (dense rows).
+// n_tok: tokens on the sparse path (the image tokens); n_spec: special tokens (dense rows).  have: bytes there are; special
+// rows that would not fit with the number of key splits they should have take fewer.
 Layout make_layout(int64_t n_tok, int heads, int block, int topk, int n_forced, s3r_dtype dtype,
-                   int64_t n_spec = 0, bool token_queries = false)
+                   int64_t n_spec = 0, bool token_queries = false, size_t have = SIZE_MAX)
 {
     Layout L{};
     L.n_blk = (n_tok + block - 1) / block;
@@ -186,13 +188,18 @@ Layout make_layout(int64_t n_tok, int heads, int block, int topk, int n_forced, 
     // compression branch with unpooled queries: fp32 compressed output per query slot
     L.oc_tok = take(token_queries ? static_cast<size_t>(L.n_blk) * block * heads * 64 * sizeof(float) : 0);
     // special rows in key splits: normalised partial results and their log-sums
-    L.spec_split = 1;
-    if (n_spec > 0 && mfma_ok(dtype, block))
-        L.spec_split = dense_splits(n_spec, heads, (L.n_blk * block + 63) / 64 + (n_spec + 63) / 64, dtype, block);
-    const size_t part_rows = L.spec_split > 1 ? static_cast<size_t>(L.spec_split) * n_spec * heads : 0;
-    L.spec_part_o = take(part_rows * 64 * sizeof(float));
-    L.spec_part_lse = take(part_rows * sizeof(float));
-    L.total = off;
+    const size_t before = off;
+    for (const int least32 : {16, 8}) {
+        off = before;
+        L.spec_split = 1;
+        if (n_spec > 0 && mfma_ok(dtype, block))
+            L.spec_split = dense_splits(n_spec, heads, (L.n_blk * block + 63) / 64 + (n_spec + 63) / 64, dtype, block, least32);
+        const size_t part_rows = L.spec_split > 1 ? static_cast<size_t>(L.spec_split) * n_spec * heads : 0;
+        L.spec_part_o = take(part_rows * 64 * sizeof(float));
+        L.spec_part_lse = take(part_rows * sizeof(float));
+        L.total = off;
+        if (L.total <= have) break;
+    }
     return L;
 }
 
@@ -557,7 +564,8 @@ s3r_status speed3r_sparse_global_attn_ex(const s3r_params *p)
     const bool token_queries = p->compress_queries == 1;
     if (token_queries && p->dtype == S3R_BF16 && !mfma_ok(p->dtype, p->block))
         return fail(S3R_ERR_UNSUPPORTED, "compress_queries = 1 on bf16 data needs the MFMA kernels (kernel choice 1 is set)");
-    const Layout L = make_layout(sp.n_img, p->heads, p->block, p->topk, n_forced, p->dtype, sp.n_spec, token_queries);
+    const Layout L = make_layout(sp.n_img, p->heads, p->block, p->topk, n_forced, p->dtype, sp.n_spec, token_queries,
+                                 p->workspace_bytes);
     if (!p->workspace) return fail(S3R_ERR_WORKSPACE, "workspace is null (%zu bytes needed)", L.total);
     if ((reinterpret_cast<uintptr_t>(p->workspace) & (kAlign - 1)) != 0)
         return fail(S3R_ERR_INVALID_ARG, "workspace must be 256-byte aligned");

@@ -232,6 +232,32 @@ def test_scores_of_small_fp32_blocks_are_added_up_exactly_enough(s3r, block):  #
     assert math.sqrt(off / total) < 3.0e-6
 
 
+@pytest.mark.parametrize("block,views,tpv,heads,grid,fewer", [(64, 40, 400, 2, None, 12), (16, 100, 400, 1, None, 10),
+                                                              (16, 30, 32 + 37 * 37, 3, (37, 37, 4), 10)])
+def test_fp32_special_rows_run_in_the_workspace_of_fewer_splits(s3r, block, views, tpv, heads, grid, fewer):  # noqa: F811
+    """Where 16 splits and more are taken for few workgroups, a workspace for the number with at least 8 will do."""
+    special = 32
+    splits = special_row_splits(s3r, views, tpv, special, heads, block, "f32", grid)
+    assert splits >= 16 > fewer
+    n_tok = views * tpv
+    q, k, v = (draw(n_tok, heads, "f32", 3200 + i).cuda() for i in range(3))
+    layout = dict(tokens_per_view=tpv, special_per_view=special, grid=grid)
+    need = s3r.speed3r_workspace_bytes_ex(n_tok, heads, 64, block, 4, s3r.S3R_F32, **layout)
+    up = lambda x: (x + 255) // 256 * 256   # noqa: E731
+    parts = lambda splits: up(splits * views * special * heads * 64 * 4) + up(splits * views * special * heads * 4)   # noqa: E731
+    out = {}
+    for n_bytes in (need, need - parts(splits) + parts(fewer)):
+        out[n_bytes] = torch.full_like(q, float("nan"))
+        s3r.speed3r_sparse_global_attn_ex(q, k, v, out[n_bytes], block, 4, workspace=torch.empty(n_bytes, dtype=torch.uint8, device="cuda"), **layout)
+    a, b = out.values()
+    rows = torch.arange(n_tok, device="cuda") % tpv < special
+    assert torch.equal(a[~rows], b[~rows])
+    assert_close(to_host_f32(a[rows]), to_host_f32(b[rows]), TOL["f32"], "special rows in more and in fewer splits")
+    with pytest.raises(s3r.Speed3rError):
+        s3r.speed3r_sparse_global_attn_ex(q, k, v, torch.empty_like(q), block, 4,
+                                          workspace=torch.empty(n_bytes - 256, dtype=torch.uint8, device="cuda"), **layout)
+
+
 def test_row_sums_of_long_fp32_rows_are_added_up_exactly_enough(s3r):  # noqa: F811
     """Rows over 274 800 outlier keys, whose sum one weight may dominate: added up unit by unit the sum leaves 3.5e-6 with
     the two bf16 parts of P and V, one key after the other onto the whole sum 6.3e-6."""
