@@ -135,13 +135,14 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
         sum = wave_sum(sum);
         if (lane == 0) inv_sum[wave] = 1.f / sum;
         if (k > 0 && row < n_blk) {  // wave-uniform
-            // order-preserving keys; 0 for blocks that do not take part: past the end, or forced (Sec. 3.3)
+            // order-preserving keys; 0 for blocks that do not take part: past the end, forced (Sec. 3.3), or with a score
+            // that is not a number (which is above no bound in the sweeps either)
             uint32_t key[NV];
 #pragma unroll
             for (int t = 0; t < NV; ++t) {
                 uint32_t o = order_key(x[t]);
                 o = o > 1u ? o : 1u;
-                bool out = 64 * t + lane >= n_blk;
+                bool out = 64 * t + lane >= n_blk || x[t] != x[t];
                 if (forced_words != nullptr && 64 * t < n_blk) out = out || ((forced_words[t] >> lane) & 1ull) != 0ull;
                 key[t] = out ? 0u : o;
             }
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
                     n_in += __popcll(__ballot(in));
                     n_near += __popcll(__ballot(near));
                 }
-                if (n_in + n_near > k) {  // (rare; never where the inputs are not numbers)
+                if (n_in + n_near > k) {  // (rare)
                     const int sub = lane & 15;
                     const floatx4 q4 = *reinterpret_cast<const floatx4 *>(qc + head + static_cast<int64_t>(row) * 64 + 4 * sub);
 #pragma unroll
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
             int32_t *dst = idx + (static_cast<int64_t>(h) * n_blk + row) * k;
 #pragma unroll
             for (int t = 0; t < NV; ++t) {
-                const bool eq = key[t] == T;
+                const bool eq = key[t] == T && T != 0u;  // (T = 0: fewer than k blocks take part)
                 const unsigned long long eq_mask = __ballot(eq);
                 const bool take = key[t] > T || (eq && n_eq + lanes_below(eq_mask) < ties);
                 const unsigned long long mask = __ballot(take);
@@ -234,6 +235,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
                 n_out += __popcll(mask);
                 n_eq += __popcll(eq_mask);
             }
+            for (int i = n_out + lane; i < k; i += 64) dst[i] = 0;  // keep the row in range
         }
     }
     __syncthreads();

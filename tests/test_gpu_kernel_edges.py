@@ -133,6 +133,22 @@ def test_near_ties_are_decided_as_by_the_sweeps(s3r, n_blk, k):  # noqa: F811
     assert np.array_equal(idx, want[:2])
 
 
+@pytest.mark.parametrize("n_blk,k", [(40, 40), (130, 64), (500, 17)])
+def test_scores_that_are_no_numbers_enter_no_list(s3r, n_blk, k):  # noqa: F811
+    """A NaN key (or query) in one launch for short sequences and, past the line, in the sweeps: the same lists, and
+    zeros where fewer than k blocks are left."""
+    rng = np.random.default_rng(n_blk + k)
+    line = 2 ** 23 // n_blk ** 2
+    one = [rng.standard_normal((2, n_blk, 64)).astype(np.float32) for _ in range(3)]
+    one[1][0, 7, 3] = np.nan
+    one[0][1, 5, 9] = np.nan
+    many = [np.concatenate([x, np.zeros((line - 1, n_blk, 64), dtype=np.float32)]) for x in one]
+    _, idx = compress_topk_case(s3r, *one, k, False)
+    _, want = compress_topk_case(s3r, *many, k, False)
+    assert np.array_equal(idx, want[:2])
+    assert not (idx[0] == 7).any() and not idx[1, 5].any()
+
+
 @pytest.mark.parametrize("n_blk,topk,n_forced", [(70, 64, 3), (200, 65, 1), (320, 64, 64), (90, 5, 90)])   # (65: scores through memory)
 def test_forced_blocks_and_long_rows_in_one_launch(s3r, oracle, n_blk, topk, n_forced):  # noqa: F811
     wl = workloads.Workload(f"short_forced_{n_blk}_{topk}_{n_forced}", 1, 16 * n_blk - 3, 2, 64, "bf16", 16, topk, 103, "normal")
