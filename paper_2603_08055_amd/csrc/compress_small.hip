@@ -12,6 +12,9 @@
 //   P.V       Oc' = P Vc, each wave 16 channels of a quarter of the keys, partial sums added up in LDS
 // The fp32 matrix pipe is 1/16 as fast as the bf16 one, and still not what the time goes into; scores and
 // probabilities are fp32 throughout, at least as exact as the two-part and fp16 scores of the sweeps.
+// Two workgroups on a CU cover each other's latency (one from 513 to 1024 blocks, with a row of 1024 scores for all of them
+// and the partial sums beside it: 645 blocks, 16 heads 431 us a call, now 409; 724 blocks 487 and 464; 965, 9 heads 403 and
+// 385): hence 64 registers, a size of its own up to 768 blocks, and above it the partial sums in the probabilities' place.
 // Whole calls, the launches that this one took the place of -> this one (MI355X): 4 x 256 tokens, 2 heads, fp32 51.5 ->
 // 21 us; 7 x 777, 5 heads, blocks of 32 59.5 -> 33; 8 x 1374, 16 heads 133 -> 103.  Where the line to the sweeps lies:
 // compress_small_takes.
@@ -47,7 +50,7 @@ __device__ __forceinline__ float wave_sum(float x) { return wave_reduce(x, [](fl
 
 // NV: score registers of a lane, n_blk <= 64 NV.  grid: (ceil(n_blk / 16), heads)
 template <int NV>
-__global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
+__global__ __launch_bounds__(kSmallWaves * 64, 8) void compress_small_kernel(
     const float *__restrict__ qc, const float *__restrict__ kc, const float *__restrict__ vc,
     float *__restrict__ o_comp, int32_t *__restrict__ idx, int n_blk, int k, float scale_log2,
     const unsigned long long *__restrict__ forced_words)
@@ -55,7 +58,11 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
     // (+ 4: the rows that a wave writes or reads at a time start in different banks, 16-byte aligned)
     constexpr int kStride = NV * 64 + 4;
     __shared__ __attribute__((aligned(16))) float s[kSmallQ][kStride];       // scores, then probabilities
-    __shared__ float part[4][kSmallQ][68];                                   // P.V of a quarter of the keys each
+    // P.V of a quarter of the keys each; in the place of the probabilities where two workgroups do not fit a CU otherwise
+    constexpr bool kInPlace = NV > 12;
+    __shared__ float part_room[kInPlace ? 1 : 4][kSmallQ][68];
+    auto part = kInPlace ? reinterpret_cast<float (*)[kSmallQ][68]>(&s[0][0]) : part_room;
+    static_assert(!kInPlace || sizeof(s) >= 4 * kSmallQ * 68 * sizeof(float), "partial sums in the probabilities' place");
     __shared__ float inv_sum[kSmallQ];
     __shared__ float key_norm2[kSmallWaves];  // largest squared norm of the keys that each wave scored
 
@@ -100,7 +107,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
     }
     // Values of the first steps of P.V, requested early: their latency runs under the row phase.
     const int ct = wave & 3, kq = wave >> 2;  // 16 channels; every fourth run of 16 keys
-    constexpr int kEarly = NV < 4 ? NV : 4;
+    constexpr int kEarly = NV < 4 ? NV : NV < 12 ? 4 : NV < 16 ? 3 : 1;  // (what 64 registers hold)
     float v[kEarly][4];
     const float *vcol = vc + head + 16 * ct + col;
     auto value = [&](int run, int i) -> float {
@@ -170,24 +177,22 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
                 const float kn2 = wave_max(key_norm2[lane & (kSmallWaves - 1)]);
                 const float two_eps = (1.f / 131072.f) * 1.15f * __builtin_sqrtf(wave_sum(qv * qv)) * __builtin_sqrtf(kn2) + 1e-36f;
                 // the k-th score itself: the smallest taken
-                float kth = INFINITY;
+                uint32_t kth_key = 0xff800000u;  // (of +inf)
 #pragma unroll
                 for (int t = 0; t < NV; ++t)
-                    if (key[t] >= T && key[t] != 0u) kth = fminf(kth, x[t]);
-                kth = -wave_max(-kth);
-                int n_in = 0, n_near = 0;
+                    if (key[t] >= T && key[t] != 0u) kth_key = kth_key < key[t] ? kth_key : key[t];
+                const float kth = -wave_max(-key_to_float(kth_key));
+                // (bounds as keys: the scores themselves need no registers beside them)
+                const uint32_t above = order_key(kth + two_eps), below = order_key(kth - two_eps);
+                int n_from = 0;
 #pragma unroll
-                for (int t = 0; t < NV; ++t) {
-                    const bool in = key[t] != 0u && x[t] > kth + two_eps, near = key[t] != 0u && !in && x[t] >= kth - two_eps;
-                    n_in += __popcll(__ballot(in));
-                    n_near += __popcll(__ballot(near));
-                }
-                if (n_in + n_near > k) {  // (rare)
+                for (int t = 0; t < NV; ++t) n_from += __popcll(__ballot(key[t] >= below && key[t] != 0u));
+                if (n_from > k && two_eps == two_eps) {  // (rare)
                     const int sub = lane & 15;
                     const floatx4 q4 = *reinterpret_cast<const floatx4 *>(qc + head + static_cast<int64_t>(row) * 64 + 4 * sub);
 #pragma unroll
                     for (int t = 0; t < NV; ++t) {
-                        const bool in = key[t] != 0u && x[t] > kth + two_eps, near = key[t] != 0u && !in && x[t] >= kth - two_eps;
+                        const bool in = key[t] > above, near = !in && key[t] >= below && key[t] != 0u;
                         key[t] = in ? 0xffffffffu : 0u;
                         unsigned long long m = __ballot(near);
                         while (m != 0ull) {  // four at a time, 16 lanes each, in the order of operations of that kernel
@@ -257,6 +262,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void compress_small_kernel(
             for (int i = 0; i < 4; ++i) w[i] = value(run, i);
             step(run, w);
         }
+        if constexpr (kInPlace) __syncthreads();  // every wave has read its probabilities
 #pragma unroll
         for (int r = 0; r < 4; ++r) part[kq][4 * g + r][16 * ct + col] = acc[r];
     }
@@ -284,6 +290,7 @@ hipError_t launch_compress_small(const float *qc, const float *kc, const float *
     S3R_SMALL(2)
     S3R_SMALL(4)
     S3R_SMALL(8)
+    S3R_SMALL(12)
     S3R_SMALL(16)
 #undef S3R_SMALL
     return hipErrorInvalidValue;

@@ -141,9 +141,9 @@ hipError_t launch_compress_small(const float *qc, const float *kc, const float *
                                  hipStream_t stream);
 // Where it is the faster one.  Its time grows with the products, which run on the fp32 matrix pipe, the sweeps' with the
 // length of their chain of launches.  Whole calls, microseconds, sweeps -> this launch (MI355X, blocks of 64, top-16):
-// 16 heads: 169 -> 138 at 256 blocks, 309 -> 284 at 512, 453 -> 457 at 768, 599 -> 630 at 1024; fp32 789 -> 770 at 512,
-// 1583 -> 1614 at 1024; 4 heads: 120 -> 90 at 512, 195 -> 158 at 1024; one head: 101 -> 68 at 1024; 8 heads, top-100
-// (scores through memory): 570 -> 542 at 512, 1169 -> 1130 at 1024.  Rows of more than kFusedTopkMaxK entries stay with the scores in
+// 16 heads: 169 -> 138 at 256 blocks, 309 -> 284 at 512, 338 -> 324 at 516, 418 -> 409 at 645, 471 -> 464 at 724; on the line
+// with fewer heads: 429 -> 429 at 836 (12), 382 -> 385 at 965 (9), 361 -> 353 at 1024 (8); fp32 797 -> 775 at 500, 1190 ->
+// 1171 at 724, 920 -> 911 at 965 (9 heads); 4 heads: 120 -> 90 at 512, 205 -> 182 at 1024; one head: 98 -> 75 at 1024.  Rows of more than kFusedTopkMaxK entries stay with the scores in
 // memory all the same: that route decides near-ties by scores of its own, and its index lists stay what they are.
 inline bool compress_small_takes(int64_t n_blk, int heads, int k)
 {

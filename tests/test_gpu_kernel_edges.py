@@ -100,7 +100,7 @@ def test_dense_attention_with_a_short_last_unit(s3r, oracle, tail):
 
 @pytest.mark.parametrize("n_blk,heads,k", [
     (1, 1, 1), (2, 3, 2), (15, 2, 15), (16, 2, 4), (17, 2, 16), (63, 1, 64), (65, 2, 1), (128, 2, 7), (129, 1, 64),
-    (256, 3, 9), (257, 2, 64), (511, 1, 64), (512, 2, 33), (513, 1, 5), (1023, 1, 64), (1024, 2, 1),
+    (256, 3, 9), (257, 2, 64), (511, 1, 64), (512, 2, 33), (513, 1, 5), (768, 2, 64), (769, 1, 7), (1023, 1, 64), (1024, 2, 1),
     (724, 16, 8), (725, 16, 8),       # either side of the line to the sweeps
 ])
 def test_short_sequences_in_one_launch(s3r, oracle, n_blk, heads, k):  # noqa: F811
