@@ -295,7 +295,7 @@ __device__ __forceinline__ void compress_block(
             for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
         float m_run = -1e30f;
         float m_lim = -1e30f + kCompressRescaleSlack;  // what a half step's largest logit must exceed to raise m_run
-        float l_run[4] = {0.f, 0.f, 0.f, 0.f};         // the row sum in four chains
+        float l_run = 0.f;
         float lowest = -INFINITY;  // where the maxima start; the compiler takes two scores per v_max3 if it does not know the value
         asm("" : "+v"(lowest));
         lowest = fmaxf(lowest, lowest);
@@ -349,8 +349,7 @@ __device__ __forceinline__ void compress_block(
                 const float alpha = fast_exp2(m_run - m_new);
                 m_run = m_new;
                 m_lim = m_new + kCompressRescaleSlack;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) l_run[c] *= alpha;
+                l_run *= alpha;
 #pragma unroll
                 for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
@@ -380,6 +379,7 @@ __device__ __forceinline__ void compress_block(
             read(0); read(1); read(2);
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc_next[r] = 0.f;
+            float lsum[4] = {0.f, 0.f, 0.f, 0.f};
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
@@ -407,17 +407,18 @@ __device__ __forceinline__ void compress_block(
                     const bf16x2 pr = {static_cast<bf16_t>(acc[j - 1]), static_cast<bf16_t>(acc[j])};
                     p_out[j >> 3][(j & 7) - 1] = pr[0];
                     p_out[j >> 3][j & 7] = pr[1];
-                    l_run[(j >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, bf16x2{static_cast<bf16_t>(1.f), static_cast<bf16_t>(1.f)},
-                                                                         l_run[(j >> 1) & 3], false);
+                    lsum[(j >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, bf16x2{static_cast<bf16_t>(1.f), static_cast<bf16_t>(1.f)},
+                                                                         lsum[(j >> 1) & 3], false);
                 }
                 // nothing needs these values before the next barrier: tie them to this slot, or the
                 // compiler moves the vector work away from the MFMAs it is meant to overlap with
-                if (j & 1) asm volatile("" : "+v"(l_run[(j >> 1) & 3]));
+                if (j & 1) asm volatile("" : "+v"(lsum[(j >> 1) & 3]));
                 else asm volatile("" : "+v"(acc[j]));
                 if ((j & 1) == 0) asm volatile("" : "+v"(bm[mt * 8 + (j >> 1)]));
                 if ((j & 7) == 7) asm volatile("" : "+v"(p_out[j >> 3]));
                 __builtin_amdgcn_sched_barrier(0);
             }
+            l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
         };
 
         floatx16 sacc0, sacc1;
@@ -473,7 +474,7 @@ __device__ __forceinline__ void compress_block(
             if (qrow < n_blk && g == 0) ft.thr[row_id] = kth == -INFINITY ? kth : kth - margin;
         }
         if (qrow < n_blk) {
-            const float inv = 1.f / compress_sum_halves((l_run[0] + l_run[1]) + (l_run[2] + l_run[3]));
+            const float inv = 1.f / compress_sum_halves(l_run);
             float *orow = o_comp + (static_cast<int64_t>(h) * n_blk + qrow) * 64;
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt)

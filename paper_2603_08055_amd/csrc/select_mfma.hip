@@ -27,8 +27,8 @@
 // What else binds: power.  Under these loops the clock falls to 1.8 to 2.0 GHz, and every vector instruction taken out of
 // a unit shows as a lower clock as much as in fewer cycles (dense attention of 21 984 rows, 16 heads: 36.5 million
 // cycles at 2.03 GHz -> 29.7 at 1.80, 2.24 -> 2.06 ms; without the exponentials 24.6 at 1.65).  So the loop is kept to the
-// instructions that the softmax needs (115 of a unit's vector instructions, 144 before): addresses on the scalar unit, no
-// exchange between the lanes of a query unless the maximum rises, the row sum in running chains, and masks that hold no
+// instructions that the softmax needs (119 of a unit's vector instructions, 144 before): addresses on the scalar unit, no
+// exchange between the lanes of a query unless the maximum rises, and masks that hold no
 // registers when they are not needed (162 -> 108, four waves per SIMD).  Measured and not kept, all within 1 %: LDS
 // operands read 4 or 8 ahead, P.V in the gaps of the exponentials, 256 or 512 query rows per workgroup (a half or a
 // quarter of the traffic into LDS, and as much more time spent waiting at its barriers).
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
     float m_run = -1e30f;
     float m_lim = -1e30f + kRescaleSlack;      // what a unit's largest logit must exceed to raise m_run
-    float l_run[4] = {0.f, 0.f, 0.f, 0.f};     // the row sum, bf16: in four chains
+    float l_run = 0.f;
 
     // how many of unit w's 64 keys exist, 64 or more: all (wave-uniform)
     auto unit_left = [&](int w) -> int {
@@ -451,8 +451,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
             const float alpha = fast_exp2(m_run - m_new);
             m_run = m_new;
             m_lim = m_new + kRescaleSlack;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) l_run[i] *= alpha;
+            l_run *= alpha;
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
@@ -471,11 +470,13 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         // The row sum adds the probabilities as the MFMA will see them (rounded to bf16), two per
         // v_dot2_f32_bf16 with a vector of ones: half the instructions of fp32 adds, and numerator and
         // denominator of the softmax then carry the same rounding.
-        // fp32: probabilities split into operand pairs, the row sum adds the fp32 values, a unit's among themselves first:
-        // in one chain per register position their rounding shows (special rows of 200 views, outlier keys, against 64
-        // bits: 3.43e-6, 6.72e-6 in running chains; in bf16 both ways 1.69376e-3).
+        // fp32: probabilities split into operand pairs, the row sum adds the fp32 values.
+        // A unit's are added among themselves first: four more additions a unit than chains that run through all units
+        // (within 1 % of the time), but beside a large weight such a chain drops weights that a unit's sum keeps (lse of 8192
+        // keys, one of weight 1 and the others of 2^-26: off by 1.5e-5, and not at all this way; special rows of 200 views
+        // in fp32, outlier keys, against 64 bits: 6.72e-6 and 3.43e-6).
+        float lsum[4] = {0.f, 0.f, 0.f, 0.f};
         if constexpr (F32) {
-            float lsum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int v = 0; v < 2 * NMT; ++v)
 #pragma unroll
@@ -486,7 +487,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
                     pb[v][i] = static_cast<bf16_t>(p);
                     pl[v][i] = static_cast<bf16_t>(p - static_cast<float>(pb[v][i]));
                 }
-            l_run[0] += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
+            l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
             return;
         }
         const bf16x2 ones = {static_cast<bf16_t>(1.f), static_cast<bf16_t>(1.f)};
@@ -497,10 +498,11 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
                 const int mt = v >> 1, r = 8 * (v & 1) + i;
                 const bf16x2 pr = {static_cast<bf16_t>(fast_exp2(sacc[mt][r] * scale_log2 - m_run)),
                                    static_cast<bf16_t>(fast_exp2(sacc[mt][r + 1] * scale_log2 - m_run))};
-                l_run[(i >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l_run[(i >> 1) & 3], false);
+                lsum[(i >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum[(i >> 1) & 3], false);
                 pb[v][i] = pr[0];
                 pb[v][i + 1] = pr[1];
             }
+        l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
     };
     // O^T += V^T P^T for the unit whose V sits in `vs`
     // (pieces: V tiles of blocks of 16 keys, see small_v_piece)
@@ -619,25 +621,23 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     }
 
     if constexpr (KS == 2) {  // the second half's result to LDS, added to the first half's there
-        float *buf = reinterpret_cast<float *>(&ring[0][0]) + rg * (37 * 64) + lane;  // [QW][37 registers][64 lanes]
-        static_assert(sizeof(ring) >= QW * 37 * 64 * sizeof(float), "partial results in the ring's place");
+        float *buf = reinterpret_cast<float *>(&ring[0][0]) + rg * (34 * 64) + lane;  // [QW][34 registers][64 lanes]
+        static_assert(sizeof(ring) >= QW * 34 * 64 * sizeof(float), "partial results in the ring's place");
         lds_barrier();        // every wave is done with the ring
         if (kh == 1) {
             buf[0] = m_run;
+            buf[64] = l_run;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) buf[(1 + i) * 64] = l_run[i];
-#pragma unroll
-            for (int x = 0; x < 32; ++x) buf[(5 + x) * 64] = oacc[x >> 4][x & 15];
+            for (int x = 0; x < 32; ++x) buf[(2 + x) * 64] = oacc[x >> 4][x & 15];
         }
         lds_barrier();
         if (kh == 1) return;
         const float m_all = fmaxf(m_run, buf[0]);
         const float f0 = fast_exp2(m_run - m_all), f1 = fast_exp2(buf[0] - m_all);
         m_run = m_all;
+        l_run = l_run * f0 + buf[64] * f1;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) l_run[i] = l_run[i] * f0 + buf[(1 + i) * 64] * f1;
-#pragma unroll
-        for (int x = 0; x < 32; ++x) oacc[x >> 4][x & 15] = oacc[x >> 4][x & 15] * f0 + buf[(5 + x) * 64] * f1;
+        for (int x = 0; x < 32; ++x) oacc[x >> 4][x & 15] = oacc[x >> 4][x & 15] * f0 + buf[(2 + x) * 64] * f1;
     }
 
     if (!row_valid) return;
@@ -647,7 +647,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         for (int s = 0; s < 4; ++s) *reinterpret_cast<bf16x8 *>(out + (trow * heads + h) * 64 + 16 * s + 8 * g) = qb[s];
         return;
     }
-    const float l_tot = sum_with_other_half((l_run[0] + l_run[1]) + (l_run[2] + l_run[3]));
+    const float l_tot = sum_with_other_half(l_run);
     const float inv = (EXTRA && DENSE && l_tot == 0.f) ? 0.f : 1.f / l_tot;  // (a key split of empty units only)
     if (lse != nullptr && g == 0)
         lse[static_cast<int64_t>(h) * lse_stride + trow] = (m_run + __builtin_log2f(l_tot)) * kLn2;

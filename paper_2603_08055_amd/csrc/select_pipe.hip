@@ -155,7 +155,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
         for (int x = 0; x < 16; ++x) oacc[dt][x] = 0.f;
     float m_run = -1e30f;
     float m_lim = -1e30f + kRescaleSlack;      // what a unit's largest logit must exceed to raise m_run
-    float l_run[4] = {0.f, 0.f, 0.f, 0.f};     // the row sum in four chains
+    float l_run = 0.f;
     float lowest = -INFINITY;  // where the maxima start; the compiler takes two scores per v_max3 if it does not know the value
     asm("" : "+v"(lowest));
     lowest = fmaxf(lowest, lowest);
@@ -219,8 +219,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
             alpha = fast_exp2(m_run - m_new);
             m_run = m_new;
             m_lim = m_new + kRescaleSlack;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) l_run[c] *= alpha;
+            l_run *= alpha;
         }
         return raised;
     };
@@ -251,6 +250,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     // their LDS latency runs under it.
     auto overlapped = [&](floatx16 (&acc)[2], floatx16 (&acc_next)[2], bf16x8 (&p_out)[4], const bf16x8 (&p_in)[4],
                           bf16x8 (&rd)[16], const bf16_t *k_src, const bf16_t *v_src) __attribute__((always_inline)) {
+        float lsum[4] = {0.f, 0.f, 0.f, 0.f};
         // MFMAs 4 .. 15 spread over the 16 half groups
         auto first_of = [](int half) { return 4 + (half * (16 - 4) + 15) / 16; };
         auto mfma = [&](int m) __attribute__((always_inline)) { matrix(m, acc_next, p_in, rd, k_src, v_src); };
@@ -273,14 +273,15 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
                 const int x = x0 + c;
                 p_out[2 * mt + (x >> 3)][x & 7] = pr[0];
                 p_out[2 * mt + (x >> 3)][(x & 7) + 1] = pr[1];
-                l_run[(q4 * 2 + (c >> 1)) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l_run[(q4 * 2 + (c >> 1)) & 3], false);
+                lsum[(q4 * 2 + (c >> 1)) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum[(q4 * 2 + (c >> 1)) & 3], false);
             }
             // nothing needs these values before the next barrier: tie them to this group, or the compiler
             // moves the vector work away from the MFMAs it is meant to overlap with
-            asm volatile("" : "+v"(l_run[(q4 * 2) & 3]), "+v"(l_run[(q4 * 2 + 1) & 3]));
+            asm volatile("" : "+v"(lsum[(q4 * 2) & 3]), "+v"(lsum[(q4 * 2 + 1) & 3]));
             if (q4 & 1) asm volatile("" : "+v"(p_out[2 * mt + (x0 >> 3)]));
             __builtin_amdgcn_sched_barrier(0);
         }
+        l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
     };
     // the same three phases one after the other, each only if its unit exists (first and last iterations)
     auto plain = [&](bool soft, bool pv, bool ss, floatx16 (&acc)[2], floatx16 (&acc_next)[2], bf16x8 (&p_out)[4],
@@ -295,6 +296,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
         }
         if (__builtin_expect(raised, 0)) rescale();
         if (soft) {
+            float lsum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -304,8 +306,9 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
                                        static_cast<bf16_t>(fast_exp2(acc[mt][x + 1] * scale_log2 - m_run))};
                     p_out[v][e] = pr[0];
                     p_out[v][e + 1] = pr[1];
-                    l_run[(e >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l_run[(e >> 1) & 3], false);
+                    lsum[(e >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum[(e >> 1) & 3], false);
                 }
+            l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
         }
         if (ss) {
 #pragma unroll
@@ -381,7 +384,7 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
     // ---- the softmax over all selected keys from the P partial ones of each row group
     constexpr int kShare = 32 / P;           // accumulator registers each partner adds up and writes
     float osum[kShare];
-    float m_all = m_run, l_all = sum_with_other_half((l_run[0] + l_run[1]) + (l_run[2] + l_run[3]));
+    float m_all = m_run, l_all = sum_with_other_half(l_run);
     if constexpr (P == 1) {
 #pragma unroll
         for (int x = 0; x < 32; ++x) osum[x] = oacc[x >> 4][x & 15];

@@ -292,6 +292,47 @@ def test_row_sums_of_long_fp32_rows_are_added_up_exactly_enough(s3r):  # noqa: F
     assert math.sqrt(off / total) < 4.5e-6
 
 
+def _one_large_weight(n_keys, twice=0):
+    """Keys whose weights are 1 for the first and 2^-26 for the others (2^-25 for every twice-th), for queries of 8 in two
+    channels: two small weights are below half of the last place of 1 (2^-24), the 32 of a lane and unit are four of
+    them."""
+    s = torch.full((n_keys,), -26.0 * math.log(2.0), dtype=torch.float64)
+    if twice:
+        s[::twice] = -25.0 * math.log(2.0)
+    s[0] = 0.0
+    hi = s.to(torch.bfloat16)
+    k = torch.zeros((n_keys, 64), dtype=torch.bfloat16)
+    k[:, 0], k[:, 1] = hi, (s - hi.to(torch.float64)).to(torch.bfloat16)
+    return k
+
+
+@pytest.mark.parametrize("block,kk,heads", [(64, 128, 5), (64, 128, 1), (64, 200, 2), (128, 64, 2)])   # one and two pairs of waves; long rows; blocks of 128
+def test_small_weights_beside_a_large_one_stay_in_the_row_sum(s3r, block, kk, heads):  # noqa: F811
+    """Added up within a unit first they all count; one after the other onto the whole sum an eighth of them is lost
+    (7e-6 to 2.4e-5 in lse)."""
+    n_tok = block * kk
+    k = _one_large_weight(n_tok)[:, None].expand(n_tok, heads, 64).contiguous().cuda()
+    q = torch.zeros_like(k)
+    q[:, :, :2] = 8.0
+    idx = torch.arange(kk, dtype=torch.int32, device="cuda").expand(heads, kk, kk).contiguous()
+    lse = torch.full((heads, n_tok), float("nan"), device="cuda")
+    s3r.speed3r_select_attn(q, k, torch.ones_like(k), idx, torch.empty_like(q), block, lse=lse)
+    assert (lse.double() - math.log1p((n_tok - 1) * 2.0 ** -26)).abs().max().item() < 2e-6
+
+
+def test_small_weights_beside_a_large_one_stay_in_the_sum_of_the_sweep(s3r):  # noqa: F811
+    n_blk = 4096
+    kc = _one_large_weight(n_blk, 63).float().numpy()[None]   # (bounds on the TopK that hold few keys: no second pass)
+    qc = np.zeros_like(kc)
+    qc[:, :, :2] = 8.0
+    vc = np.ones_like(kc)
+    vc[:, 0] = 0.0
+    o_comp, _ = compress_topk_case(s3r, qc, kc, vc, 4, False)
+    small = (n_blk - 1 + (n_blk - 1) // 63) * 2.0 ** -26
+    want = small / (1.0 + small)
+    assert np.abs(o_comp / want - 1.0).max() < 2e-6
+
+
 @pytest.mark.parametrize("n_blk,kk", [(8, 3), (9, 8), (3000, 48)])   # edge iterations only; full ones; two pairs of waves
 def test_probabilities_waiting_while_the_maximum_rises(s3r, n_blk, kk):  # noqa: F811
     """Pipelined selection: the running maximum rises by just under 9 (powers of two) while the probabilities of the
