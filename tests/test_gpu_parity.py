@@ -441,7 +441,7 @@ def compress_topk_case(s3r, qc, kc, vc, k, accurate, scale=0.0):
 
 
 @pytest.mark.parametrize("n_blk,k,span", [(5, 3, 2), (63, 7, 2), (64, 64, 3), (65, 1, 2), (200, 16, 8), (1000, 64, 8),
-                                          (2100, 32, 8), (2100, 64, 1), (50, 1000, 4)])
+                                          (1025, 7, 2), (2100, 32, 8), (2100, 64, 1), (50, 1000, 4)])
 def test_compress_attn_topk_exact_on_integer_scores(s3r, oracle, n_blk, k, span):
     """Pooled tensors of small integers: every product and sum is exact in bf16 pairs, fp32 and
     fp64 alike, so the TopK sets must equal the oracle's bit for bit, ties (there are many) going to
@@ -458,7 +458,8 @@ def test_compress_attn_topk_exact_on_integer_scores(s3r, oracle, n_blk, k, span)
 
 
 @pytest.mark.parametrize("n_blk,heads,k,accurate", [(16, 2, 4, True), (172, 4, 16, False), (172, 4, 16, True),
-                                                    (1000, 2, 64, False), (2147, 3, 32, False), (33, 1, 5, False)])
+                                                    (1000, 2, 64, False), (2147, 3, 32, False), (33, 1, 5, False),
+                                                    (1025, 2, 4, True), (1100, 4, 64, False)])   # from 1025 on: the sweeps
 def test_compress_attn_topk_random(s3r, oracle, n_blk, heads, k, accurate):
     rng = np.random.default_rng(n_blk + 13 * k)
     qc, kc, vc = (rng.standard_normal((heads, n_blk, 64)).astype(np.float32) for _ in range(3))
@@ -471,7 +472,7 @@ def test_compress_attn_topk_random(s3r, oracle, n_blk, heads, k, accurate):
 
 
 @pytest.mark.parametrize("accurate", [False, True])
-@pytest.mark.parametrize("route", ["in_sweep", "stored"])
+@pytest.mark.parametrize("route", ["one_launch", "in_sweep", "stored"])
 @pytest.mark.parametrize("step", [0.25, 0.5, -0.25])
 def test_compress_attn_running_maximum_rises_along_the_keys(s3r, oracle, route, accurate, step):
     """Logits that grow steadily with the key index (by `step` per key, i.e. by 8 or 16 per 32 keys): the
@@ -490,8 +491,13 @@ def test_compress_attn_running_maximum_rises_along_the_keys(s3r, oracle, route, 
     vc = rng.standard_normal((heads, n_blk, 64)).astype(np.float32)
     s64 = oracle.scores(qc.astype(np.float64), kc.astype(np.float64))
     ref = oracle.compressed_attn(s64, vc.astype(np.float64), 0.125)
-    if route == "in_sweep":
-        o_comp, idx = compress_topk_case(s3r, qc, kc, vc, 16, accurate, scale=0.125)
+    if route != "stored":
+        # 94 heads, each of the two 47 times, are past the line up to which one launch does it all
+        times = 1 if route == "one_launch" else 47
+        o_comp, idx = compress_topk_case(s3r, *(np.tile(x, (times, 1, 1)) for x in (qc, kc, vc)), 16, accurate, scale=0.125)
+        assert np.array_equal(o_comp, np.tile(o_comp[:heads], (times, 1, 1)))
+        assert np.array_equal(idx, np.tile(idx[:heads], (times, 1, 1)))
+        o_comp, idx = o_comp[:heads], idx[:heads]
         check_topk_sets(s64, idx, 16)
     else:
         s_dev = torch.full((heads, n_blk, n_blk), float("nan"), device="cuda")
@@ -533,7 +539,8 @@ def test_select_attn_running_maximum_rises_along_the_keys(s3r, oracle, block, kk
     assert float(np.max(np.abs(got_l - l_ref.reshape(heads, -1)))) <= TOL["bf16"]
 
 
-@pytest.mark.parametrize("n_blk,k,offset,noise", [(1000, 16, 0.5, 0.05), (1500, 64, 0.5, 0.05), (700, 8, 0.25, 0.2)])
+@pytest.mark.parametrize("n_blk,k,offset,noise", [(1000, 16, 0.5, 0.05), (1500, 64, 0.5, 0.05), (700, 8, 0.25, 0.2),
+                                                    (1100, 16, 0.5, 0.05), (1300, 8, 0.25, 0.2)])   # from 1025 blocks on: the sweeps
 def test_compress_attn_topk_large_common_component(s3r, oracle, n_blk, k, offset, noise):
     """Pooled keys that share a large common vector: all scores of a row sit within a narrow band on
     top of |q||k| ~ 16..64, so scores computed from the bf16 hi parts alone (error up to 2^-8 |q||k|)
@@ -555,13 +562,14 @@ def test_compress_attn_topk_large_common_component(s3r, oracle, n_blk, k, offset
 
 
 @pytest.mark.parametrize("q_mag,k_mag", [(3e4, 1e-5), (1e-7, 1e-6), (2e6, 5e5), (1.0, 1.0)])
-def test_compress_attn_topk_input_magnitudes(s3r, oracle, q_mag, k_mag):
+@pytest.mark.parametrize("n_blk", [900, 1100])   # one launch; the sweeps
+def test_compress_attn_topk_input_magnitudes(s3r, oracle, q_mag, k_mag, n_blk):
     """The sweeps work on fp16 copies of the pooled tensors, scaled per head by a power of two: sets and
     outputs must not depend on the magnitude of the inputs (far outside fp16's range here), heads of
     very different magnitude must not disturb each other, and rows of tiny norm beside rows of large
     norm must still get valid sets."""
     rng = np.random.default_rng(5)
-    heads, n_blk, k = 3, 900, 16
+    heads, k = 3, 16
     qc, kc, vc = (rng.standard_normal((heads, n_blk, 64)) for _ in range(3))
     head_mag = np.array([1.0, 1e-3, 64.0])[:, None, None]
     qc = qc * q_mag * head_mag
@@ -653,10 +661,11 @@ def test_topk_in_sweep_candidate_overflow_falls_back(s3r, oracle):
                         wl.dtype, rows=rows2, label="half-tie rows")
 
 
-def test_topk_in_sweep_is_deterministic_and_agrees_with_stored_scores(s3r):
+@pytest.mark.parametrize("n_blk", [700, 1100])   # one launch; the sweeps
+def test_topk_in_sweep_is_deterministic_and_agrees_with_stored_scores(s3r, n_blk):
     """Two runs agree bit for bit; the stored-score route picks the same sets except where the two
     roundings of a score resolve a near-tie differently (rare), and Oc' agrees within the bf16 tolerance."""
-    wl = workloads.Workload("two_routes", 1, 700 * 64, 2, 64, "bf16", 64, 12, 95, "normal")
+    wl = workloads.Workload("two_routes", 1, n_blk * 64, 2, 64, "bf16", 64, 12, 95, "normal")
     q, kx, v = workloads.make_inputs(wl, device="cuda")
     a = run_device(s3r, q, kx, v, wl.block, wl.topk)
     b = run_device(s3r, q, kx, v, wl.block, wl.topk)
@@ -1124,7 +1133,7 @@ def test_strides_are_validated(s3r):
     (64 * 140 + 40, 60, 45, True),       # forced blocks the smaller part of a long row
 ])
 def test_long_index_rows_pair_kernel(s3r, oracle, n_tok, topk, n_forced, with_gate):
-    """Rows of more than 96 blocks of 64 tokens, at least half of them forced, run two query blocks
+    """Rows of more than 128 blocks of 64 tokens, at least half of them forced, run two query blocks
     per workgroup on the union of their lists; other long rows one; every output against the oracle."""
     wl = workloads.Workload(f"longrows_{n_tok}_{topk}_{n_forced}", 1, n_tok, 2, 64, "bf16", 64, topk, 111, "clustered")
     forced = None
@@ -1133,20 +1142,21 @@ def test_long_index_rows_pair_kernel(s3r, oracle, n_tok, topk, n_forced, with_ga
     end_to_end(s3r, oracle, wl, with_gate=with_gate, forced=forced)
 
 
-def test_long_index_rows_spatial_windows(s3r, oracle):
-    """The same kernel with 8 x 8 windows (per-block lengths, cut edge windows): 9 views of 37 x 37
-    patches = 225 blocks (odd), 60 of them forced (the corner windows among them), 50 selected."""
+@pytest.mark.parametrize("n_forced,topk", [(60, 50), (84, 60)])   # pipelined kernel; two query blocks per workgroup
+def test_long_index_rows_spatial_windows(s3r, oracle, n_forced, topk):
+    """The same kernels with 8 x 8 windows (per-block lengths, cut edge windows): 9 views of 37 x 37
+    patches = 225 blocks (odd), some of them forced (the corner windows among them)."""
     views, special, grid = 9, 5, (37, 37, 8)
     tpv = special + 37 * 37
-    wl = workloads.Workload("longrows_windows", views, tpv, 2, 64, "bf16", 64, 50, 113, "normal")
+    wl = workloads.Workload("longrows_windows", views, tpv, 2, 64, "bf16", 64, topk, 113, "normal")
     q, k, v = workloads.make_inputs(wl)
     gate = workloads.make_gate_logits(wl)
-    forced = np.unique(np.concatenate([[4, 20, 24, 224], np.random.default_rng(114).choice(225, 56, replace=False)]))
+    forced = np.unique(np.concatenate([[4, 20, 24, 224], np.random.default_rng(114).choice(225, n_forced - 4, replace=False)]))
     forced = forced.astype(np.int32)
-    res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), 64, 50, gate=gate.cuda(), forced=forced, tokens_per_view=tpv,
+    res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), 64, topk, gate=gate.cuda(), forced=forced, tokens_per_view=tpv,
                      special_per_view=special, grid=grid)
     stats = compare_windows_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v),
-                                        to_host_f32(gate), 50, "bf16", views, tpv, special, grid, forced=forced,
+                                        to_host_f32(gate), topk, "bf16", views, tpv, special, grid, forced=forced,
                                         label=wl.name)
     log(f"{wl.name}: {stats}")
 
