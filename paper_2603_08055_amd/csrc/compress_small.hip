@@ -171,7 +171,8 @@ __global__ __launch_bounds__(kSmallWaves * 64, 8) void compress_small_kernel(
             // This score and the one of topk_candidates_kernel differ by at most eps = 72 2^-24 |q||k| (64 roundings in a row
             // here, 8 there: chains of 4 and a tree of 16).  Keys more than 2 eps above the k-th score are in by
             // either, those more than 2 eps below are out; if others lie between than just as many as are wanted, the scores of
-            // topk_candidates_kernel decide among them.
+            // topk_candidates_kernel decide among them.  (Outlier keys widen the band for their head, all but equal ones put every
+            // key into it: 500 blocks, 16 heads 296 and 375 us a call, 292 on clustered keys; by the sweeps 330, 512 and 322.)
             {
                 const float qv = qc[head + static_cast<int64_t>(row) * 64 + lane];
                 const float kn2 = wave_max(key_norm2[lane & (kSmallWaves - 1)]);

@@ -24,7 +24,7 @@
 // and brings nothing: the work mapping already runs neighbours on the same XCD at the same time,
 // so their shared key blocks hit in that XCD's L2.
 //
-// What else binds: power.  Under these loops the clock falls to 1.8 to 2.0 GHz, and every vector instruction taken out of
+// What else binds: power.  Under these loops the clock falls to 1.6 to 1.9 GHz, and every vector instruction taken out of
 // a unit shows as a lower clock as much as in fewer cycles (dense attention of 21 984 rows, 16 heads: 36.5 million
 // cycles at 2.03 GHz -> 29.7 at 1.80, 2.24 -> 2.06 ms; without the exponentials 24.6 at 1.65).  So the loop is kept to the
 // instructions that the softmax needs (119 of a unit's vector instructions, 144 before): addresses on the scalar unit, no
