@@ -142,8 +142,8 @@ size_t speed3r_workspace_bytes(int64_t n_tok, int heads, int head_dim, int block
 
 /* The same from a filled-in parameter block (only its shape fields are read: n_tok, heads, head_dim,
  * block, topk, dtype, n_forced, tokens_per_view, special_per_view); needed with special tokens.
- * (fp32 with few special rows: room for at least 16 key splits of these; a workspace that holds the number with at
- * least 8 is accepted too, and the call then runs in that many.) */
+ * Special rows run in key splits, whose partial results take room here; they are more than the time alone asks for,
+ * for their precision, and a workspace that holds only the leaner number is accepted too: the call then runs in that many. */
 size_t speed3r_workspace_bytes_ex(const s3r_params *p);
 
 /* Number of blocks n_blk of the sequence the sparse path works on, for a filled-in parameter block

@@ -77,18 +77,19 @@ size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 // 7.6e-6 in 2, 5.7e-6 in 6, 5.4e-6 in 8, 5.0e-6 in 16).  A unit is therefore weighed at four times the 1.95 us it takes
 // (small blocks: twice), against the start and the combine kernel: in fp32 this is a rule for exactness more than a model
 // of the time.  There are at least 8 splits although fewer can be faster, and with up to 48 workgroups, which 8 leave at one
-// or two to a CU where two run at once, at least 16 if the workspace has room (least32: the least number it is to be).
+// or two to a CU where two run at once, at least 16.
 // In bf16 it is the rounding of P, which gains from the splits, every split's largest probability being exact (outlier keys,
 // against 64 bits: 30 views in 4 x 4 windows, 8 heads 1.80e-3 in one split, 1.69e-3 in 32, 1.67e-3 in 48; 20 views, 4 heads
 // 1.680e-3 in 28 splits, 1.668e-3 in 36; blocks of 32, 40 views, 16 heads 1.705e-3 in 16, 1.689e-3 in 24).  So the units of
 // small blocks stay weighed at what they took with another kernel: as many splits as then, 10 % of this launch at 20 views.
+// lean: the counts that the time alone would give (bf16), or at least 8 (fp32), for workspaces that hold no more.
 constexpr int kMaxDenseSplit = 64;
-int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, int block, int least32)
+int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, int block, bool lean)
 {
     const bool bf16 = dtype == S3R_BF16;
     const int64_t wgs = (n_rows + 127) / 128 * heads;
     if (wgs >= 3072) return 1;  // 12 workgroups and more per CU: even enough
-    const double unit_us = bf16 ? (block >= 64 ? 0.68 : 1.1) : (block >= 64 ? 8.0 : 3.8);
+    const double unit_us = bf16 ? (block >= 64 ? (lean ? 0.64 : 0.68) : (lean ? 0.7 : 1.1)) : (block >= 64 ? 8.0 : 3.8);
     const int64_t at_once = bf16 ? 3 : 1;
     const double left_over[3] = {0.0, bf16 ? 0.75 : 0.0, bf16 ? 0.3 : 0.0};
     auto time_us = [&](int s) {
@@ -100,7 +101,7 @@ int dense_splits(int64_t n_rows, int heads, int64_t n_units, s3r_dtype dtype, in
     };
     int most = static_cast<int>(n_units / 4 < kMaxDenseSplit ? n_units / 4 : kMaxDenseSplit);  // at least 4 units each
     if (most < 1) most = 1;
-    if (wgs > 48) least32 = 8;
+    const int least32 = wgs <= 48 && !lean ? 16 : 8;
     const int least = bf16 ? 1 : (most < least32 ? most : least32);
     double us[kMaxDenseSplit + 1], shortest = INFINITY;
     for (int s = least; s <= most; ++s) {
@@ -189,11 +190,11 @@ Layout make_layout(int64_t n_tok, int heads, int block, int topk, int n_forced, 
     L.oc_tok = take(token_queries ? static_cast<size_t>(L.n_blk) * block * heads * 64 * sizeof(float) : 0);
     // special rows in key splits: normalised partial results and their log-sums
     const size_t before = off;
-    for (const int least32 : {16, 8}) {
+    for (const bool lean : {false, true}) {
         off = before;
         L.spec_split = 1;
         if (n_spec > 0 && mfma_ok(dtype, block))
-            L.spec_split = dense_splits(n_spec, heads, (L.n_blk * block + 63) / 64 + (n_spec + 63) / 64, dtype, block, least32);
+            L.spec_split = dense_splits(n_spec, heads, (L.n_blk * block + 63) / 64 + (n_spec + 63) / 64, dtype, block, lean);
         const size_t part_rows = L.spec_split > 1 ? static_cast<size_t>(L.spec_split) * n_spec * heads : 0;
         L.spec_part_o = take(part_rows * 64 * sizeof(float));
         L.spec_part_lse = take(part_rows * sizeof(float));

@@ -251,17 +251,18 @@ def test_scores_of_small_fp32_blocks_are_added_up_exactly_enough(s3r, block):  #
     assert math.sqrt(off / total) < 3.0e-6
 
 
-@pytest.mark.parametrize("block,views,tpv,heads,grid,fewer", [(64, 40, 400, 2, None, 12), (16, 100, 400, 1, None, 10),
-                                                              (16, 30, 32 + 37 * 37, 3, (37, 37, 4), 10)])
-def test_fp32_special_rows_run_in_the_workspace_of_fewer_splits(s3r, block, views, tpv, heads, grid, fewer):  # noqa: F811
-    """Where 16 splits and more are taken for few workgroups, a workspace for the number with at least 8 will do."""
-    special = 32
-    splits = special_row_splits(s3r, views, tpv, special, heads, block, "f32", grid)
-    assert splits >= 16 > fewer
+@pytest.mark.parametrize("dtype,block,views,tpv,special,heads,grid,fewer", [
+    ("f32", 64, 40, 400, 32, 2, None, 12), ("f32", 16, 100, 400, 32, 1, None, 10), ("f32", 16, 30, 32 + 37 * 37, 32, 3, (37, 37, 4), 10),
+    ("bf16", 16, 20, 5 + 37 * 37, 5, 16, (37, 37, 4), 16), ("bf16", 16, 2, 1374, 5, 1, None, 9), ("bf16", 64, 20, 1374, 5, 1, None, 24),
+])
+def test_special_rows_run_in_the_workspace_of_fewer_splits(s3r, dtype, block, views, tpv, special, heads, grid, fewer):  # noqa: F811
+    """Special rows take more key splits than the time alone would ask for; a workspace for the leaner number will do."""
+    splits = special_row_splits(s3r, views, tpv, special, heads, block, dtype, grid)
+    assert splits > fewer
     n_tok = views * tpv
-    q, k, v = (draw(n_tok, heads, "f32", 3200 + i).cuda() for i in range(3))
+    q, k, v = (draw(n_tok, heads, dtype, 3200 + i).cuda() for i in range(3))
     layout = dict(tokens_per_view=tpv, special_per_view=special, grid=grid)
-    need = s3r.speed3r_workspace_bytes_ex(n_tok, heads, 64, block, 4, s3r.S3R_F32, **layout)
+    need = s3r.speed3r_workspace_bytes_ex(n_tok, heads, 64, block, 4, s3r.S3R_F32 if dtype == "f32" else s3r.S3R_BF16, **layout)
     up = lambda x: (x + 255) // 256 * 256   # noqa: E731
     parts = lambda splits: up(splits * views * special * heads * 64 * 4) + up(splits * views * special * heads * 4)   # noqa: E731
     out = {}
@@ -271,7 +272,7 @@ def test_fp32_special_rows_run_in_the_workspace_of_fewer_splits(s3r, block, view
     a, b = out.values()
     rows = torch.arange(n_tok, device="cuda") % tpv < special
     assert torch.equal(a[~rows], b[~rows])
-    assert_close(to_host_f32(a[rows]), to_host_f32(b[rows]), TOL["f32"], "special rows in more and in fewer splits")
+    assert_close(to_host_f32(a[rows]), to_host_f32(b[rows]), TOL[dtype], "special rows in more and in fewer splits")
     with pytest.raises(s3r.Speed3rError):
         s3r.speed3r_sparse_global_attn_ex(q, k, v, torch.empty_like(q), block, 4,
                                           workspace=torch.empty(n_bytes - 256, dtype=torch.uint8, device="cuda"), **layout)
