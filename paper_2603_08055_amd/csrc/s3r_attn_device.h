@@ -9,6 +9,8 @@ namespace s3r {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kRescaleSlack = 8.0f;
+// A lane's probabilities of a unit add up to more than this if one of them is above 2^kRescaleSlack (rounded to bf16).
+constexpr float kMaxUnitSum = 255.0f;
 constexpr int kUnitKeys = 64;
 constexpr int kUnitElems = kUnitKeys * 64;  // bf16 elements of one K (or V) unit: 8 KiB
 

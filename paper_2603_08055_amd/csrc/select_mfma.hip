@@ -35,7 +35,7 @@
 //
 // Softmax.  The running row maximum is only raised when a unit exceeds it by more than
 // kRescaleSlack (log2 units), so the rescale of the output accumulators is skipped for almost every
-// unit; probabilities then range up to 2^kRescaleSlack, which fp32 sums and bf16 operands carry as
+// unit, and so is the search for a unit's maximum (see softmax); probabilities then range up to 2^kRescaleSlack, which fp32 sums and bf16 operands carry as
 // well as values below 1, and the final normalisation uses the same maximum: plain softmax.
 #include "s3r_device.h"
 #include "s3r_attn_device.h"
@@ -361,7 +361,6 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
     float m_run = -1e30f;
-    float m_lim = -1e30f + kRescaleSlack;      // what a unit's largest logit must exceed to raise m_run
     float l_run = 0.f;
 
     // how many of unit w's 64 keys exist, 64 or more: all (wave-uniform)
@@ -398,9 +397,6 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         return first_keys(unit_left(unit_of(s)));
     };
 
-    float lowest = -INFINITY;  // where the maxima start; the compiler takes two scores per v_max3 if it does not know the value
-    asm("" : "+v"(lowest));
-    lowest = fmaxf(lowest, lowest);
     floatx16 sacc[2];
     bf16x8 pb[4];  // probabilities of one unit as MFMA operands
     bf16x8 pl[F32 ? 4 : 1];  // F32: their lo parts
@@ -427,7 +423,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     };
     // keys past the end of a block or of the sequence do not exist
     auto mask_scores = [&](unsigned long long vmask) __attribute__((always_inline)) {
-        asm volatile("" ::: "memory");    // keep this rare path a real branch
+        asm volatile("" : "+s"(vmask)::"memory");  // keep this rare path a real branch, and all of it in there
         // In every run of 16 keys the first n exist; n compared with constants, because a bit test per register would
         // have its 32 masks held in registers all through the loop (54 registers).  Runs that are whole are passed over.
 #pragma unroll
@@ -442,15 +438,27 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
             }
         }
     };
-    // The running maximum after a unit whose largest score (per lane) is mx.  The two lanes of a query look at their own
-    // halves of the unit; they exchange them only when either has to raise the maximum (rare after the first unit).
-    auto raise_max = [&](float mx) __attribute__((always_inline)) {
-        if (__builtin_expect(__any(mx * scale_log2 > m_lim), 0)) {
-            const float m_tile = max_with_other_half(mx) * scale_log2;
+    // The running maximum, raised only when the unit exceeds it by more than the slack.  The two lanes of a query look at
+    // their own halves of the unit; they exchange them only when either has to raise the maximum.
+    // looks: see softmax below; a raise has the coming units looked at as well (the first unit's does not count).
+    constexpr int kFirstLooks = 4, kLooks = 64;
+    int looks = kFirstLooks;
+    auto look_at_max = [&]() __attribute__((always_inline)) {
+        asm volatile("" ::: "memory");  // a real branch, taken or not as one
+        float lowest = -INFINITY;  // the compiler takes two scores per v_max3 if it does not know the value
+        asm("" : "+v"(lowest));
+        float mx[2] = {lowest, lowest};  // two chains of v_max3
+#pragma unroll
+        for (int mt = 0; mt < NMT; ++mt)
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) mx[mt] = fmaxf(fmaxf(mx[mt], sacc[mt][r]), sacc[mt][r + 1]);
+        const float mx_own = fmaxf(mx[0], mx[1]), m_lim = m_run + kRescaleSlack;
+        if (__builtin_expect(__any(mx_own * scale_log2 > m_lim), 0)) {
+            const float m_tile = max_with_other_half(mx_own) * scale_log2;
             const float m_new = m_tile > m_lim ? m_tile : m_run;
             const float alpha = fast_exp2(m_run - m_new);
             m_run = m_new;
-            m_lim = m_new + kRescaleSlack;
+            looks = looks == kFirstLooks ? looks : kLooks;
             l_run *= alpha;
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt)
@@ -458,15 +466,8 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
                 for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
         }
     };
-    // online softmax of sacc[X] -> pb[X]
-    auto softmax = [&](unsigned long long vmask) __attribute__((always_inline)) {
-        if (vmask != ~0ull) mask_scores(vmask);
-        float mx[2] = {lowest, lowest};  // two chains of v_max3
-#pragma unroll
-        for (int mt = 0; mt < NMT; ++mt)
-#pragma unroll
-            for (int r = 0; r < 16; r += 2) mx[mt] = fmaxf(fmaxf(mx[mt], sacc[mt][r]), sacc[mt][r + 1]);
-        raise_max(fmaxf(mx[0], mx[1]));
+    // exp2(sacc - m_run) -> pb; returns their sum over the lane's keys
+    auto probabilities = [&]() __attribute__((always_inline)) -> float {
         // The row sum adds the probabilities as the MFMA will see them (rounded to bf16), two per
         // v_dot2_f32_bf16 with a vector of ones: half the instructions of fp32 adds, and numerator and
         // denominator of the softmax then carry the same rounding.
@@ -487,22 +488,57 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
                     pb[v][i] = static_cast<bf16_t>(p);
                     pl[v][i] = static_cast<bf16_t>(p - static_cast<float>(pb[v][i]));
                 }
-            l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
-            return;
+            return (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
         }
+        // Groups of eight scores: exponents, then packs; the sums when all are done.  (Fenced: in the compiler's own order, two
+        // exponents at a time with their pack and sum behind them, the dense kernel takes 6 % longer; groups of 4 and 16 are
+        // within 1 %, packs and sums laid between the exponents 1 to 5 % longer.)
         const bf16x2 ones = {static_cast<bf16_t>(1.f), static_cast<bf16_t>(1.f)};
+#pragma unroll
+        for (int v = 0; v < 2 * NMT; ++v) {
+            const int mt = v >> 1, r0 = 8 * (v & 1);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sacc[mt][r0 + i] = sacc[mt][r0 + i] * scale_log2 - m_run;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sacc[mt][r0 + i] = fast_exp2(sacc[mt][r0 + i]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) pb[v][i] = static_cast<bf16_t>(sacc[mt][r0 + i]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int v = 0; v < 2 * NMT; ++v)
 #pragma unroll
-            for (int i = 0; i < 8; i += 2) {
-                const int mt = v >> 1, r = 8 * (v & 1) + i;
-                const bf16x2 pr = {static_cast<bf16_t>(fast_exp2(sacc[mt][r] * scale_log2 - m_run)),
-                                   static_cast<bf16_t>(fast_exp2(sacc[mt][r + 1] * scale_log2 - m_run))};
-                lsum[(i >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum[(i >> 1) & 3], false);
-                pb[v][i] = pr[0];
-                pb[v][i + 1] = pr[1];
+            for (int i = 0; i < 4; ++i) {
+                const bf16x2 pr = {pb[v][2 * i], pb[v][2 * i + 1]};
+                lsum[i] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum[i], false);
             }
-        l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
+        return (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
+    };
+    // Scores and online softmax of the unit whose K sits in `ks` -> pb.  A unit's maximum is only there to see whether it
+    // exceeds the running one by more than the slack, which is rare, and the row sum shows that as well: one probability above
+    // 2^slack makes it larger than 2^slack.  So the probabilities are formed against the running maximum as it stands (the
+    // first ones while the matrix pipe still adds up the second tile of scores), and a unit whose sum comes out too large is
+    // done once more with a look at its maximum: the same results with 16 of 119 vector instructions fewer (16 views dense
+    // 2.14 -> 2.04 ms, in bf16 where the loop is short of vector slots; fp32 always looks).
+    // Where units keep raising the maximum (outlier keys: 23 times in 256 units) doing them twice costs more than the looks
+    // (60 views, blocks of 128, top-128: 6.35 ms with looks only, 6.67 without): so kLooks units are looked at first
+    // after a raise, and the first kFirstLooks ones, which show such data early.
+    auto softmax = [&](const bf16_t *ks, unsigned long long vmask) __attribute__((always_inline)) {
+        float sum;
+        for (;;) {  // once; twice if the sum is too large
+            scores(ks);
+            if (__builtin_expect(vmask != ~0ull, 0)) mask_scores(vmask);
+            if (F32 || __builtin_expect(looks > 0, 0)) look_at_max();
+            sum = probabilities();
+            if (F32 || (__builtin_expect(looks <= 0, 1) && __builtin_expect(!__any(!(sum <= kMaxUnitSum)), 1))) break;
+            --looks;
+            asm volatile("" : "+s"(looks));  // (one copy of the code above, whether the maximum is looked at or not)
+            if (looks >= 0) break;
+            looks = kLooks;
+        }
+        l_run += sum;
     };
     // O^T += V^T P^T for the unit whose V sits in `vs`
     // (pieces: V tiles of blocks of 16 keys, see small_v_piece)
@@ -589,8 +625,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
             if (!mine) continue;
             const unsigned long long vmask = unit_mask_of(j);
             if (vmask == 0ull) continue;
-            scores(&ring[stage][0]);
-            softmax(vmask);
+            softmax(&ring[stage][0], vmask);
             accumulate(&ring[stage][kUnitElems], std::false_type{});
         }
     } else {
@@ -612,8 +647,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         const unsigned long long vmask = unit_mask(s);
         if ((KS == 1 ? vmask : vmask >> (32 * kh)) == 0ull) continue;  // second half of a short last block
         // (a key half: the second 32-row tile of K, the second two key steps of V)
-        scores(&ring[stage][kh * kRowTileElems]);
-        softmax(vmask);
+        softmax(&ring[stage][kh * kRowTileElems], vmask);
         const bf16_t *vs = &ring[stage][kUnitElems + kh * kRowTileElems];
         if (SMALL && bpu_shift == 2 && s + u_begin < n_units1) accumulate(vs, std::integral_constant<bool, SMALL>{});  // wave-uniform
         else accumulate(vs, std::false_type{});

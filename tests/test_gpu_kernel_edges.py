@@ -337,6 +337,32 @@ def test_small_weights_beside_a_large_one_stay_in_the_sum_of_the_sweep(s3r):  # 
     assert np.abs(o_comp / want - 1.0).max() < 2e-6
 
 
+# (unit, rise): in the first four units the maximum is looked at, afterwards a unit is done again; then looked at for 64 units
+@pytest.mark.parametrize("block", [0, 64, 128])   # dense attention; long rows; blocks of 128
+@pytest.mark.parametrize("rises", [[(2, 9)], [(4, 7.9)], [(4, 8.1)], [(5, 60), (6, 69)], [(7, 300)], [(4, 20), (68, 29), (80, 40), (150, 52)]])
+def test_units_done_again_when_the_maximum_rises(s3r, block, rises):  # noqa: F811
+    """Keys of ever larger weight for the even queries only (the odd ones of a wave keep their maximum), in units whose
+    probabilities were formed against the maximum before; the last unit is short."""
+    n_units = max(rises[-1][0] + 3, 130 if block == 64 else 0) // 2 * 2 + 2
+    n_tok = 64 * n_units - 9
+    wl = workloads.Workload(f"again_{block}_{rises[0][0]}", 1, n_tok, 2, 64, "bf16", max(block, 64), 1, 110, "normal")
+    q, k, v = workloads.make_inputs(wl)
+    q[:, :, 0] = 8.0
+    q[1::2, :, 0] = 0.0
+    k[:, :, 0] = 0.0
+    for unit, rise in rises:
+        k[64 * unit + 11:64 * (unit + 1):19, :, 0] = rise * math.log(2.0)
+    out = torch.full_like(q, float("nan")).cuda()
+    if block == 0:
+        s3r.speed3r_dense_attn(q.cuda(), k.cuda(), v.cuda(), out)
+    else:
+        n_blk = -(-n_tok // block)
+        idx = torch.arange(n_blk, dtype=torch.int32, device="cuda").expand(2, n_blk, n_blk).contiguous()
+        s3r.speed3r_select_attn(q.cuda(), k.cuda(), v.cuda(), idx, out, block)
+    p = torch.softmax(torch.matmul(q.double().transpose(0, 1), k.double().permute(1, 2, 0)) / 8.0, dim=-1)
+    assert_close(out.float().cpu().numpy(), torch.matmul(p, v.double().transpose(0, 1)).transpose(0, 1).numpy(), TOL["bf16"], wl.name)
+
+
 # one pair of waves: edge iterations only; full ones.  Two pairs: few query blocks, edge and full; long rows on long sequences
 @pytest.mark.parametrize("n_blk,kk", [(8, 3), (513, 8), (9, 8), (40, 24), (3000, 48)])
 def test_probabilities_waiting_while_the_maximum_rises(s3r, n_blk, kk):  # noqa: F811
