@@ -64,12 +64,15 @@ namespace s3r {
 //         real one does (same work mapping, ring, waits and barriers) but does no arithmetic on them; it
 //         writes its Q rows to `out`, so Q is read and `out` written as well.  Its run time is what the data
 //         movement of the selection stage costs by itself.
-// F32   : fp32 q, gate, out and o_sel (the pointers below are then float pointers in disguise), K/V tiles in bf16
-//         parts ([hi tiles | lo tiles | K only: lo2 tiles], lo_off elements apart), x = hi + lo (+ lo2).  Scores
-//         take Q and K in three parts each and the six products whose weight is above 2^-24 (a logit's error
-//         enters the result in absolute terms, so it must not grow with the size of the entries); P.V takes
-//         two parts each, hi.hi + hi.lo + lo.hi (2^-17 relative, of values in [0, 1] times V).  All on the
-//         bf16 matrix pipe with fp32 accumulation: fp32-grade results at nine MFMAs per tile step in place of two.
+// F32   : fp32 q, gate, out and o_sel (the pointers below are then float pointers in disguise), K/V tiles in parts
+//         ([hi tiles | lo tiles | K only: see below], lo_off elements apart).  P.V takes two bf16 parts each, hi.hi + hi.lo +
+//         lo.hi (2^-17 relative, of values in [0, 1] times V).  Scores, whose error enters the result in absolute terms
+//         and must not grow with the size of the entries, take K and Q either
+//           in two fp16 parts with a power of two in front (HALF, see half_parts; the third array holds the factors of K's
+//           blocks) and three products, the small ones first, or
+//           in three bf16 parts and the six products whose weight is above 2^-24 (SMALL: over the tiles that
+//           select_direct.hip reads, see f32_key_parts).
+//         All on the 16-bit matrix pipe with fp32 accumulation: fp32-grade results at six (nine) MFMAs per tile step in place of two.
 // KS    : 2: twice the waves, the second half of them on the second 32 keys of every unit for the same query rows, with a
 //         softmax of their own; the two partial results (m, l, O) of a row are added up through LDS at the end.  For
 //         fp32 selection with blocks of 64: two workgroups of two waves were all that an 80 KiB ring lets a CU
@@ -88,7 +91,8 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
 {
     constexpr int NW = QW * KS;        // waves per workgroup
     constexpr int NMT = 2 / KS;        // 32-key tiles of a unit that a wave works on
-    constexpr int NCH = F32 ? 40 : 16; // 1 KiB chunks of a unit: 8 K + 8 V (F32: then 8 K lo + 8 V lo + 8 K lo2)
+    constexpr bool HALF = F32 && !SMALL;
+    constexpr int NCH = HALF ? 32 : F32 ? 40 : 16; // 1 KiB chunks of a unit: 8 K + 8 V (F32: then 8 K lo + 8 V lo, and 8 K lo2 unless HALF)
     constexpr int CPW = NCH / NW;      // ... issued by each wave
     constexpr int D = NS - 1;          // units in flight
     static_assert(NCH % NW == 0 && 16 % NW == 0, "waves must split the chunks of a unit evenly");
@@ -96,8 +100,8 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     static_assert(!SMALL || DENSE, "selection with small blocks: select_direct.hip");
     static_assert(KS == 1 || (KS == 2 && !DENSE && !PAIR && !PROBE), "key halves: plain selection");
     static_assert(!F32 || (!PAIR && !PROBE), "operand parts: the plain and the dense kernels");
-    // [stage][K 8 KiB | V 8 KiB] (F32: then [K lo 8 KiB | V lo 8 KiB | K lo2 8 KiB])
-    constexpr int kStageParts = F32 ? 5 : 2;
+    // [stage][K 8 KiB | V 8 KiB] (F32: then [K lo 8 KiB | V lo 8 KiB], and [K lo2 8 KiB] unless HALF)
+    constexpr int kStageParts = HALF ? 4 : F32 ? 5 : 2;
     __shared__ __attribute__((aligned(1024))) bf16_t ring[NS][kStageParts * kUnitElems];
     constexpr int kLoElems = 2 * kUnitElems;  // from a hi part of a stage to its lo part, and on to K's lo2 part
 
@@ -151,30 +155,43 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     // each step anyway (two stages), and a plain early load of Q is 1 % faster there, except on long index
     // rows (ASMQ chooses).
     bf16x8 qb[4];
-    bf16x8 ql[F32 ? 4 : 1], ql2[F32 ? 4 : 1];   // F32: the lo and lo2 parts of Q
+    half8 qh[HALF ? 4 : 1], qhl[HALF ? 4 : 1];  // HALF: the parts of Q
+    float scale_q = scale_log2;                 // HALF: scale over the power of two in front of Q
+    bf16x8 ql[F32 && !HALF ? 4 : 1], ql2[F32 && !HALF ? 4 : 1];   // F32 otherwise: qb and the lo and lo2 parts of Q
     constexpr bool kAsmQ = ASMQ && !F32;
     if constexpr (F32) {
         const float *qf = reinterpret_cast<const float *>(q);
+        float f[4][8], top = 0.f;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            float f[8];
             if (row_valid) {
                 const int64_t qo = EXTRA ? x.in.at(trow, h, heads) : (trow * heads + h) * 64;
                 const floatx4 a = *reinterpret_cast<const floatx4 *>(qf + qo + 16 * s + 8 * g);
                 const floatx4 b = *reinterpret_cast<const floatx4 *>(qf + qo + 16 * s + 8 * g + 4);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { f[i] = a[i]; f[4 + i] = b[i]; }
+                for (int i = 0; i < 4; ++i) { f[s][i] = a[i]; f[s][4 + i] = b[i]; }
             } else {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) f[i] = 0.f;
+                for (int i = 0; i < 8; ++i) f[s][i] = 0.f;
             }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                qb[s][i] = static_cast<bf16_t>(f[i]);
-                const float r1 = f[i] - static_cast<float>(qb[s][i]);
-                ql[s][i] = static_cast<bf16_t>(r1);
-                ql2[s][i] = static_cast<bf16_t>(r1 - static_cast<float>(ql[s][i]));
-            }
+            for (int i = 0; i < 8; ++i) top = fmaxf(top, fabsf(f[s][i]));
+        }
+        if constexpr (HALF) {
+            const int e = half_exponent(max_with_other_half(top));
+            scale_q = ldexpf(scale_log2, -e);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) half_parts(f[s], e, qh[s], qhl[s]);
+        } else {
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    qb[s][i] = static_cast<bf16_t>(f[s][i]);
+                    const float r1 = f[s][i] - static_cast<float>(qb[s][i]);
+                    ql[s][i] = static_cast<bf16_t>(r1);
+                    ql2[s][i] = static_cast<bf16_t>(r1 - static_cast<float>(ql[s][i]));
+                }
         }
     } else if constexpr (!kAsmQ) {
 #pragma unroll
@@ -333,7 +350,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
             return;
         }
         const int w = unit_of(s);
-        if constexpr (F32) {  // chunk = 16 * part + (0..7: K, 8..15: V), part 0 = hi, 1 = lo, 2 = lo2 (K only)
+        if constexpr (F32) {  // chunk = 16 * part + (0..7: K, 8..15: V), part 0 = hi, 1 = lo (2 = lo2, K only)
             const bool second = DENSE && w >= n_units1;
             const int64_t unit = static_cast<int64_t>(second ? w - n_units1 : w) * kUnitElems;
             const int64_t lo = second ? lo_off2 : lo_off;
@@ -397,6 +414,25 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         return first_keys(unit_left(unit_of(s)));
     };
 
+    // HALF: the powers of two in front of the K blocks of 64 steps, one step per lane, and with the query's own and the softmax
+    // scale what the scores of a unit are to be multiplied by.
+    float k_factor = 1.f, unit_scale = scale_log2;
+    auto load_factors = [&](int s) {  // of steps s .. s + 63
+        const float *fk = reinterpret_cast<const float *>(kb + 2 * lo_off) + static_cast<int64_t>(h) * n_blk;
+        const int step = s + lane < n_steps ? s + lane : n_steps - 1;
+        if constexpr (DENSE) {
+            const int u = step + u_begin;
+            k_factor = u < n_units1 ? fk[u >> upb_shift]
+                                    : reinterpret_cast<const float *>(kb2 + 2 * lo_off2)[static_cast<int64_t>(h) * n_units2 + (u - n_units1)];
+        } else {
+            k_factor = fk[sel_at(sel, step >> upb_shift)];
+        }
+        asm volatile("" : "+v"(k_factor));  // (waited for in here, not in front of its use in every step)
+    };
+    auto set_unit_scale = [&](int s) {  // (never 0: a key that does not exist has a score of -inf)
+        unit_scale = fmaxf(scale_q * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(k_factor), s & 63)), 1e-37f);
+    };
+    auto score_scale = [&]() -> float { return HALF ? unit_scale : scale_log2; };
     floatx16 sacc[2];
     bf16x8 pb[4];  // probabilities of one unit as MFMA operands
     bf16x8 pl[F32 ? 4 : 1];  // F32: their lo parts
@@ -408,16 +444,31 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
 #pragma unroll
         for (int i = 0; i < 4 * NMT; ++i) {
             const int mt = DENSE ? i >> 2 : i & (NMT - 1), c = DENSE ? i & 3 : i / NMT;
-            const bf16x8 ka = *reinterpret_cast<const bf16x8 *>(ks + ((mt * 4 + c) * 64 + lane) * 8);
+            const bf16_t *at = ks + ((mt * 4 + c) * 64 + lane) * 8;
+            if constexpr (HALF) {  // the small products
+                const half8 kh = *reinterpret_cast<const half8 *>(at), kl = *reinterpret_cast<const half8 *>(at + kLoElems);
+                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh, qhl[c], c == 0 ? zero16 : sacc[mt], 0, 0, 0);
+                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl, qh[c], sacc[mt], 0, 0, 0);
+                continue;
+            }
+            const bf16x8 ka = *reinterpret_cast<const bf16x8 *>(at);
             sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[c], c == 0 ? zero16 : sacc[mt], 0, 0, 0);
             if constexpr (F32) {
-                const bf16x8 kl = *reinterpret_cast<const bf16x8 *>(ks + kLoElems + ((mt * 4 + c) * 64 + lane) * 8);
-                const bf16x8 kl2 = *reinterpret_cast<const bf16x8 *>(ks + 2 * kLoElems + ((mt * 4 + c) * 64 + lane) * 8);
+                const bf16x8 kl = *reinterpret_cast<const bf16x8 *>(at + kLoElems);
+                const bf16x8 kl2 = *reinterpret_cast<const bf16x8 *>(at + 2 * kLoElems);
                 sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, ql[c], sacc[mt], 0, 0, 0);
                 sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qb[c], sacc[mt], 0, 0, 0);
                 sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, ql2[c], sacc[mt], 0, 0, 0);
                 sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, ql[c], sacc[mt], 0, 0, 0);
                 sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl2, qb[c], sacc[mt], 0, 0, 0);
+            }
+        }
+        if constexpr (HALF) {
+#pragma unroll
+            for (int i = 0; i < 4 * NMT; ++i) {
+                const int mt = i >> 2, c = i & 3;
+                const half8 kh = *reinterpret_cast<const half8 *>(ks + ((mt * 4 + c) * 64 + lane) * 8);
+                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh, qh[c], sacc[mt], 0, 0, 0);
             }
         }
     };
@@ -452,9 +503,10 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
             for (int r = 0; r < 16; r += 2) mx[mt] = fmaxf(fmaxf(mx[mt], sacc[mt][r]), sacc[mt][r + 1]);
-        const float mx_own = fmaxf(mx[0], mx[1]), m_lim = m_run + kRescaleSlack;
-        if (__builtin_expect(__any(mx_own * scale_log2 > m_lim), 0)) {
-            const float m_tile = max_with_other_half(mx_own) * scale_log2;
+        const float mx_own = fmaxf(mx[0], mx[1]) * score_scale();
+        const float m_lim = m_run + kRescaleSlack;
+        if (__builtin_expect(__any(mx_own > m_lim), 0)) {
+            const float m_tile = max_with_other_half(mx_own);
             const float m_new = m_tile > m_lim ? m_tile : m_run;
             const float alpha = fast_exp2(m_run - m_new);
             m_run = m_new;
@@ -483,7 +535,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const int mt = v >> 1, r = 8 * (v & 1) + i;
-                    const float p = fast_exp2(sacc[mt][r] * scale_log2 - m_run);
+                    const float p = fast_exp2(sacc[mt][r] * score_scale() - m_run);
                     lsum[i & 3] += p;
                     pb[v][i] = static_cast<bf16_t>(p);
                     pl[v][i] = static_cast<bf16_t>(p - static_cast<float>(pb[v][i]));
@@ -644,6 +696,10 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         if constexpr (PROBE) continue;
         if constexpr (SMALL)
             if ((s & 63) == 0) load_masks(s);
+        if constexpr (HALF) {
+            if ((s & 63) == 0) load_factors(s);
+            set_unit_scale(s);
+        }
         const unsigned long long vmask = unit_mask(s);
         if ((KS == 1 ? vmask : vmask >> (32 * kh)) == 0ull) continue;  // second half of a short last block
         // (a key half: the second 32-row tile of K, the second two key steps of V)

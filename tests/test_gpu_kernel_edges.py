@@ -337,6 +337,40 @@ def test_small_weights_beside_a_large_one_stay_in_the_sum_of_the_sweep(s3r):  # 
     assert np.abs(o_comp / want - 1.0).max() < 2e-6
 
 
+@pytest.mark.parametrize("block,n_tok", [(0, 64 * 3 + 7), (0, 64 * 67), (64, 64 * 5 + 1), (64, 64 * 5 + 33), (64, 64), (128, 128 * 3 + 70), (128, 128 * 2 + 64)])
+@pytest.mark.parametrize("spread", ["none", "keys", "channels", "blocks", "tiny queries", "zero blocks"])
+def test_fp32_keys_of_all_sizes(s3r, oracle, block, n_tok, spread):  # noqa: F811
+    """K in fp16 parts with one power of two for a block, Q with one for a row: entries of very different sizes in a row, a
+    block and from block to block, the other operand as much smaller where a channel is large.  More than 64 units: the
+    factors are read 64 at a time; few keys in the last unit: one key half without work."""
+    heads = 2
+    wl = workloads.Workload(f"f32_{spread}_{block}_{n_tok}", 1, n_tok, heads, 64, "f32", max(block, 64), 1, 111, "normal")
+    q, k, v = workloads.make_inputs(wl)
+    gen = torch.Generator().manual_seed(112)
+    if spread == "keys":        # logits stay ordinary: large keys have small entries where queries are not 0
+        k *= torch.exp2(torch.randint(-12, 1, (n_tok, heads, 1), generator=gen).float())
+    elif spread == "channels":
+        size = torch.exp2(torch.randint(-9, 10, (1, heads, 64), generator=gen).float())
+        q, k = q / size, k * size
+    elif spread == "blocks":    # every block of keys of its own size, down to 2^-60
+        k *= torch.exp2(-20.0 * ((torch.arange(n_tok) // max(block, 64)) % 4).float())[:, None, None]
+    elif spread == "tiny queries":
+        q, k = q * 1e-18, k * 1e18
+    elif spread == "zero blocks":
+        k[:40] = 0.0
+        k[-3:] = 0.0
+        q[1::3] = 0.0
+    out = torch.full_like(q, float("nan")).cuda()
+    if block == 0:
+        s3r.speed3r_dense_attn(q.cuda(), k.cuda(), v.cuda(), out)
+    else:
+        n_blk = -(-n_tok // block)
+        idx = torch.arange(n_blk, dtype=torch.int32, device="cuda").expand(heads, n_blk, n_blk).contiguous()
+        s3r.speed3r_select_attn(q.cuda(), k.cuda(), v.cuda(), idx, out, block)
+    ref = oracle.dense_attn(*(to_host_f32(x) for x in (q, k, v)), 0.125)
+    assert_close(to_host_f32(out), ref, TOL["f32"], wl.name)
+
+
 # (unit, rise): in the first four units the maximum is looked at, afterwards a unit is done again; then looked at for 64 units
 @pytest.mark.parametrize("block", [0, 64, 128])   # dense attention; long rows; blocks of 128
 @pytest.mark.parametrize("rises", [[(2, 9)], [(4, 7.9)], [(4, 8.1)], [(5, 60), (6, 69)], [(7, 300)], [(4, 20), (68, 29), (80, 40), (150, 52)]])
