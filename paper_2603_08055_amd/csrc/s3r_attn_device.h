@@ -42,6 +42,16 @@ __device__ __forceinline__ void lds_dma_16_x1(const void *base, unsigned voff, u
                  : "memory", "m0");
 }
 
+// Two consecutive 1 KiB chunks, see lds_dma_16_x4.
+__device__ __forceinline__ void lds_dma_16_x2(const void *base, unsigned voff, unsigned lds_byte)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, %1\n\t"
+                 "global_load_lds_dwordx4 %0, %1 offset:1024"
+                 ::"v"(voff), "s"(base), "s"(lds_byte)
+                 : "memory", "m0");
+}
+
 // Four consecutive 1 KiB chunks of a contiguous run with a wave-uniform start address: lane L's 16 bytes of chunk
 // c come from base + voff + c KiB (voff = 16 L, or 16 L + 4096 for the second half of an 8 KiB run: the
 // constant offset of the instruction reaches 4095 bytes) and land at LDS byte lds_byte + c KiB + 16 L: the

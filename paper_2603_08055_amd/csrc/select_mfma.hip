@@ -100,10 +100,13 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     static_assert(!SMALL || DENSE, "selection with small blocks: select_direct.hip");
     static_assert(KS == 1 || (KS == 2 && !DENSE && !PAIR && !PROBE), "key halves: plain selection");
     static_assert(!F32 || (!PAIR && !PROBE), "operand parts: the plain and the dense kernels");
-    // [stage][K 8 KiB | V 8 KiB] (F32: then [K lo 8 KiB | V lo 8 KiB], and [K lo2 8 KiB] unless HALF)
-    constexpr int kStageParts = HALF ? 4 : F32 ? 5 : 2;
-    __shared__ __attribute__((aligned(1024))) bf16_t ring[NS][kStageParts * kUnitElems];
-    constexpr int kLoElems = 2 * kUnitElems;  // from a hi part of a stage to its lo part, and on to K's lo2 part
+    // [stage][K 8 KiB | V 8 KiB] (F32: then [K lo 8 KiB | V lo 8 KiB | K lo2 8 KiB]).  HALF: [stage][K | K lo] and, of one unit
+    // only, [V | V lo] behind them; with KS = 2 one stage of K as well.
+    constexpr int kStageParts = F32 && !HALF ? 5 : 2;
+    static_assert(!HALF || NS == 2, "its own stages");
+    constexpr int kKeyStages = KS == 2 ? 1 : 2;  // HALF
+    __shared__ __attribute__((aligned(1024))) bf16_t ring[HALF ? kKeyStages + 1 : NS][kStageParts * kUnitElems];
+    constexpr int kLoElems = HALF ? kUnitElems : 2 * kUnitElems;  // from a hi part of a stage to its lo part (and on to K's lo2 part)
 
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -350,19 +353,6 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
             return;
         }
         const int w = unit_of(s);
-        if constexpr (F32) {  // chunk = 16 * part + (0..7: K, 8..15: V), part 0 = hi, 1 = lo (2 = lo2, K only)
-            const bool second = DENSE && w >= n_units1;
-            const int64_t unit = static_cast<int64_t>(second ? w - n_units1 : w) * kUnitElems;
-            const int64_t lo = second ? lo_off2 : lo_off;
-            static_assert(!F32 || NW == 4, "chunk c * 4 + wave: its kind and part are those of c * 4, known at compile time");
-#pragma unroll
-            for (int c = 0; c < CPW; ++c) {
-                const int base = c * NW;
-                const bf16_t *arr = (base & 8) ? (second ? vb2_h : vb_h) : (second ? kb2_h : kb_h);
-                lds_dma_16_x1(arr + unit + (base >> 4) * lo + ((base & 7) + wave) * 512, lane * 16, stage_byte + (base + wave) * 1024);
-            }
-            return;
-        }
         // all chunks of a wave are of one kind (K or V) here: runs of 4 KiB with a wave-uniform start
         static_assert(SMALL || F32 || CPW == 4 || CPW == 8, "a wave's chunks must be all K or all V");
         const bool second = DENSE && w >= n_units1;
@@ -370,6 +360,18 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         const unsigned dst = stage_byte + wave * (CPW * 1024);
         lds_dma_16_x4(unit, lane * 16, dst);
         if constexpr (CPW == 8) lds_dma_16_x4(unit, lane * 16 + 4096, dst + 4096);
+    };
+
+    // HALF: this wave's share of K (or V) of step s -> LDS stage `stage`: four 1 KiB chunks, two of either part
+    auto issue_half = [&](int s, int stage, bool is_k) {
+        static_assert(!HALF || NW == 4, "two chunks of a part for each wave");
+        const int w = unit_of(s);
+        const bool second = DENSE && w >= n_units1;
+        const int64_t unit = static_cast<int64_t>(second ? w - n_units1 : w) * kUnitElems, lo = second ? lo_off2 : lo_off;
+        const bf16_t *src = (is_k ? (second ? kb2_h : kb_h) : (second ? vb2_h : vb_h)) + unit + wave * 1024;
+        const unsigned dst = ring_base + static_cast<unsigned>(stage) * (kStageParts * kUnitElems * 2) + wave * 2048;
+        lds_dma_16_x2(src, lane * 16, dst);
+        lds_dma_16_x2(src + lo, lane * 16, dst + kUnitElems * 2);
     };
 
     floatx16 oacc[2];
@@ -680,6 +682,31 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
             softmax(&ring[stage][0], vmask);
             accumulate(&ring[stage][kUnitElems], std::false_type{});
         }
+    } else if constexpr (HALF) {
+        // V has one stage: requested when every wave is done with the unit before, waited for when its probabilities are there,
+        // under the scores and the softmax.  So has K in the kernel for blocks of 64, requested under P.V of the unit before.
+        // Fewer requests are on their way per workgroup, but 48 KiB let a CU hold three of them (by registers four for blocks of
+        // 64 with 32 KiB), where two whole stages leave room for two, and it is the waves that hide each other's chains of
+        // products here (matrix pipe 39 % and vector ALU 42 % busy with two waves on a SIMD).  A call on 30 views, top-16, blocks of
+        // 64: 854 us with two whole stages, 775 with one of V, 761 with one of both; 8 x 8 windows 1754, 1585, 1547; blocks of 128
+        // (30 views, top-32, outlier keys) 2307 and 2055; dense, 5496 rows, 392 and 364.
+        if (n_steps > 0) issue_half(0, 0, true);
+        for (int s = 0; s < n_steps; ++s) {
+            wait_vmcnt<0>();  // K(s)
+            lds_barrier();    // everybody's K(s), and everybody is done with V(s - 1) (two K stages: and with K(s - 1))
+            issue_half(s, kKeyStages, false);
+            if (kKeyStages == 2 && s + 1 < n_steps) issue_half(s + 1, (s + 1) & 1, true);
+            if ((s & 63) == 0) load_factors(s);
+            set_unit_scale(s);
+            const unsigned long long vmask = unit_mask(s);
+            const bool any = (KS == 1 ? vmask : vmask >> (32 * kh)) != 0ull;  // (none: second half of a short last block)
+            // (a key half: the second 32-row tile of K, the second two key steps of V)
+            if (any) softmax(&ring[kKeyStages == 2 ? s & 1 : 0][kh * kRowTileElems], vmask);
+            if (kKeyStages == 2 && s + 1 < n_steps) wait_vmcnt<4>(); else wait_vmcnt<0>();  // V(s); K(s + 1) may be on its way
+            lds_barrier();    // everybody's V(s), and everybody is done with the scores of K(s)
+            if (kKeyStages == 1 && s + 1 < n_steps) issue_half(s + 1, 0, true);
+            if (any) accumulate(&ring[kKeyStages][kh * kRowTileElems], std::false_type{});
+        }
     } else {
     for (int s = 0; s < D && s < n_steps; ++s) issue(s, s);  // D < NS: stage = s
     if constexpr (kAsmQ) load_q_dense();
@@ -696,10 +723,6 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         if constexpr (PROBE) continue;
         if constexpr (SMALL)
             if ((s & 63) == 0) load_masks(s);
-        if constexpr (HALF) {
-            if ((s & 63) == 0) load_factors(s);
-            set_unit_scale(s);
-        }
         const unsigned long long vmask = unit_mask(s);
         if ((KS == 1 ? vmask : vmask >> (32 * kh)) == 0ull) continue;  // second half of a short last block
         // (a key half: the second 32-row tile of K, the second two key steps of V)
@@ -876,8 +899,6 @@ hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream)
         if (a.qmap.period != 0 && a.n_tok > 0x7fffffffLL) return hipErrorInvalidValue;
         if (a.idx == nullptr) {
             if (a.n_keys2 > 0 && (a.kb2 == nullptr || a.vb2 == nullptr || a.lo_off2 <= 0)) return hipErrorInvalidValue;
-            // two stages, 80 KiB: two workgroups per CU (three stages and addresses from scratch memory: 8256 rows,
-            // 16 heads 3.95 ms, now 1.15)
             return small ? run_select<4, true, 2, true, true, false, true>(a, stream)
                          : run_select<4, true, 2, false, true, false, true>(a, stream);
         }
