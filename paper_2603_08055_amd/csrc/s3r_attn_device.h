@@ -73,6 +73,108 @@ template <int N> __device__ __forceinline__ void wait_vmcnt()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// ---- merge with the compressed branch and store (eqs. 5, 7, 8) ---------------------------------
+// The end of a selection kernel: out = g o_comp + (1 - g) o_sel for the lane's channels of its row, and o_sel itself
+// where it is wanted.  An MFMA leaves a lane runs of four channels; two lanes of a query exchange halves of two runs (join) and then
+// hold eight channels in a row each, in pairs of runs j = 0 .. NP - 1: 16 bytes per load and store in bf16, half as many of them.
+// All loads are issued before the first value is used (load), where one run after the other waited out a memory latency, and the
+// stores before it, eight times over (2.2 of 10 us of the fp32 kernel on 4 views of 256 rows).
+template <typename IO> struct Io8;
+template <> struct Io8<bf16_t> {
+    bf16x8 x;
+    __device__ __forceinline__ void load(const bf16_t *p) { x = *reinterpret_cast<const bf16x8 *>(p); }
+    __device__ __forceinline__ float get(int i) const { return static_cast<float>(x[i]); }
+    static __device__ __forceinline__ void store(bf16_t *p, const float (&f)[8])
+    {
+        bf16x8 r;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r[i] = static_cast<bf16_t>(f[i]);
+        *reinterpret_cast<bf16x8 *>(p) = r;
+    }
+};
+template <> struct Io8<float> {
+    floatx4 a, b;
+    __device__ __forceinline__ void load(const float *p)
+    {
+        a = *reinterpret_cast<const floatx4 *>(p);
+        b = *reinterpret_cast<const floatx4 *>(p + 4);
+    }
+    __device__ __forceinline__ float get(int i) const { return i < 4 ? a[i & 3] : b[i & 3]; }
+    static __device__ __forceinline__ void store(float *p, const float (&f)[8])
+    {
+        *reinterpret_cast<floatx4 *>(p) = floatx4{f[0], f[1], f[2], f[3]};
+        *reinterpret_cast<floatx4 *>(p + 4) = floatx4{f[4], f[5], f[6], f[7]};
+    }
+};
+
+template <typename IO, int NP> struct MergeRow {
+    const float *oc;   // o_comp of the row, or null: out = o_sel
+    const IO *gate;    // of the row, or null: g = 1/2
+    Io8<float> c[NP];
+    Io8<IO> gl[NP];
+
+    // channel(j): the first of the lane's eight channels of pair j
+    template <typename Channel> __device__ __forceinline__ void load(const float *oc_row, const IO *gate_row, Channel &&channel)
+    {
+        oc = oc_row;
+        gate = gate_row;
+        if (oc != nullptr) {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) c[j].load(oc + channel(j));
+            if (gate != nullptr) {
+#pragma unroll
+                for (int j = 0; j < NP; ++j) gl[j].load(gate + channel(j));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // os[j]: o_sel in these channels
+    template <typename Channel>
+    __device__ __forceinline__ void store(const float (&os)[NP][8], IO *out_row, IO *o_sel_row, Channel &&channel)
+    {
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            float res[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) res[i] = os[j][i];
+            if (oc != nullptr) {
+                float gt[8] = {0.5f, 0.5f, 0.5f, 0.5f, 0.5f, 0.5f, 0.5f, 0.5f};
+                if (gate != nullptr) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) gt[i] = 1.f / (1.f + __expf(-gl[j].get(i)));
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) res[i] = gt[i] * c[j].get(i) + (1.f - gt[i]) * os[j][i];
+            }
+            Io8<IO>::store(out_row + channel(j), res);
+            if (o_sel_row != nullptr) Io8<IO>::store(o_sel_row + channel(j), os[j]);
+        }
+    }
+};
+
+// Runs a and b of a 32x32 MFMA's accumulators, four registers each: the lane's rows 8 r + 4 g .. + 3 and 8 (r + 1) + 4 g .. + 3
+// (g = lane / 32) -> rows 8 (r + g) .. + 7.
+__device__ __forceinline__ void join_runs_32(const float (&a)[4], const float (&b)[4], float (&o)[8])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[e]), __float_as_uint(b[e]), false, false);
+        o[e] = __uint_as_float(x[0]);
+        o[4 + e] = __uint_as_float(x[1]);
+    }
+}
+
+// The same for two 16x16 tiles, rows 4 g .. + 3 of either (g = lane / 16): rows 8 (g / 2) .. + 7 of tile g % 2.
+__device__ __forceinline__ void join_runs_16(const float (&a)[4], const float (&b)[4], float (&o)[8])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[e]), __float_as_uint(b[e]), false, false);
+        o[e] = __uint_as_float(x[0]);
+        o[4 + e] = __uint_as_float(x[1]);
+    }
+}
+
 // Work mapping of the selection kernels: workgroup id mod 8 is its XCD, and each XCD has an L2 of its own.  Neighbouring
 // query blocks share key blocks, so an XCD works on neighbours: on a contiguous eighth of every head's query blocks, all
 // XCDs on the same head at a time, or (whole_heads) on a contiguous eighth of all (head, query block) pairs.

@@ -267,48 +267,33 @@ __global__ __launch_bounds__(256, OCC) void select_direct_kernel(
         }
     }
 
+    typedef typename std::conditional<F32, float, bf16_t>::type io_t;
+    const int64_t o = (trow * heads + h) * 64;
+    constexpr int kPairs = NT * NR / 8;  // runs of four channels, two by two
+    auto channel = [&](int j) -> int { return B == 16 ? 16 * (2 * j + (g & 1)) + 8 * (g >> 1) : 16 * j + 8 * g; };
+    MergeRow<io_t, kPairs> merge;
+    merge.load(o_comp_tok != nullptr ? o_comp_tok + ((row_valid ? t : set * B) * heads + h) * 64
+               : o_comp != nullptr   ? o_comp + (static_cast<int64_t>(h) * n_blk + set) * 64
+                                     : nullptr,
+               gate_ != nullptr ? static_cast<const io_t *>(gate_) + o : nullptr, channel);
     float l_tot = sum_with_other_half(l_run);
     if constexpr (B == 16) l_tot = sum_with_other_rows(l_tot);
-    if (!row_valid) return;
     const float inv = 1.f / l_tot;
-    if (lse != nullptr && g == 0) lse[static_cast<int64_t>(h) * lse_stride + trow] = (m_run + __builtin_log2f(l_tot)) * kLn2;
-    const int64_t o = (trow * heads + h) * 64;
-    const float *oc = o_comp_tok != nullptr ? o_comp_tok + (t * heads + h) * 64
-                      : o_comp != nullptr   ? o_comp + (static_cast<int64_t>(h) * n_blk + set) * 64
-                                            : nullptr;
-    typedef typename std::conditional<F32, float, bf16_t>::type io_t;
-    typedef typename std::conditional<F32, floatx4, bf16x4>::type io4_t;
-    const io_t *gate = static_cast<const io_t *>(gate_);
-    io_t *out = static_cast<io_t *>(out_), *o_sel = static_cast<io_t *>(o_sel_);
+    float os[kPairs][8];
 #pragma unroll
-    for (int c = 0; c < NT; ++c)
+    for (int j = 0; j < kPairs; ++j) {
+        float a[4], b[4];
 #pragma unroll
-        for (int r4 = 0; r4 < NR / 4; ++r4) {
-            const int d0 = B * c + 8 * r4 + 4 * g;
-            float os[4], res[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) res[e] = os[e] = oacc[c][4 * r4 + e] * inv;
-            if (oc != nullptr) {
-                const floatx4 c4 = *reinterpret_cast<const floatx4 *>(oc + d0);
-                float gt[4] = {0.5f, 0.5f, 0.5f, 0.5f};
-                if (gate != nullptr) {
-                    const io4_t g4 = *reinterpret_cast<const io4_t *>(gate + o + d0);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) gt[e] = 1.f / (1.f + __expf(-static_cast<float>(g4[e])));
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) res[e] = gt[e] * c4[e] + (1.f - gt[e]) * os[e];
-            }
-            io4_t ro;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) ro[e] = static_cast<io_t>(res[e]);
-            *reinterpret_cast<io4_t *>(out + o + d0) = ro;
-            if (o_sel != nullptr) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) ro[e] = static_cast<io_t>(os[e]);
-                *reinterpret_cast<io4_t *>(o_sel + o + d0) = ro;
-            }
+        for (int e = 0; e < 4; ++e) {  // B = 16: a run is a tile; 32: four runs of a tile
+            a[e] = (B == 16 ? oacc[2 * j][e] : oacc[(2 * j) >> 2][4 * ((2 * j) & 3) + e]) * inv;
+            b[e] = (B == 16 ? oacc[2 * j + 1][e] : oacc[(2 * j + 1) >> 2][4 * ((2 * j + 1) & 3) + e]) * inv;
         }
+        if constexpr (B == 16) join_runs_16(a, b, os[j]);
+        else join_runs_32(a, b, os[j]);
+    }
+    if (!row_valid) return;
+    if (lse != nullptr && g == 0) lse[static_cast<int64_t>(h) * lse_stride + trow] = (m_run + __builtin_log2f(l_tot)) * kLn2;
+    merge.store(os, static_cast<io_t *>(out_) + o, o_sel_ != nullptr ? static_cast<io_t *>(o_sel_) + o : nullptr, channel);
 }
 
 template <int B, bool F32, int NBU, int OCC>

@@ -753,81 +753,53 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         for (int x = 0; x < 32; ++x) oacc[x >> 4][x & 15] = oacc[x >> 4][x & 15] * f0 + buf[(2 + x) * 64] * f1;
     }
 
-    if (!row_valid) return;
     if constexpr (PROBE) {
+        if (!row_valid) return;
         static_assert(!PROBE || (!DENSE && !PAIR && !SMALL && !EXTRA), "probe of the plain selection kernels only");
 #pragma unroll
         for (int s = 0; s < 4; ++s) *reinterpret_cast<bf16x8 *>(out + (trow * heads + h) * 64 + 16 * s + 8 * g) = qb[s];
         return;
     }
+    typedef typename std::conditional<F32, float, bf16_t>::type io_t;
+    const int64_t o = (trow * heads + h) * 64;
+    const float *oc = nullptr;  // (dense attention has no compressed branch to merge with)
+    if (!DENSE && o_comp != nullptr) oc = o_comp + (static_cast<int64_t>(h) * n_blk + (row_valid ? t : 0) / block) * 64;
+    if constexpr (EXTRA && !DENSE)
+        if (x.o_comp_tok != nullptr) oc = x.o_comp_tok + ((row_valid ? t : 0) * heads + h) * 64;  // this query's own compressed output
     const float l_tot = sum_with_other_half(l_run);
     const float inv = (EXTRA && DENSE && l_tot == 0.f) ? 0.f : 1.f / l_tot;  // (a key split of empty units only)
-    if (lse != nullptr && g == 0)
+    if (lse != nullptr && g == 0 && row_valid)
         lse[static_cast<int64_t>(h) * lse_stride + trow] = (m_run + __builtin_log2f(l_tot)) * kLn2;
-    const int64_t o = (trow * heads + h) * 64;
-    const float *oc = (o_comp != nullptr) ? o_comp + (static_cast<int64_t>(h) * n_blk + t / block) * 64 : nullptr;
-    if constexpr (EXTRA)
-        if (x.o_comp_tok != nullptr) oc = x.o_comp_tok + (t * heads + h) * 64;  // this query's own compressed output
-    if (EXTRA && DENSE && x.out_f32 != nullptr) {  // fp32, by (key split and) query slot
-        const int64_t slot = (static_cast<int64_t>(split) * n_tok + t) * heads + h;
+    // One half of the channels after the other: both at once take 142 registers in the fp32 kernel for blocks of 64, which is to
+    // stay below 128 (four workgroups per CU).
 #pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
+    for (int dt = 0; dt < 2; ++dt) {
+        auto channel = [&](int j) -> int { return 32 * dt + 16 * j + 8 * g; };
+        MergeRow<io_t, 2> merge;
+        merge.load(oc, !DENSE && gate != nullptr ? reinterpret_cast<const io_t *>(gate) + o : nullptr, channel);
+        float os[2][8];
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                floatx4 o4;
+        for (int j = 0; j < 2; ++j) {
+            float a[4], b[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) o4[i] = oacc[dt][4 * r4 + i] * inv;
-                *reinterpret_cast<floatx4 *>(x.out_f32 + slot * 64 + 32 * dt + 8 * r4 + 4 * g) = o4;
+            for (int i = 0; i < 4; ++i) {
+                a[i] = oacc[dt][8 * j + i] * inv;
+                b[i] = oacc[dt][8 * j + 4 + i] * inv;
             }
-        // base-2 logarithm of the split's sum of exponentials: what weighs it against the other splits.  Only an empty sum
-        // stands for a share without keys: one that is not a number has to reach the row
-        if (x.part_lse != nullptr && g == 0) x.part_lse[slot] = l_tot == 0.f ? -INFINITY : m_run + __builtin_log2f(l_tot);
-        return;
-    }
-#pragma unroll
-    for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            const int d0 = 32 * dt + 8 * r4 + 4 * g;
-            float os[4], res[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) res[i] = os[i] = oacc[dt][4 * r4 + i] * inv;
-            if (oc != nullptr) {
-                const floatx4 c4 = *reinterpret_cast<const floatx4 *>(oc + d0);
-                float gt[4] = {0.5f, 0.5f, 0.5f, 0.5f};
-                if (gate != nullptr) {
-                    float gl[4];
-                    if constexpr (F32) {
-                        const floatx4 g4 = *reinterpret_cast<const floatx4 *>(reinterpret_cast<const float *>(gate) + o + d0);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) gl[i] = g4[i];
-                    } else {
-                        const bf16x4 g4 = *reinterpret_cast<const bf16x4 *>(gate + o + d0);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) gl[i] = static_cast<float>(g4[i]);
-                    }
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) gt[i] = 1.f / (1.f + __expf(-gl[i]));
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) res[i] = gt[i] * c4[i] + (1.f - gt[i]) * os[i];
-            }
-            if constexpr (F32) {
-                *reinterpret_cast<floatx4 *>(reinterpret_cast<float *>(out) + o + d0) = floatx4{res[0], res[1], res[2], res[3]};
-                if (o_sel != nullptr)
-                    *reinterpret_cast<floatx4 *>(reinterpret_cast<float *>(o_sel) + o + d0) = floatx4{os[0], os[1], os[2], os[3]};
-            } else {
-                bf16x4 ro;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) ro[i] = static_cast<bf16_t>(res[i]);
-                *reinterpret_cast<bf16x4 *>(out + o + d0) = ro;
-                if (o_sel != nullptr) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) ro[i] = static_cast<bf16_t>(os[i]);
-                    *reinterpret_cast<bf16x4 *>(o_sel + o + d0) = ro;
-                }
-            }
+            join_runs_32(a, b, os[j]);
         }
+        if (!row_valid) continue;
+        if (EXTRA && DENSE && x.out_f32 != nullptr) {  // fp32, by (key split and) query slot
+            const int64_t slot = (static_cast<int64_t>(split) * n_tok + t) * heads + h;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) Io8<float>::store(x.out_f32 + slot * 64 + channel(j), os[j]);
+            // base-2 logarithm of the split's sum of exponentials: what weighs it against the other splits.  Only an empty sum
+            // stands for a share without keys: one that is not a number has to reach the row
+            if (dt == 0 && x.part_lse != nullptr && g == 0) x.part_lse[slot] = l_tot == 0.f ? -INFINITY : m_run + __builtin_log2f(l_tot);
+            continue;
+        }
+        merge.store(os, reinterpret_cast<io_t *>(out) + o, o_sel != nullptr ? reinterpret_cast<io_t *>(o_sel) + o : nullptr, channel);
+    }
 }
 
 template <int QW, bool DENSE, int NS, bool SMALL, bool EXTRA, bool ASMQ, bool PAIR, bool PROBE = false, bool F32 = false, int KS = 1>
@@ -891,6 +863,7 @@ static hipError_t run_select(const SelectArgs &a, hipStream_t stream)
 hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream)
 {
     if (a.kb == nullptr || a.vb == nullptr) return hipErrorInvalidValue;
+    if (a.idx == nullptr && (a.o_comp != nullptr || a.x.o_comp_tok != nullptr)) return hipErrorInvalidValue;
     if (!a.is_bf16) {
         // fp32 problems: K/V tiles in bf16 operand parts
         if (a.lo_off <= 0 || a.loads_only) return hipErrorInvalidValue;

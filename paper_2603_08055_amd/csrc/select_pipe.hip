@@ -383,6 +383,12 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
 
     // ---- the softmax over all selected keys from the P partial ones of each row group
     constexpr int kShare = 32 / P;           // accumulator registers each partner adds up and writes
+    constexpr int kPairs = kShare / 8;       // ... in pairs of runs of four
+    auto channel = [&](int j) -> int { return 16 * (p * kPairs + j) + 8 * g; };
+    const int64_t o = (trow * heads + h) * 64;
+    MergeRow<bf16_t, kPairs> merge;          // (requested before the partial results are exchanged)
+    merge.load(o_comp != nullptr ? o_comp + (static_cast<int64_t>(h) * n_blk + set) * 64 : nullptr,
+               gate != nullptr ? gate + o : nullptr, channel);
     float osum[kShare];
     float m_all = m_run, l_all = sum_with_other_half(l_run);
     if constexpr (P == 1) {
@@ -415,42 +421,21 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
 #pragma unroll
             for (int x = 0; x < kShare; ++x) osum[x] += obuf[((2 * j + r) * 32 + p * kShare + x) * 64 + lane];
     }
-    if (!row_valid) return;
     const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
-    if (lse != nullptr && g == 0 && p == 0) lse[static_cast<int64_t>(h) * lse_stride + trow] = (m_all + __builtin_log2f(l_all)) * kLn2;
-    const int64_t o = (trow * heads + h) * 64;
-    const float *oc = (o_comp != nullptr) ? o_comp + (static_cast<int64_t>(h) * n_blk + set) * 64 : nullptr;
+    float os[kPairs][8];
 #pragma unroll
-    for (int x4 = 0; x4 < kShare / 4; ++x4) {
-        {
-            const int reg = p * kShare + 4 * x4;         // accumulator register dt * 16 + 4 r4 (+ e)
-            const int dt = reg >> 4, r4 = (reg & 15) >> 2;
-            const int d0 = 32 * dt + 8 * r4 + 4 * g;
-            float os[4], res[4];
+    for (int j = 0; j < kPairs; ++j) {
+        float a[4], b[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) res[e] = os[e] = osum[4 * x4 + e] * inv;
-            if (oc != nullptr) {
-                const floatx4 c4 = *reinterpret_cast<const floatx4 *>(oc + d0);
-                float gt[4] = {0.5f, 0.5f, 0.5f, 0.5f};
-                if (gate != nullptr) {
-                    const bf16x4 gl = *reinterpret_cast<const bf16x4 *>(gate + o + d0);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) gt[e] = 1.f / (1.f + __expf(-static_cast<float>(gl[e])));
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) res[e] = gt[e] * c4[e] + (1.f - gt[e]) * os[e];
-            }
-            bf16x4 ro;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) ro[e] = static_cast<bf16_t>(res[e]);
-            *reinterpret_cast<bf16x4 *>(out + o + d0) = ro;
-            if (o_sel != nullptr) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) ro[e] = static_cast<bf16_t>(os[e]);
-                *reinterpret_cast<bf16x4 *>(o_sel + o + d0) = ro;
-            }
+        for (int e = 0; e < 4; ++e) {
+            a[e] = osum[8 * j + e] * inv;
+            b[e] = osum[8 * j + 4 + e] * inv;
         }
+        join_runs_32(a, b, os[j]);
     }
+    if (!row_valid) return;
+    if (lse != nullptr && g == 0 && p == 0) lse[static_cast<int64_t>(h) * lse_stride + trow] = (m_all + __builtin_log2f(l_all)) * kLn2;
+    merge.store(os, out + o, o_sel != nullptr ? o_sel + o : nullptr, channel);
 }
 
 template <int P, int NSK, int NSV, int AHEAD>
