@@ -9,24 +9,33 @@ namespace s3r {
 
 template <int B> constexpr int kPoolHeads = B < 32 ? 32 / B : 1;
 
-template <typename T> struct Load8;
-template <> struct Load8<bf16_t> {
-    static __device__ __forceinline__ void run(const bf16_t *p, float (&f)[8], bf16x8 &raw)
+// Eight channels of a row as they are loaded, 16 bytes at a time.
+template <typename T> struct Raw8;
+template <> struct Raw8<bf16_t> {
+    bf16x8 x;
+    __device__ __forceinline__ void load(const bf16_t *p) { x = *reinterpret_cast<const bf16x8 *>(p); }
+    // the values and their hi parts; zeros for a row that does not exist
+    __device__ __forceinline__ void get(bool valid, float (&f)[8], bf16x8 &hi) const
     {
-        raw = *reinterpret_cast<const bf16x8 *>(p);
+        typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+        hi = __builtin_bit_cast(bf16x8, valid ? __builtin_bit_cast(u32x4, x) : u32x4{0u, 0u, 0u, 0u});
 #pragma unroll
-        for (int i = 0; i < 8; ++i) f[i] = static_cast<float>(raw[i]);
+        for (int i = 0; i < 8; ++i) f[i] = static_cast<float>(hi[i]);
     }
 };
-template <> struct Load8<float> {
-    static __device__ __forceinline__ void run(const float *p, float (&f)[8], bf16x8 &raw)
+template <> struct Raw8<float> {
+    floatx4 a, b;
+    __device__ __forceinline__ void load(const float *p)
     {
-        const floatx4 a = *reinterpret_cast<const floatx4 *>(p);
-        const floatx4 b = *reinterpret_cast<const floatx4 *>(p + 4);
+        a = *reinterpret_cast<const floatx4 *>(p);
+        b = *reinterpret_cast<const floatx4 *>(p + 4);
+    }
+    __device__ __forceinline__ void get(bool valid, float (&f)[8], bf16x8 &hi) const
+    {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { f[i] = a[i]; f[4 + i] = b[i]; }
+        for (int i = 0; i < 4; ++i) { f[i] = valid ? a[i] : 0.f; f[4 + i] = valid ? b[i] : 0.f; }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) raw[i] = static_cast<bf16_t>(f[i]);   // the hi part of the operand pair
+        for (int i = 0; i < 8; ++i) hi[i] = static_cast<bf16_t>(f[i]);
     }
 };
 
@@ -51,12 +60,32 @@ __device__ __forceinline__ bf16x8 lo2_parts(const float (&f)[8], const bf16x8 &h
     return lo2;
 }
 
+// A 16-byte piece of a tile; PAST: past the L2, where the tiles are more than the caches keep for the kernels that read them (us of
+// this kernel through it / past it: 100 views 272 / 269, 1000 views 2765 / 2655).  Short sequences are read from there: 8 views 19.8 / 18.8,
+// but the kernel that reads the tiles takes as much longer.
+template <bool PAST> __device__ __forceinline__ void store_tile(bf16_t *dst, const bf16x8 &x)
+{
+    if constexpr (PAST) __builtin_nontemporal_store(x, reinterpret_cast<bf16x8 *>(dst));
+    else *reinterpret_cast<bf16x8 *>(dst) = x;
+}
+
+// Whether every thread requests all of its rows at once.  With one load at a time a short sequence waits for the memory's
+// latency six times (blocks of 64) where once would do; a long one, whose waves keep the memory busy anyway, is faster with the
+// fewer requests on their way, blocks of 128 apart (16 heads, us of this kernel at a time / all at once, tiles through the L2: bf16,
+// 8 views 21.4 / 19.8, 100 views 279 / 284, 1000 views 2701 / 2924, 300 views in blocks of 128 893 / 864; fp32, 30 views 172 / 160).
+constexpr int64_t kPoolAheadBytes = int64_t(256) << 20;  // of q, k and v
+
+inline bool pool_ahead(int64_t n_tok, int heads, int block, bool is_bf16)
+{
+    return !is_bf16 || block == 128 || n_tok * heads * (3 * 64 * 2) <= kPoolAheadBytes;
+}
+
 // grid: one workgroup per (block j, head h), head fastest; 256 threads.  Blocks of 16 rows: two heads per workgroup,
 // which would leave half of its threads without a row otherwise (100 views in 4 x 4 windows: 0.37 -> 0.31 ms, the call
 // 3.22 -> 3.17).
 // Thread (r0 = tid / 8, c = tid % 8) handles channels 8c..8c+7 of rows r0, r0 + 32, ...
 // KP: parts of K (fp32 inputs that are re-laid-out; otherwise 1).
-template <typename T, int B, bool REPACK, int KP>
+template <typename T, int B, bool REPACK, int KP, bool AHEAD>
 __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, const T *__restrict__ k,
                                                    const T *__restrict__ v, float *__restrict__ qc,
                                                    float *__restrict__ kc, float *__restrict__ vc,
@@ -101,53 +130,68 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, cons
     auto k_tile = [&](int r) -> bf16_t * {
         return (B >= 32) ? kb + tile_base + (r >> 5) * kRowTileElems + row_tile_chunk_offset(r & 31, c) : kb + tile_base + (c * 16 + r) * 8;
     };
+    // AHEAD: every row of a thread is requested before the first is used; otherwise one load at a time, see pool_ahead.
+    // (Ahead: rows and heads that do not exist read one that does.)
+    constexpr int NA = AHEAD ? B / RT : 1;
+    Raw8<T> rq[NA], rk[NA], rv[NA];
+    auto offset_of = [&](int n) -> int64_t {
+        const int r = r0 + n * RT;
+        return in.at(map.row(r < len ? t0 + r : t0), have_head ? h : h0, heads) + c * 8;
+    };
+    if constexpr (AHEAD) {
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+            const int64_t off = offset_of(n);
+            rq[n].load(q + off);
+            rk[n].load(k + off);
+            rv[n].load(v + off);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
     float kf[HALF ? B / RT : 1][8];  // HALF: K waits for the largest entry of the block
 #pragma unroll
     for (int n = 0; n < B / RT; ++n) {
         if (!have_head) break;
         const int r = r0 + n * RT;
-        float f[8];
-        bf16x8 raw;
         const bool valid = r < len;
-        const int64_t off = in.at(map.row(valid ? t0 + r : t0), h, heads) + c * 8;
-        if (valid) {
-            Load8<T>::run(q + off, f, raw);
+        const int64_t off = AHEAD ? 0 : offset_of(n);
+        const int na = AHEAD ? n : 0;
+        const bool wanted = B > 16 || valid;  // (blocks of 16: slots that windows cut off; 100 views in 4 x 4 windows 330 us, 301 so)
+        float f[8];
+        bf16x8 hi;
+        if (!AHEAD && wanted) rq[na].load(q + off);
+        rq[na].get(valid, f, hi);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) acc[0][i] += f[i];
-            Load8<T>::run(k + off, f, raw);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[1][i] += f[i];
+        for (int i = 0; i < 8; ++i) acc[0][i] += f[i];
+        if constexpr (!AHEAD) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (wanted) rk[na].load(k + off);
         }
+        rk[na].get(valid, f, hi);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[1][i] += f[i];
+        if constexpr (HALF) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) kf[n][i] = f[i];
+        } else if constexpr (REPACK) {
+            bf16_t *dst = k_tile(r);
+            store_tile<!AHEAD>(dst, hi);
+            if constexpr (PAIRS) {
+                const bf16x8 lo = lo_parts(f, hi);
+                *reinterpret_cast<bf16x8 *>(dst + lo_off) = lo;
+                *reinterpret_cast<bf16x8 *>(dst + 2 * lo_off) = lo2_parts(f, hi, lo);
+            }
+        }
+        if constexpr (!AHEAD) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (wanted) rv[na].load(v + off);
+        }
+        rv[na].get(valid, f, hi);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[2][i] += f[i];
         if constexpr (REPACK) {
-            if (!valid) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) { raw[i] = static_cast<bf16_t>(0.f); f[i] = 0.f; }
-            }
-            if constexpr (HALF) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) kf[n][i] = f[i];
-            } else {
-                bf16_t *dst = k_tile(r);
-                *reinterpret_cast<bf16x8 *>(dst) = raw;
-                if constexpr (PAIRS) {
-                    const bf16x8 lo = lo_parts(f, raw);
-                    *reinterpret_cast<bf16x8 *>(dst + lo_off) = lo;
-                    *reinterpret_cast<bf16x8 *>(dst + 2 * lo_off) = lo2_parts(f, raw, lo);
-                }
-            }
-        }
-        if (valid) {
-            Load8<T>::run(v + off, f, raw);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[2][i] += f[i];
-        }
-        if constexpr (REPACK) {
-            if (!valid) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) { raw[i] = static_cast<bf16_t>(0.f); f[i] = 0.f; }
-            }
-            *reinterpret_cast<bf16x8 *>(&vs[hh * B + r][c * 8]) = raw;
-            if constexpr (PAIRS) *reinterpret_cast<bf16x8 *>(&vs_lo[hh * B + r][c * 8]) = lo_parts(f, raw);
+            *reinterpret_cast<bf16x8 *>(&vs[hh * B + r][c * 8]) = hi;
+            if constexpr (PAIRS) *reinterpret_cast<bf16x8 *>(&vs_lo[hh * B + r][c * 8]) = lo_parts(f, hi);
         }
     }
 #pragma unroll
@@ -202,7 +246,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, cons
             bf16x8 o;
 #pragma unroll
             for (int i = 0; i < 8; ++i) o[i] = vs[row_of(i)][channel_of(i)];
-            *reinterpret_cast<bf16x8 *>(vb + tile_base + static_cast<int64_t>(ci) * 8) = o;
+            store_tile<!AHEAD>(vb + tile_base + static_cast<int64_t>(ci) * 8, o);
             if constexpr (PAIRS) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) o[i] = vs_lo[row_of(i)][channel_of(i)];
@@ -212,14 +256,14 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, cons
     }
 }
 
-template <typename T, int B, bool REPACK, int KP = 1>
+template <typename T, int B, bool REPACK, int KP = 1, bool AHEAD = true>
 static hipError_t run_pool(const void *q, const void *k, const void *v, float *qc, float *kc,
                            float *vc, void *kb, void *vb, int64_t n_tok, int heads, int64_t n_blk,
                            TokenMap map, InStride in, hipStream_t stream)
 {
     const int64_t grid = n_blk * ((heads + kPoolHeads<B> - 1) / kPoolHeads<B>);
     const int64_t lo_off = static_cast<int64_t>(heads) * n_blk * B * 64;   // fp32 inputs: [hi tiles | lo tiles | K: lo2 tiles or factors]
-    hipLaunchKernelGGL((pool_kernel<T, B, REPACK, KP>), dim3(static_cast<unsigned>(grid)), dim3(256), 0,
+    hipLaunchKernelGGL((pool_kernel<T, B, REPACK, KP, AHEAD>), dim3(static_cast<unsigned>(grid)), dim3(256), 0,
                        stream, static_cast<const T *>(q), static_cast<const T *>(k),
                        static_cast<const T *>(v), qc, kc, vc, static_cast<bf16_t *>(kb),
                        static_cast<bf16_t *>(vb), n_tok, heads, n_blk, map, in, lo_off);
@@ -254,6 +298,14 @@ hipError_t launch_pool(const void *q, const void *k, const void *v, float *qc, f
     if (repack && !is_bf16 && (key_parts != 2 || block < 64) && (key_parts != 3 || block > 64)) return hipErrorInvalidValue;
 #define S3R_POOL_CASE(TT, BB, ...) \
     return run_pool<TT, BB, __VA_ARGS__>(q, k, v, qc, kc, vc, kb, vb, n_tok, heads, n_blk, map, in, stream)
+    if (!pool_ahead(n_tok, heads, block, is_bf16)) {
+        switch (block) {
+        case 16: if (repack) S3R_POOL_CASE(bf16_t, 16, true, 1, false); else S3R_POOL_CASE(bf16_t, 16, false, 1, false);
+        case 32: if (repack) S3R_POOL_CASE(bf16_t, 32, true, 1, false); else S3R_POOL_CASE(bf16_t, 32, false, 1, false);
+        case 64: if (repack) S3R_POOL_CASE(bf16_t, 64, true, 1, false); else S3R_POOL_CASE(bf16_t, 64, false, 1, false);
+        }
+        return hipErrorInvalidValue;
+    }
     if (is_bf16) {
         switch (block) {
         case 16: if (repack) S3R_POOL_CASE(bf16_t, 16, true); else S3R_POOL_CASE(bf16_t, 16, false);

@@ -493,3 +493,45 @@ def test_bound_of_scores_of_one_sign(s3r, oracle, dtype, n_blk, topk, lean):  # 
     res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), 16, topk)
     log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v), None, 16,
                                                  topk, dtype, label=wl.name)))
+
+
+@pytest.mark.parametrize("heads,n_tok", [(17, 41120), (17, 41121), (17, 41137), (16, 43691)])   # 256 MiB of q, k, v in bf16 and past it
+@pytest.mark.parametrize("block", [16, 32, 64, 128])
+def test_pooling_with_rows_requested_at_once_and_one_by_one(s3r, heads, n_tok, block):  # noqa: F811
+    wl = workloads.Workload("pool_line", 1, n_tok, heads, 64, "bf16", block, 1, 108, "outliers")
+    tensors = workloads.make_inputs(wl, device="cuda")
+    n_blk = (n_tok + block - 1) // block
+    outs = [torch.full((heads, n_blk, 64), float("nan"), device="cuda") for _ in range(3)]
+    s3r.speed3r_pool_blocks(*tensors, *outs, block)
+    for x, got in zip(tensors, outs):
+        x = torch.cat([x.double(), x.new_zeros((n_blk * block - n_tok, heads, 64)).double()]).view(n_blk, block, heads, 64)
+        lens = torch.full((n_blk, 1, 1), float(block), device="cuda", dtype=torch.double)
+        lens[-1] = n_tok - (n_blk - 1) * block
+        want = (x.sum(1) / lens).permute(1, 0, 2)
+        # up to 128 terms, each added with 2^-24 of the sum so far, and the division
+        bound = (x.abs().sum(1) / lens).permute(1, 0, 2) * (block + 1) * 2.0 ** -24
+        assert ((got.double() - want).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("dtype,block,n_tok,heads,topk,n_forced", [
+    ("bf16", 64, 64 * 9 + 33, 2, 5, 0), ("bf16", 64, 64 * 300 + 1, 3, 7, 2),     # two pairs of waves (few query blocks), one pair
+    ("bf16", 64, 64 * 200 + 5, 2, 20, 120), ("bf16", 128, 128 * 9 + 70, 3, 4, 0),  # long rows, blocks of 128
+    ("bf16", 16, 16 * 37 + 3, 3, 5, 1), ("bf16", 32, 32 * 21 + 17, 3, 5, 0),
+    ("f32", 16, 16 * 37 + 3, 3, 5, 0), ("f32", 32, 32 * 21 + 17, 3, 5, 0), ("f32", 64, 64 * 9 + 33, 3, 5, 0), ("f32", 128, 128 * 9 + 70, 3, 4, 0),
+])
+@pytest.mark.parametrize("gated", [False, True])
+def test_every_channel_is_merged_with_its_own(s3r, dtype, block, n_tok, heads, topk, n_forced, gated):  # noqa: F811
+    """out = g o_comp + (1 - g) o_sel channel by channel, from the outputs themselves (o_sel as it was stored)."""
+    wl = workloads.Workload("merge", 1, n_tok, heads, 64, dtype, block, topk, 109, "normal")
+    q, k, v = workloads.make_inputs(wl, device="cuda")
+    gate = workloads.make_gate_logits(wl, device="cuda") if gated else None
+    res = run_device(s3r, q, k, v, block, topk, gate=gate, forced=list(range(n_forced)) if n_forced else None)
+    g = torch.sigmoid(gate.double()) if gated else torch.full(q.shape, 0.5, device="cuda", dtype=torch.double)
+    comp = res["o_comp"].double().permute(1, 0, 2)[torch.arange(n_tok, device="cuda") // block]
+    sel, out = res["o_sel"].double(), res["out"].double()
+    # rounding of o_sel and of out to 8 significant bits (2^-8 at most, just above a power of two); fp32: the few operations of the merge
+    ulp = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -22
+    # the gate: e^-x to 2^-20 (hardware exponential, logits up to 6 or so) moves it by g (1 - g) 2^-20 <= 2^-22, and 1 + e, 1 / ., 1 - g
+    # are rounded at a size of up to 1 (so that 1 - g is not exact to its own size)
+    bound = ulp * ((1 - g) * sel.abs() + out.abs()) + 2.0 ** -21 * (comp.abs() + sel.abs())
+    assert ((out - (g * comp + (1 - g) * sel)).abs() <= bound).all()
