@@ -78,6 +78,9 @@ namespace s3r {
 //         fp32 selection with blocks of 64: two workgroups of two waves were all that an 80 KiB ring lets a CU
 //         hold, one wave per SIMD (30 views, top-16: 1.10 -> 0.98 ms a call; the shorter chains of sums also leave
 //         less error, outlier keys against 64 bits 3.6e-6 -> 3.3e-6).
+//         4: two units at a time, each with a stage of its own for K and for V.  For so few query blocks that a CU has one workgroup
+//         at most, and a row takes as long as its chain of units (us a call, 2 -> 4: 64 query blocks, 8 units 24.5 -> 22.7;
+//         228, 16 units 37.4 -> 33.6; 252, 32 units 56.0 -> 48.6; 157, 40 units 69.3 -> 57.9).
 template <int QW, bool DENSE, int NS, bool SMALL, bool EXTRA, bool ASMQ, bool PAIR = false, bool PROBE = false,
           bool F32 = false, int KS = 1>
 __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
@@ -90,7 +93,8 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     int64_t lo_off, int64_t lo_off2)
 {
     constexpr int NW = QW * KS;        // waves per workgroup
-    constexpr int NMT = 2 / KS;        // 32-key tiles of a unit that a wave works on
+    constexpr int NMT = KS == 1 ? 2 : 1;  // 32-key tiles of a unit that a wave works on
+    constexpr int NU = KS == 4 ? 2 : 1;   // units in work at a time
     constexpr bool HALF = F32 && !SMALL;
     constexpr int NCH = HALF ? 32 : F32 ? 40 : 16; // 1 KiB chunks of a unit: 8 K + 8 V (F32: then 8 K lo + 8 V lo, and 8 K lo2 unless HALF)
     constexpr int CPW = NCH / NW;      // ... issued by each wave
@@ -98,20 +102,21 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     static_assert(NCH % NW == 0 && 16 % NW == 0, "waves must split the chunks of a unit evenly");
     static_assert(CPW * D < 64, "vmcnt budget");
     static_assert(!SMALL || DENSE, "selection with small blocks: select_direct.hip");
-    static_assert(KS == 1 || (KS == 2 && !DENSE && !PAIR && !PROBE), "key halves: plain selection");
+    static_assert(KS == 1 || (!DENSE && !PAIR && !PROBE && (KS == 2 || (KS == 4 && HALF && QW == 2))), "key halves: plain selection");
     static_assert(!F32 || (!PAIR && !PROBE), "operand parts: the plain and the dense kernels");
     // [stage][K 8 KiB | V 8 KiB] (F32: then [K lo 8 KiB | V lo 8 KiB | K lo2 8 KiB]).  HALF: [stage][K | K lo] and, of one unit
     // only, [V | V lo] behind them; with KS = 2 one stage of K as well.
     constexpr int kStageParts = F32 && !HALF ? 5 : 2;
     static_assert(!HALF || NS == 2, "its own stages");
-    constexpr int kKeyStages = KS == 2 ? 1 : 2;  // HALF
-    __shared__ __attribute__((aligned(1024))) bf16_t ring[HALF ? kKeyStages + 1 : NS][kStageParts * kUnitElems];
+    constexpr int kKeyStages = KS == 1 ? 2 : 1;  // HALF
+    __shared__ __attribute__((aligned(1024))) bf16_t ring[HALF ? NU * (kKeyStages + 1) : NS][kStageParts * kUnitElems];
     constexpr int kLoElems = HALF ? kUnitElems : 2 * kUnitElems;  // from a hi part of a stage to its lo part (and on to K's lo2 part)
 
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = KS == 1 ? wave : wave & (QW - 1);  // which 32 query rows
-    const int kh = KS == 1 ? 0 : wave / QW;            // which half of every unit's keys
+    const int kh = KS == 1 ? 0 : (wave / QW) & 1;      // which half of every unit's keys
+    const int nu = NU == 1 ? 0 : wave / (2 * QW);      // which of the units in work
     int h;
     int64_t set;    // query group (query block for selection) of this workgroup
     int split = 0;  // dense attention in key splits: which share of the key units
@@ -162,40 +167,15 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     float scale_q = scale_log2;                 // HALF: scale over the power of two in front of Q
     bf16x8 ql[F32 && !HALF ? 4 : 1], ql2[F32 && !HALF ? 4 : 1];   // F32 otherwise: qb and the lo and lo2 parts of Q
     constexpr bool kAsmQ = ASMQ && !F32;
+    floatx4 q_raw[F32 ? 4 : 1][2];  // F32: requested here, made operands of once the first unit has been requested as well
     if constexpr (F32) {
-        const float *qf = reinterpret_cast<const float *>(q);
-        float f[4][8], top = 0.f;
+        const float *qf = reinterpret_cast<const float *>(q) + (EXTRA ? x.in.at(trow, h, heads) : (trow * heads + h) * 64) + 8 * g;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            if (row_valid) {
-                const int64_t qo = EXTRA ? x.in.at(trow, h, heads) : (trow * heads + h) * 64;
-                const floatx4 a = *reinterpret_cast<const floatx4 *>(qf + qo + 16 * s + 8 * g);
-                const floatx4 b = *reinterpret_cast<const floatx4 *>(qf + qo + 16 * s + 8 * g + 4);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { f[s][i] = a[i]; f[s][4 + i] = b[i]; }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) f[s][i] = 0.f;
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) top = fmaxf(top, fabsf(f[s][i]));
+            q_raw[s][0] = *reinterpret_cast<const floatx4 *>(qf + 16 * s);
+            q_raw[s][1] = *reinterpret_cast<const floatx4 *>(qf + 16 * s + 4);
         }
-        if constexpr (HALF) {
-            const int e = half_exponent(max_with_other_half(top));
-            scale_q = ldexpf(scale_log2, -e);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) half_parts(f[s], e, qh[s], qhl[s]);
-        } else {
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    qb[s][i] = static_cast<bf16_t>(f[s][i]);
-                    const float r1 = f[s][i] - static_cast<float>(qb[s][i]);
-                    ql[s][i] = static_cast<bf16_t>(r1);
-                    ql2[s][i] = static_cast<bf16_t>(r1 - static_cast<float>(ql[s][i]));
-                }
-        }
+        __builtin_amdgcn_sched_barrier(0);
     } else if constexpr (!kAsmQ) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -208,6 +188,33 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
             }
         }
     }
+    auto parts_of_q = [&]() __attribute__((always_inline)) {
+        float f[4][8], top = 0.f;
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                f[s][i] = row_valid ? q_raw[F32 ? s : 0][i >> 2][i & 3] : 0.f;
+                top = fmaxf(top, fabsf(f[s][i]));
+            }
+        if constexpr (HALF) {
+            const int e = half_exponent(max_with_other_half(top));
+            scale_q = ldexpf(scale_log2, -e);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) half_parts(f[s], e, qh[s], qhl[s]);
+        } else if constexpr (F32) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    qb[s][i] = static_cast<bf16_t>(f[s][i]);
+                    const float r1 = f[s][i] - static_cast<float>(qb[s][i]);
+                    ql[s][i] = static_cast<bf16_t>(r1);
+                    ql2[s][i] = static_cast<bf16_t>(r1 - static_cast<float>(ql[s][i]));
+                }
+        }
+    };
+    if constexpr (F32 && !HALF) parts_of_q();
     auto load_q_dense = [&]() __attribute__((always_inline)) {
         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
         u32x4 q0, q1, q2, q3;
@@ -252,10 +259,8 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     }
     // An entry of the index list, held into [0, n_blk): the lists of the library's own TopK are always in range,
     // a caller's (speed3r_select_attn) are not trusted with the address arithmetic.
-    auto sel_at = [&](const int32_t *list, int pos) -> int {
-        const int j = list[pos];
-        return j < 0 ? 0 : (j >= static_cast<int>(n_blk) ? static_cast<int>(n_blk) - 1 : j);
-    };
+    auto in_range = [&](int j) -> int { return j < 0 ? 0 : (j >= static_cast<int>(n_blk) ? static_cast<int>(n_blk) - 1 : j); };
+    auto sel_at = [&](const int32_t *list, int pos) -> int { return in_range(list[pos]); };
     // SMALL: the c-th key block of unit s, or -1 past the end of the sequence
     auto block_at = [&](int s, int c) -> int {
         const int pos = (s << bpu_shift) + c;
@@ -364,12 +369,12 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
 
     // HALF: this wave's share of K (or V) of step s -> LDS stage `stage`: four 1 KiB chunks, two of either part
     auto issue_half = [&](int s, int stage, bool is_k) {
-        static_assert(!HALF || NW == 4, "two chunks of a part for each wave");
+        static_assert(!HALF || NW == 4 * NU, "two chunks of a part for each of a unit's waves");
         const int w = unit_of(s);
         const bool second = DENSE && w >= n_units1;
         const int64_t unit = static_cast<int64_t>(second ? w - n_units1 : w) * kUnitElems, lo = second ? lo_off2 : lo_off;
-        const bf16_t *src = (is_k ? (second ? kb2_h : kb_h) : (second ? vb2_h : vb_h)) + unit + wave * 1024;
-        const unsigned dst = ring_base + static_cast<unsigned>(stage) * (kStageParts * kUnitElems * 2) + wave * 2048;
+        const bf16_t *src = (is_k ? (second ? kb2_h : kb_h) : (second ? vb2_h : vb_h)) + unit + (wave & 3) * 1024;
+        const unsigned dst = ring_base + static_cast<unsigned>(nu * (kKeyStages + 1) + stage) * (kStageParts * kUnitElems * 2) + (wave & 3) * 2048;
         lds_dma_16_x2(src, lane * 16, dst);
         lds_dma_16_x2(src + lo, lane * 16, dst + kUnitElems * 2);
     };
@@ -419,15 +424,17 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     // HALF: the powers of two in front of the K blocks of 64 steps, one step per lane, and with the query's own and the softmax
     // scale what the scores of a unit are to be multiplied by.
     float k_factor = 1.f, unit_scale = scale_log2;
-    auto load_factors = [&](int s) {  // of steps s .. s + 63
+    auto factor_step = [&](int s) -> int { return s + lane < n_steps ? s + lane : n_steps - 1; };
+    // entry: selection: the index list at factor_step(s)
+    auto load_factors = [&](int s, int entry) {  // of steps s .. s + 63
         const float *fk = reinterpret_cast<const float *>(kb + 2 * lo_off) + static_cast<int64_t>(h) * n_blk;
-        const int step = s + lane < n_steps ? s + lane : n_steps - 1;
+        const int step = factor_step(s);
         if constexpr (DENSE) {
             const int u = step + u_begin;
             k_factor = u < n_units1 ? fk[u >> upb_shift]
                                     : reinterpret_cast<const float *>(kb2 + 2 * lo_off2)[static_cast<int64_t>(h) * n_units2 + (u - n_units1)];
         } else {
-            k_factor = fk[sel_at(sel, step >> upb_shift)];
+            k_factor = fk[in_range(entry)];
         }
         asm volatile("" : "+v"(k_factor));  // (waited for in here, not in front of its use in every step)
     };
@@ -690,22 +697,30 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         // products here (matrix pipe 39 % and vector ALU 42 % busy with two waves on a SIMD).  A call on 30 views, top-16, blocks of
         // 64: 854 us with two whole stages, 775 with one of V, 761 with one of both; 8 x 8 windows 1754, 1585, 1547; blocks of 128
         // (30 views, top-32, outlier keys) 2307 and 2055; dense, 5496 rows, 392 and 364.
-        if (n_steps > 0) issue_half(0, 0, true);
-        for (int s = 0; s < n_steps; ++s) {
+        auto entry_of = [&](int s) -> int { return DENSE ? 0 : sel[factor_step(s) >> upb_shift]; };
+        // What the start waits for is requested side by side: Q (above), the index list, then K(0), then the factors.
+        int entry = n_steps > 0 ? entry_of(0) : 0;
+        __builtin_amdgcn_sched_barrier(0);
+        if (nu < n_steps) issue_half(nu, 0, true);
+        parts_of_q();
+        for (int s0 = 0; s0 < n_steps; s0 += NU) {
+            const int s = s0 + nu;
+            const bool have = NU == 1 || s < n_steps, more = s + NU < n_steps;
+            if ((s0 & 63) == 0) load_factors(s0, s0 == 0 ? entry : entry_of(s0));
             wait_vmcnt<0>();  // K(s)
-            lds_barrier();    // everybody's K(s), and everybody is done with V(s - 1) (two K stages: and with K(s - 1))
-            issue_half(s, kKeyStages, false);
-            if (kKeyStages == 2 && s + 1 < n_steps) issue_half(s + 1, (s + 1) & 1, true);
-            if ((s & 63) == 0) load_factors(s);
-            set_unit_scale(s);
-            const unsigned long long vmask = unit_mask(s);
+            lds_barrier();    // everybody's K(s), and everybody is done with V of the units before (two K stages: and with K)
+            if (have) issue_half(s, kKeyStages, false);
+            if (kKeyStages == 2 && more) issue_half(s + NU, (s + 1) & 1, true);
+            if (have) set_unit_scale(s);
+            const unsigned long long vmask = have ? unit_mask(s) : 0ull;
             const bool any = (KS == 1 ? vmask : vmask >> (32 * kh)) != 0ull;  // (none: second half of a short last block)
+            const bf16_t *stages = &ring[nu * (kKeyStages + 1)][0];
             // (a key half: the second 32-row tile of K, the second two key steps of V)
-            if (any) softmax(&ring[kKeyStages == 2 ? s & 1 : 0][kh * kRowTileElems], vmask);
-            if (kKeyStages == 2 && s + 1 < n_steps) wait_vmcnt<4>(); else wait_vmcnt<0>();  // V(s); K(s + 1) may be on its way
+            if (any) softmax(stages + (kKeyStages == 2 ? s & 1 : 0) * (kStageParts * kUnitElems) + kh * kRowTileElems, vmask);
+            if (kKeyStages == 2 && more) wait_vmcnt<4>(); else wait_vmcnt<0>();  // V(s); K of the next may be on its way
             lds_barrier();    // everybody's V(s), and everybody is done with the scores of K(s)
-            if (kKeyStages == 1 && s + 1 < n_steps) issue_half(s + 1, 0, true);
-            if (any) accumulate(&ring[kKeyStages][kh * kRowTileElems], std::false_type{});
+            if (kKeyStages == 1 && more) issue_half(s + NU, 0, true);
+            if (any) accumulate(stages + kKeyStages * (kStageParts * kUnitElems) + kh * kRowTileElems, std::false_type{});
         }
     } else {
     for (int s = 0; s < D && s < n_steps; ++s) issue(s, s);  // D < NS: stage = s
@@ -733,24 +748,31 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     }
     }
 
-    if constexpr (KS == 2) {  // the second half's result to LDS, added to the first half's there
-        float *buf = reinterpret_cast<float *>(&ring[0][0]) + rg * (34 * 64) + lane;  // [QW][34 registers][64 lanes]
-        static_assert(sizeof(ring) >= QW * 34 * 64 * sizeof(float), "partial results in the ring's place");
+    if constexpr (KS > 1) {  // the other shares' results to LDS, added to the first one's there
+        float *buf = reinterpret_cast<float *>(&ring[0][0]) + rg * (34 * 64) + lane;  // [KS - 1][QW][34 registers][64 lanes]
+        constexpr int kShare = QW * 34 * 64;
+        static_assert(sizeof(ring) >= (KS - 1) * kShare * sizeof(float), "partial results in the ring's place");
+        const int share = wave / QW;
         lds_barrier();        // every wave is done with the ring
-        if (kh == 1) {
-            buf[0] = m_run;
-            buf[64] = l_run;
+        if (share > 0) {
+            float *mine = buf + (share - 1) * kShare;
+            mine[0] = m_run;
+            mine[64] = l_run;
 #pragma unroll
-            for (int x = 0; x < 32; ++x) buf[(2 + x) * 64] = oacc[x >> 4][x & 15];
+            for (int x = 0; x < 32; ++x) mine[(2 + x) * 64] = oacc[x >> 4][x & 15];
         }
         lds_barrier();
-        if (kh == 1) return;
-        const float m_all = fmaxf(m_run, buf[0]);
-        const float f0 = fast_exp2(m_run - m_all), f1 = fast_exp2(buf[0] - m_all);
-        m_run = m_all;
-        l_run = l_run * f0 + buf[64] * f1;
+        if (share > 0) return;
 #pragma unroll
-        for (int x = 0; x < 32; ++x) oacc[x >> 4][x & 15] = oacc[x >> 4][x & 15] * f0 + buf[(2 + x) * 64] * f1;
+        for (int j = 0; j < KS - 1; ++j) {
+            const float *other = buf + j * kShare;
+            const float m_all = fmaxf(m_run, other[0]);
+            const float f0 = fast_exp2(m_run - m_all), f1 = fast_exp2(other[0] - m_all);
+            m_run = m_all;
+            l_run = l_run * f0 + other[64] * f1;
+#pragma unroll
+            for (int x = 0; x < 32; ++x) oacc[x >> 4][x & 15] = oacc[x >> 4][x & 15] * f0 + other[(2 + x) * 64] * f1;
+        }
     }
 
     if constexpr (PROBE) {
@@ -876,8 +898,12 @@ hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream)
                          : run_select<4, true, 2, false, true, false, true>(a, stream);
         }
         if (a.n_keys != a.n_tok || a.n_keys2 != 0) return hipErrorInvalidValue;
+        // (KS = 4: a CU holds one such workgroup, so while there is one for each; with fewer than two units for either half of it
+        // it is no faster.)
         return small          ? launch_select_direct(a, stream)
-               : a.block == 64 ? run_select<2, false, 2, false, false, false, true, 2>(a, stream)
+               : a.block == 64 ? (a.n_blk * a.heads <= 256 && a.kk >= 4
+                                      ? run_select<2, false, 2, false, false, false, true, 4>(a, stream)
+                                      : run_select<2, false, 2, false, false, false, true, 2>(a, stream))
                                : run_select<4, false, 2, false, false, false, true>(a, stream);
     }
     // One query block per workgroup, two LDS stages: measured best on MI355X.  A third stage is slower even

@@ -535,3 +535,20 @@ def test_every_channel_is_merged_with_its_own(s3r, dtype, block, n_tok, heads, t
     # are rounded at a size of up to 1 (so that 1 - g is not exact to its own size)
     bound = ulp * ((1 - g) * sel.abs() + out.abs()) + 2.0 ** -21 * (comp.abs() + sel.abs())
     assert ((out - (g * comp + (1 - g) * sel)).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("n_tok,heads,topk,n_forced", [
+    (64 * 2, 1, 2, 0), (64 * 9 + 1, 2, 1, 0), (64 * 9 + 33, 2, 3, 0), (64 * 9 + 31, 3, 4, 0), (64 * 40, 1, 33, 4), (64 * 70 + 5, 1, 64, 1),
+    (64 * 85, 3, 5, 0), (64 * 85 + 1, 3, 5, 0),       # 255 and 258 query blocks: two units in work at a time, one
+])
+@pytest.mark.parametrize("strided", [False, True])
+def test_two_units_at_a_time_for_few_fp32_query_blocks(s3r, oracle, n_tok, heads, topk, n_forced, strided):  # noqa: F811
+    wl = workloads.Workload(f"few_f32_{n_tok}_{heads}_{topk}", 1, n_tok, heads, 64, "f32", 64, topk, 110, "outliers")
+    tensors = workloads.make_inputs(wl)
+    dev = [t.cuda() for t in tensors]
+    if strided:
+        dev = list(torch.stack(dev, dim=1).unbind(1))
+    forced = list(range(n_forced)) if n_forced else None
+    res = run_device(s3r, *dev, 64, topk, forced=forced)
+    log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, *(to_host_f32(t) for t in tensors), None, 64, topk, "f32",
+                                                 label=wl.name, forced=forced)))
