@@ -479,6 +479,10 @@ hipError_t launch_select_pipe(const SelectArgs &a, hipStream_t stream)
     // half the iterations (microseconds a call, one pair -> two: 258 query blocks, 4 blocks a row 22.6 -> 21.2, 16 blocks
     // 34.6 -> 28.2; 344, 64 blocks 82.9 -> 57.7; 430, 32 blocks 51.2 -> 39.2; 512, 8 blocks 26.6 -> 23.4; but 540, 16
     // blocks 38.7 -> 41.0; 688 35.2 -> 36.3; 903 44.1 -> 47.5).
+    // One workgroup per CU at most: four pairs, whose 128 KiB leave no room for a second (two pairs -> four: 157 query blocks, 64 blocks a
+    // row 46.8 -> 42.9; 250, 100 blocks 71.4 -> 66.8, 48 blocks 37.5 -> 35.2; 252, 32 blocks 30.4 -> 29.2, 24 blocks 26.2 -> 25.4;
+    // 228, 16 blocks 22.5 -> 22.1; 256, 12 blocks 20.3 -> 20.5).
+    if (a.kk >= 16 && a.n_blk * a.heads <= 256) return run_pipe<4, 2, 2, 3>(a, stream);
     if (a.kk >= 4 && a.n_blk * a.heads <= 512) return run_pipe<2, 2, 2, 3>(a, stream);
     return run_pipe<1, 2, 2, 3>(a, stream);
 }

@@ -552,3 +552,16 @@ def test_two_units_at_a_time_for_few_fp32_query_blocks(s3r, oracle, n_tok, heads
     res = run_device(s3r, *dev, 64, topk, forced=forced)
     log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, *(to_host_f32(t) for t in tensors), None, 64, topk, "f32",
                                                  label=wl.name, forced=forced)))
+
+
+@pytest.mark.parametrize("n_tok,heads,topk,n_forced", [
+    (64 * 16, 16, 15, 0), (64 * 16, 16, 16, 0), (64 * 17, 16, 16, 0),     # 256 query blocks and 272; 15 and 16 blocks a row
+    (64 * 21 - 1, 12, 17, 0), (64 * 21 - 60, 12, 18, 1), (64 * 40 + 5, 1, 19, 0), (64 * 128, 2, 128, 0), (64 * 130, 1, 101, 26),
+])
+def test_four_pairs_of_waves_for_few_query_blocks(s3r, oracle, n_tok, heads, topk, n_forced):  # noqa: F811
+    wl = workloads.Workload(f"four_pairs_{n_tok}_{heads}_{topk}", 1, n_tok, heads, 64, "bf16", 64, topk, 111, "outliers")
+    q, k, v = workloads.make_inputs(wl)
+    forced = list(range(n_forced)) if n_forced else None
+    res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), 64, topk, forced=forced)
+    log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v), None, 64,
+                                                 topk, "bf16", forced=forced, label=wl.name)))
