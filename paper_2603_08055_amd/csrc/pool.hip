@@ -41,9 +41,9 @@ template <> struct Raw8<float> {
 
 // Operand parts of fp32 inputs: x = hi + lo + O(2^-17 |x|) with hi = bf16(x), lo = bf16(x - hi); with the third part
 // lo2 = bf16(x - hi - lo) the sum is x itself (each residual has 8 significant bits fewer than the one before).
-// V goes to the matrix pipe as a pair (its products with probabilities in [0, 1] need no more), K as such a triple or as
-// two fp16 parts with a power of two in front (half_parts): the error of a logit enters the result through an exponential, in
-// absolute terms, so the scores must keep all bits of K and Q however large their entries are.
+// V goes to the matrix pipe as a pair (its products with probabilities in [0, 1] need no more), K as a triple:
+// the error of a logit enters the result through an exponential, in absolute terms, so the scores must keep
+// all 24 bits of K and Q however large their entries, or those beside them, are.
 __device__ __forceinline__ bf16x8 lo_parts(const float (&f)[8], const bf16x8 &hi)
 {
     bf16x8 lo;
@@ -84,8 +84,7 @@ inline bool pool_ahead(int64_t n_tok, int heads, int block, bool is_bf16)
 // which would leave half of its threads without a row otherwise (100 views in 4 x 4 windows: 0.37 -> 0.31 ms, the call
 // 3.22 -> 3.17).
 // Thread (r0 = tid / 8, c = tid % 8) handles channels 8c..8c+7 of rows r0, r0 + 32, ...
-// KP: parts of K (fp32 inputs that are re-laid-out; otherwise 1).
-template <typename T, int B, bool REPACK, int KP, bool AHEAD>
+template <typename T, int B, bool REPACK, bool AHEAD>
 __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, const T *__restrict__ k,
                                                    const T *__restrict__ v, float *__restrict__ qc,
                                                    float *__restrict__ kc, float *__restrict__ vc,
@@ -93,19 +92,15 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, cons
                                                    int64_t n_tok, int heads, int64_t n_blk, TokenMap map,
                                                    InStride in, int64_t lo_off)
 {
-    // fp32 inputs are re-laid-out as operand parts: the lo tiles lie lo_off elements after the hi ones, K's third
-    // part (KP = 2: the factors of its blocks) another lo_off elements on
+    // fp32 inputs are re-laid-out as bf16 operand parts: the lo tiles lie lo_off elements after the hi ones, K's
+    // third part another lo_off elements on
     constexpr bool PAIRS = REPACK && sizeof(T) == 4;
-    constexpr bool HALF = KP == 2;
-    static_assert(PAIRS ? KP == 2 || KP == 3 : KP == 1, "parts of K");
-    static_assert(!HALF || kPoolHeads<B> == 1, "one head per workgroup");
     constexpr int VS_STRIDE = 72;  // bf16 elements per staged V row (64 + pad: conflict-free columns)
     constexpr int HP = kPoolHeads<B>;     // heads of a workgroup
     constexpr int RT = 32 / HP;           // rows that the threads of a head cover at a time
     __shared__ float red[3][32][65];
     __shared__ bf16_t vs[REPACK ? HP * B : 1][VS_STRIDE];
     __shared__ bf16_t vs_lo[PAIRS ? HP * B : 1][VS_STRIDE];
-    __shared__ float k_top[HALF ? 4 : 1];  // largest |k| that each wave has seen
 
     const int64_t bid = blockIdx.x;
     const int groups = (heads + HP - 1) / HP;
@@ -148,7 +143,6 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, cons
         }
         __builtin_amdgcn_sched_barrier(0);
     }
-    float kf[HALF ? B / RT : 1][8];  // HALF: K waits for the largest entry of the block
 #pragma unroll
     for (int n = 0; n < B / RT; ++n) {
         if (!have_head) break;
@@ -170,10 +164,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, cons
         rk[na].get(valid, f, hi);
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[1][i] += f[i];
-        if constexpr (HALF) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) kf[n][i] = f[i];
-        } else if constexpr (REPACK) {
+        if constexpr (REPACK) {
             bf16_t *dst = k_tile(r);
             store_tile<!AHEAD>(dst, hi);
             if constexpr (PAIRS) {
@@ -198,29 +189,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, cons
     for (int x = 0; x < 3; ++x)
 #pragma unroll
         for (int i = 0; i < 8; ++i) red[x][hh * RT + r0][c * 8 + i] = acc[x][i];
-    if constexpr (HALF) {
-        float top = 0.f;
-#pragma unroll
-        for (int n = 0; n < B / RT; ++n)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) top = fmaxf(top, fabsf(kf[n][i]));
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) top = fmaxf(top, __shfl_xor(top, d, 64));
-        if ((tid & 63) == 0) k_top[tid >> 6] = top;
-    }
     __syncthreads();
-    if constexpr (HALF) {
-        const int e = half_exponent(fmaxf(fmaxf(k_top[0], k_top[1]), fmaxf(k_top[2], k_top[3])));
-#pragma unroll
-        for (int n = 0; n < B / RT; ++n) {
-            half8 hi, lo;
-            half_parts(kf[n], e, hi, lo);
-            bf16_t *dst = k_tile(r0 + n * RT);
-            *reinterpret_cast<half8 *>(dst) = hi;
-            *reinterpret_cast<half8 *>(dst + lo_off) = lo;
-        }
-        if (tid == 0) reinterpret_cast<float *>(kb + 2 * lo_off)[static_cast<int64_t>(h) * n_blk + j] = ldexpf(1.f, -e);
-    }
 
     if (qc != nullptr) {
         for (int e = tid; e < 192 * HP; e += 256) {
@@ -256,14 +225,14 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, cons
     }
 }
 
-template <typename T, int B, bool REPACK, int KP = 1, bool AHEAD = true>
+template <typename T, int B, bool REPACK, bool AHEAD = true>
 static hipError_t run_pool(const void *q, const void *k, const void *v, float *qc, float *kc,
                            float *vc, void *kb, void *vb, int64_t n_tok, int heads, int64_t n_blk,
                            TokenMap map, InStride in, hipStream_t stream)
 {
     const int64_t grid = n_blk * ((heads + kPoolHeads<B> - 1) / kPoolHeads<B>);
-    const int64_t lo_off = static_cast<int64_t>(heads) * n_blk * B * 64;   // fp32 inputs: [hi tiles | lo tiles | K: lo2 tiles or factors]
-    hipLaunchKernelGGL((pool_kernel<T, B, REPACK, KP, AHEAD>), dim3(static_cast<unsigned>(grid)), dim3(256), 0,
+    const int64_t lo_off = static_cast<int64_t>(heads) * n_blk * B * 64;   // fp32 inputs: [hi tiles | lo tiles | K: lo2 tiles]
+    hipLaunchKernelGGL((pool_kernel<T, B, REPACK, AHEAD>), dim3(static_cast<unsigned>(grid)), dim3(256), 0,
                        stream, static_cast<const T *>(q), static_cast<const T *>(k),
                        static_cast<const T *>(v), qc, kc, vc, static_cast<bf16_t *>(kb),
                        static_cast<bf16_t *>(vb), n_tok, heads, n_blk, map, in, lo_off);
@@ -289,20 +258,19 @@ hipError_t launch_block_lens(TokenMap map, int block, int64_t n_tok, int64_t n_b
 
 hipError_t launch_pool(const void *q, const void *k, const void *v, float *qc, float *kc, float *vc,
                        void *kb, void *vb, int64_t n_tok, int heads, int block, bool is_bf16,
-                       TokenMap map, InStride in, int key_parts, hipStream_t stream)
+                       TokenMap map, InStride in, hipStream_t stream)
 {
     const int64_t n_blk = (n_tok + block - 1) / block;
     if (n_blk * heads > 0x7fffffffLL) return hipErrorInvalidValue;
     if (map.period != 0 && n_tok > 0x7fffffffLL) return hipErrorInvalidValue;
     const bool repack = kb != nullptr;
-    if (repack && !is_bf16 && (key_parts != 2 || block < 64) && (key_parts != 3 || block > 64)) return hipErrorInvalidValue;
 #define S3R_POOL_CASE(TT, BB, ...) \
     return run_pool<TT, BB, __VA_ARGS__>(q, k, v, qc, kc, vc, kb, vb, n_tok, heads, n_blk, map, in, stream)
     if (!pool_ahead(n_tok, heads, block, is_bf16)) {
         switch (block) {
-        case 16: if (repack) S3R_POOL_CASE(bf16_t, 16, true, 1, false); else S3R_POOL_CASE(bf16_t, 16, false, 1, false);
-        case 32: if (repack) S3R_POOL_CASE(bf16_t, 32, true, 1, false); else S3R_POOL_CASE(bf16_t, 32, false, 1, false);
-        case 64: if (repack) S3R_POOL_CASE(bf16_t, 64, true, 1, false); else S3R_POOL_CASE(bf16_t, 64, false, 1, false);
+        case 16: if (repack) S3R_POOL_CASE(bf16_t, 16, true, false); else S3R_POOL_CASE(bf16_t, 16, false, false);
+        case 32: if (repack) S3R_POOL_CASE(bf16_t, 32, true, false); else S3R_POOL_CASE(bf16_t, 32, false, false);
+        case 64: if (repack) S3R_POOL_CASE(bf16_t, 64, true, false); else S3R_POOL_CASE(bf16_t, 64, false, false);
         }
         return hipErrorInvalidValue;
     }
@@ -315,13 +283,10 @@ hipError_t launch_pool(const void *q, const void *k, const void *v, float *qc, f
         }
     } else {
         switch (block) {
-        case 16: if (repack) S3R_POOL_CASE(float, 16, true, 3); else S3R_POOL_CASE(float, 16, false);
-        case 32: if (repack) S3R_POOL_CASE(float, 32, true, 3); else S3R_POOL_CASE(float, 32, false);
-        case 64:
-            if (repack && key_parts == 2) S3R_POOL_CASE(float, 64, true, 2);
-            else if (repack) S3R_POOL_CASE(float, 64, true, 3);
-            else S3R_POOL_CASE(float, 64, false);
-        case 128: if (repack) S3R_POOL_CASE(float, 128, true, 2); else S3R_POOL_CASE(float, 128, false);
+        case 16: if (repack) S3R_POOL_CASE(float, 16, true); else S3R_POOL_CASE(float, 16, false);
+        case 32: if (repack) S3R_POOL_CASE(float, 32, true); else S3R_POOL_CASE(float, 32, false);
+        case 64: if (repack) S3R_POOL_CASE(float, 64, true); else S3R_POOL_CASE(float, 64, false);
+        case 128: if (repack) S3R_POOL_CASE(float, 128, true); else S3R_POOL_CASE(float, 128, false);
         }
     }
 #undef S3R_POOL_CASE

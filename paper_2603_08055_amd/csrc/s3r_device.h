@@ -56,32 +56,6 @@ template <typename T> __device__ __forceinline__ T from_float(float x);
 template <> __device__ __forceinline__ float from_float<float>(float x) { return x; }
 template <> __device__ __forceinline__ bf16_t from_float<bf16_t>(float x) { return static_cast<bf16_t>(x); }
 
-// ---- fp32 scores on the matrix pipe -----------------------------------------------------------
-// K and Q of fp32 problems go into the scores as two fp16 parts each, hi = fp16(x 2^e) and lo = fp16(x 2^e - hi), and the
-// three products hi.hi, hi.lo, lo.hi: 22 bits of an operand, so that a product is off by 2^-22 at most and by a quarter of that in the
-// mean, less than what adding up 64 of them in fp32 loses.  (Three bf16 parts, 24 bits, take six products for it.)  e
-// is common to a block of K and to a row of Q and brings its largest entry into [2^14, 2^15): entries down to
-// 2^-18 of it keep all their bits, and what smaller ones lose is below 2^-29 of it.
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ int half_exponent(float top)
-{
-    if (!(top > 0.f) || !(top < INFINITY)) return 0;
-    int x;
-    frexpf(top, &x);
-    return 15 - (x < -100 ? -100 : x);
-}
-
-__device__ __forceinline__ void half_parts(const float (&f)[8], int e, half8 &hi, half8 &lo)
-{
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float x = ldexpf(f[i], e);
-        hi[i] = static_cast<_Float16>(x);
-        lo[i] = static_cast<_Float16>(x - static_cast<float>(hi[i]));
-    }
-}
-
 // Value held by the lane 32 positions away (wave64).
 __device__ __forceinline__ float other_half(float x)
 {

@@ -73,19 +73,12 @@ hipError_t launch_block_lens(TokenMap map, int block, int64_t n_tok, int64_t n_b
 // Block means of q, k, v (fp32 [heads][n_blk][64]; any of qc/kc/vc may be null together) and,
 // when kb/vb are given (bf16 input), the per-(head, block) K and V tiles in MFMA operand order:
 // kb, vb are bf16 [heads][n_blk][block * 64] (blocks of 16 rows: K half tiles, V in pieces, see small_v_piece).  fp32 input:
-// kb, vb are [3][heads][n_blk][block * 64] (of vb two are written): V as bf16 hi parts and lo parts (x - hi rounded to
-// bf16), K in key_parts parts: 3: bf16 hi, lo and lo2; 2: fp16 hi and lo of x 2^e, and in the third array the factors 2^-e
-// as floats [heads][n_blk], one for each block (see half_parts).  n_tok counts the tokens of the
+// kb, vb are [3][heads][n_blk][block * 64] (of vb two are written), the bf16 hi parts, the lo parts (x - hi rounded to bf16) and
+// K's lo2 parts (x - hi - lo).  n_tok counts the tokens of the
 // sub-sequence `map` picks out of q, k, v; blocks are runs of that sub-sequence.
-// Where K comes in how many parts: two take three products instead of six and two tile arrays instead of three (30 views,
-// top-16, blocks of 64 986 -> 870 us a call; 30 views, blocks of 128, top-32, outlier keys 2780 -> 2287; dense, 5496 rows, 500 -> 416) and, with the small
-// products added up first, leave less error than the six in their order there (outlier keys against 64 bits, o_sel 3.33e-6 ->
-// 3.29e-6, lse 1.45e-6 -> 0.85e-6).  Blocks of 16 and 32 would gain as much time (1.15 to 1.2), but select_direct.hip adds
-// up its six in the better order already: 3.627e-6 -> 3.634e-6, lse 0.78e-6 -> 0.90e-6.  They keep three parts.
-inline int f32_key_parts(int block) { return block >= 64 ? 2 : 3; }
 hipError_t launch_pool(const void *q, const void *k, const void *v, float *qc, float *kc, float *vc,
                        void *kb, void *vb, int64_t n_tok, int heads, int block, bool is_bf16,
-                       TokenMap map, InStride in, int key_parts, hipStream_t stream);
+                       TokenMap map, InStride in, hipStream_t stream);
 
 // Per-head figures the TopK sweeps need: power-of-two factors that bring the largest |component| of the
 // head's pooled queries (sq) and keys (sk) into [0.5, 1), their product and its inverse, and the largest
@@ -195,8 +188,8 @@ struct SelectArgs {
     const void *q, *k, *v;     // the caller's layout: [rows][heads][64], or the strides x.in
     const void *kb, *vb;       // operand-order tiles of the keys (MFMA path only)
     const void *kb2 = nullptr, *vb2 = nullptr;  // MFMA dense only: a second key segment, 64-key tiles
-    int64_t lo_off = 0, lo_off2 = 0;  // fp32 problems on the MFMA path: kb, vb (kb2, vb2) hold their parts this many elements
-                                      // after one another (K in f32_key_parts(block))
+    int64_t lo_off = 0, lo_off2 = 0;  // fp32 problems on the MFMA path: kb, vb (kb2, vb2) hold [hi tiles | lo tiles | K: lo2
+                                      // tiles], each array this many elements after the one before
     const int32_t *idx;        // [heads][n_blk][kk]; null = every key (dense attention)
     const float *o_comp;       // [heads][n_blk][64] or null (no merge)
     const void *gate;          // [rows][heads][64] or null

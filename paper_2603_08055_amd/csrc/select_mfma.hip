@@ -64,23 +64,22 @@ namespace s3r {
 //         real one does (same work mapping, ring, waits and barriers) but does no arithmetic on them; it
 //         writes its Q rows to `out`, so Q is read and `out` written as well.  Its run time is what the data
 //         movement of the selection stage costs by itself.
-// F32   : fp32 q, gate, out and o_sel (the pointers below are then float pointers in disguise), K/V tiles in parts
-//         ([hi tiles | lo tiles | K only: see below], lo_off elements apart).  P.V takes two bf16 parts each, hi.hi + hi.lo +
-//         lo.hi (2^-17 relative, of values in [0, 1] times V).  Scores, whose error enters the result in absolute terms
-//         and must not grow with the size of the entries, take K and Q either
-//           in two fp16 parts with a power of two in front (HALF, see half_parts; the third array holds the factors of K's
-//           blocks) and three products, the small ones first, or
-//           in three bf16 parts and the six products whose weight is above 2^-24 (SMALL: over the tiles that
-//           select_direct.hip reads, see f32_key_parts).
-//         All on the 16-bit matrix pipe with fp32 accumulation: fp32-grade results at six (nine) MFMAs per tile step in place of two.
+// F32   : fp32 q, gate, out and o_sel (the pointers below are then float pointers in disguise), K/V tiles in bf16
+//         parts ([hi tiles | lo tiles | K only: lo2 tiles], lo_off elements apart), x = hi + lo (+ lo2).  Scores
+//         take Q and K in three parts each and the six products whose weight is above 2^-24 (a logit's error
+//         enters the result in absolute terms, so it must not grow with the size of the entries); P.V takes
+//         two parts each, hi.hi + hi.lo + lo.hi (2^-17 relative, of values in [0, 1] times V).  All on the
+//         bf16 matrix pipe with fp32 accumulation: fp32-grade results at nine MFMAs per tile step in place of two.
+//         (Two fp16 parts with a power of two per block of K and row of Q in front and three products took 0.8 of the time and lost
+//         entries 2^40 below the block's largest: ordinary keys beside one masked through a bias channel, or q / s and k s, came out wrong.)
 // KS    : 2: twice the waves, the second half of them on the second 32 keys of every unit for the same query rows, with a
 //         softmax of their own; the two partial results (m, l, O) of a row are added up through LDS at the end.  For
 //         fp32 selection with blocks of 64: two workgroups of two waves were all that an 80 KiB ring lets a CU
 //         hold, one wave per SIMD (30 views, top-16: 1.10 -> 0.98 ms a call; the shorter chains of sums also leave
 //         less error, outlier keys against 64 bits 3.6e-6 -> 3.3e-6).
 //         4: two units at a time, each with a stage of its own for K and for V.  For so few query blocks that a CU has one workgroup
-//         at most, and a row takes as long as its chain of units (us a call, 2 -> 4: 64 query blocks, 8 units 24.5 -> 22.7;
-//         228, 16 units 37.4 -> 33.6; 252, 32 units 56.0 -> 48.6; 157, 40 units 69.3 -> 57.9).
+//         at most, and a row takes as long as its chain of units (us a call, 2 -> 4: 64 query blocks, 8 units 25.3 -> 24.4;
+//         228, 16 units 41.5 -> 40.1; 252, 32 units 62.1 -> 55.8; 157, 32 units 64.9 -> 55.7).
 template <int QW, bool DENSE, int NS, bool SMALL, bool EXTRA, bool ASMQ, bool PAIR = false, bool PROBE = false,
           bool F32 = false, int KS = 1>
 __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
@@ -95,22 +94,21 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     constexpr int NW = QW * KS;        // waves per workgroup
     constexpr int NMT = KS == 1 ? 2 : 1;  // 32-key tiles of a unit that a wave works on
     constexpr int NU = KS == 4 ? 2 : 1;   // units in work at a time
-    constexpr bool HALF = F32 && !SMALL;
-    constexpr int NCH = HALF ? 32 : F32 ? 40 : 16; // 1 KiB chunks of a unit: 8 K + 8 V (F32: then 8 K lo + 8 V lo, and 8 K lo2 unless HALF)
+    constexpr bool LEAN = F32 && !SMALL;  // stages of its own, see the loop
+    constexpr int NCH = F32 ? 40 : 16; // 1 KiB chunks of a unit: 8 K + 8 V (F32: then 8 K lo + 8 V lo + 8 K lo2)
     constexpr int CPW = NCH / NW;      // ... issued by each wave
     constexpr int D = NS - 1;          // units in flight
-    static_assert(NCH % NW == 0 && 16 % NW == 0, "waves must split the chunks of a unit evenly");
+    static_assert(LEAN || (NCH % NW == 0 && 16 % NW == 0), "waves must split the chunks of a unit evenly");
     static_assert(CPW * D < 64, "vmcnt budget");
     static_assert(!SMALL || DENSE, "selection with small blocks: select_direct.hip");
-    static_assert(KS == 1 || (!DENSE && !PAIR && !PROBE && (KS == 2 || (KS == 4 && HALF && QW == 2))), "key halves: plain selection");
+    static_assert(KS == 1 || (!DENSE && !PAIR && !PROBE && (KS == 2 || (KS == 4 && LEAN && QW == 2))), "key halves: plain selection");
     static_assert(!F32 || (!PAIR && !PROBE), "operand parts: the plain and the dense kernels");
-    // [stage][K 8 KiB | V 8 KiB] (F32: then [K lo 8 KiB | V lo 8 KiB | K lo2 8 KiB]).  HALF: [stage][K | K lo] and, of one unit
-    // only, [V | V lo] behind them; with KS = 2 one stage of K as well.
-    constexpr int kStageParts = F32 && !HALF ? 5 : 2;
-    static_assert(!HALF || NS == 2, "its own stages");
-    constexpr int kKeyStages = KS == 1 ? 2 : 1;  // HALF
-    __shared__ __attribute__((aligned(1024))) bf16_t ring[HALF ? NU * (kKeyStages + 1) : NS][kStageParts * kUnitElems];
-    constexpr int kLoElems = HALF ? kUnitElems : 2 * kUnitElems;  // from a hi part of a stage to its lo part (and on to K's lo2 part)
+    // [stage][K 8 KiB | V 8 KiB] (F32: then [K lo 8 KiB | V lo 8 KiB | K lo2 8 KiB]).  LEAN, for each unit in work: [K | K lo | K lo2 |
+    // V | V lo], and with KS = 2 a KiB that keeps a fourth workgroup off the CU, see the loop.
+    constexpr int kKeyElems = 3 * kUnitElems;  // LEAN: where V begins
+    constexpr int kStageElems = (F32 ? 5 : 2) * kUnitElems + (LEAN && KS == 2 ? 512 : 0);
+    __shared__ __attribute__((aligned(1024))) bf16_t ring[LEAN ? NU : NS][kStageElems];
+    constexpr int kLoElems = (LEAN ? 1 : 2) * kUnitElems;  // from a hi part of a stage to its lo part, and on to K's lo2 part
 
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -163,9 +161,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     // each step anyway (two stages), and a plain early load of Q is 1 % faster there, except on long index
     // rows (ASMQ chooses).
     bf16x8 qb[4];
-    half8 qh[HALF ? 4 : 1], qhl[HALF ? 4 : 1];  // HALF: the parts of Q
-    float scale_q = scale_log2;                 // HALF: scale over the power of two in front of Q
-    bf16x8 ql[F32 && !HALF ? 4 : 1], ql2[F32 && !HALF ? 4 : 1];   // F32 otherwise: qb and the lo and lo2 parts of Q
+    bf16x8 ql[F32 ? 4 : 1], ql2[F32 ? 4 : 1];   // F32: the lo and lo2 parts of Q
     constexpr bool kAsmQ = ASMQ && !F32;
     floatx4 q_raw[F32 ? 4 : 1][2];  // F32: requested here, made operands of once the first unit has been requested as well
     if constexpr (F32) {
@@ -189,32 +185,20 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         }
     }
     auto parts_of_q = [&]() __attribute__((always_inline)) {
-        float f[4][8], top = 0.f;
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                f[s][i] = row_valid ? q_raw[F32 ? s : 0][i >> 2][i & 3] : 0.f;
-                top = fmaxf(top, fabsf(f[s][i]));
-            }
-        if constexpr (HALF) {
-            const int e = half_exponent(max_with_other_half(top));
-            scale_q = ldexpf(scale_log2, -e);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) half_parts(f[s], e, qh[s], qhl[s]);
-        } else if constexpr (F32) {
+        if constexpr (F32) {
 #pragma unroll
             for (int s = 0; s < 4; ++s)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    qb[s][i] = static_cast<bf16_t>(f[s][i]);
-                    const float r1 = f[s][i] - static_cast<float>(qb[s][i]);
+                    const float f = row_valid ? q_raw[s][i >> 2][i & 3] : 0.f;
+                    qb[s][i] = static_cast<bf16_t>(f);
+                    const float r1 = f - static_cast<float>(qb[s][i]);
                     ql[s][i] = static_cast<bf16_t>(r1);
                     ql2[s][i] = static_cast<bf16_t>(r1 - static_cast<float>(ql[s][i]));
                 }
         }
     };
-    if constexpr (F32 && !HALF) parts_of_q();
+    if constexpr (F32 && !LEAN) parts_of_q();
     auto load_q_dense = [&]() __attribute__((always_inline)) {
         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
         u32x4 q0, q1, q2, q3;
@@ -297,7 +281,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         return UnitBlocks{f0, b1 >= 0 ? b1 : f0, b2 >= 0 ? b2 : f0, b3 >= 0 ? b3 : f0};
     };
     auto issue = [&](int s, int stage) {  // this wave's share of step s -> LDS stage `stage`
-        const unsigned stage_byte = ring_base + static_cast<unsigned>(stage) * (kStageParts * kUnitElems * 2);
+        const unsigned stage_byte = ring_base + static_cast<unsigned>(stage) * (kStageElems * 2);
         if constexpr (SMALL) {
             // (dense: the second key segment is stored as plain 64-key units)
             const int u = s + u_begin;
@@ -367,16 +351,17 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         if constexpr (CPW == 8) lds_dma_16_x4(unit, lane * 16 + 4096, dst + 4096);
     };
 
-    // HALF: this wave's share of K (or V) of step s -> LDS stage `stage`: four 1 KiB chunks, two of either part
-    auto issue_half = [&](int s, int stage, bool is_k) {
-        static_assert(!HALF || NW == 4 * NU, "two chunks of a part for each of a unit's waves");
+    // LEAN: this wave's share of K (or V) of step s -> LDS: two 1 KiB chunks of each part
+    auto issue_parts = [&](int s, bool is_k) {
+        static_assert(!LEAN || NW == 4 * NU, "two chunks of a part for each of a unit's waves");
         const int w = unit_of(s);
         const bool second = DENSE && w >= n_units1;
         const int64_t unit = static_cast<int64_t>(second ? w - n_units1 : w) * kUnitElems, lo = second ? lo_off2 : lo_off;
         const bf16_t *src = (is_k ? (second ? kb2_h : kb_h) : (second ? vb2_h : vb_h)) + unit + (wave & 3) * 1024;
-        const unsigned dst = ring_base + static_cast<unsigned>(nu * (kKeyStages + 1) + stage) * (kStageParts * kUnitElems * 2) + (wave & 3) * 2048;
+        const unsigned dst = ring_base + static_cast<unsigned>(nu * kStageElems + (is_k ? 0 : kKeyElems)) * 2 + (wave & 3) * 2048;
         lds_dma_16_x2(src, lane * 16, dst);
         lds_dma_16_x2(src + lo, lane * 16, dst + kUnitElems * 2);
+        if (is_k) lds_dma_16_x2(src + 2 * lo, lane * 16, dst + 2 * kUnitElems * 2);
     };
 
     floatx16 oacc[2];
@@ -421,27 +406,6 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         return first_keys(unit_left(unit_of(s)));
     };
 
-    // HALF: the powers of two in front of the K blocks of 64 steps, one step per lane, and with the query's own and the softmax
-    // scale what the scores of a unit are to be multiplied by.
-    float k_factor = 1.f, unit_scale = scale_log2;
-    auto factor_step = [&](int s) -> int { return s + lane < n_steps ? s + lane : n_steps - 1; };
-    // entry: selection: the index list at factor_step(s)
-    auto load_factors = [&](int s, int entry) {  // of steps s .. s + 63
-        const float *fk = reinterpret_cast<const float *>(kb + 2 * lo_off) + static_cast<int64_t>(h) * n_blk;
-        const int step = factor_step(s);
-        if constexpr (DENSE) {
-            const int u = step + u_begin;
-            k_factor = u < n_units1 ? fk[u >> upb_shift]
-                                    : reinterpret_cast<const float *>(kb2 + 2 * lo_off2)[static_cast<int64_t>(h) * n_units2 + (u - n_units1)];
-        } else {
-            k_factor = fk[in_range(entry)];
-        }
-        asm volatile("" : "+v"(k_factor));  // (waited for in here, not in front of its use in every step)
-    };
-    auto set_unit_scale = [&](int s) {  // (never 0: a key that does not exist has a score of -inf)
-        unit_scale = fmaxf(scale_q * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(k_factor), s & 63)), 1e-37f);
-    };
-    auto score_scale = [&]() -> float { return HALF ? unit_scale : scale_log2; };
     floatx16 sacc[2];
     bf16x8 pb[4];  // probabilities of one unit as MFMA operands
     bf16x8 pl[F32 ? 4 : 1];  // F32: their lo parts
@@ -454,30 +418,29 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         for (int i = 0; i < 4 * NMT; ++i) {
             const int mt = DENSE ? i >> 2 : i & (NMT - 1), c = DENSE ? i & 3 : i / NMT;
             const bf16_t *at = ks + ((mt * 4 + c) * 64 + lane) * 8;
-            if constexpr (HALF) {  // the small products
-                const half8 kh = *reinterpret_cast<const half8 *>(at), kl = *reinterpret_cast<const half8 *>(at + kLoElems);
-                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh, qhl[c], c == 0 ? zero16 : sacc[mt], 0, 0, 0);
-                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl, qh[c], sacc[mt], 0, 0, 0);
-                continue;
-            }
             const bf16x8 ka = *reinterpret_cast<const bf16x8 *>(at);
-            sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[c], c == 0 ? zero16 : sacc[mt], 0, 0, 0);
+            // F32: the products of the smaller parts first: what their sums lose is rounding of their own size, and only the products of
+            // the high parts are added up at the size of the score.  Step by step, each step's high product first, outlier keys are 3.29e-6
+            // (blocks of 64) and 3.63e-6 (128) off 64 bits, lse 0.84e-6 and 0.87e-6; so 3.25e-6 and 3.57e-6, lse 0.48e-6 and 0.52e-6,
+            // in the same time within 0.5 %.
             if constexpr (F32) {
                 const bf16x8 kl = *reinterpret_cast<const bf16x8 *>(at + kLoElems);
                 const bf16x8 kl2 = *reinterpret_cast<const bf16x8 *>(at + 2 * kLoElems);
-                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, ql[c], sacc[mt], 0, 0, 0);
-                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qb[c], sacc[mt], 0, 0, 0);
-                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, ql2[c], sacc[mt], 0, 0, 0);
+                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, ql2[c], c == 0 ? zero16 : sacc[mt], 0, 0, 0);
                 sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, ql[c], sacc[mt], 0, 0, 0);
                 sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl2, qb[c], sacc[mt], 0, 0, 0);
+                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, ql[c], sacc[mt], 0, 0, 0);
+                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qb[c], sacc[mt], 0, 0, 0);
+            } else {
+                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[c], c == 0 ? zero16 : sacc[mt], 0, 0, 0);
             }
         }
-        if constexpr (HALF) {
+        if constexpr (F32) {
 #pragma unroll
             for (int i = 0; i < 4 * NMT; ++i) {
                 const int mt = i >> 2, c = i & 3;
-                const half8 kh = *reinterpret_cast<const half8 *>(ks + ((mt * 4 + c) * 64 + lane) * 8);
-                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh, qh[c], sacc[mt], 0, 0, 0);
+                const bf16x8 ka = *reinterpret_cast<const bf16x8 *>(ks + ((mt * 4 + c) * 64 + lane) * 8);
+                sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[c], sacc[mt], 0, 0, 0);
             }
         }
     };
@@ -512,7 +475,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
             for (int r = 0; r < 16; r += 2) mx[mt] = fmaxf(fmaxf(mx[mt], sacc[mt][r]), sacc[mt][r + 1]);
-        const float mx_own = fmaxf(mx[0], mx[1]) * score_scale();
+        const float mx_own = fmaxf(mx[0], mx[1]) * scale_log2;
         const float m_lim = m_run + kRescaleSlack;
         if (__builtin_expect(__any(mx_own > m_lim), 0)) {
             const float m_tile = max_with_other_half(mx_own);
@@ -544,7 +507,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const int mt = v >> 1, r = 8 * (v & 1) + i;
-                    const float p = fast_exp2(sacc[mt][r] * score_scale() - m_run);
+                    const float p = fast_exp2(sacc[mt][r] * scale_log2 - m_run);
                     lsum[i & 3] += p;
                     pb[v][i] = static_cast<bf16_t>(p);
                     pl[v][i] = static_cast<bf16_t>(p - static_cast<float>(pb[v][i]));
@@ -689,38 +652,32 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
             softmax(&ring[stage][0], vmask);
             accumulate(&ring[stage][kUnitElems], std::false_type{});
         }
-    } else if constexpr (HALF) {
-        // V has one stage: requested when every wave is done with the unit before, waited for when its probabilities are there,
-        // under the scores and the softmax.  So has K in the kernel for blocks of 64, requested under P.V of the unit before.
-        // Fewer requests are on their way per workgroup, but 48 KiB let a CU hold three of them (by registers four for blocks of
-        // 64 with 32 KiB), where two whole stages leave room for two, and it is the waves that hide each other's chains of
-        // products here (matrix pipe 39 % and vector ALU 42 % busy with two waves on a SIMD).  A call on 30 views, top-16, blocks of
-        // 64: 854 us with two whole stages, 775 with one of V, 761 with one of both; 8 x 8 windows 1754, 1585, 1547; blocks of 128
-        // (30 views, top-32, outlier keys) 2307 and 2055; dense, 5496 rows, 392 and 364.
-        auto entry_of = [&](int s) -> int { return DENSE ? 0 : sel[factor_step(s) >> upb_shift]; };
-        // What the start waits for is requested side by side: Q (above), the index list, then K(0), then the factors.
-        int entry = n_steps > 0 ? entry_of(0) : 0;
-        __builtin_amdgcn_sched_barrier(0);
-        if (nu < n_steps) issue_half(nu, 0, true);
+    } else if constexpr (LEAN) {
+        // One stage of K and one of V: V is requested when every wave is done with the unit before and waited for when its
+        // probabilities are there, under the scores and the softmax; K under P.V of the unit before.  Fewer requests are on their way per
+        // workgroup, but 40 KiB let a CU hold three of them where two whole stages leave room for two, and it is the waves that
+        // hide each other's chains of products here.  Two whole stages -> one of each, us a call: 30 views, blocks of 64, top-16
+        // 999 -> 921, 8 x 8 windows 1117 -> 1010; 100 views, top-32 5833 -> 5596, top-64 10.4 to 10.6 ms either way; blocks of 128
+        // (30 views, top-32, outlier keys) 2790 -> 2570; dense, 5496 rows, 475 -> 453.  A second stage of K, two workgroups: blocks of 128
+        // 2804, dense 482.  Four workgroups, which the registers of blocks of 64 allow: 30 views, top-16 922, but top-64 2974 for 2917 and on 100
+        // views 11258 for 10502, the fabric being what long rows wait for: three.
+        // What the start waits for is requested side by side: Q (above), then K(0).
+        if (nu < n_steps) issue_parts(nu, true);
         parts_of_q();
         for (int s0 = 0; s0 < n_steps; s0 += NU) {
             const int s = s0 + nu;
             const bool have = NU == 1 || s < n_steps, more = s + NU < n_steps;
-            if ((s0 & 63) == 0) load_factors(s0, s0 == 0 ? entry : entry_of(s0));
             wait_vmcnt<0>();  // K(s)
-            lds_barrier();    // everybody's K(s), and everybody is done with V of the units before (two K stages: and with K)
-            if (have) issue_half(s, kKeyStages, false);
-            if (kKeyStages == 2 && more) issue_half(s + NU, (s + 1) & 1, true);
-            if (have) set_unit_scale(s);
+            lds_barrier();    // everybody's K(s), and everybody is done with V of the units before
+            if (have) issue_parts(s, false);
             const unsigned long long vmask = have ? unit_mask(s) : 0ull;
             const bool any = (KS == 1 ? vmask : vmask >> (32 * kh)) != 0ull;  // (none: second half of a short last block)
-            const bf16_t *stages = &ring[nu * (kKeyStages + 1)][0];
             // (a key half: the second 32-row tile of K, the second two key steps of V)
-            if (any) softmax(stages + (kKeyStages == 2 ? s & 1 : 0) * (kStageParts * kUnitElems) + kh * kRowTileElems, vmask);
-            if (kKeyStages == 2 && more) wait_vmcnt<4>(); else wait_vmcnt<0>();  // V(s); K of the next may be on its way
+            if (any) softmax(&ring[nu][kh * kRowTileElems], vmask);
+            wait_vmcnt<0>();  // V(s)
             lds_barrier();    // everybody's V(s), and everybody is done with the scores of K(s)
-            if (kKeyStages == 1 && more) issue_half(s + NU, 0, true);
-            if (any) accumulate(stages + kKeyStages * (kStageParts * kUnitElems) + kh * kRowTileElems, std::false_type{});
+            if (more) issue_parts(s + NU, true);
+            if (any) accumulate(&ring[nu][kKeyElems + kh * kRowTileElems], std::false_type{});
         }
     } else {
     for (int s = 0; s < D && s < n_steps; ++s) issue(s, s);  // D < NS: stage = s
@@ -792,8 +749,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     const float inv = (EXTRA && DENSE && l_tot == 0.f) ? 0.f : 1.f / l_tot;  // (a key split of empty units only)
     if (lse != nullptr && g == 0 && row_valid)
         lse[static_cast<int64_t>(h) * lse_stride + trow] = (m_run + __builtin_log2f(l_tot)) * kLn2;
-    // One half of the channels after the other: both at once take 142 registers in the fp32 kernel for blocks of 64, which is to
-    // stay below 128 (four workgroups per CU).
+    // One half of the channels after the other: both at once take 14 registers more (fp32, blocks of 64).
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt) {
         auto channel = [&](int j) -> int { return 32 * dt + 16 * j + 8 * g; };
@@ -898,10 +854,11 @@ hipError_t launch_select_mfma(const SelectArgs &a, hipStream_t stream)
                          : run_select<4, true, 2, false, true, false, true>(a, stream);
         }
         if (a.n_keys != a.n_tok || a.n_keys2 != 0) return hipErrorInvalidValue;
-        // (KS = 4: a CU holds one such workgroup, so while there is one for each; with fewer than two units for either half of it
-        // it is no faster.)
+        // KS = 4: as long as there is a CU for every workgroup (260 query blocks, which fill three places on some CUs before, take 1.2 of
+        // the time), and from rows of five blocks on (64 to 256 query blocks, time against KS = 2: 1 to 3 blocks a row 1.02 to 1.06,
+        // 4 blocks 1.00 to 1.02, 6 blocks 0.97 to 1.00, 8 blocks 0.95 to 0.99, 16 blocks 0.89 to 0.97, 32 blocks 0.86 to 0.91).
         return small          ? launch_select_direct(a, stream)
-               : a.block == 64 ? (a.n_blk * a.heads <= 256 && a.kk >= 4
+               : a.block == 64 ? (a.n_blk * a.heads <= 256 && a.kk >= 5
                                       ? run_select<2, false, 2, false, false, false, true, 4>(a, stream)
                                       : run_select<2, false, 2, false, false, false, true, 2>(a, stream))
                                : run_select<4, false, 2, false, false, false, true>(a, stream);

@@ -50,7 +50,7 @@ int g_kernel_choice = 0;  // 0 auto, 1 generic attention kernels only, 2 TopK fr
 
 // every supported block size, bf16 and fp32 (the latter with K/V in bf16 operand parts)
 bool mfma_ok(s3r_dtype dtype, int block) { (void)dtype; (void)block; return g_kernel_choice != 1; }
-// copies of a K (or V) tile array the MFMA kernels read: fp32 problems keep parts hi, lo and (K) lo2 or the blocks' factors
+// copies of a K (or V) tile array the MFMA kernels read: fp32 problems keep bf16 parts hi, lo and (K) lo2
 size_t tile_parts(s3r_dtype dtype) { return dtype == S3R_BF16 ? 1 : 3; }
 
 // Dense attention of few query rows (the special tokens) in key splits: the number of splits with the shortest time
@@ -602,7 +602,7 @@ s3r_status speed3r_sparse_global_attn_ex(const s3r_params *p)
             S3R_HIP(s3r::launch_block_lens(sp.img, p->block, sp.n_img, L.n_blk, blk_len, stream), "block length kernel launch");
         }
         S3R_HIP(s3r::launch_pool(p->q, p->k, p->v, qc, kc, vc, kb, vb, sp.n_img, p->heads, p->block, is_bf16,
-                                 sp.img, in, s3r::f32_key_parts(p->block), stream),
+                                 sp.img, in, stream),
                 "pool kernel launch");
     }
     FusedBufs fb;
@@ -680,7 +680,7 @@ s3r_status speed3r_sparse_global_attn_ex(const s3r_params *p)
             {
                 StageTimer tm(S3R_STAGE_POOL, stream);
                 S3R_HIP(s3r::launch_pool(p->q, p->k, p->v, nullptr, nullptr, nullptr, kb_s, vb_s, sp.n_spec, p->heads,
-                                         64, is_bf16, sp.spec, in, s3r::f32_key_parts(p->block), stream),
+                                         64, is_bf16, sp.spec, in, stream),
                         "pool kernel launch (special tokens)");
             }
             d.kb = kb; d.vb = vb; d.n_keys = sp.n_img; d.n_blk = L.n_blk;      // image keys, then special keys
@@ -759,7 +759,7 @@ s3r_status speed3r_pool_blocks(const void *q, const void *k, const void *v, floa
     if (!aligned16(q) || !aligned16(k) || !aligned16(v)) return fail(S3R_ERR_INVALID_ARG, "device pointers must be 16-byte aligned");
     StageTimer tm(S3R_STAGE_POOL, static_cast<hipStream_t>(stream));
     S3R_HIP(s3r::launch_pool(q, k, v, qc, kc, vc, nullptr, nullptr, n_tok, heads, block, dtype == S3R_BF16,
-                             s3r::TokenMap{}, s3r::InStride{}, 0, static_cast<hipStream_t>(stream)),
+                             s3r::TokenMap{}, s3r::InStride{}, static_cast<hipStream_t>(stream)),
             "pool kernel launch");
     return S3R_OK;
 }
@@ -876,7 +876,7 @@ s3r_status speed3r_select_attn(const void *q, const void *k, const void *v, cons
         StageTimer tm(S3R_STAGE_POOL, s);
         S3R_HIP(s3r::launch_pool(q, k, v, nullptr, nullptr, nullptr, const_cast<void *>(a.kb),
                                  const_cast<void *>(a.vb), n_tok, heads, block, dtype == S3R_BF16, s3r::TokenMap{},
-                                 s3r::InStride{}, s3r::f32_key_parts(block), s),
+                                 s3r::InStride{}, s),
                 "pool kernel launch");
     }
     a.q = q; a.k = k; a.v = v; a.idx = idx; a.o_comp = o_comp; a.gate = gate_logits; a.out = out;
@@ -916,7 +916,7 @@ s3r_status speed3r_probe_select_loads(const void *q, const void *k, const void *
     {
         StageTimer tm(S3R_STAGE_POOL, s);
         S3R_HIP(s3r::launch_pool(q, k, v, nullptr, nullptr, nullptr, const_cast<void *>(a.kb), const_cast<void *>(a.vb),
-                                 n_tok, heads, block, true, s3r::TokenMap{}, s3r::InStride{}, 0, s),
+                                 n_tok, heads, block, true, s3r::TokenMap{}, s3r::InStride{}, s),
                 "pool kernel launch");
     }
     a.q = q; a.k = k; a.v = v; a.idx = idx; a.out = out;
@@ -952,7 +952,7 @@ s3r_status speed3r_dense_attn(const void *q, const void *k, const void *v, void 
         StageTimer tm(S3R_STAGE_POOL, s);
         S3R_HIP(s3r::launch_pool(q, k, v, nullptr, nullptr, nullptr, const_cast<void *>(a.kb),
                                  const_cast<void *>(a.vb), n_tok, heads, block, dtype == S3R_BF16, s3r::TokenMap{},
-                                 s3r::InStride{}, s3r::f32_key_parts(block), s),
+                                 s3r::InStride{}, s),
                 "pool kernel launch");
     }
     a.q = q; a.k = k; a.v = v; a.idx = nullptr; a.o_comp = nullptr; a.gate = nullptr; a.out = out;

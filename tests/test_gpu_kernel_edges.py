@@ -340,9 +340,8 @@ def test_small_weights_beside_a_large_one_stay_in_the_sum_of_the_sweep(s3r):  # 
 @pytest.mark.parametrize("block,n_tok", [(0, 64 * 3 + 7), (0, 64 * 67), (64, 64 * 5 + 1), (64, 64 * 5 + 33), (64, 64), (128, 128 * 3 + 70), (128, 128 * 2 + 64)])
 @pytest.mark.parametrize("spread", ["none", "keys", "channels", "blocks", "tiny queries", "zero blocks"])
 def test_fp32_keys_of_all_sizes(s3r, oracle, block, n_tok, spread):  # noqa: F811
-    """K in fp16 parts with one power of two for a block, Q with one for a row: entries of very different sizes in a row, a
-    block and from block to block, the other operand as much smaller where a channel is large.  More than 64 units: the
-    factors are read 64 at a time; few keys in the last unit: one key half without work."""
+    """Entries of different sizes in a row, a block and from block to block, the other operand as much smaller where a channel
+    is large.  Few keys in the last unit: one key half without work."""
     heads = 2
     wl = workloads.Workload(f"f32_{spread}_{block}_{n_tok}", 1, n_tok, heads, 64, "f32", max(block, 64), 1, 111, "normal")
     q, k, v = workloads.make_inputs(wl)
@@ -368,6 +367,53 @@ def test_fp32_keys_of_all_sizes(s3r, oracle, block, n_tok, spread):  # noqa: F81
         idx = torch.arange(n_blk, dtype=torch.int32, device="cuda").expand(heads, n_blk, n_blk).contiguous()
         s3r.speed3r_select_attn(q.cuda(), k.cuda(), v.cuda(), idx, out, block)
     ref = oracle.dense_attn(*(to_host_f32(x) for x in (q, k, v)), 0.125)
+    assert_close(to_host_f32(out), ref, TOL["f32"], wl.name)
+
+
+@pytest.mark.parametrize("where", ["dense", "blocks of 64", "few blocks of 64", "blocks of 128", "blocks of 32", "special, 64", "special, 128", "special, 16"])
+@pytest.mark.parametrize("what,size", [("mask", 1e4), ("mask", 1e6), ("mask", 1e8), ("mask", 1e30), ("channels", 20), ("channels", 40),
+                                       ("one channel", 24), ("one channel", 60), ("one key", 30), ("one key", 60), ("far apart", 80)])
+def test_fp32_scores_of_ordinary_keys_beside_large_entries(s3r, oracle, where, what, size):  # noqa: F811
+    """What one key or one channel holds takes no bits from the others: keys masked through a channel that is the same in
+    all queries, channels scaled against each other (q / s, k s), one large key that no query sees, and the largest entries
+    of q and k in channels where the other one is zero.  The scores that count are ordinary throughout."""
+    special = 3 if "special" in where else 0
+    block = 64 if where == "dense" else int(where.split()[-1])
+    views, heads = (1, 2) if where in ("dense", "few blocks of 64", "blocks of 128", "blocks of 32") else (2, 3)
+    tpv = 64 * 45 + 9 if where == "blocks of 64" else 64 * 6 + 41      # 270 query blocks; 14 and fewer
+    wl = workloads.Workload(f"large_{what}_{size}_{where}", views, tpv, heads, 64, "f32", block, 1, 113, "normal")
+    q, k, v = workloads.make_inputs(wl)
+    rows, gen = torch.arange(views * tpv), torch.Generator().manual_seed(114)
+    if what == "mask":
+        q[:, :, 0] = 1.0
+        k[rows % 16 == 5, :, 0] = -size
+    elif what == "channels":
+        s = torch.exp2(torch.randint(-size, size + 1, (1, heads, 64), generator=gen).float())
+        q, k = q / s, k * s
+    elif what == "one channel":
+        q[:, :, 7] *= 2.0 ** -size
+        k[:, :, 7] *= 2.0 ** size
+    elif what == "one key":
+        q[:, :, 9] = 0.0
+        k[70, :, 9] = 2.0 ** size
+    else:
+        q[:, :, 0], q[:, :, 1] = 2.0 ** size, 0.0
+        k[:, :, 0], k[:, :, 1] = 0.0, 2.0 ** size
+    dev = [x.cuda() for x in (q, k, v)]
+    ref = oracle.dense_attn(*(to_host_f32(x) for x in (q, k, v)), 0.125)
+    if special:
+        n_blk = -(-views * (tpv - special) // block)
+        out = run_device(s3r, *dev, block, min(n_blk, 8), want=(), tokens_per_view=tpv, special_per_view=special)["out"]
+        at = (rows % tpv < special).numpy()
+        assert_close(to_host_f32(out)[at], ref[at], TOL["f32"], wl.name)
+        return
+    out = torch.full_like(dev[0], float("nan"))
+    if where == "dense":
+        s3r.speed3r_dense_attn(*dev, out)
+    else:
+        n_blk = -(-views * tpv // block)
+        idx = torch.arange(n_blk, dtype=torch.int32, device="cuda").expand(heads, n_blk, n_blk).contiguous()
+        s3r.speed3r_select_attn(*dev, idx, out, block)
     assert_close(to_host_f32(out), ref, TOL["f32"], wl.name)
 
 
@@ -538,7 +584,7 @@ def test_every_channel_is_merged_with_its_own(s3r, dtype, block, n_tok, heads, t
 
 
 @pytest.mark.parametrize("n_tok,heads,topk,n_forced", [
-    (64 * 2, 1, 2, 0), (64 * 9 + 1, 2, 1, 0), (64 * 9 + 33, 2, 3, 0), (64 * 9 + 31, 3, 4, 0), (64 * 40, 1, 33, 4), (64 * 70 + 5, 1, 64, 1),
+    (64 * 2, 1, 2, 0), (64 * 9 + 1, 2, 1, 0), (64 * 9 + 33, 2, 3, 0), (64 * 9 + 31, 3, 4, 0), (64 * 9 + 31, 3, 5, 0), (64 * 9 + 33, 2, 6, 1), (64 * 40, 1, 33, 4), (64 * 70 + 5, 1, 64, 1),
     (64 * 85, 3, 5, 0), (64 * 85 + 1, 3, 5, 0),       # 255 and 258 query blocks: two units in work at a time, one
 ])
 @pytest.mark.parametrize("strided", [False, True])
