@@ -369,7 +369,8 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
-    float m_run = -1e30f;
+    constexpr float kNoMaximum = -1e30f;
+    float m_run = kNoMaximum;
     float l_run = 0.f;
 
     // how many of unit w's 64 keys exist, 64 or more: all (wave-uniform)
@@ -463,7 +464,7 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
     };
     // The running maximum, raised only when the unit exceeds it by more than the slack.  The two lanes of a query look at
     // their own halves of the unit; they exchange them only when either has to raise the maximum.
-    // looks: see softmax below; a raise has the coming units looked at as well (the first unit's does not count).
+    // looks: see softmax below; a raise has the coming units looked at as well (not one from the start value, the first unit's).
     constexpr int kFirstLooks = 4, kLooks = 64;
     int looks = kFirstLooks;
     auto look_at_max = [&]() __attribute__((always_inline)) {
@@ -478,11 +479,11 @@ __global__ __launch_bounds__(QW * KS * 64, 2) void select_mfma_kernel(
         const float mx_own = fmaxf(mx[0], mx[1]) * scale_log2;
         const float m_lim = m_run + kRescaleSlack;
         if (__builtin_expect(__any(mx_own > m_lim), 0)) {
+            if (__any(mx_own > m_lim && m_run > kNoMaximum)) looks = kLooks;
             const float m_tile = max_with_other_half(mx_own);
             const float m_new = m_tile > m_lim ? m_tile : m_run;
             const float alpha = fast_exp2(m_run - m_new);
             m_run = m_new;
-            looks = looks == kFirstLooks ? looks : kLooks;
             l_run *= alpha;
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt)

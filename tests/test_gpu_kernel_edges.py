@@ -419,7 +419,8 @@ def test_fp32_scores_of_ordinary_keys_beside_large_entries(s3r, oracle, where, w
 
 # (unit, rise): in the first four units the maximum is looked at, afterwards a unit is done again; then looked at for 64 units
 @pytest.mark.parametrize("block", [0, 64, 128])   # dense attention; long rows; blocks of 128
-@pytest.mark.parametrize("rises", [[(2, 9)], [(4, 7.9)], [(4, 8.1)], [(5, 60), (6, 69)], [(7, 300)], [(4, 20), (68, 29), (80, 40), (150, 52)]])
+@pytest.mark.parametrize("rises", [[(2, 9)], [(4, 7.9)], [(4, 8.1)], [(5, 60), (6, 69)], [(7, 300)], [(4, 20), (68, 29), (80, 40), (150, 52)],
+                                   [(5, 20), (65, 29), (66, 38), (70, 47), (131, 56)]])   # a raise 60 units after another, and soon after that
 def test_units_done_again_when_the_maximum_rises(s3r, block, rises):  # noqa: F811
     """Keys of ever larger weight for the even queries only (the odd ones of a wave keep their maximum), in units whose
     probabilities were formed against the maximum before; the last unit is short."""
