@@ -60,20 +60,27 @@ __device__ __forceinline__ bf16x8 lo2_parts(const float (&f)[8], const bf16x8 &h
     return lo2;
 }
 
-// A 16-byte piece of a tile; PAST: past the L2, where the tiles are more than the caches keep for the kernels that read them (us of
-// this kernel through it / past it: 100 views 272 / 269, 1000 views 2765 / 2655).  Short sequences are read from there: 8 views 19.8 / 18.8,
-// but the kernel that reads the tiles takes as much longer.
+// A 16-byte piece of a tile; PAST: past the L2, where the tiles are more than the caches keep for the kernels that read them (us a
+// call, one row at a time, through it / past it: 36 views 453.4 / 453.4, in blocks of 32 411 / 407; 100 views 1215 / 1209, in blocks of 32
+// 1163 / 1157; 1000 views, this kernel, 2765 / 2655).  Short sequences are read from there: 8 views, this kernel 23.0 / 21.5, but the one that
+// reads the tiles takes as much longer (in blocks of 32 the call 91.4 / 94.5; 16 views 179 / 188).
 template <bool PAST> __device__ __forceinline__ void store_tile(bf16_t *dst, const bf16x8 &x)
 {
     if constexpr (PAST) __builtin_nontemporal_store(x, reinterpret_cast<bf16x8 *>(dst));
     else *reinterpret_cast<bf16x8 *>(dst) = x;
 }
 
-// Whether every thread requests all of its rows at once.  With one load at a time a short sequence waits for the memory's
-// latency six times (blocks of 64) where once would do; a long one, whose waves keep the memory busy anyway, is faster with the
-// fewer requests on their way, blocks of 128 apart (16 heads, us of this kernel at a time / all at once, tiles through the L2: bf16,
-// 8 views 21.4 / 19.8, 100 views 279 / 284, 1000 views 2701 / 2924, 300 views in blocks of 128 893 / 864; fp32, 30 views 172 / 160).
-constexpr int64_t kPoolAheadBytes = int64_t(256) << 20;  // of q, k and v
+// Whether every thread requests all of its rows at once (and stores the tiles through the L2).  With one load at a time a short
+// sequence waits for the memory's latency six times (blocks of 64) where once would do; a long one, whose waves keep the memory
+// busy anyway, is faster with the fewer requests on their way, blocks of 128 apart (16 heads, us of this kernel at once / at a time, tiles
+// through the L2: 12 views 29.4 / 32.4, 100 views 281 / 270, 1000 views 2924 / 2701; blocks of 128, 300 views 864 / 893; fp32, 30 views
+// 160 / 172).  Between them (us a call, at once and through the L2 / at a time and past it; blocks of 64, 32, 4 x 4 windows):
+//   12 views, 101 MB   150.4 / 153.9   137.1 / 141.8   233 / 245
+//   16 views, 135 MB   194.6 / 196.4   178.6 / 188.0   295 / 309
+//   24 views, 203 MB   302.0 / 302.2   289.2 / 282.1   444 / 447
+//   30 views, 253 MB   381.2 / 375.7   352.5 / 345.3   556 / 555
+//   45 views, 380 MB   559.3 / 553.8   509.6 / 499.1   859 / 857
+constexpr int64_t kPoolAheadBytes = int64_t(192) << 20;  // of q, k and v
 
 inline bool pool_ahead(int64_t n_tok, int heads, int block, bool is_bf16)
 {

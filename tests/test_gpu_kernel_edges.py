@@ -542,7 +542,8 @@ def test_bound_of_scores_of_one_sign(s3r, oracle, dtype, n_blk, topk, lean):  # 
                                                  topk, dtype, label=wl.name)))
 
 
-@pytest.mark.parametrize("heads,n_tok", [(17, 41120), (17, 41121), (17, 41137), (16, 43691)])   # 256 MiB of q, k, v in bf16 and past it
+# 192 MiB of q, k, v in bf16 and past it; longer ones
+@pytest.mark.parametrize("heads,n_tok", [(17, 30840), (17, 30841), (17, 30857), (16, 32768), (16, 32769), (17, 41120), (17, 41121), (17, 41137), (16, 43691)])
 @pytest.mark.parametrize("block", [16, 32, 64, 128])
 def test_pooling_with_rows_requested_at_once_and_one_by_one(s3r, heads, n_tok, block):  # noqa: F811
     wl = workloads.Workload("pool_line", 1, n_tok, heads, 64, "bf16", block, 1, 108, "outliers")
