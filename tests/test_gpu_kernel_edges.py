@@ -613,3 +613,33 @@ def test_four_pairs_of_waves_for_few_query_blocks(s3r, oracle, n_tok, heads, top
     res = run_device(s3r, q.cuda(), k.cuda(), v.cuda(), 64, topk, forced=forced)
     log(f"{wl.name}: " + str(compare_with_oracle(oracle, res, to_host_f32(q), to_host_f32(k), to_host_f32(v), None, 64,
                                                  topk, "bf16", forced=forced, label=wl.name)))
+
+
+@pytest.mark.parametrize("block,views,tpv,special,grid", [
+    (16, 97, 1351, 0, None), (16, 97, 1352, 0, None),      # 192 MiB of 4 heads are 131 072 rows: 131 047 and 131 144
+    (32, 97, 1351, 0, None), (32, 97, 1352, 0, None), (64, 97, 1352, 0, None), (32, 96, 1374, 5, None), (64, 96, 1374, 5, None),
+    (16, 96, 1374, 5, (37, 37, 4)), (16, 388, 339, 1, (13, 26, 4)),   # windows of 16, 8, 4 and 2 cells: slots that do not exist are passed over
+    (64, 96, 1374, 5, (37, 37, 8)),
+])
+def test_pooling_past_the_line_writes_the_same_tiles(s3r, block, views, tpv, special, grid):  # noqa: F811
+    """Four heads at once against the same heads two at a time, whose pooling stays below the line between its two forms: every
+    output comes from the tiles and the means it writes."""
+    assert 2 * views * tpv * 3 * 128 < 192 * 2 ** 20
+    wl = workloads.Workload(f"pool_tiles_{block}", views, tpv, 4, 64, "bf16", block, 4, 115, "outliers")
+    tensors = [*workloads.make_inputs(wl, device="cuda"), workloads.make_gate_logits(wl, device="cuda")]
+    image = (torch.arange(views * tpv, device="cuda") % tpv) >= special
+
+    def call(heads):
+        q, k, v, gate = (x[:, heads].contiguous() for x in tensors)
+        return run_device(s3r, q, k, v, block, 4, gate=gate, tokens_per_view=tpv, special_per_view=special, grid=grid)
+
+    whole = call(slice(0, 4))
+    for heads in (slice(0, 2), slice(2, 4)):
+        part = call(heads)
+        for name in ("idx", "o_comp"):
+            assert torch.equal(whole[name][heads], part[name]), name
+        assert torch.equal(whole["lse"][heads][:, image], part["lse"][:, image])
+        for name in ("o_sel", "out"):
+            assert torch.equal(whole[name][image][:, heads], part[name][image]), name
+        if special:   # another number of key splits, each share's probabilities rounded against its own maximum
+            assert_close(to_host_f32(whole["out"][~image][:, heads]), to_host_f32(part["out"][~image]), TOL["bf16"], wl.name)
