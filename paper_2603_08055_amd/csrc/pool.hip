@@ -80,7 +80,8 @@ template <bool PAST> __device__ __forceinline__ void store_tile(bf16_t *dst, con
 //   24 views, 203 MB   302.0 / 302.2   289.2 / 282.1   444 / 447
 //   30 views, 253 MB   381.2 / 375.7   352.5 / 345.3   556 / 555
 //   45 views, 380 MB   559.3 / 553.8   509.6 / 499.1   859 / 857
-constexpr int64_t kPoolAheadBytes = int64_t(192) << 20;  // of q, k and v
+// From 200 to 270 MB it is one or the other by shape (36 calls of 192 to 256 MiB, at a time / at once: 0.98 to 1.02, in the mean 0.998).
+constexpr int64_t kPoolAheadBytes = int64_t(256) << 20;  // of q, k and v
 
 inline bool pool_ahead(int64_t n_tok, int heads, int block, bool is_bf16)
 {

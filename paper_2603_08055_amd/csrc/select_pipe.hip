@@ -392,7 +392,8 @@ __global__ __launch_bounds__(128 * P, 2) void select_pipe_kernel(
                    gate != nullptr ? gate + o : nullptr, channel);
     };
     // Two pairs, the kernel of long sequences, ask for them after the exchange of the partial results: before it 1000 views take 0.3 %
-    // longer (42.27 and 42.13 ms a call).
+    // longer (42.27 and 42.13 ms a call).  Few query blocks, which come here as well, take the same time either way (us a call, after /
+    // before: 260 query blocks, 16 blocks a row 28.5 / 28.3; 430, 32 blocks 40.6 / 40.7; 512, 64 blocks 63.9 / 63.8).
     if constexpr (P != 2) request();
     float osum[kShare];
     float m_all = m_run, l_all = sum_with_other_half(l_run);
