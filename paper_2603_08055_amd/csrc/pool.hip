@@ -73,8 +73,8 @@ template <bool PAST> __device__ __forceinline__ void store_tile(bf16_t *dst, con
 // Whether every thread requests all of its rows at once (and stores the tiles through the L2).  With one load at a time a short
 // sequence waits for the memory's latency six times (blocks of 64) where once would do; a long one, whose waves keep the memory
 // busy anyway, is faster with the fewer requests on their way, blocks of 128 apart (16 heads, us of this kernel at once / at a time, tiles
-// through the L2: 12 views 29.4 / 32.4, 100 views 281 / 270, 1000 views 2924 / 2701; blocks of 128, 300 views 864 / 893; fp32, 30 views
-// 160 / 172).  Between them (us a call, at once and through the L2 / at a time and past it; blocks of 64, 32, 4 x 4 windows):
+// through the L2: 12 views 29.4 / 32.4, 100 views 281 / 270, 1000 views 2924 / 2701; blocks of 128, 300 views 864 / 893; fp32,
+// 8 views 43.0 / 45.1, blocks of 128 46.2 / 48.9, 30 views 167.7 / 168.2, 100 views 604 / 606, blocks of 16 563 / 554).  Between them (us a call, at once and through the L2 / at a time and past it; blocks of 64, 32, 4 x 4 windows):
 //   12 views, 101 MB   150.4 / 153.9   137.1 / 141.8   233 / 245
 //   16 views, 135 MB   194.6 / 196.4   178.6 / 188.0   295 / 309
 //   24 views, 203 MB   302.0 / 302.2   289.2 / 282.1   444 / 447
